@@ -57,7 +57,7 @@ int32_t specvlm_last_hip_error(void) { return g_last_hip_error; }
 size_t specvlm_tree_verify_attn_workspace_bytes(const specvlm_attn_desc* desc) {
     if (!desc || check_attn_desc(*desc)) return 0;
     if (desc->dtype == SPECVLM_F32) return 256;
-    return attn_mfma_workspace_bytes(*desc);
+    return attn_mfma_workspace_bytes(*desc, attn_mfma_pick_splits(*desc));
 }
 
 int32_t specvlm_tree_verify_attn_num_splits(const specvlm_attn_desc* desc) {
@@ -92,8 +92,9 @@ static int32_t tree_verify_attn(const specvlm_attn_desc* desc, const void* q_dev
     a.workspace = workspace_dev; a.workspace_bytes = workspace_bytes;
     a.err_flag = err_flag_dev; a.stream = static_cast<hipStream_t>(stream);
     if (desc->dtype == SPECVLM_F32 || mode == kVectorAluKernel) return launch_attn_valu(a);
-    const size_t need = attn_mfma_workspace_bytes(*desc);
-    if (attn_mfma_pick_splits(*desc) > 1) {
+    a.num_splits = attn_mfma_pick_splits(*desc);
+    const size_t need = attn_mfma_workspace_bytes(*desc, a.num_splits);
+    if (need) {
         if (static_workspace) {
             if (need > SPECVLM_STATIC_WORKSPACE_BYTES) return SPECVLM_WORKSPACE_TOO_SMALL;
             rc = attn_static_workspace(&a.workspace);

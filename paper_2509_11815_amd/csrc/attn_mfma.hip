@@ -248,8 +248,7 @@ int32_t attn_mfma_pick_splits(const specvlm_attn_desc& d) {
 // zeros, never where one stored partial results.
 static size_t counter_bytes(const specvlm_attn_desc&) { return static_cast<size_t>(kMaxSplitHeads) * 4 * kCounterStride * sizeof(int32_t); }
 
-size_t attn_mfma_workspace_bytes(const specvlm_attn_desc& d) {
-    const int splits = attn_mfma_pick_splits(d);
+size_t attn_mfma_workspace_bytes(const specvlm_attn_desc& d, int32_t splits) {
     if (splits == 1) return 0;
     const size_t parts = static_cast<size_t>(d.B) * d.H_q * splits;
     return counter_bytes(d) + parts * (static_cast<size_t>(kQRows) * d.D * 2 + kQRows * 8);
@@ -290,7 +289,7 @@ int32_t launch_attn_mfma(const AttnArgs& a) {
                  d.max_blocks_per_req, d.num_blocks,
                  d.paged ? d.max_blocks_per_req * SPECVLM_PAGE_SIZE : d.kv_capacity};
     p.N_max = d.N_max; p.H_q = d.H_q; p.group = d.H_q / d.H_kv;
-    p.num_splits = attn_mfma_pick_splits(d);
+    p.num_splits = a.num_splits;
     p.scale = a.scale;
     p.q = static_cast<const uint16_t*>(a.q);
     p.k = static_cast<const uint16_t*>(a.k);

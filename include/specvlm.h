@@ -111,9 +111,10 @@ int32_t specvlm_last_hip_error(void);
 size_t specvlm_tree_verify_attn_workspace_bytes(const specvlm_attn_desc *desc);
 
 /*
- * Number of key-range splits per (request, head) specvlm_tree_verify_attn will use for
+ * Number of key-range splits per (request, head) specvlm_tree_verify_attn plans with for
  * `desc` (desc->num_splits when that is positive, otherwise the library's choice for the
- * shape).  Returns 0 when desc is invalid, 1 for SPECVLM_F32 (no split path).
+ * shape; in the latter case a call that divides the query rows among workgroups as well may use
+ * fewer).  Returns 0 when desc is invalid, 1 for SPECVLM_F32 (no split path).
  */
 int32_t specvlm_tree_verify_attn_num_splits(const specvlm_attn_desc *desc);
 

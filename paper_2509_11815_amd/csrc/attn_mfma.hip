@@ -44,40 +44,16 @@
 //             block) -- merges the splits, adding a split up while the next ones still load
 #include <atomic>
 
-#include "common.hpp"
+#include "attn_common.hpp"
 
 namespace specvlm {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef short s16x4 __attribute__((ext_vector_type(4)));
-typedef short s16x8 __attribute__((ext_vector_type(8)));
-
-// ds_read_b64_tr_b16: inside a block of 16 lanes, lane i receives element i % 4 of the four
-// 8-byte rows whose addresses lanes i/4, i/4 + 4, i/4 + 8 and i/4 + 12 pass.
-__device__ __forceinline__ s16x4 lds_read_tr16(const unsigned char* generic_lds_addr) {
-    typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-    return __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)generic_lds_addr);
-}
 
 constexpr int kWaves = 8;           // wavefronts per workgroup: two per SIMD
 constexpr int kShare = 4;           // wavefronts sharing one key stream, 64/kShare query rows each
 constexpr int kAhead = 2;           // tiles per stream kept in flight ahead of the one being consumed
 constexpr int kStreamsPerWg = kWaves / kShare;
 constexpr int kThreads = kWaves * 64;
-constexpr int kQRows = 64;          // padded query rows: 4 MFMA column blocks of 16
 constexpr int kTile = 32;           // keys per tile
-constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLn2 = 0.6931471805599453f;
-constexpr float kTau = 8.0f;        // log2 of how far a probability may exceed 1 before the reference max moves
-constexpr int kMaxSplitHeads = 1024;  // (request, head) pairs a split call can have: one set of ticket counters each
-constexpr int kCounterStride = 32;    // int32 words from one ticket counter to the next: every counter has a 128-byte line of
-                                      // its own (with the counters of eight heads in one line, 256 atomics queued up on it:
-                                      // 17.1 -> 16.6 us per call at the 2880-visual-token prefix, 12.4 -> 11.3 us at 576)
 
 struct MfmaParams {
     KvGeom g;
@@ -93,71 +69,6 @@ struct MfmaParams {
     float* ws_acc;              // [B*H_q*num_splits][4 qb][NT/2][64 lanes] 16-byte vectors of packed bf16
     float* ws_ml;               // [B*H_q*num_splits][64 q][2] (max, sum)
 };
-
-__device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
-    f32x2 f = {lo, hi};
-    bf16x2 h = __builtin_convertvector(f, bf16x2);      // v_cvt_pk_bf16_f32, round to nearest even
-    return __builtin_bit_cast(uint32_t, h);
-}
-
-__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-
-// 16 bytes per lane from global memory straight into LDS at lds_dst + 16*lane (the LDS base
-// travels in M0).  The compiler does not see the LDS write: every consumer sits behind
-// wait_vmcnt<>() below, which is also a compiler memory barrier.
-__device__ __forceinline__ void dma16(const void* gsrc, uint32_t lds_dst) {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt"
-                 :
-                 : "v"(gsrc), "s"(lds_dst)
-                 : "memory");
-}
-
-// Same with a wavefront-uniform base address and a 32-bit lane offset in bytes.
-__device__ __forceinline__ void dma16s(const void* sbase, uint32_t voff, uint32_t lds_dst) {
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
-                 :
-                 : "v"(voff), "s"(sbase), "s"(lds_dst)
-                 : "memory");
-}
-
-// Same, 4 bytes per lane: lds_dst + 4*lane.
-__device__ __forceinline__ void dma4(const void* gsrc, uint32_t lds_dst) {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off"
-                 :
-                 : "v"(gsrc), "s"(lds_dst)
-                 : "memory");
-}
-
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-    asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
-}
-
-// The same for a count that is a constant only after loop unrolling (an even number up to 30).
-__device__ __forceinline__ void wait_vmcnt_unrolled(int n) {
-    switch (n) {
-#define SPECVLM_WAIT_CASE(N) case N: wait_vmcnt<N>(); break;
-        SPECVLM_WAIT_CASE(0) SPECVLM_WAIT_CASE(2) SPECVLM_WAIT_CASE(4) SPECVLM_WAIT_CASE(6) SPECVLM_WAIT_CASE(8)
-        SPECVLM_WAIT_CASE(10) SPECVLM_WAIT_CASE(12) SPECVLM_WAIT_CASE(14) SPECVLM_WAIT_CASE(16) SPECVLM_WAIT_CASE(18)
-        SPECVLM_WAIT_CASE(20) SPECVLM_WAIT_CASE(22) SPECVLM_WAIT_CASE(24) SPECVLM_WAIT_CASE(26) SPECVLM_WAIT_CASE(28)
-        SPECVLM_WAIT_CASE(30)
-#undef SPECVLM_WAIT_CASE
-        default: wait_vmcnt<0>(); break;
-    }
-}
-
-// Write-through (device-coherent) 16-byte store for data that another workgroup, possibly
-// behind another L2, reads in the same kernel.
-// (A store of more than 8 bytes reads its data registers for a cycle after it has issued: a
-// vector instruction that overwrites them right behind it would corrupt the data of the last
-// lanes.  The compiler pads its own stores; it cannot know that this asm is one, hence the s_nop.)
-__device__ __forceinline__ void store16_coherent(void* dst, u32x4 v) {
-    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" : : "v"(dst), "v"(v) : "memory");
-}
-
-__device__ __forceinline__ void store8_coherent(void* dst, u32x2 v) {
-    asm volatile("global_store_dwordx2 %0, %1, off sc0 sc1" : : "v"(dst), "v"(v) : "memory");
-}
 
 // Writes one wavefront's 16 query rows: out[t][i] = O^T[d = 16t + 4g + i][q], unnormalised.
 template <int NT>
@@ -243,10 +154,65 @@ int32_t attn_mfma_pick_splits(const specvlm_attn_desc& d) {
     return best;
 }
 
+// How a call is divided among workgroups: query rows and key ranges, or key ranges only.
+//
+// With few (request, head) pairs the chip can be filled in two ways.  Key ranges (the kernels of this
+// file): every workgroup takes all 64 query rows, K and V are fetched once, and the 2 - 64 partial results
+// of a head meet at the end.  Query rows as well (attn_wave.hip): workgroups of 16 or 32 rows, whose
+// K and V come from L2 for all but the first of a head's row blocks, with a quarter or half of the
+// arithmetic each, so that fewer or no partial results have to meet, and those are a quarter or half the size.
+// The model below is fitted to measured calls (us; 1 x 32 heads x 128, 60 nodes, all on 256 workgroups):
+//   260 keys   key ranges 10.7 (1 split)   32 rows  8.4 (4)   16 rows  7.3 (1)
+//   828        key ranges 11.4 (8)         32 rows  9.9 (4)   16 rows  9.9 (2)
+//   3324       key ranges 16.5 (8)         32 rows 16.8 (4)   16 rows 23.6 (2)
+// so rows win until the repeated K and V traffic (at most ~14 TB/s from L2) costs more than the merge.
+struct AttnPlan { int block_rows, splits; };           // block_rows 0: key ranges only
+AttnPlan attn_plan(const specvlm_attn_desc& d, int32_t nominal) {
+    const int cus = 256;
+    const int group = d.H_q / d.H_kv, rows = group * d.N_max;
+    const int cap = d.paged ? d.max_blocks_per_req * SPECVLM_PAGE_SIZE : d.kv_capacity;
+    const int ntile = (cap + kTile - 1) / kTile;
+    const double half = d.D == 128 ? 1.0 : 0.5;            // tile size relative to head size 128
+    auto rounds_of = [&](double items, auto&& one) {       // us of `items` workgroups, 256 at a time
+        const int full = static_cast<int>(items / cus), rest = static_cast<int>(items) - full * cus;
+        return full * one(cus) + (rest ? one(rest) : 0.0);
+    };
+    const double heads = static_cast<double>(d.B) * d.H_q;
+    const int steps = (ntile + kStreamsPerWg * nominal - 1) / (kStreamsPerWg * nominal);
+    const double step = d.D == 128 ? 0.85 : 0.6;
+    const double merge = nominal == 1 ? 0.0 : nominal <= 8 ? 2.8 : 0.8 * nominal;
+    const double items = heads * nominal;
+    AttnPlan best{0, nominal};
+    double best_t = items > cus && items <= 2 * cus
+        ? 6.5 + merge + steps * fmax(2 * step, items * half * 32768 / 6.2e6)
+        : rounds_of(items, [&](int active) { return 6.5 + merge + steps * fmax(step, active * half * 32768 / 8.0e6); });
+    // what the row-dividing kernels assume (32-bit offsets into a request's query rows and a half tile)
+    if (d.kv_stride_t >= (1 << 22) || (d.N_max * d.q_stride_n + group * d.q_stride_h) >= (1ll << 30) ||
+        heads * 4 * nominal >= (1 << 24))
+        return best;
+    for (int br = 16; br <= 32; br *= 2) {
+        if (br == 32 && rows <= 16) break;
+        const int rb = (rows + br - 1) / br;
+        const double units = static_cast<double>(d.B) * d.H_kv * rb;
+        const double a = br == 16 ? (d.D == 128 ? 4.8 : 4.3) : (d.D == 128 ? 5.2 : 4.6);
+        const double c = br == 16 ? 1.9 : 2.5, b = (br == 16 ? 0.9 : 1.05) * (d.D == 128 ? 1.0 : 0.57);
+        const int s_lo = d.num_splits > 0 ? nominal : 1;      // a caller's count is taken as given
+        for (int s = s_lo; s <= nominal; ++s) {
+            if (s > 1 && units > kMaxSplitHeads) break;    // one set of ticket counters per unit
+            const int r = (ntile + 4 * s - 1) / (4 * s);
+            const double t = rounds_of(units * s, [&](int active) {
+                return a + (s > 1 ? c + 0.8 * ((s - 1) / 8) : 0.0) + r * fmax(b, active * half * 65536 / 13.5e6);
+            });
+            if (t < best_t * 0.98) { best_t = t; best = AttnPlan{br, s}; }
+        }
+    }
+    return best;
+}
+
 // The ticket counters occupy a region of fixed size at the start of the workspace, whatever the
 // shape: a later call of another shape then finds its counters where every earlier call left
 // zeros, never where one stored partial results.
-static size_t counter_bytes(const specvlm_attn_desc&) { return static_cast<size_t>(kMaxSplitHeads) * 4 * kCounterStride * sizeof(int32_t); }
+static size_t counter_bytes(const specvlm_attn_desc&) { return kCounterBytes; }
 
 size_t attn_mfma_workspace_bytes(const specvlm_attn_desc& d, int32_t splits) {
     if (splits == 1) return 0;
@@ -284,6 +250,8 @@ int32_t attn_static_workspace(void** ptr_out) {
 
 int32_t launch_attn_mfma(const AttnArgs& a) {
     const specvlm_attn_desc& d = a.d;
+    const AttnPlan plan = attn_plan(d, a.num_splits);
+    if (plan.block_rows) return launch_attn_wave(a, plan.block_rows, plan.splits);
     MfmaParams p;
     p.g = KvGeom{d.kv_stride_b, d.kv_stride_h, d.kv_stride_t, d.paged ? a.block_table : nullptr,
                  d.max_blocks_per_req, d.num_blocks,

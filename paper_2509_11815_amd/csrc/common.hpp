@@ -128,6 +128,8 @@ int32_t launch_attn_valu(const AttnArgs& a);
 
 // bf16 MFMA split-key kernel + merge.
 int32_t launch_attn_mfma(const AttnArgs& a);
+// ... and the kernel whose workgroups take 16 or 32 query rows each (same workspace layout rules).
+int32_t launch_attn_wave(const AttnArgs& a, int block_rows, int splits);
 size_t attn_mfma_workspace_bytes(const specvlm_attn_desc& d, int32_t splits);
 int32_t attn_mfma_pick_splits(const specvlm_attn_desc& d);
 // Device address of the current device's library-owned scratch array (SPECVLM_STATIC_WORKSPACE_BYTES).

@@ -175,9 +175,9 @@ int32_t specvlm_tree_verify_attn_static(const specvlm_attn_desc *desc,
 
 /*
  * Measurement aid, not part of the verification path: the same operation and arguments as
- * specvlm_tree_verify_attn_static, computed by the vector-ALU kernel that serves SPECVLM_F32
+ * specvlm_tree_verify_attn_static, computed by a vector-ALU kernel
  * (one workgroup per (request, head, node), no matrix cores, no key-range splits, no scratch)
- * also when desc->dtype is SPECVLM_BF16.  It exists so that the choice of the matrix-core kernel
+ * whatever desc->dtype is.  It exists so that the choice of the matrix-core kernel
  * for bf16 can be re-measured on the same inputs (bench.py --vector-alu-evidence); results
  * agree with specvlm_tree_verify_attn within the bf16 tolerance.
  */

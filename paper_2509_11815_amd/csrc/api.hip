@@ -91,7 +91,8 @@ static int32_t tree_verify_attn(const specvlm_attn_desc* desc, const void* q_dev
     a.parent = parent_dev; a.o = o_dev; a.lse = lse_dev;
     a.workspace = workspace_dev; a.workspace_bytes = workspace_bytes;
     a.err_flag = err_flag_dev; a.stream = static_cast<hipStream_t>(stream);
-    if (desc->dtype == SPECVLM_F32 || mode == kVectorAluKernel) return launch_attn_valu(a);
+    if (mode == kVectorAluKernel) return launch_attn_valu(a);
+    if (desc->dtype == SPECVLM_F32) return launch_attn_f32(a);
     a.num_splits = attn_mfma_pick_splits(*desc);
     const size_t need = attn_mfma_workspace_bytes(*desc, a.num_splits);
     if (need) {

@@ -122,8 +122,8 @@ struct AttnArgs {
     hipStream_t stream;
 };
 
-// fp32 VALU kernel: exact-ish path for SPECVLM_F32 (and a bf16 VALU variant kept for
-// comparison measurements).
+// fp32 path, and the vector-ALU kernel kept for comparison measurements (fp32 or bf16 input).
+int32_t launch_attn_f32(const AttnArgs& a);
 int32_t launch_attn_valu(const AttnArgs& a);
 
 // bf16 MFMA split-key kernel + merge.

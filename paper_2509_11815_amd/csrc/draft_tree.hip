@@ -15,7 +15,7 @@
 // hundred entries.
 #include <limits.h>
 
-#include "common.hpp"
+#include "wave_ops.hpp"
 
 namespace specvlm {
 
@@ -25,64 +25,39 @@ constexpr int kThreadsDT = 1024;
 constexpr int kWavesDT = kThreadsDT / 64;
 constexpr int kCandCap = 1024;           // Top-K fast path: entries at or above the threshold kept in LDS
 
+// Eight consecutive entries of a row, as loaded.
 template <typename T>
-struct Lane16;
+struct Chunk;
 template <>
-struct Lane16<uint16_t> {
-    static constexpr int kPerVec = 8;
-    __device__ static float at(const uint4& w, int e) {
+struct Chunk<uint16_t> {
+    uint4 w;
+    __device__ __forceinline__ void load(const uint16_t* p) { w = *reinterpret_cast<const uint4*>(p); }
+    __device__ __forceinline__ void fill() { w = uint4{0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u}; }     // -inf
+    __device__ __forceinline__ float at(int e) const {
         const uint32_t x = (&w.x)[e >> 1];
         return __uint_as_float((e & 1) ? (x & 0xFFFF0000u) : (x << 16));
     }
-    __device__ static float one(const uint16_t* p) { return bf16_bits_to_float(*p); }
 };
 template <>
-struct Lane16<float> {
-    static constexpr int kPerVec = 4;
-    __device__ static float at(const uint4& w, int e) { return __uint_as_float((&w.x)[e]); }
-    __device__ static float one(const float* p) { return *p; }
-};
-
-// NS entries of a row in a thread's registers, as loaded: bf16 entries stay packed two to a
-// register and are widened where they are used (one shift or mask).
-template <typename T, int NS>
-struct RowRegs;
-template <int NS>
-struct RowRegs<uint16_t, NS> {
-    uint32_t w[NS / 2];
-    __device__ __forceinline__ float get(int s) const {
-        const uint32_t x = w[s >> 1];
-        return __uint_as_float((s & 1) ? (x & 0xFFFF0000u) : (x << 16));
+struct Chunk<float> {
+    float f[8];
+    __device__ __forceinline__ void load(const float* p) {
+        *reinterpret_cast<float4*>(f) = *reinterpret_cast<const float4*>(p);
+        *reinterpret_cast<float4*>(f + 4) = *reinterpret_cast<const float4*>(p + 4);
     }
-    __device__ __forceinline__ void put_vec(int j, const uint4& x) {          // entries 8j .. 8j+7
-        w[4 * j] = x.x; w[4 * j + 1] = x.y; w[4 * j + 2] = x.z; w[4 * j + 3] = x.w;
-    }
-    __device__ __forceinline__ void fill_vec(int j) {                         // -inf
-        w[4 * j] = w[4 * j + 1] = w[4 * j + 2] = w[4 * j + 3] = 0xFF80FF80u;
-    }
-    // Called between two passes over the entries: the compiler then widens the entries again in
-    // the next pass instead of keeping NS widened copies alive beside the packed ones.
-    __device__ __forceinline__ void repack() {
+    __device__ __forceinline__ void fill() {
 #pragma unroll
-        for (int i = 0; i < NS / 2; ++i) asm volatile("" : "+v"(w[i]));
+        for (int e = 0; e < 8; ++e) f[e] = -INFINITY;
     }
-    __device__ __forceinline__ void put_one(int s, const uint16_t* p) {       // p == nullptr: -inf; even s first
-        const uint32_t b = p ? *p : 0xFF80u;
-        w[s >> 1] = (s & 1) ? (w[s >> 1] | (b << 16)) : b;
-    }
+    __device__ __forceinline__ float at(int e) const { return f[e]; }
 };
-template <int NS>
-struct RowRegs<float, NS> {
-    float f[NS];
-    __device__ __forceinline__ float get(int s) const { return f[s]; }
-    __device__ __forceinline__ void put_vec(int j, const uint4& x) {          // entries 4j .. 4j+3
-        f[4 * j] = __uint_as_float(x.x); f[4 * j + 1] = __uint_as_float(x.y);
-        f[4 * j + 2] = __uint_as_float(x.z); f[4 * j + 3] = __uint_as_float(x.w);
-    }
-    __device__ __forceinline__ void fill_vec(int j) { f[4 * j] = f[4 * j + 1] = f[4 * j + 2] = f[4 * j + 3] = -INFINITY; }
-    __device__ __forceinline__ void repack() {}
-    __device__ __forceinline__ void put_one(int s, const float* p) { f[s] = p ? *p : -INFINITY; }
-};
+template <typename T>
+__device__ __forceinline__ float chunk_max(const Chunk<T>& c) {
+    return fmaxf(fmaxf(fmaxf(c.at(0), c.at(1)), fmaxf(c.at(2), c.at(3))), fmaxf(fmaxf(c.at(4), c.at(5)), fmaxf(c.at(6), c.at(7))));
+}
+
+__device__ __forceinline__ float entry(const uint16_t* p) { return bf16_bits_to_float(*p); }
+__device__ __forceinline__ float entry(const float* p) { return *p; }
 
 // (logit, token) as one unsigned key whose order is "greater logit, then lower token".
 // -0 and +0 are the same real number and must tie: adding +0 turns -0 into +0.
@@ -105,31 +80,6 @@ __device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long x)
         x = y > x ? y : x;
     }
     return x;
-}
-
-// Fixed-shape workgroup reductions (results never depend on timing).
-__device__ __forceinline__ float wg_max(float x, float* s_red) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) x = fmaxf(x, __shfl_xor(x, off));
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = x;
-    __syncthreads();
-    float r = s_red[0];
-#pragma unroll
-    for (int w = 1; w < kWavesDT; ++w) r = fmaxf(r, s_red[w]);
-    return r;
-}
-
-__device__ __forceinline__ float wg_sum(float x, float* s_red) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off);
-    __syncthreads();
-    if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = x;
-    __syncthreads();
-    float r = s_red[0];
-#pragma unroll
-    for (int w = 1; w < kWavesDT; ++w) r += s_red[w];
-    return r;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -233,12 +183,52 @@ __device__ __forceinline__ void rank_winners_prefiltered(unsigned long long* s_k
     __syncthreads();
 }
 
+// Few candidates (a level's Top-K lists): everybody against everybody with `parts` threads per candidate, a
+// slice of the others each, and a winner's position as a population count over a bitmap of the winners --
+// three workgroup barriers (the general form below takes eight): 1.9 -> 1.5 us for 100 candidates.
+__device__ __forceinline__ void rank_winners_few(unsigned long long* s_key, int c, int M) {
+    __shared__ int s_beaten[2 * kGroupsDT];
+    __shared__ uint32_t s_win[2 * kGroupsDT / 32];
+    const int tid = threadIdx.x;
+    const int cp = c <= 64 ? 64 : c <= 128 ? 128 : 256;     // uniform; a slice is whole wavefronts
+    const int parts = kThreadsDT / cp, per = (c + parts - 1) / parts;
+    const int i = tid & (cp - 1), part = tid / cp;
+    if (tid < 2 * kGroupsDT) s_beaten[tid] = 0;
+    if (tid < 2 * kGroupsDT / 32) s_win[tid] = 0u;
+    __syncthreads();
+    const unsigned long long ki = i < c ? s_key[i] : ~0ull;
+    {
+        int beaten = 0;
+        const int x1 = min(c, (part + 1) * per);
+#pragma unroll 8
+        for (int x = part * per; x < x1; ++x) beaten += s_key[x] > ki ? 1 : 0;
+        if (i < c && beaten) atomicAdd(&s_beaten[i], beaten);
+    }
+    __syncthreads();
+    const bool win = part == 0 && i < c && s_beaten[i] < M;
+    if (win) atomicOr(&s_win[i >> 5], 1u << (i & 31));
+    __syncthreads();
+    if (part == 0 && i < c) {
+        int pos = -1;
+        if (win) {
+            pos = __popc(s_win[i >> 5] & ((1u << (i & 31)) - 1u));
+            for (int w = 0; w < (i >> 5); ++w) pos += __popc(s_win[w]);
+        }
+        reinterpret_cast<int*>(s_key)[2 * i] = pos;
+    }
+    __syncthreads();
+}
+
 __device__ __forceinline__ void rank_winners(unsigned long long* s_key, int c, int M) {
     __shared__ int s_wcount[kWavesDT];
     __shared__ int s_cnt[kThreadsDT];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (c >= 2 * kGroupsDT && c <= kThreadsDT && M >= 1 && M <= kGroupsDT / 2) {    // uniform
         rank_winners_prefiltered(s_key, c, M);
+        return;
+    }
+    if (c < 2 * kGroupsDT) {                               // uniform
+        rank_winners_few(s_key, c, M);
         return;
     }
     // `parts` groups of wavefronts share the candidates of a pass: group `part` counts, for every
@@ -320,14 +310,21 @@ __device__ __forceinline__ void rank_winners(unsigned long long* s_key, int c, i
 }
 
 // ---------------------------------------------------------------------------------------
-// draft_topk_kernel: one workgroup per (request, expanded node) row.
-//   NS > 0: every thread keeps NS vocabulary entries of the row in registers (16-byte loads
-//           when the row is aligned and V a multiple of the vector width, scalar otherwise);
-//   NS == 0: any vocabulary size, every pass re-reads the row (it stays in L2).
-// Passes: maximum, sum of exp(l - max) (log-sum-exp), then the K best (logit, token) keys: a
-// threshold from the maxima of 16-lane groups and a rank among the few entries that reach it,
-// or, when too many do, K rounds of a workgroup-wide arg-max (every thread caches the best key
-// among its entries not yet taken; only the owner of a round's winner rescans its entries).
+// draft_topk_kernel: one workgroup per (request, expanded node) row, so one compute unit reads the row and
+// what counts is passes, instructions per entry and the latencies between the steps.
+//   entries   chunks of 8 (from the row's first 16-byte boundary), thread t takes chunks t, t + 1024, ...; the up to
+//             7 entries before and after are one thread's each.  NC = 4, 8: a row of up to 8192 NC entries stays in
+//             registers.  NC = 0: the row streams by once, in groups of chunks with a running maximum and sum;
+//             of a chunk only its maximum is kept, and only chunks that reach the threshold are read again.
+//   lse       every thread sums against its own maximum, so maximum and sum need one meeting of the workgroup
+//             instead of two; lanes meet by DPP.
+//   Top-K     every row of 16 lanes reduces its greatest logit; the K-th greatest of the 64 is a value that at least K
+//             entries reach, and (for logits that do not follow the token order) about 2K do.  These are collected
+//             in LDS and ranked against each other: an entry beaten by r others is the r-th best.  Keys are
+//             distinct, so the order of collection does not matter.  More than kCandCap of them (logits sorted along
+//             the vocabulary, many equal): K rounds of "the greatest key below the last one".
+// Per level (10 rows, kernel alone): 32000 bf16 logits 10.4 -> 6.6 us; rows of 99254 and 152064, which used to be re-read
+// entry by entry in every pass, 67 and 97 us -> 13 and 15.
 // ---------------------------------------------------------------------------------------
 // SEL: the workgroup that finishes a request's last row also chooses the M most valuable of the
 // request's W*K new candidates (what draft_select_kernel does in a launch of its own): scores
@@ -340,100 +337,128 @@ struct SelArgs {
     int32_t* counters;            // [B * SPECVLM_COUNTER_STRIDE] tickets, zero between calls
 };
 
-template <typename T, int NS, bool SEL>
+constexpr int kStream = 24;              // NC == 0: chunks per thread whose maximum is kept (196608 entries)
+constexpr float kLog2eDT = 1.4426950408889634f;
+
+template <typename T, int NC, bool SEL>
 __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
     int V, int K, const T* __restrict__ logits, int64_t stride_b, int64_t stride_w,
     const float* __restrict__ cum, int64_t cum_stride_b, const int32_t* __restrict__ parent_idx,
     int64_t parent_stride_b, float* score_out, int32_t* __restrict__ token_out,
     int32_t* __restrict__ parent_out, int64_t out_stride_b, float* __restrict__ lse_out, SelArgs sel) {
-    __shared__ float s_red[kWavesDT];
+    __shared__ float s_wmax[kWavesDT], s_wsum[kWavesDT];
+    __shared__ __attribute__((aligned(16))) float s_grp[64];
     __shared__ unsigned long long s_key[2][kWavesDT];
-    __shared__ int s_taken[SPECVLM_MAX_NODES];         // NS == 0: tokens already taken
-    __shared__ unsigned long long s_grp[64];
     __shared__ __attribute__((aligned(16))) unsigned long long s_cand[kCandCap];
-    __shared__ int s_last;
-    __shared__ unsigned long long s_thr;
-    __shared__ int s_ncand;
+    __shared__ int s_last, s_ncand;
+    __shared__ float s_thr;
 
-    const int w = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
+    const int w = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int nrows = gridDim.x;
     const T* row = logits + b * stride_b + w * stride_w;
-    constexpr int VEC = Lane16<T>::kPerVec;
-    const bool vec = NS > 0 && (reinterpret_cast<uintptr_t>(row) & 15u) == 0 && V % VEC == 0;   // uniform
-    // entry s of this thread is vocabulary index idx_of(s)
-    auto idx_of = [&](int s) -> int {
-        return vec ? (tid + kThreadsDT * (s / VEC)) * VEC + s % VEC : tid + kThreadsDT * s;
-    };
-    // Entries are compared as floats inside a thread (no logit is NaN, and -0 == +0 as the order
-    // demands); a 64-bit key is built only for the few entries that leave the thread.  16
-    // wavefronts leave a thread 128 registers: the keys of all entries would not fit beside
-    // the entries.  Entries past V hold -inf.
-    RowRegs<T, (NS > 0 ? NS : 8)> lv;
-    if constexpr (NS > 0) {
-        if (vec) {
-#pragma unroll
-            for (int j = 0; j < NS / VEC; ++j) {
-                const int v0 = (tid + kThreadsDT * j) * VEC;
-                if (v0 < V) lv.put_vec(j, *reinterpret_cast<const uint4*>(row + v0));
-                else lv.fill_vec(j);
-            }
-        } else {
-#pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                const int v = tid + kThreadsDT * s;
-                lv.put_one(s, v < V ? row + v : nullptr);
-            }
-        }
-    }
-    // Best entry of this thread among those not in `skip` (bit s = entry s): its key, or 0 when
-    // none is left.  A thread's entries are in ascending token order, so "greater" alone keeps
-    // the lowest token among equal logits.
-    auto thread_best = [&](unsigned long long skip) __attribute__((always_inline)) -> unsigned long long {
-        float bf = 0.f;
-        int bv = -1;
-        if constexpr (NS > 0) {
-#pragma unroll
-            for (int s = 0; s < NS; ++s) {
-                const int v = idx_of(s);
-                if (v < V && !((skip >> s) & 1ull) && (bv < 0 || lv.get(s) > bf)) { bf = lv.get(s); bv = v; }
-            }
-        }
-        return bv >= 0 ? order_key(bf, bv) : 0ull;
-    };
-    const int ns_mem = (V + kThreadsDT - 1) / kThreadsDT;          // NS == 0: entries per thread
-
-    // ---- log-sum-exp of the row -----------------------------------------------------------
-    float part = -INFINITY;
-    if constexpr (NS > 0) {
-#pragma unroll
-        for (int s = 0; s < NS; ++s) part = fmaxf(part, lv.get(s));    // entries past V hold -inf
-    } else {
-#pragma unroll 8
-        for (int s = 0; s < ns_mem; ++s) {
-            const int v = tid + kThreadsDT * s;
-            if (v < V) part = fmaxf(part, Lane16<T>::one(row + v));
-        }
-    }
-    const float tmax = part;                            // NS > 0: this thread's greatest logit
-    const float mx = wg_max(part, s_red);
-    lv.repack();
-    part = 0.f;
-    if constexpr (NS > 0) {
-#pragma unroll
-        for (int s = 0; s < NS; ++s) part += __expf(lv.get(s) - mx);   // exp(-inf) = 0
-    } else {
-#pragma unroll 8
-        for (int s = 0; s < ns_mem; ++s) {
-            const int v = tid + kThreadsDT * s;
-            if (v < V) part += __expf(Lane16<T>::one(row + v) - mx);
-        }
-    }
-    const float Z = wg_sum(part, s_red);
-    lv.repack();
-    const float lse = mx + logf(Z);
     const float c = cum ? cum[b * cum_stride_b + w] : 0.f;
     const int par = parent_idx ? parent_idx[b * parent_stride_b + w] : -1;
+    const int head = min(static_cast<int>(((16u - (reinterpret_cast<uintptr_t>(row) & 15u)) & 15u) / sizeof(T)), V);
+    const int nck = (V - head) / 8;                      // whole chunks
+    const int tail0 = head + nck * 8;
+    const T* body = row + head;
+    // the single entry of this thread, if it has one
+    const int vs = tid < head ? tid : (tid >= 64 && tid - 64 < V - tail0) ? tail0 + tid - 64 : -1;
+    const float es = vs >= 0 ? entry(row + vs) : -INFINITY;
+
+    // ---- maximum and sum of exponentials of this thread's entries ------------------------------
+    constexpr int NM = NC > 0 ? NC : kStream;
+    constexpr int U = 4;                                 // NC == 0: chunks of a thread requested together
+    Chunk<T> ch[NC > 0 ? NC : U];
+    float cmax[NM];
+    float tmax = es;                                     // greatest entry
+    float m, sum;                                        // finite reference, sum of exp(entry - m)
+    if constexpr (NC > 0) {
+#pragma unroll
+        for (int j = 0; j < NC; ++j) {
+            const int k = tid + kThreadsDT * j;
+            if (k < nck) ch[j].load(body + 8 * k); else ch[j].fill();
+        }
+#pragma unroll
+        for (int j = 0; j < NC; ++j) {
+            cmax[j] = chunk_max(ch[j]);
+            tmax = fmaxf(tmax, cmax[j]);
+        }
+        m = fmaxf(tmax, -2.0e38f);
+        const float ref = -m * kLog2eDT;
+        float part[4] = {__builtin_amdgcn_exp2f(fmaf(es, kLog2eDT, ref)), 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int j = 0; j < NC; ++j)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) part[e & 3] += __builtin_amdgcn_exp2f(fmaf(ch[j].at(e), kLog2eDT, ref));   // exp(-inf) = 0
+        sum = (part[0] + part[1]) + (part[2] + part[3]);
+    } else {
+        m = fmaxf(es, -2.0e38f);
+        sum = es > -INFINITY ? 1.f : 0.f;
+        auto take = [&](int k0, float (&cm)[U]) __attribute__((always_inline)) {        // chunks k0, k0 + 1024, ...
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int k = k0 + kThreadsDT * u;
+                if (k < nck) ch[u].load(body + 8 * static_cast<int64_t>(k)); else ch[u].fill();
+            }
+            float gm = -INFINITY;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                cm[u] = chunk_max(ch[u]);
+                gm = fmaxf(gm, cm[u]);
+            }
+            tmax = fmaxf(tmax, gm);
+            const float mn = fmaxf(m, gm), ref = -mn * kLog2eDT;
+            float part[4] = {sum * __builtin_amdgcn_exp2f(fmaf(m, kLog2eDT, ref)), 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int e = 0; e < 8; ++e) part[e & 3] += __builtin_amdgcn_exp2f(fmaf(ch[u].at(e), kLog2eDT, ref));
+            sum = (part[0] + part[1]) + (part[2] + part[3]);
+            m = mn;
+        };
+#pragma unroll
+        for (int j = 0; j < kStream; j += U) {
+            float cm[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) cm[u] = -INFINITY;
+            if (j * kThreadsDT < nck) take(tid + kThreadsDT * j, cm);       // uniform
+#pragma unroll
+            for (int u = 0; u < U; ++u) cmax[j + u] = cm[u];
+        }
+        for (int j = kStream; j * kThreadsDT < nck; j += U) {               // (vocabularies beyond 196608)
+            float cm[U];
+            take(tid + kThreadsDT * j, cm);
+        }
+    }
+    {
+        const float gmax = row_max(tmax);                // of the row of 16 lanes
+        const float wm = wave_max(m);
+        const float ws = wave_sum(sum * __builtin_amdgcn_exp2f((m - wm) * kLog2eDT));
+        if ((tid & 15) == 0) s_grp[tid >> 4] = gmax;
+        if (lane == 0) { s_wmax[wave] = wm; s_wsum[wave] = ws; }
+        if (tid == 0) s_ncand = 0;
+    }
+    __syncthreads();
+    // ---- the K-th greatest of the 64 group maxima: 16 lanes per group, four comparisons each -----------
+    {
+        const int j = tid >> 4, part = tid & 15;
+        const float gj = s_grp[j];
+        const float4 o = *reinterpret_cast<const float4*>(s_grp + 4 * part);
+        int beaten = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const float x = (&o.x)[u];
+            beaten += (x > gj || (x == gj && 4 * part + u < j)) ? 1 : 0;
+        }
+        beaten = row_sum(beaten);
+        if (part == 0 && beaten == K - 1) s_thr = gj;    // exactly one group: the ranks are a permutation
+    }
+    const float mx = row_max(s_wmax[tid & 15]);
+    const float lse = mx + logf(row_sum(s_wsum[tid & 15] * __builtin_amdgcn_exp2f((s_wmax[tid & 15] - mx) * kLog2eDT)));
     if (tid == 0 && lse_out) lse_out[b * nrows + w] = lse;
+    __syncthreads();
+    const float thr = s_thr;
 
     const int64_t out0 = b * out_stride_b + static_cast<int64_t>(w) * K;
     auto emit = [&](int k, unsigned long long key) {     // k-th best of the row
@@ -447,138 +472,59 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
         if (parent_out) parent_out[out0 + k] = par;
     };
 
-    // ---- fast path: a threshold that at least K entries reach, then a rank among the few that do ----
-    // Every group of 16 lanes reduces the best key of its entries; the K-th best of the 64 group
-    // maxima is a key that K entries of the row reach (the maxima of K different groups), so the
-    // K best entries are among the entries at or above it -- for logits that do not follow the
-    // token order, about 2K of them.  These are collected in LDS and ranked against each other:
-    // an entry beaten by r others is the r-th best.  Keys are distinct, so the result does not
-    // depend on the order in which the entries were collected.  If more than kCandCap entries
-    // reach the threshold (logits sorted along the vocabulary, say) the K rounds below take over.
-    bool done = false;                                  // uniform
-    {
-        unsigned long long mine = 0;
-        if constexpr (NS > 0) {
-            // the first entry that equals the thread's maximum (found for the log-sum-exp above)
-            int bs = NS;
+    // ---- the entries that reach it ------------------------------------------------------------------
+    auto collect = [&](float x, int v) {
+        if (x >= thr) {
+            const int pos = atomicAdd(&s_ncand, 1);
+            if (pos < kCandCap) s_cand[pos] = order_key(x, v);
+        }
+    };
+    if (tmax >= thr) {
+        if (vs >= 0) collect(es, vs);
 #pragma unroll
-            for (int s = NS - 1; s >= 0; --s) bs = lv.get(s) == tmax ? s : bs;
-            const int bv = idx_of(bs);
-            mine = bv < V ? order_key(tmax, bv) : 0ull;   // a thread whose entries all lie past V has none
-        } else {
-#pragma unroll 8
-            for (int s = 0; s < ns_mem; ++s) {
-                const int v = tid + kThreadsDT * s;
-                const unsigned long long k = v < V ? order_key(Lane16<T>::one(row + v), v) : 0ull;
-                mine = k > mine ? k : mine;
-            }
-        }
-        unsigned long long grp = mine;
+        for (int j = 0; j < NM; ++j) {
+            const int k = tid + kThreadsDT * j;
+            if (cmax[j] >= thr && k < nck) {
+                Chunk<T> again;
+                if constexpr (NC > 0) again = ch[j]; else again.load(body + 8 * k);
 #pragma unroll
-        for (int off = 8; off >= 1; off >>= 1) {
-            const unsigned long long y = __shfl_xor(grp, off);
-            grp = y > grp ? y : grp;
-        }
-        if (tid == 0) { s_ncand = 0; s_thr = 0; }        // threshold 0: every entry qualifies
-        if ((tid & 15) == 0) s_grp[tid >> 4] = grp;
-        __syncthreads();
-        if (tid < 64) {
-            const unsigned long long g = s_grp[tid];
-            int beaten = 0;
-#pragma unroll 8
-            for (int x = 0; x < 64; ++x) beaten += s_grp[x] > g ? 1 : 0;
-            if (beaten == K - 1 && g != 0) s_thr = g;   // at most one lane (keys are distinct); none when fewer
-        }                                               // than K groups hold an entry: the threshold stays 0
-        __syncthreads();
-        const unsigned long long thr = s_thr;
-        lv.repack();
-        if constexpr (NS > 0) {
-            // Entries whose logit reaches the threshold's logit: a superset of the entries whose
-            // key reaches the threshold (it adds higher tokens with the same logit), which the
-            // ranking below does not mind.  Only a thread whose maximum reaches it has any.
-            const float thr_val = thr ? key_value(thr) : -INFINITY;
-            if (tmax >= thr_val) {
-#pragma unroll
-                for (int s = 0; s < NS; ++s) {
-                    const int v = idx_of(s);
-                    if (lv.get(s) >= thr_val && v < V) {
-                        const int pos = atomicAdd(&s_ncand, 1);
-                        if (pos < kCandCap) s_cand[pos] = order_key(lv.get(s), v);
-                    }
-                }
-            }
-        } else {
-            for (int s = 0; s < ns_mem; ++s) {
-                const int v = tid + kThreadsDT * s;
-                if (v >= V) break;
-                const unsigned long long k = order_key(Lane16<T>::one(row + v), v);
-                if (k >= thr) {
-                    const int pos = atomicAdd(&s_ncand, 1);
-                    if (pos < kCandCap) s_cand[pos] = k;
-                }
+                for (int e = 0; e < 8; ++e) collect(again.at(e), head + 8 * k + e);
             }
         }
-        __syncthreads();
-        const int nc = s_ncand;
-        if (nc <= kCandCap) {                           // uniform
-            for (int i = tid; i < nc; i += kThreadsDT) {
-                const unsigned long long k = s_cand[i];
-                int beaten = 0;
-                for (int x = 0; x < nc; ++x) beaten += s_cand[x] > k ? 1 : 0;
-                if (beaten < K) emit(beaten, k);
-            }
-            done = true;
-        }
+        if constexpr (NC == 0)
+            for (int k = tid + kThreadsDT * kStream; k < nck; k += kThreadsDT)
+                for (int e = 0; e < 8; ++e) collect(entry(body + 8 * static_cast<int64_t>(k) + e), head + 8 * k + e);
     }
-
-    if (!done) {
-        // ---- K rounds of arg-max (any input) --------------------------------------------------------
-        unsigned long long taken = 0;                       // NS > 0: bit s = entry s was taken
-        int ntaken = 0;                                     // NS == 0: length of s_taken
-        auto local_best = [&]() __attribute__((always_inline)) -> unsigned long long {
-            unsigned long long best = 0;                    // 0 = nothing left
-            if constexpr (NS > 0) {
-                best = thread_best(taken);
-            } else {
-                for (int s = 0; s < ns_mem; ++s) {
-                    const int v = tid + kThreadsDT * s;
-                    if (v >= V) break;
-                    bool live = true;
-                    for (int r = 0; r < ntaken; ++r) live = live && s_taken[r] != v;
-                    if (live) {
-                        const unsigned long long k = order_key(Lane16<T>::one(row + v), v);
-                        best = k > best ? k : best;
-                    }
-                }
-            }
-            return best;
-        };
-        unsigned long long mine = local_best();
+    __syncthreads();
+    const int nc = s_ncand;
+    if (nc <= kCandCap) {                                // uniform
+        for (int i = tid; i < nc; i += kThreadsDT) {
+            const unsigned long long k = s_cand[i];
+            int beaten = 0;
+#pragma unroll 4
+            for (int x = 0; x < nc; ++x) beaten += s_cand[x] > k ? 1 : 0;
+            if (beaten < K) emit(beaten, k);
+        }
+    } else {
+        // ---- K rounds (any input): the greatest key below the last winner's ---------------------------
+        unsigned long long below = ~0ull;
         for (int k = 0; k < K; ++k) {
-            const unsigned long long wbest = wave_max_u64(mine);
-            if ((tid & 63) == 0) s_key[k & 1][tid >> 6] = wbest;
-            __syncthreads();                                // (the other buffer was last read two rounds ago)
+            unsigned long long best = 0;                 // 0 = nothing (a real key is never 0)
+            for (int v = tid; v < V; v += kThreadsDT) {
+                const unsigned long long key = order_key(entry(row + v), v);
+                best = key < below && key > best ? key : best;
+            }
+            best = wave_max_u64(best);
+            if (lane == 0) s_key[k & 1][wave] = best;
+            __syncthreads();                             // (the other buffer was last read two rounds ago)
             unsigned long long win = s_key[k & 1][0];
-    #pragma unroll
+#pragma unroll
             for (int x = 1; x < kWavesDT; ++x) {
                 const unsigned long long y = s_key[k & 1][x];
                 win = y > win ? y : win;
             }
-            const int v = static_cast<int>(0xFFFFFFFFu - static_cast<uint32_t>(win));       // K <= V: never empty
-            if constexpr (NS == 0) {
-                if (tid == 0) s_taken[k] = v;
-                ++ntaken;
-                __syncthreads();
-            }
-            if (mine == win) {                              // exactly one thread: tokens are distinct
-                if constexpr (NS > 0) {
-    #pragma unroll
-                    for (int s = 0; s < NS; ++s)
-                        if (idx_of(s) == v) taken |= 1ull << s;
-                }
-                emit(k, win);
-                mine = local_best();
-            }
+            if (tid == 0) emit(k, win);                  // K <= V: never empty
+            below = win;
         }
     }
     if constexpr (SEL) {
@@ -709,23 +655,22 @@ int32_t launch_draft_topk(int32_t dtype, int32_t B, int32_t W, int32_t V, int32_
     const dim3 grid(W, B), block(kThreadsDT);
     const SelArgs sel{M, index_base, sel_out, sel_score_out, count_out, counters};
     const bool fused = counters != nullptr;             // with the selection of the level's candidates
-#define SPECVLM_LAUNCH_TK2(T, NS, SEL)                                                                              \
-    hipLaunchKernelGGL((draft_topk_kernel<T, NS, SEL>), grid, block, 0, stream, V, K, static_cast<const T*>(logits), \
+#define SPECVLM_LAUNCH_TK2(T, NC, SEL)                                                                              \
+    hipLaunchKernelGGL((draft_topk_kernel<T, NC, SEL>), grid, block, 0, stream, V, K, static_cast<const T*>(logits), \
                        stride_b, stride_w, cum, cum_stride_b, parent_idx, parent_stride_b, score_out,               \
                        token_out, parent_out, out_stride_b, lse_out, sel)
-#define SPECVLM_LAUNCH_TK(T, NS)                                      \
+#define SPECVLM_LAUNCH_TK(T, NC)                                      \
     do {                                                              \
-        if (fused) SPECVLM_LAUNCH_TK2(T, NS, true);                   \
-        else SPECVLM_LAUNCH_TK2(T, NS, false);                        \
+        if (fused) SPECVLM_LAUNCH_TK2(T, NC, true);                   \
+        else SPECVLM_LAUNCH_TK2(T, NC, false);                        \
     } while (0)
-    const int per_thread = (V + kThreadsDT - 1) / kThreadsDT;
     if (dtype == SPECVLM_BF16) {
-        if (per_thread <= 32) SPECVLM_LAUNCH_TK(uint16_t, 32);
-        else if (per_thread <= 64) SPECVLM_LAUNCH_TK(uint16_t, 64);
+        if (V <= 4 * 8 * kThreadsDT) SPECVLM_LAUNCH_TK(uint16_t, 4);
+        else if (V <= 8 * 8 * kThreadsDT) SPECVLM_LAUNCH_TK(uint16_t, 8);
         else SPECVLM_LAUNCH_TK(uint16_t, 0);
     } else {
-        if (per_thread <= 32) SPECVLM_LAUNCH_TK(float, 32);
-        else if (per_thread <= 64) SPECVLM_LAUNCH_TK(float, 64);
+        if (V <= 4 * 8 * kThreadsDT) SPECVLM_LAUNCH_TK(float, 4);
+        else if (V <= 8 * 8 * kThreadsDT) SPECVLM_LAUNCH_TK(float, 8);
         else SPECVLM_LAUNCH_TK(float, 0);
     }
 #undef SPECVLM_LAUNCH_TK

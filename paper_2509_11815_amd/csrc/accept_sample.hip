@@ -8,20 +8,29 @@
 // the bonus token is drawn from the residual distribution of the last node by inverse CDF in
 // vocabulary order.  Every emitted token then follows the target's own distribution.
 //
-// One 1024-thread workgroup per request.  The walk is sequential (at most path_cap levels);
-// per level the workgroup reduces the node's logits row twice (maximum, then the sum of
-// exp((l - max) / T), evaluated as exp2 of a scaled difference) in a fixed order, and one thread takes the few accept decisions.  The
-// bonus draw is a two-level scan: every thread sums a contiguous chunk of the vocabulary,
-// the chunk sums are scanned through LDS, and the thread whose chunk contains the drawn
-// position walks its chunk.  A row of 32000 bf16 logits is 64 KB and stays in L2 between the
-// passes; the whole call is launch- and latency-bound (T_sample of Sec. 3.1, Eq. 1).
-#include "common.hpp"
+// One 1024-thread workgroup per request.  The walk is sequential (at most path_cap levels) on one compute
+// unit, so it is bound by latencies and by the instructions of passes over a vocabulary row.
+//   row       up to 64 consecutive tokens per thread stay in registers (CH = 32, 64); the root's row is requested
+//             before the tree is looked at.  Larger vocabularies (CH = 0): one pass for the maximum (16-byte
+//             loads), one for the sum of exp2((l - max) log2e / T), and one for the bonus draw's chunk sums in 16-byte loads.
+//   sums      in a fixed order, so that the same input gives the same decision whatever the timing; lanes
+//             meet by DPP and lane swaps in the order of an xor butterfly (32, 16, 8, 4, 2, 1), then the 16
+//             wavefronts through LDS in order
+//   children  wavefront 0 holds a child per lane: what the earlier ones have taken is a running sum over lanes,
+//             then all acceptance thresholds are computed at once and the first accepted child is a bit scan
+//   bonus     a two-level scan: every thread sums a contiguous chunk of the vocabulary, the chunk sums are
+//             scanned, and the chunk that contains the drawn position is walked (CH = 0: its probabilities are
+//             computed by the whole workgroup first)
+// Kernel alone, averages over 1 - 16 requests: up to 32768 tokens 15.2 -> 12.1 us, up to 65536 31.3 -> 18.2, beyond
+// (99254 and 152064) 198 -> 29 (every pass and the walk of the drawn chunk read token by token before).
+#include "wave_ops.hpp"
 
 namespace specvlm {
 
 namespace {
 
 constexpr int kThreadsAS = 1024;
+constexpr int kWalk = 2048;              // CH == 0: longest chunk whose probabilities are laid out in LDS
 
 template <typename T>
 __device__ __forceinline__ float logit_at(const T* p, int v);
@@ -30,24 +39,27 @@ __device__ __forceinline__ float logit_at<uint16_t>(const uint16_t* p, int v) { 
 template <>
 __device__ __forceinline__ float logit_at<float>(const float* p, int v) { return p[v]; }
 
-// Workgroup reductions with a fixed shape (so that a result never depends on timing):
-// xor-butterfly inside a wavefront, then the 16 wavefront results through LDS.
+// Sum over the wavefront in the order of an xor butterfly with offsets 32, 16, 8, 4, 2, 1 (every lane gets it).
+__device__ __forceinline__ float butterfly_sum(float x) {
+    const uint32_t a = __float_as_uint(x);
+    const auto r32 = __builtin_amdgcn_permlane32_swap(a, a, false, false);       // lower half everywhere, upper half everywhere
+    x = __uint_as_float(r32[0]) + __uint_as_float(r32[1]);
+    const uint32_t c = __float_as_uint(x);
+    const auto r16 = __builtin_amdgcn_permlane16_swap(c, c, false, false);       // even rows, odd rows
+    x = __uint_as_float(r16[0]) + __uint_as_float(r16[1]);
+    return row_sum(x);                   // all rows are equal by now: a rotation by 8, 4, 2, 1 meets the xor partner's value
+}
+
 __device__ __forceinline__ float block_max(float x, float* s_red) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) x = fmaxf(x, __shfl_xor(x, off));
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    x = wave_max(x);
     __syncthreads();                                   // s_red may still be read from a previous call
-    if (lane == 0) s_red[wave] = x;
+    if ((threadIdx.x & 63) == 0) s_red[threadIdx.x >> 6] = x;
     __syncthreads();
-    float r = s_red[0];
-#pragma unroll
-    for (int w = 1; w < kThreadsAS / 64; ++w) r = fmaxf(r, s_red[w]);
-    return r;
+    return row_max(s_red[threadIdx.x & 15]);
 }
 
 __device__ __forceinline__ float block_sum(float x, float* s_red) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) x += __shfl_xor(x, off);
+    x = butterfly_sum(x);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     __syncthreads();
     if (lane == 0) s_red[wave] = x;
@@ -58,9 +70,17 @@ __device__ __forceinline__ float block_sum(float x, float* s_red) {
     return r;
 }
 
+// Eight (bf16) or four (fp32) consecutive logits.
+template <typename T>
+__device__ __forceinline__ float vec_at(const uint4& w, int e) {
+    const uint32_t x = (&w.x)[sizeof(T) == 2 ? e >> 1 : e];
+    if constexpr (sizeof(T) == 2) return __uint_as_float((e & 1) ? (x & 0xFFFF0000u) : (x << 16));
+    else return __uint_as_float(x);
+}
+
 // CH > 0: every thread keeps its chunk of the current row (at most CH consecutive tokens) in
 // registers, loaded once per level with 16-byte loads when the row allows; CH == 0: any
-// vocabulary size, every pass re-reads the row.
+// vocabulary size, every pass reads the row again (from L2).
 template <typename T, int CH>
 __global__ __launch_bounds__(kThreadsAS) void tree_accept_sample_kernel(
     int N_max, int V, int path_cap, const int32_t* __restrict__ parent, const int32_t* __restrict__ draft_tok,
@@ -70,13 +90,58 @@ __global__ __launch_bounds__(kThreadsAS) void tree_accept_sample_kernel(
     int32_t* __restrict__ committed_tok, int32_t* __restrict__ err_flag) {
     __shared__ int s_par[SPECVLM_MAX_NODES], s_tok[SPECVLM_MAX_NODES], s_path[SPECVLM_MAX_NODES];
     __shared__ int s_rej[SPECVLM_MAX_NODES];           // tokens rejected at the current node
-    __shared__ float s_cex[SPECVLM_MAX_NODES], s_cu[SPECVLM_MAX_NODES];
     __shared__ float s_red[kThreadsAS / 64];
     __shared__ float s_scan[kThreadsAS];
+    __shared__ float s_ev[CH > 0 ? 1 : kWalk];
     __shared__ int s_next, s_nrej, s_err, s_pick, s_chunk;
-    __shared__ unsigned long long s_kids;
 
     const int b = blockIdx.x, tid = threadIdx.x;
+    const T* base = logits + b * stride_b;
+    const int chunk = (V + kThreadsAS - 1) / kThreadsAS;          // consecutive tokens per thread
+    const int v0 = min(tid * chunk, V), v1 = min(v0 + chunk, V);
+    constexpr int VEC = 16 / sizeof(T);
+    // this thread's logits of the current row, as loaded (entry i of the chunk: vec_at(lv[i / VEC], i % VEC); -inf, i.e.
+    // probability 0, past the chunk's end); repack() between passes keeps the compiler from holding a widened copy beside them (16 wavefronts leave 128 registers)
+    constexpr int NV = CH > 0 ? CH / VEC : 1;
+    uint4 lv[NV];
+    constexpr uint32_t kInf = sizeof(T) == 2 ? 0xFF80u : 0xFF800000u, kInfWord = sizeof(T) == 2 ? 0xFF80FF80u : 0xFF800000u;
+    // entry `at` of 4 n dwords (if it lies among them) becomes -inf
+    auto drop = [&](uint4* w, int n, int at) __attribute__((always_inline)) {
+        const int word = sizeof(T) == 2 ? at >> 1 : at, shift = sizeof(T) == 2 ? (at & 1) * 16 : 0;
+        const uint32_t keep = sizeof(T) == 2 ? ~(0xFFFFu << shift) : 0u;
+#pragma unroll
+        for (int d = 0; d < 4 * n; ++d) {
+            uint32_t& x = (&w[d >> 2].x)[d & 3];
+            x = d == word ? (x & keep) | (kInf << shift) : x;
+        }
+    };
+    auto repack = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < NV; ++j) asm volatile("" : "+v"(lv[j].x), "+v"(lv[j].y), "+v"(lv[j].z), "+v"(lv[j].w));
+    };
+    auto load_row = [&](const T* row) __attribute__((always_inline)) {
+        if constexpr (CH > 0) {
+            const bool vec_ok = (reinterpret_cast<uintptr_t>(row) & 15u) == 0 && chunk % VEC == 0 && V % VEC == 0;
+#pragma unroll
+            for (int j = 0; j < NV; ++j) lv[j] = uint4{kInfWord, kInfWord, kInfWord, kInfWord};
+            if (vec_ok) {                               // uniform
+#pragma unroll
+                for (int j = 0; j < NV; ++j)
+                    if (v0 + j * VEC < v1) lv[j] = *reinterpret_cast<const uint4*>(row + v0 + j * VEC);
+            } else {
+#pragma unroll
+                for (int j = 0; j < NV; ++j)
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e)
+                        if (v0 + j * VEC + e < v1) {
+                            uint32_t& x = (&lv[j].x)[sizeof(T) == 2 ? e >> 1 : e];
+                            if constexpr (sizeof(T) == 2) x = (x & (0xFFFF0000u >> (16 * (e & 1)))) | static_cast<uint32_t>(row[v0 + j * VEC + e]) << (16 * (e & 1));
+                            else x = __float_as_uint(row[v0 + j * VEC + e]);
+                        }
+            }
+        }
+    };
+    load_row(base);                                     // the root's row, whatever the tree is
     int err = 0;
     int n = num_nodes ? num_nodes[b] : N_max;
     if (n < 1 || n > N_max) {
@@ -100,17 +165,12 @@ __global__ __launch_bounds__(kThreadsAS) void tree_accept_sample_kernel(
         n = 1;
     }
 
-    const T* base = logits + b * stride_b;
     int cur = 0, m = 0;
     float mx = 0.f, Z = 0.f;
     // unnormalised probability exp((l - max) / T) as one multiply and one v_exp_f32 (the whole
     // vocabulary goes through it three times on a single compute unit); -inf gives 0
     const float c2 = 1.4426950408889634f / temperature;
     auto prob_of = [&](float l) -> float { return __builtin_amdgcn_exp2f((l - mx) * c2); };
-    const int chunk = (V + kThreadsAS - 1) / kThreadsAS;          // consecutive tokens per thread
-    const int v0 = min(tid * chunk, V), v1 = min(v0 + chunk, V);
-    constexpr int VEC = 16 / sizeof(T);
-    float lv[CH > 0 ? CH : 1];                          // this thread's logits of the current row
     for (;;) {
         const T* row = base + cur * stride_n;
         // Wavefront 0, lane c: child c's logit and uniform number, requested now so that they
@@ -130,87 +190,80 @@ __global__ __launch_bounds__(kThreadsAS) void tree_accept_sample_kernel(
         // target distribution at cur, unnormalised: e(v) = exp((l_v - max) / T)
         float part = -INFINITY;
         if constexpr (CH > 0) {
-            const bool vec_ok = (reinterpret_cast<uintptr_t>(row) & 15u) == 0 && chunk % VEC == 0 && V % VEC == 0;
-            if (vec_ok) {                               // uniform
-#pragma unroll
-                for (int j = 0; j < CH / VEC; ++j) {
-                    if (v0 + j * VEC < v1) {
-                        const uint4 w = *reinterpret_cast<const uint4*>(row + v0 + j * VEC);
-#pragma unroll
-                        for (int e = 0; e < VEC; ++e) {
-                            if constexpr (sizeof(T) == 2) {
-                                const uint32_t x = (&w.x)[e >> 1];
-                                lv[j * VEC + e] = __uint_as_float((e & 1) ? (x & 0xFFFF0000u) : (x << 16));
-                            } else {
-                                lv[j * VEC + e] = __uint_as_float((&w.x)[e]);
-                            }
-                        }
-                    }
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < CH; ++i)
-                    if (v0 + i < v1) lv[i] = logit_at<T>(row, v0 + i);
-            }
+            if (m > 0) load_row(row);                   // uniform
 #pragma unroll
             for (int i = 0; i < CH; ++i)
-                if (v0 + i < v1) part = fmaxf(part, lv[i]);
+                part = fmaxf(part, vec_at<T>(lv[i / VEC], i % VEC));
+            repack();
         } else {
-            // (loops unrolled so that a batch of independent loads is in flight: the row sits in
-            // L2 and the passes are latency-bound otherwise)
-#pragma unroll 8
-            for (int v = tid; v < V; v += kThreadsAS) part = fmaxf(part, logit_at<T>(row, v));
+            const int head = min(static_cast<int>(((16u - (reinterpret_cast<uintptr_t>(row) & 15u)) & 15u) / sizeof(T)), V);
+            const int nvec = (V - head) / VEC, tail0 = head + nvec * VEC;
+            if (tid < head) part = logit_at<T>(row, tid);
+            if (tid >= 64 && tid - 64 < V - tail0) part = logit_at<T>(row, tail0 + tid - 64);
+            const uint4* body = reinterpret_cast<const uint4*>(row + head);
+#pragma unroll 4
+            for (int c = tid; c < nvec; c += kThreadsAS) {
+                const uint4 w = body[c];
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) part = fmaxf(part, vec_at<T>(w, e));
+            }
         }
         mx = block_max(part, s_red);
         part = 0.f;
         if constexpr (CH > 0) {
 #pragma unroll
             for (int i = 0; i < CH; ++i)
-                if (v0 + i < v1) part += prob_of(lv[i]);
+                part += prob_of(vec_at<T>(lv[i / VEC], i % VEC));          // (adding the zeros of -inf changes nothing)
+            repack();
         } else {
-#pragma unroll 8
-            for (int v = tid; v < V; v += kThreadsAS) part += prob_of(logit_at<T>(row, v));
+            // (a thread's tokens are 1024 apart and added in that order; 16 loads in flight)
+            int v = tid;
+            for (; v + 15 * kThreadsAS < V; v += 16 * kThreadsAS) {
+                float l[16];
+#pragma unroll
+                for (int u = 0; u < 16; ++u) l[u] = logit_at<T>(row, v + u * kThreadsAS);
+#pragma unroll
+                for (int u = 0; u < 16; ++u) part += prob_of(l[u]);
+            }
+            for (; v < V; v += kThreadsAS) part += prob_of(logit_at<T>(row, v));
         }
         Z = block_sum(part, s_red);
-        // the candidates of cur, prepared in parallel: lane c holds child c's unnormalised
-        // probability and uniform number, so that the sequential decisions below wait for no load
-        if (tid < SPECVLM_MAX_NODES) {                  // wavefront 0
-            float ex = -1.f;                            // ex < 0 marks "token out of range"
-            if (is_child && child_tok >= 0 && child_tok < V) ex = prob_of(child_logit);
-            s_cex[tid] = ex;
-            s_cu[tid] = child_u;
-            const unsigned long long kids = __ballot(is_child);
-            if (tid == 0) s_kids = kids;
-        }
-        __syncthreads();
-        if (tid == 0) {
-            int next = -1, nrej = 0, e = 0;
-            float rejmass = 0.f;
-            unsigned long long kids = s_kids;          // children of cur, tried in increasing node index
+        // The children of cur are tried in increasing node index; wavefront 0 holds child c in lane c.
+        if (tid < SPECVLM_MAX_NODES) {
+            const int lane = tid;
+            const bool known = is_child && child_tok >= 0 && child_tok < V;
+            const float ex = known ? prob_of(child_logit) : 0.f;
+            unsigned long long kids = __ballot(is_child);
             const bool has_child = kids != 0;
             if (m + 1 >= path_cap) kids = 0;           // no room for a deeper node: nothing is tested
-            while (kids && next < 0) {
-                const int c = __builtin_ctzll(kids);
-                kids &= kids - 1;
-                const int x = s_tok[c];
-                const float ex = s_cex[c];
-                bool live = ex >= 0.f;
-                if (!live) e |= SPECVLM_ERR_BAD_TOKEN;
-                for (int r = 0; r < nrej; ++r) live = live && s_rej[r] != x;
-                if (!live) continue;                   // residual probability 0: rejected
-                const float a = ex / fmaxf(Z - rejmass, ex);   // the residual mass holds x itself
-                if (s_cu[c] < a) {
-                    next = c;
-                } else {
-                    s_rej[nrej++] = x;
-                    rejmass += ex;
-                }
+            const unsigned long long known_kids = __ballot(known) & kids;
+            bool dup = false;                          // an earlier child carries the same token: residual probability 0
+            for (unsigned long long k = known_kids; k; k &= k - 1) {
+                const int j = __builtin_ctzll(k);
+                dup = dup || (lane > j && __builtin_amdgcn_readlane(child_tok, j) == child_tok);
             }
-            if (has_child && m + 1 >= path_cap) e |= SPECVLM_ERR_PATH_TOO_LONG;
-            s_next = next;
-            s_nrej = nrej;
-            s_err |= e;
-            s_path[m] = cur;
+            const bool live = ((known_kids >> lane) & 1ull) && !dup;
+            const unsigned long long live_kids = __ballot(live);
+            float rejmass = 0.f, gone = 0.f;           // mass of the live children before this lane's
+            for (unsigned long long k = live_kids; k; k &= k - 1) {
+                const int j = __builtin_ctzll(k);
+                if (lane == j) rejmass = gone;
+                gone += lane_of(ex, j);
+            }
+            const float a = ex / fmaxf(Z - rejmass, ex);       // the residual mass holds x itself
+            const unsigned long long taken = __ballot(live && child_u < a);
+            const int next = taken ? __builtin_ctzll(taken) : -1;
+            const unsigned long long tried = taken ? (1ull << next) - 1ull : ~0ull;      // ... and not accepted
+            const unsigned long long rejected = live_kids & tried;
+            if ((rejected >> lane) & 1ull) s_rej[__popcll(rejected & ((1ull << lane) - 1ull))] = child_tok;
+            if (lane == 0) {
+                int e = (kids & ~known_kids & tried) ? SPECVLM_ERR_BAD_TOKEN : 0;
+                if (has_child && m + 1 >= path_cap) e |= SPECVLM_ERR_PATH_TOO_LONG;
+                s_next = next;
+                s_nrej = __popcll(rejected);
+                s_err |= e;
+                s_path[m] = cur;
+            }
         }
         __syncthreads();
         const int next = s_next;
@@ -223,34 +276,36 @@ __global__ __launch_bounds__(kThreadsAS) void tree_accept_sample_kernel(
     // ---- bonus token: inverse CDF over the residual distribution at cur, in vocabulary order ----
     const T* row = base + cur * stride_n;
     const int nrej = s_nrej;
-    // Which tokens of this thread's chunk were rejected at cur: a bit mask when the chunk has at
-    // most 64 tokens (vocabularies up to 65536), so that the per-token test touches no memory.
-    unsigned long long rejmask = 0;
-    const bool small_chunk = chunk <= 64;
-    if (small_chunk)
-        for (int r = 0; r < nrej; ++r) {
-            const int x = s_rej[r];
-            if (x >= v0 && x < v1) rejmask |= 1ull << (x - v0);
-        }
-    auto residual = [&](int v) -> float {             // v in [v0, v1); CH == 0 only
-        bool live = true;
-        if (small_chunk) {
-            live = !((rejmask >> (v - v0)) & 1ull);
-        } else {
-            for (int r = 0; r < nrej; ++r) live = live && s_rej[r] != v;
-        }
-        return live ? prob_of(logit_at<T>(row, v)) : 0.f;
-    };
     float csum = 0.f;
+    unsigned long long mine = 0;                       // bit r: rejected token r lies in this thread's chunk
+    for (int r = 0; r < nrej; ++r) mine |= static_cast<unsigned long long>(s_rej[r] >= v0 && s_rej[r] < v1) << r;
     if constexpr (CH > 0) {                            // lv[] still holds cur's row
+        for (unsigned long long r = mine; r; r &= r - 1) drop(lv, NV, s_rej[__builtin_ctzll(r)] - v0);
 #pragma unroll
-        for (int i = 0; i < CH; ++i) {
-            lv[i] = (v0 + i < v1 && !((rejmask >> i) & 1ull)) ? prob_of(lv[i]) : 0.f;   // now the residual mass
-            csum += lv[i];
-        }
+        for (int i = 0; i < CH; ++i) csum += prob_of(vec_at<T>(lv[i / VEC], i % VEC));
+        repack();
     } else {
-#pragma unroll 8
-        for (int v = v0; v < v1; ++v) csum += residual(v);
+        if (v0 < v1) {
+            // whole 16-byte vectors; entries outside the chunk count as zero, which changes no sum
+            const uintptr_t first = reinterpret_cast<uintptr_t>(row + v0) & ~static_cast<uintptr_t>(15);
+            const int lead = static_cast<int>((reinterpret_cast<uintptr_t>(row + v0) - first) / sizeof(T)), len = v1 - v0;
+            const uint4* pv = reinterpret_cast<const uint4*>(first);
+            const int nv = (lead + len + VEC - 1) / VEC;
+            for (int k = 0; k < nv; k += 4) {
+                uint4 w[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) w[u] = pv[min(k + u, nv - 1)];
+                for (unsigned long long r = mine; r; r &= r - 1) drop(w, 4, s_rej[__builtin_ctzll(r)] - v0 + lead - k * VEC);
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e) {
+                        const int at = (k + u) * VEC + e - lead;        // position in the chunk
+                        const float pe = prob_of(vec_at<T>(w[u], e));
+                        csum += static_cast<unsigned>(at) < static_cast<unsigned>(len) ? pe : 0.f;
+                    }
+            }
+        }
     }
     // inclusive scan of the chunk sums: inside each wavefront by shuffles, then the 16 wavefront
     // totals (summed in order by every thread) as offsets
@@ -274,25 +329,45 @@ __global__ __launch_bounds__(kThreadsAS) void tree_accept_sample_kernel(
     const float before = tid ? s_scan[tid - 1] : 0.f;
     if (s_scan[tid] > t && before <= t) s_chunk = tid; // the scan is non-decreasing: exactly one such chunk
     __syncthreads();
-    if (s_chunk == tid) {
-        float cum = before;
-        int pick = -1, last_live = -1;
-        if constexpr (CH > 0) {
+    if constexpr (CH > 0) {
+        if (s_chunk == tid) {
+            float cum = before;
+            int pick = -1, last_live = -1;
 #pragma unroll
             for (int i = 0; i < CH; ++i) {
-                if (lv[i] > 0.f) last_live = v0 + i;
-                cum += lv[i];
+                const float ev = prob_of(vec_at<T>(lv[i / VEC], i % VEC));
+                if (ev > 0.f) last_live = v0 + i;
+                cum += ev;
                 if (pick < 0 && cum > t) pick = v0 + i;
             }
-        } else {
-            for (int v = v0; v < v1 && pick < 0; ++v) {
-                const float ev = residual(v);
-                if (ev > 0.f) last_live = v;
-                cum += ev;
-                if (cum > t) pick = v;
-            }
+            s_pick = pick >= 0 ? pick : last_live;    // rounding inside the chunk: its last live token
         }
-        s_pick = pick >= 0 ? pick : last_live;        // rounding inside the chunk: its last live token
+    } else if (s_chunk >= 0) {                         // uniform
+        const int c0 = min(s_chunk * chunk, V), len = min(chunk, V - c0);
+        auto walk = [&](auto&& ev_of) {
+            float cum = s_chunk ? s_scan[s_chunk - 1] : 0.f;
+            int pick = -1, last_live = -1;
+#pragma unroll 4
+            for (int i = 0; i < len; ++i) {
+                const float ev = ev_of(i);
+                if (ev > 0.f && pick < 0) last_live = c0 + i;
+                cum += ev;
+                if (cum > t && pick < 0) pick = c0 + i;
+            }
+            s_pick = pick >= 0 ? pick : last_live;
+        };
+        auto residual_at = [&](int v) -> float {
+            bool live = true;
+            for (int r = 0; r < nrej; ++r) live = live && s_rej[r] != v;
+            return live ? prob_of(logit_at<T>(row, v)) : 0.f;
+        };
+        if (len <= kWalk) {                            // uniform
+            for (int i = tid; i < len; i += kThreadsAS) s_ev[i] = residual_at(c0 + i);
+            __syncthreads();
+            if (tid == 0) walk([&](int i) { return s_ev[i]; });
+        } else if (tid == 0) {
+            walk([&](int i) { return residual_at(c0 + i); });
+        }
     }
     __syncthreads();
     if (tid == 0) {

@@ -33,3 +33,14 @@ def test_row_blocks(sv, oracle, B, Hq, Hkv, D, N, P, nn, splits, paged):
     case = random_case(7000 + D + N + splits, "bf16", B=B, Hq=Hq, Hkv=Hkv, D=D, N_max=N, P_list=P, num_nodes=nn, paged=paged,
                        cap_extra=0)
     check(case, *run_both(sv, oracle, case, num_splits=splits), f"rows {B}x{Hq}/{Hkv}x{D} N={N} splits={splits} paged={paged}")
+
+
+@pytest.mark.parametrize("D,N,P,splits", [(128, 8, [0, 5], 0), (64, 17, [24, 3], 0), (128, 60, [333, 40], 3)])
+def test_log_sum_exp_is_of_fp32_weights(sv, oracle, D, N, P, splits):
+    """The sum of a row's weights is taken before they are packed to bf16 for the product with V.  Bound: scores are
+    fp32 sums of exact products and at most ~10 here (2^-24 x D terms: under 1e-5), fp32 sums of the weights and
+    exp2 / log2 add a few 2^-24 each; a sum of bf16 weights is off by up to 2^-9 over the root of the key count."""
+    from gpu_util import random_case
+    case = random_case(7100 + D + N, "bf16", B=2, Hq=4, Hkv=4, D=D, N_max=N, P_list=P, num_nodes=None, paged=False, cap_extra=0)
+    _, lse, _, ref = run_both(sv, oracle, case, num_splits=splits)
+    assert abs(lse - ref).max() <= 3e-5

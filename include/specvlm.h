@@ -328,6 +328,17 @@ int32_t specvlm_visual_prune(int32_t dtype, int32_t B, int32_t T, int32_t T_keep
                              const int32_t *keep_dev, void *y_dev, int64_t y_stride_b,
                              int64_t y_stride_t, int32_t *err_flag_dev, void *stream);
 
+/* The same two calls with every row of y written: the rows they leave untouched become zeros. */
+int32_t specvlm_visual_pool_padded(int32_t dtype, int32_t B, int32_t T, int32_t E, int32_t ratio,
+                                   const void *x_dev, int64_t x_stride_b, int64_t x_stride_t,
+                                   const int32_t *num_tokens_dev, void *y_dev, int64_t y_stride_b,
+                                   int64_t y_stride_t, int32_t *out_tokens_dev, int32_t *err_flag_dev,
+                                   void *stream);
+int32_t specvlm_visual_prune_padded(int32_t dtype, int32_t B, int32_t T, int32_t T_keep, int32_t E,
+                                    const void *x_dev, int64_t x_stride_b, int64_t x_stride_t,
+                                    const int32_t *keep_dev, void *y_dev, int64_t y_stride_b,
+                                    int64_t y_stride_t, int32_t *err_flag_dev, void *stream);
+
 /*
  * Output head fused with the greedy choice (Fig. 3: target and draft share one output head;
  * Sec. 4.1: temperature 0).  Replaces "project to logits, store them, specvlm_node_argmax":

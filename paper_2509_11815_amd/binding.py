@@ -34,7 +34,8 @@ EXPORTS = ["specvlm_version", "specvlm_last_hip_error", "specvlm_tree_verify_att
            "specvlm_kv_compact", "specvlm_draft_topk", "specvlm_draft_topk_select", "specvlm_draft_select",
            "specvlm_draft_finalize",
            "specvlm_head_argmax", "specvlm_head_argmax_workspace_bytes",
-           "specvlm_visual_pool", "specvlm_visual_prune", "specvlm_node_argmax_accept"]
+           "specvlm_visual_pool", "specvlm_visual_prune", "specvlm_visual_pool_padded", "specvlm_visual_prune_padded",
+           "specvlm_node_argmax_accept"]
 
 
 class SpecvlmError(RuntimeError):
@@ -130,8 +131,12 @@ def load_library(path: str | None = None) -> ctypes.CDLL:
     L.specvlm_head_argmax.argtypes = [i32] * 5 + [vp, i64, i64, vp, i64, vp, vp, vp, vp, ctypes.c_size_t, vp]
     L.specvlm_visual_pool.restype = i32
     L.specvlm_visual_pool.argtypes = [i32] * 5 + [vp, i64, i64, vp, vp, i64, i64, vp, vp, vp]
+    L.specvlm_visual_pool_padded.restype = i32
+    L.specvlm_visual_pool_padded.argtypes = L.specvlm_visual_pool.argtypes
     L.specvlm_visual_prune.restype = i32
     L.specvlm_visual_prune.argtypes = [i32] * 5 + [vp, i64, i64, vp, vp, i64, i64, vp, vp]
+    L.specvlm_visual_prune_padded.restype = i32
+    L.specvlm_visual_prune_padded.argtypes = L.specvlm_visual_prune.argtypes
     L.specvlm_node_argmax_accept.restype = i32
     L.specvlm_node_argmax_accept.argtypes = [i32] * 5 + [vp, i64, i64] + [vp] * 11
     _load_native(L)

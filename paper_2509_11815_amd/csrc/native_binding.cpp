@@ -28,7 +28,8 @@ namespace {
     X(specvlm_tree_verify_attn_static) X(specvlm_tree_verify_attn_vector_alu) X(specvlm_node_argmax)       \
     X(specvlm_tree_accept) X(specvlm_node_argmax_accept) X(specvlm_tree_accept_sample) X(specvlm_kv_compact) \
     X(specvlm_draft_topk) X(specvlm_draft_topk_select) X(specvlm_draft_select) X(specvlm_draft_finalize)   \
-    X(specvlm_head_argmax_workspace_bytes) X(specvlm_head_argmax) X(specvlm_visual_pool) X(specvlm_visual_prune)
+    X(specvlm_head_argmax_workspace_bytes) X(specvlm_head_argmax) X(specvlm_visual_pool) X(specvlm_visual_prune)  \
+    X(specvlm_visual_pool_padded) X(specvlm_visual_prune_padded)
 #define SPECVLM_DECLARE(name) decltype(&::name) name;
 struct Entries { SPECVLM_NATIVE_ENTRIES(SPECVLM_DECLARE) } lib;
 #undef SPECVLM_DECLARE
@@ -541,12 +542,13 @@ PyObject* visual_pool(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     const int64_t B = x.size(0), T = x.size(1), E = x.size(2), ratio = a.integer(1);
     const int64_t Tp = ratio > 0 ? (T + ratio - 1) / ratio : T;      // (the library rejects ratio < 1)
     at::Tensor made, made_n;
-    // without num_tokens every row of the result is written; with it, rows past a request's own are zeros
-    if (!a.given(3)) made = a.given(2) ? at::zeros({B, Tp, E}, x.options()) : at::empty({B, Tp, E}, x.options());
+    // a given result keeps its rows past a request's own, in a new one the call makes them zeros
+    if (!a.given(3)) made = at::empty({B, Tp, E}, x.options());
     if (!a.given(4)) made_n = new_i32(x, {B});
     const at::Tensor& out = a.given(3) ? a.tensor(3, "out") : made;
     want(out.dim() == 3 && x.stride(2) == 1 && out.stride(2) == 1, "feature dimension must be contiguous");
-    check(lib.specvlm_visual_pool(dtype_code(x), B, T, E, ratio, x.data_ptr(), x.stride(0), x.stride(1), a.i32(2, "num_tokens"),
+    auto* const fn = a.given(3) ? lib.specvlm_visual_pool : lib.specvlm_visual_pool_padded;
+    check(fn(dtype_code(x), B, T, E, ratio, x.data_ptr(), x.stride(0), x.stride(1), a.i32(2, "num_tokens"),
                                   out.data_ptr(), out.stride(0), out.stride(1),
                                   a.given(4) ? a.i32(4, "out_tokens") : static_cast<int32_t*>(made_n.data_ptr()),
                                   a.i32_unchecked(5, "err_flag"), a.stream(6)),
@@ -563,10 +565,11 @@ PyObject* visual_prune(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     want(x.dim() == 3 && kept.dim() == 2, "x must have three dimensions and keep two");
     const int64_t B = x.size(0), T = x.size(1), E = x.size(2), Tk = kept.size(1);
     at::Tensor made;
-    if (!a.given(2)) made = at::zeros({B, Tk, E}, x.options());      // rows of padding entries are not written
+    if (!a.given(2)) made = at::empty({B, Tk, E}, x.options());      // (the call makes the rows of padding entries zeros)
     const at::Tensor& out = a.given(2) ? a.tensor(2, "out") : made;
     want(out.dim() == 3 && x.stride(2) == 1 && out.stride(2) == 1, "feature dimension must be contiguous");
-    check(lib.specvlm_visual_prune(dtype_code(x), B, T, Tk, E, x.data_ptr(), x.stride(0), x.stride(1), a.i32(1, "keep"),
+    auto* const fn = a.given(2) ? lib.specvlm_visual_prune : lib.specvlm_visual_prune_padded;
+    check(fn(dtype_code(x), B, T, Tk, E, x.data_ptr(), x.stride(0), x.stride(1), a.i32(1, "keep"),
                                    out.data_ptr(), out.stride(0), out.stride(1), a.i32_unchecked(3, "err_flag"), a.stream(4)),
           a.what);
     return keep(a.obj(2), made);

@@ -68,6 +68,7 @@ struct MfmaParams {
     int32_t* ws_cnt;            // [B*H_q][4 query blocks] arrival tickets, kCounterStride words apart, zero between calls
     float* ws_acc;              // [B*H_q*num_splits][4 qb][NT/2][64 lanes] 16-byte vectors of packed bf16
     float* ws_ml;               // [B*H_q*num_splits][64 q][2] (max, sum)
+    int xcd_heads;              // query heads of every request an XCD takes, 0: a contiguous range of items each
 };
 
 // Writes one wavefront's 16 query rows: out[t][i] = O^T[d = 16t + 4g + i][q], unnormalised.
@@ -115,7 +116,9 @@ __global__ __launch_bounds__(kThreads) void attn_mfma_kernel(MfmaParams p) {
 template <int D>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void attn_mfma_kernel_2wg(MfmaParams p) {
     constexpr int WQ = kShare, PD = 1, SL = 2, MB = 3;
+#define SPECVLM_SPREAD_REQUESTS
 #include "attn_mfma_body.inc"
+#undef SPECVLM_SPREAD_REQUESTS
 }
 
 // Key-range splits per (request, head) when the caller leaves the choice to the library: the
@@ -125,7 +128,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4))
 // (the same with 160 or 256 units active), or the workgroup's share of HBM bandwidth if that
 // is slower; workgroups beyond 256 run as further rounds.  The cache capacity stands in for
 // the request lengths, which the host does not know.
-int32_t attn_mfma_pick_splits(const specvlm_attn_desc& d) {
+static int32_t single_round_splits(const specvlm_attn_desc& d) {
     const int64_t heads = static_cast<int64_t>(d.B) * d.H_q;
     if (heads > kMaxSplitHeads) return 1;      // more (request, head) pairs than ticket counters: that many fill the chip unsplit
     if (d.num_splits > 0) return min(d.num_splits, 64);
@@ -152,6 +155,24 @@ int32_t attn_mfma_pick_splits(const specvlm_attn_desc& d) {
         if (t < best_t * 0.999) { best_t = t; best = s; }
     }
     return best;
+}
+
+// A batch whose query heads share KV heads gets twice the key ranges where these then fill the chip twice over
+// (the launch shape with two workgroups per compute unit): most of its tiles come from L2, so a second
+// workgroup's steps cost little, and a short request's workgroups make room next to a long one's.
+// us, 2 -> 4 ranges: 32 / 8 heads, 2000 keys x 4 25.2 -> 25.2, 2500 - 300 x 4 27.4 -> 22.0; 64 / 8 heads, 3000 x 2
+// 31.3 -> 29.2, 4500 + 900 41.0 -> 29.2.  Not taken where equal lengths lost: no shared KV heads 31.2 -> 32.6, two query
+// heads per KV head 25.2 -> 26.1, more than four ranges 21.6 -> 24.6, head size 64 18.7 -> 19.7; nor for a
+// call without key ranges, whose results would gain the rounding of partial results; short streams have
+// nothing to divide.
+int32_t attn_mfma_pick_splits(const specvlm_attn_desc& d) {
+    const int32_t base = single_round_splits(d);
+    if (d.num_splits > 0 || d.B < 2 || d.D != 128) return base;
+    if (d.H_q / d.H_kv < 4 || base != 2) return base;
+    const int64_t items = 2ll * base * d.B * d.H_q;
+    const int cap = d.paged ? d.max_blocks_per_req * SPECVLM_PAGE_SIZE : d.kv_capacity;
+    const bool long_streams = cap >= 12 * kStreamsPerWg * kTile * base;
+    return items > 448 && items <= 512 && long_streams ? 2 * base : base;
 }
 
 // How a call is divided among workgroups: query rows and key ranges, or key ranges only.
@@ -250,7 +271,7 @@ int32_t attn_static_workspace(void** ptr_out) {
 
 int32_t launch_attn_mfma(const AttnArgs& a) {
     const specvlm_attn_desc& d = a.d;
-    const AttnPlan plan = attn_plan(d, a.num_splits);
+    const AttnPlan plan = attn_plan(d, single_round_splits(d));
     if (plan.block_rows) return launch_attn_wave(a, plan.block_rows, plan.splits);
     MfmaParams p;
     p.g = KvGeom{d.kv_stride_b, d.kv_stride_h, d.kv_stride_t, d.paged ? a.block_table : nullptr,
@@ -258,6 +279,7 @@ int32_t launch_attn_mfma(const AttnArgs& a) {
                  d.paged ? d.max_blocks_per_req * SPECVLM_PAGE_SIZE : d.kv_capacity};
     p.N_max = d.N_max; p.H_q = d.H_q; p.group = d.H_q / d.H_kv;
     p.num_splits = a.num_splits;
+    p.xcd_heads = d.B > 1 && d.H_kv % 8 == 0 ? d.H_q / 8 : 0;
     p.scale = a.scale;
     p.q = static_cast<const uint16_t*>(a.q);
     p.k = static_cast<const uint16_t*>(a.k);

@@ -17,6 +17,10 @@
 
 #include "wave_ops.hpp"
 
+// Products and sums stay apart: which of them the compiler fuses differs between instantiations of one kernel, and a
+// level selected in the same launch has the scores of one selected in a launch of its own.
+#pragma clang fp contract(off)
+
 namespace specvlm {
 
 namespace {
@@ -338,7 +342,11 @@ struct SelArgs {
 };
 
 constexpr int kStream = 24;              // NC == 0: chunks per thread whose maximum is kept (196608 entries)
-constexpr float kLog2eDT = 1.4426950408889634f;
+
+// exp(x) for a difference x <= 0 of two logits.  The difference is taken first: the row's greatest entry then adds
+// exactly 1, the sum is at least 1 and no log-probability is positive, so a child never outranks its parent
+// (a fused multiply-add with the reference already scaled saves an instruction, but adds 2^r, r the rounding of that).
+__device__ __forceinline__ float exp_of(float x) { return __builtin_amdgcn_exp2f(x * 1.4426950408889634f); }
 
 template <typename T, int NC, bool SEL>
 __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
@@ -385,12 +393,11 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
             tmax = fmaxf(tmax, cmax[j]);
         }
         m = fmaxf(tmax, -2.0e38f);
-        const float ref = -m * kLog2eDT;
-        float part[4] = {__builtin_amdgcn_exp2f(fmaf(es, kLog2eDT, ref)), 0.f, 0.f, 0.f};
+        float part[4] = {exp_of(es - m), 0.f, 0.f, 0.f};
 #pragma unroll
         for (int j = 0; j < NC; ++j)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) part[e & 3] += __builtin_amdgcn_exp2f(fmaf(ch[j].at(e), kLog2eDT, ref));   // exp(-inf) = 0
+            for (int e = 0; e < 8; ++e) part[e & 3] += exp_of(ch[j].at(e) - m);         // exp(-inf) = 0
         sum = (part[0] + part[1]) + (part[2] + part[3]);
     } else {
         m = fmaxf(es, -2.0e38f);
@@ -408,12 +415,12 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
                 gm = fmaxf(gm, cm[u]);
             }
             tmax = fmaxf(tmax, gm);
-            const float mn = fmaxf(m, gm), ref = -mn * kLog2eDT;
-            float part[4] = {sum * __builtin_amdgcn_exp2f(fmaf(m, kLog2eDT, ref)), 0.f, 0.f, 0.f};
+            const float mn = fmaxf(m, gm);
+            float part[4] = {sum * exp_of(m - mn), 0.f, 0.f, 0.f};         // (times exactly 1 where the maximum stays)
 #pragma unroll
             for (int u = 0; u < U; ++u)
 #pragma unroll
-                for (int e = 0; e < 8; ++e) part[e & 3] += __builtin_amdgcn_exp2f(fmaf(ch[u].at(e), kLog2eDT, ref));
+                for (int e = 0; e < 8; ++e) part[e & 3] += exp_of(ch[u].at(e) - mn);
             sum = (part[0] + part[1]) + (part[2] + part[3]);
             m = mn;
         };
@@ -434,7 +441,7 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
     {
         const float gmax = row_max(tmax);                // of the row of 16 lanes
         const float wm = wave_max(m);
-        const float ws = wave_sum(sum * __builtin_amdgcn_exp2f((m - wm) * kLog2eDT));
+        const float ws = wave_sum(sum * exp_of(m - wm));
         if ((tid & 15) == 0) s_grp[tid >> 4] = gmax;
         if (lane == 0) { s_wmax[wave] = wm; s_wsum[wave] = ws; }
         if (tid == 0) s_ncand = 0;
@@ -455,7 +462,7 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
         if (part == 0 && beaten == K - 1) s_thr = gj;    // exactly one group: the ranks are a permutation
     }
     const float mx = row_max(s_wmax[tid & 15]);
-    const float lse = mx + logf(row_sum(s_wsum[tid & 15] * __builtin_amdgcn_exp2f((s_wmax[tid & 15] - mx) * kLog2eDT)));
+    const float lse = mx + logf(row_sum(s_wsum[tid & 15] * exp_of(s_wmax[tid & 15] - mx)));
     if (tid == 0 && lse_out) lse_out[b * nrows + w] = lse;
     __syncthreads();
     const float thr = s_thr;

@@ -1,0 +1,78 @@
+"""Log-probabilities of specvlm_draft_topk are never positive: a child's score does not exceed its parent's, and a
+tree cut between the two is closed.  Rows with one sharp peak (a confident draft) have log-probabilities near zero."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def sv():
+    import paper_2509_11815_amd as sv
+    sv.load_library()
+    return sv
+
+
+def _peaked(peaks, V, dtype, floor):
+    """One row per peak: the peak somewhere in the row, every other logit 60 (or `floor`) below it."""
+    peaks = torch.as_tensor(peaks, dtype=torch.float32).to(dtype).cuda()
+    x = (peaks.float() - floor).to(dtype)[None, :, None].expand(1, len(peaks), V).contiguous()
+    at = (torch.arange(len(peaks), device="cuda") * 7919 + 13) % V
+    x[0, torch.arange(len(peaks), device="cuda"), at] = peaks
+    return x, peaks, at
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("V", [4096, 40000, 65536, 65600, 152064])          # registers (4, 8 chunks), streamed rows
+def test_scores_do_not_rise_from_parent_to_child(sv, V, dtype):
+    g = torch.Generator().manual_seed(V)
+    grid = torch.cat([torch.arange(8, 128, 0.5), -torch.arange(8, 128, 7.5)])
+    for first in range(0, len(grid), 64):
+        x, peaks, at = _peaked(grid[first:first + 64], V, dtype, 120.0)
+        W = len(peaks)
+        cum = (-20 * torch.rand((1, W), generator=g)).cuda()
+        lse = torch.empty((1, W), dtype=torch.float32, device="cuda")
+        score, token, _ = sv.specvlm_draft_topk(x, 2, cum=cum, lse_out=lse)
+        best = score.view(1, W, 2)[:, :, 0]
+        assert torch.equal(token.view(W, 2)[:, 0].long(), at)
+        assert bool((best <= cum).all()), (best - cum).max().item()
+        # exp(-120) x V is below half a unit in the last place of 1: the sum is 1, the log-sum-exp the peak
+        assert torch.equal(lse[0], peaks.float())
+
+
+@pytest.mark.parametrize("V", [1000, 32000, 65536, 99254, 152064])
+@pytest.mark.parametrize("sigma,mean", [(2.0, 0.0), (8.0, 0.0), (8.0, 30.0)])
+def test_log_sum_exp_error(sv, V, sigma, mean):
+    """Against fp64: half a unit in the last place of the stored result, and of its two addends' (|lse| < 128: 2^-18 in
+    all), is what fp32 storage costs; the fp32 sum and its logarithm add a few 2^-24 more."""
+    g = torch.Generator(device="cuda").manual_seed(V)
+    x = torch.randn((1, 32, V), device="cuda", generator=g) * sigma + mean
+    lse = torch.empty((1, 32), dtype=torch.float32, device="cuda")
+    sv.specvlm_draft_topk(x, 10, lse_out=lse)
+    ref = torch.logsumexp(x.double(), -1)
+    ulp = 2.0 ** (torch.floor(torch.log2(ref.abs())) - 23)
+    assert bool(((lse.double() - ref).abs() <= ulp + 1e-6).all()), (lse.double() - ref).abs().max().item()
+
+
+@pytest.mark.parametrize("V", [32000, 70000])
+def test_tree_is_closed_wherever_it_is_cut(sv, V):
+    """Ten nearly equal children of the root, each with one near-certain child of its own: parent and child have
+    scores that differ by rounding only, and every size of the tree cuts between some of them."""
+    rng = np.random.default_rng(V)
+    K = 10
+    root = torch.full((1, 1, V), -30.0, dtype=torch.bfloat16, device="cuda")
+    root[0, 0, 100:100 + K] = torch.from_numpy((20 + rng.integers(0, 2, K) * 0.125).astype(np.float32)).cuda().to(torch.bfloat16)
+    peaks = np.sort(rng.choice(np.arange(8, 128, 0.5), K, replace=False)).astype(np.float32)
+    x, _, _ = _peaked(peaks, V, torch.bfloat16, 100.0)
+    s0, t0, _ = sv.specvlm_draft_topk(root, K)
+    idx = torch.arange(K, dtype=torch.int32, device="cuda")[None]
+    s1, t1, p1 = sv.specvlm_draft_topk(x, K, cum=s0, parent_idx=idx)
+    score, token = torch.cat([s0, s1], 1), torch.cat([t0, t1], 1)
+    par = torch.cat([torch.full_like(t0, -1), p1], 1)
+    err = torch.zeros(1, dtype=torch.int32, device="cuda")
+    tok = torch.zeros(1, dtype=torch.int32, device="cuda")
+    for N in range(2, 2 * K + 2):
+        parent = sv.specvlm_draft_finalize(score, par, token, tok, N, err_flag=err)[0]
+        assert err.item() == 0, N
+        assert bool((parent[0, 1:] >= 0).all())

@@ -341,6 +341,7 @@ struct SelArgs {
     int32_t* counters;            // [B * SPECVLM_COUNTER_STRIDE] tickets, zero between calls
 };
 
+constexpr float kLowest = -3.402823466e38f;         // reference of a thread without entries: no finite logit is below it
 constexpr int kStream = 24;              // NC == 0: chunks per thread whose maximum is kept (196608 entries)
 
 // exp(x) for a difference x <= 0 of two logits.  The difference is taken first: the row's greatest entry then adds
@@ -392,7 +393,7 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
             cmax[j] = chunk_max(ch[j]);
             tmax = fmaxf(tmax, cmax[j]);
         }
-        m = fmaxf(tmax, -2.0e38f);
+        m = fmaxf(tmax, kLowest);
         float part[4] = {exp_of(es - m), 0.f, 0.f, 0.f};
 #pragma unroll
         for (int j = 0; j < NC; ++j)
@@ -400,7 +401,7 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
             for (int e = 0; e < 8; ++e) part[e & 3] += exp_of(ch[j].at(e) - m);         // exp(-inf) = 0
         sum = (part[0] + part[1]) + (part[2] + part[3]);
     } else {
-        m = fmaxf(es, -2.0e38f);
+        m = fmaxf(es, kLowest);
         sum = es > -INFINITY ? 1.f : 0.f;
         auto take = [&](int k0, float (&cm)[U]) __attribute__((always_inline)) {        // chunks k0, k0 + 1024, ...
 #pragma unroll

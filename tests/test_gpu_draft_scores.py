@@ -76,3 +76,22 @@ def test_tree_is_closed_wherever_it_is_cut(sv, V):
         parent = sv.specvlm_draft_finalize(score, par, token, tok, N, err_flag=err)[0]
         assert err.item() == 0, N
         assert bool((parent[0, 1:] >= 0).all())
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
+@pytest.mark.parametrize("V", [7, 5000, 40000, 70001])
+def test_extreme_maxima(sv, V, dtype):
+    """Any finite maximum is a maximum: the type's lowest value (a masked row), its greatest, and both in one row."""
+    lo, hi = torch.finfo(dtype).min, torch.finfo(dtype).max
+    x = torch.full((1, 4, V), lo, dtype=dtype, device="cuda")
+    x[0, 1, 2:4] = hi
+    x[0, 2, 5] = 0.0
+    x[0, 3] = -float("inf")
+    x[0, 3, 4] = lo
+    lse = torch.empty((1, 4), dtype=torch.float32, device="cuda")
+    score, token, _ = sv.specvlm_draft_topk(x, 2, lse_out=lse)
+    assert token.view(4, 2).tolist() == [[0, 1], [2, 3], [5, 0], [4, 0]]
+    # log(V) and log 2 vanish beside values of 1e38; a masked row's entries are all equal to its log-sum-exp then
+    assert lse[0].tolist() == [lo, hi, 0.0, lo]
+    want = [[0.0, 0.0], [0.0, 0.0], [0.0, lo], [0.0, -float("inf")]]
+    assert score.view(4, 2).tolist() == want

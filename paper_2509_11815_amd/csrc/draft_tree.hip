@@ -27,7 +27,8 @@ namespace {
 
 constexpr int kThreadsDT = 1024;
 constexpr int kWavesDT = kThreadsDT / 64;
-constexpr int kCandCap = 1024;           // Top-K fast path: entries at or above the threshold kept in LDS
+constexpr int kCandCap = 1024;           // Top-K: entries at or above a threshold kept in LDS
+constexpr int kRankDirect = 320;         // ... and ranked as they are (square of their number: 2.7 us; 27 us for 1000)
 
 // Eight consecutive entries of a row, as loaded.
 template <typename T>
@@ -325,10 +326,13 @@ __device__ __forceinline__ void rank_winners(unsigned long long* s_key, int c, i
 //   Top-K     every row of 16 lanes reduces its greatest logit; the K-th greatest of the 64 is a value that at least K
 //             entries reach, and (for logits that do not follow the token order) about 2K do.  These are collected
 //             in LDS and ranked against each other: an entry beaten by r others is the r-th best.  Keys are
-//             distinct, so the order of collection does not matter.  More than kCandCap of them (logits sorted along
-//             the vocabulary, many equal): K rounds of "the greatest key below the last one".
+//             distinct, so the order of collection does not matter.  More than kRankDirect of them (many equal, logits
+//             sorted along the vocabulary, fewer than K groups with finite ones): the threshold becomes the K-th best
+//             of the threads' best keys, with the token order among equal logits; if that does not help either
+//             (the best entries sit in few threads), K rounds of one winner each.
 // Per level (10 rows, kernel alone): 32000 bf16 logits 10.4 -> 6.6 us; rows of 99254 and 152064, which used to be re-read
-// entry by entry in every pass, 67 and 97 us -> 13 and 15.
+// entry by entry in every pass, 66 and 96 us -> 12.9 and 14.4.  Ten rows of equal logits, one call: 32000 42.7 -> 18.7,
+// 152064 97.9 -> 57.7; sorted along the vocabulary 44.5 -> 16.1 and 97.7 -> 41.0.
 // ---------------------------------------------------------------------------------------
 // SEL: the workgroup that finishes a request's last row also chooses the M most valuable of the
 // request's W*K new candidates (what draft_select_kernel does in a launch of its own): scores
@@ -359,6 +363,7 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
     __shared__ __attribute__((aligned(16))) float s_grp[64];
     __shared__ unsigned long long s_key[2][kWavesDT];
     __shared__ __attribute__((aligned(16))) unsigned long long s_cand[kCandCap];
+    __shared__ unsigned long long s_grp_key[64], s_thr_key;
     __shared__ int s_last, s_ncand;
     __shared__ float s_thr;
 
@@ -504,8 +509,8 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
                 for (int e = 0; e < 8; ++e) collect(entry(body + 8 * static_cast<int64_t>(k) + e), head + 8 * k + e);
     }
     __syncthreads();
-    const int nc = s_ncand;
-    if (nc <= kCandCap) {                                // uniform
+    int nc = s_ncand;
+    auto rank_them = [&]() __attribute__((always_inline)) {
         for (int i = tid; i < nc; i += kThreadsDT) {
             const unsigned long long k = s_cand[i];
             int beaten = 0;
@@ -513,26 +518,112 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
             for (int x = 0; x < nc; ++x) beaten += s_cand[x] > k ? 1 : 0;
             if (beaten < K) emit(beaten, k);
         }
+    };
+    if (nc <= kRankDirect) {                             // uniform
+        rank_them();
     } else {
-        // ---- K rounds (any input): the greatest key below the last winner's ---------------------------
-        unsigned long long below = ~0ull;
-        for (int k = 0; k < K; ++k) {
-            unsigned long long best = 0;                 // 0 = nothing (a real key is never 0)
-            for (int v = tid; v < V; v += kThreadsDT) {
-                const unsigned long long key = order_key(entry(row + v), v);
-                best = key < below && key > best ? key : best;
-            }
-            best = wave_max_u64(best);
-            if (lane == 0) s_key[k & 1][wave] = best;
-            __syncthreads();                             // (the other buffer was last read two rounds ago)
-            unsigned long long win = s_key[k & 1][0];
+        // ---- too many: a threshold from the threads' best entries -----------------------------------------
+        // every entry of this thread, in ascending token order
+        auto each = [&](auto&& f) __attribute__((always_inline)) {
+            if (vs >= 0 && vs < head) f(es, vs);
+            if constexpr (NC > 0) {
 #pragma unroll
-            for (int x = 1; x < kWavesDT; ++x) {
-                const unsigned long long y = s_key[k & 1][x];
-                win = y > win ? y : win;
+                for (int j = 0; j < NC; ++j) {
+                    const int k = tid + kThreadsDT * j;
+                    if (k < nck)
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) f(ch[j].at(e), head + 8 * k + e);
+                }
+            } else {
+                for (int k0 = tid; k0 < nck; k0 += U * kThreadsDT) {
+#pragma unroll
+                    for (int u = 0; u < U; ++u) ch[u].load(body + 8 * static_cast<int64_t>(min(k0 + kThreadsDT * u, nck - 1)));
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int k = k0 + kThreadsDT * u;
+                        if (k < nck)
+#pragma unroll
+                            for (int e = 0; e < 8; ++e) f(ch[u].at(e), head + 8 * k + e);
+                    }
+                }
             }
-            if (tid == 0) emit(k, win);                  // K <= V: never empty
-            below = win;
+            if (vs >= tail0) f(es, vs);
+        };
+        // the key of the best of them that comes after (bx, bv) in the order, 0 if there is none (a real key is never 0);
+        // "greater" alone keeps the lowest token among equal logits (no logit is NaN)
+        auto best_after = [&](float bx, int bv) __attribute__((always_inline)) -> unsigned long long {
+            float bf = 0.f;
+            int bi = -1;
+            each([&](float x, int v) __attribute__((always_inline)) {
+                const bool take = ((x < bx) | ((x == bx) & (v > bv))) & ((x > bf) | (bi < 0));
+                bf = take ? x : bf;
+                bi = take ? v : bi;
+            });
+            return bi >= 0 ? order_key(bf, bi) : 0ull;
+        };
+        unsigned long long mine = best_after(INFINITY, -1);
+        {
+            unsigned long long grp = mine;               // best of the row of 16 lanes
+#pragma unroll
+            for (int off = 8; off >= 1; off >>= 1) {
+                const unsigned long long y = __shfl_xor(grp, off);
+                grp = y > grp ? y : grp;
+            }
+            if ((tid & 15) == 0) s_grp_key[tid >> 4] = grp;
+            if (tid == 0) { s_thr_key = 0; s_ncand = 0; }
+        }
+        __syncthreads();
+        // the K-th best of `n` keys, if there are so many, becomes the threshold (keys are distinct; 0: no entry)
+        auto kth_of = [&](const unsigned long long* keys, int n) __attribute__((always_inline)) {
+            if (tid < n) {
+                const unsigned long long k = keys[tid];
+                int beaten = 0;
+#pragma unroll 4
+                for (int x = 0; x < n; ++x) beaten += keys[x] > k ? 1 : 0;
+                if (beaten == K - 1 && k != 0) s_thr_key = k;
+            }
+        };
+        auto collect_key = [&](unsigned long long k) __attribute__((always_inline)) {
+            const int pos = atomicAdd(&s_ncand, 1);
+            if (pos < kCandCap) s_cand[pos] = k;
+        };
+        kth_of(s_grp_key, 64);
+        __syncthreads();
+        if (mine != 0 && mine >= s_thr_key) collect_key(mine);       // threads of K groups, or all
+        __syncthreads();
+        nc = s_ncand;
+        __syncthreads();
+        if (tid == 0) s_ncand = 0;
+        kth_of(s_cand, nc);
+        __syncthreads();
+        const unsigned long long thr_key = s_thr_key;
+        if (mine >= thr_key)                             // K threads, or all
+            each([&](float x, int v) __attribute__((always_inline)) {
+                const unsigned long long k = order_key(x, v);
+                if (k >= thr_key) collect_key(k);
+            });
+        __syncthreads();
+        nc = s_ncand;
+        if (nc <= kCandCap) {                            // uniform
+            rank_them();
+        } else {
+            // ---- still too many (the best entries sit in few threads): one winner per round; only its owner looks
+            // for its next best --------------------------------------------------------------------------
+            for (int k = 0; k < K; ++k) {
+                const unsigned long long best = wave_max_u64(mine);
+                if (lane == 0) s_key[k & 1][wave] = best;
+                __syncthreads();                         // (the other buffer was last read two rounds ago)
+                unsigned long long win = s_key[k & 1][0];
+#pragma unroll
+                for (int x = 1; x < kWavesDT; ++x) {
+                    const unsigned long long y = s_key[k & 1][x];
+                    win = y > win ? y : win;
+                }
+                if (mine == win) {                       // exactly one thread (K <= V: never empty)
+                    emit(k, win);
+                    mine = best_after(key_value(win), static_cast<int>(0xFFFFFFFFu - static_cast<uint32_t>(win)));
+                }
+            }
         }
     }
     if constexpr (SEL) {

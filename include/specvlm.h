@@ -131,7 +131,10 @@ int32_t specvlm_tree_verify_attn_num_splits(const specvlm_attn_desc *desc);
  * logical slots [prefix_len[b], prefix_len[b]+num_nodes[b]) of the cache, with
  * position encoding applied.  Rows i >= num_nodes[b] of o / lse are not written.
  * Slots at or beyond prefix_len[b]+num_nodes[b] may be fetched (see the geometry note
- * above) but never influence a result.  A block table entry outside [0, num_blocks)
+ * above) but never influence a result.  SPECVLM_F32: nor does what a tree node i does not see.
+ * SPECVLM_BF16: V of the request's tree nodes must be finite (an invisible node's V is multiplied
+ * by a weight of zero, so an infinity or NaN there reaches the other nodes; its K may be anything).
+ * A block table entry outside [0, num_blocks)
  * sets SPECVLM_ERR_BAD_BLOCK (memory outside the pool is still never touched).
  *
  *   q_dev, o_dev         device, desc->dtype, geometry from desc; 16-byte aligned rows

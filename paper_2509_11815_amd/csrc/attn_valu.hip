@@ -236,6 +236,21 @@ __global__ __launch_bounds__(kF32Waves * 64) void attn_f32_kernel(ValuParams p) 
 #pragma unroll
             for (int t = 0; t < ND; ++t) vf[i][t] = vr[16 * t];
         }
+        // Not every row sees every node, and a weight of zero times a V that is not finite is NaN: in a tile with tree
+        // nodes such entries leave the product and are added below to the rows that see them.
+        bool special = false;
+        if (16 * tile + 16 > P) {              // uniform
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int t = 0; t < ND; ++t) special |= !(fabsf(vf[i][t]) < INFINITY);
+            special = __any(special);
+            if (special)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int t = 0; t < ND; ++t) vf[i][t] = fabsf(vf[i][t]) < INFINITY ? vf[i][t] : 0.f;
+        }
         f32x4 s = {0.f, 0.f, 0.f, 0.f};        // s[i]: key 4g + i of the tile against this lane's query
 #pragma unroll
         for (int c = 0; c < ND; ++c)
@@ -265,6 +280,22 @@ __global__ __launch_bounds__(kF32Waves * 64) void attn_f32_kernel(ValuParams p) 
 #pragma unroll
             for (int i = 0; i < 4; ++i) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][t], w[i], acc[t], 0, 0, 0);
         }
+        if (special)
+            for (int k4 = 0; k4 < 4; ++k4)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int key = 16 * tile + 4 * k4 + i, rel = key - P;
+                    const float weight = __shfl(w[i], 16 * k4 + l16);      // of this key for this lane's query
+                    const bool visible = key < S && (rel < 0 || ((mask >> (rel & 63)) & 1ull));
+                    const float* vr = static_cast<const float*>(p.v) + base + min(4 * k4 + i, last) * p.g.stride_t + 4 * g;
+#pragma unroll
+                    for (int t = 0; t < ND; ++t) {
+                        const f32x4 x = *reinterpret_cast<const f32x4*>(vr + 16 * t);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (visible && !(fabsf(x[e]) < INFINITY)) acc[t][e] += weight * x[e];
+                    }
+                }
     }
     if (bad_block && p.err_flag) atomicOr(p.err_flag, SPECVLM_ERR_BAD_BLOCK);
     // merge: acc[t][i] is O^T at head dim 16t + 4g + i, query l16

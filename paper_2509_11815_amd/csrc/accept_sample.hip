@@ -23,6 +23,7 @@
 //             computed by the whole workgroup first)
 // Kernel alone, averages over 1 - 16 requests: up to 32768 tokens 15.2 -> 12.1 us, up to 65536 31.3 -> 18.2, beyond
 // (99254 and 152064) 198 -> 29 (every pass and the walk of the drawn chunk read token by token before).
+#include "chunk_vectors.hpp"
 #include "wave_ops.hpp"
 
 namespace specvlm {
@@ -286,15 +287,28 @@ __global__ __launch_bounds__(kThreadsAS) void tree_accept_sample_kernel(
         repack();
     } else {
         if (v0 < v1) {
-            // whole 16-byte vectors; entries outside the chunk count as zero, which changes no sum
-            const uintptr_t first = reinterpret_cast<uintptr_t>(row + v0) & ~static_cast<uintptr_t>(15);
-            const int lead = static_cast<int>((reinterpret_cast<uintptr_t>(row + v0) - first) / sizeof(T)), len = v1 - v0;
-            const uint4* pv = reinterpret_cast<const uint4*>(first);
-            const int nv = (lead + len + VEC - 1) / VEC;
-            for (int k = 0; k < nv; k += 4) {
+            // 16-byte vectors; entries outside the chunk count as zero, which changes no sum.  A vector that is not
+            // whole inside the row is replaced by another one of it, then patched entry by entry.
+            const ChunkVectors cv(reinterpret_cast<uintptr_t>(row), v0, v1, V, VEC);
+            const int lead = cv.lead, len = v1 - v0;
+            const uint4* pv = reinterpret_cast<const uint4*>(row + v0 - lead);
+            for (int k = 0; k < cv.count; k += 4) {
                 uint4 w[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) w[u] = pv[min(k + u, nv - 1)];
+                for (int u = 0; u < 4; ++u) w[u] = pv[min(max(k + u, cv.lo), cv.hi)];
+                if (k < cv.lo || (cv.hi < cv.count - 1 && k + 3 > cv.hi)) {       // (the row's first and last threads only)
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (k + u < cv.lo || k + u > cv.hi)
+#pragma unroll
+                            for (int e = 0; e < VEC; ++e) {
+                                const int at = (k + u) * VEC + e - lead;
+                                if (static_cast<unsigned>(at) >= static_cast<unsigned>(len)) continue;
+                                uint32_t& x = (&w[u].x)[sizeof(T) == 2 ? e >> 1 : e];
+                                if constexpr (sizeof(T) == 2) x = (x & (0xFFFF0000u >> (16 * (e & 1)))) | static_cast<uint32_t>(row[v0 + at]) << (16 * (e & 1));
+                                else x = __float_as_uint(row[v0 + at]);
+                            }
+                }
                 for (unsigned long long r = mine; r; r &= r - 1) drop(w, 4, s_rej[__builtin_ctzll(r)] - v0 + lead - k * VEC);
 #pragma unroll
                 for (int u = 0; u < 4; ++u)

@@ -79,6 +79,19 @@ struct Arguments {
         if (v == -1 && PyErr_Occurred()) throw python_error();
         return v;
     }
+    // what int() / float() make of the argument
+    int64_t as_int(int i) const {
+        THPObjectPtr number(PyNumber_Long(obj(i)));
+        const long long v = number ? PyLong_AsLongLong(number) : -1;
+        if (v == -1 && PyErr_Occurred()) throw python_error();
+        return v;
+    }
+    float as_float(int i) const {
+        THPObjectPtr number(PyNumber_Float(obj(i)));
+        const double v = number ? PyFloat_AsDouble(number) : -1.0;
+        if (v == -1.0 && PyErr_Occurred()) throw python_error();
+        return static_cast<float>(v);
+    }
     float real(int i) const {
         const double v = PyFloat_AsDouble(obj(i));
         if (v == -1.0 && PyErr_Occurred()) throw python_error();
@@ -139,18 +152,21 @@ at::Tensor counters_of(const Arguments& a, int i, const at::Tensor& like, int64_
     return t;
 }
 
-// The four outputs of an acceptance walk: argument i's tuple, or new tensors.
+// The four outputs of an acceptance walk: argument i's tuple, which has the path capacity of its path, or new tensors
+// with that of argument cap.
 struct WalkOutputs {
+    THPObjectPtr seq;                                // keeps the given tensors (the argument may be any iterable)
     at::Tensor accept_len, path, bonus, committed;
     PyObject* given[4] = {Py_None, Py_None, Py_None, Py_None};
     int64_t path_cap;
-    WalkOutputs(const Arguments& a, int i, const at::Tensor& like, int64_t B, int64_t cap) : path_cap(cap) {
+    WalkOutputs(const Arguments& a, int i, const at::Tensor& like, int64_t B, int cap_arg) {
         if (!a.given(i)) {
+            const int64_t cap = path_cap = a.integer(cap_arg);
             accept_len = new_i32(like, {B}); path = new_i32(like, {B, cap});
             bonus = new_i32(like, {B}); committed = new_i32(like, {B, cap});
             return;
         }
-        THPObjectPtr seq(PySequence_Fast(a.obj(i), "out must be a sequence"));
+        seq = PySequence_Fast(a.obj(i), "out must be a sequence");
         if (!seq) throw python_error();
         want(PySequence_Fast_GET_SIZE(seq.get()) == 4, "out must hold accept_len, path, bonus_tok and committed_tok");
         at::Tensor* to[4] = {&accept_len, &path, &bonus, &committed};
@@ -195,8 +211,8 @@ PyObject* tree_verify_attn(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
         d.dtype = dtype_code(q);
         d.B = q.size(0); d.N_max = q.size(1); d.H_q = q.size(2); d.D = q.size(3);
         d.H_kv = k.size(1);
-        d.softmax_scale = a.real(11);
-        d.num_splits = static_cast<int32_t>(a.integer(12));
+        d.softmax_scale = a.as_float(11);
+        d.num_splits = static_cast<int32_t>(a.as_int(12));
         d.q_stride_b = q.stride(0); d.q_stride_n = q.stride(1); d.q_stride_h = q.stride(2);
         d.o_stride_b = out.stride(0); d.o_stride_n = out.stride(1); d.o_stride_h = out.stride(2);
         d.kv_stride_b = k.stride(0); d.kv_stride_h = k.stride(1); d.kv_stride_t = k.stride(2);
@@ -244,6 +260,7 @@ PyObject* kv_compact(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     HANDLE_TH_ERRORS
     const Arguments a{args, nargs, "specvlm_kv_compact"};
     const at::Tensor &k = a.tensor(0, "k_caches"), &path = a.tensor(3, "path");
+    want(path.dim() == 2, "path must have two dimensions");
     const int64_t B = path.size(0), cap = path.size(1);
     const bool by_ptr = a.given(8);
     const int x = by_ptr ? 0 : 1;                    // first per-layer dimension
@@ -313,8 +330,9 @@ PyObject* tree_accept(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     HANDLE_TH_ERRORS
     const Arguments a{args, nargs, "specvlm_tree_accept"};
     const at::Tensor& parent = a.tensor(0, "parent");
+    want(parent.dim() == 2, "parent must have two dimensions");
     const int64_t B = parent.size(0);
-    const WalkOutputs o(a, 6, parent, B, a.integer(4));
+    const WalkOutputs o(a, 6, parent, B, 4);
     check(lib.specvlm_tree_accept(B, parent.size(1), o.path_cap, a.i32(0, "parent"), a.i32(1, "draft_tok"), a.i32(2, "amax"),
                                   a.i32(3, "num_nodes"), o.p(o.accept_len), o.p(o.path), o.p(o.bonus), o.p(o.committed),
                                   a.i32_unchecked(5, "err_flag"), a.stream(7)),
@@ -329,7 +347,7 @@ PyObject* node_argmax_accept(PyObject*, PyObject* const* args, Py_ssize_t nargs)
     const Arguments a{args, nargs, "specvlm_node_argmax_accept"};
     const at::Tensor& l = logits_of(a, 0);
     const int64_t B = l.size(0), N = l.size(1);
-    const WalkOutputs o(a, 8, l, B, a.integer(4));
+    const WalkOutputs o(a, 8, l, B, 4);
     at::Tensor made;
     if (!a.given(6)) made = new_i32(l, {B, N});
     int32_t* amax = a.given(6) ? a.i32(6, "amax") : static_cast<int32_t*>(made.data_ptr());
@@ -355,7 +373,7 @@ PyObject* tree_accept_sample(PyObject*, PyObject* const* args, Py_ssize_t nargs)
         fail(PyExc_ValueError, "u_accept must be a contiguous float32 tensor of shape (%lld, %lld)", static_cast<long long>(B), static_cast<long long>(N));
     if (ub.scalar_type() != at::kFloat || ub.dim() != 1 || ub.size(0) != B || !ub.is_contiguous())
         fail(PyExc_ValueError, "u_bonus must be a contiguous float32 tensor of shape (%lld,)", static_cast<long long>(B));
-    const WalkOutputs o(a, 9, l, B, a.integer(7));
+    const WalkOutputs o(a, 9, l, B, 7);
     check(lib.specvlm_tree_accept_sample(dtype_code(l), B, N, l.size(2), o.path_cap, a.i32(0, "parent"), a.i32(1, "draft_tok"),
                                          l.data_ptr(), l.stride(0), l.stride(1), a.i32(6, "num_nodes"), a.real(5),
                                          static_cast<const float*>(ua.data_ptr()), static_cast<const float*>(ub.data_ptr()),
@@ -455,6 +473,7 @@ PyObject* draft_select(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     HANDLE_TH_ERRORS
     const Arguments a{args, nargs, "specvlm_draft_select"};
     const at::Tensor& score = a.tensor(0, "score");
+    want(score.dim() == 2, "score must have two dimensions");
     a.f32(0, "score");
     const int64_t B = score.size(0), M = a.integer(1);
     const Selection s(a, 4, score, B, M);
@@ -471,6 +490,7 @@ PyObject* draft_finalize(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     HANDLE_TH_ERRORS
     const Arguments a{args, nargs, "specvlm_draft_finalize"};
     const at::Tensor &score = a.tensor(0, "cand_score"), &par = a.tensor(1, "cand_parent"), &tok = a.tensor(2, "cand_token");
+    want(score.dim() == 2, "cand_score must have two dimensions");
     a.f32(0, "cand_score");
     const int64_t B = score.size(0), N = a.integer(4);
     for (const at::Tensor* t : {&par, &tok})

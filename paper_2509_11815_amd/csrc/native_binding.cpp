@@ -122,6 +122,16 @@ void check(int32_t rc, const char* what) {
     fail(g_error, "%s", msg.c_str());
 }
 
+// A library call without the interpreter lock: a launch can block on a full queue, and other threads go on meanwhile.
+// (The caller's frame holds the tensors; arguments are taken from Python objects before the lock is given up.)
+template <typename F, typename... A>
+int32_t unlocked(F* entry, A... args) {
+    PyThreadState* const state = PyEval_SaveThread();
+    const int32_t rc = entry(args...);
+    PyEval_RestoreThread(state);
+    return rc;
+}
+
 void want(bool ok, const char* message) {
     if (!ok) fail(PyExc_ValueError, "%s", message);
 }
@@ -244,11 +254,11 @@ PyObject* tree_verify_attn(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
             scratch = at::zeros({static_cast<int64_t>(bytes)}, q.options().dtype(at::kByte));   // zero-filled once, as the ABI asks
             ws = scratch.data_ptr();
         }
-        rc = lib.specvlm_tree_verify_attn(desc, q.data_ptr(), k.data_ptr(), v.data_ptr(), table, prefix, nn, parent,
+        rc = unlocked(lib.specvlm_tree_verify_attn, desc, q.data_ptr(), k.data_ptr(), v.data_ptr(), table, prefix, nn, parent,
                                           out.data_ptr(), lse, ws, bytes, err, stream);
     } else {
         auto* fn = entry == 1 ? lib.specvlm_tree_verify_attn_static : lib.specvlm_tree_verify_attn_vector_alu;
-        rc = fn(desc, q.data_ptr(), k.data_ptr(), v.data_ptr(), table, prefix, nn, parent, out.data_ptr(), lse, err, stream);
+        rc = unlocked(fn, desc, q.data_ptr(), k.data_ptr(), v.data_ptr(), table, prefix, nn, parent, out.data_ptr(), lse, err, stream);
     }
     check(rc, what);
     return keep(a.obj(7), made);
@@ -292,7 +302,7 @@ PyObject* kv_compact(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     at::Tensor made;
     if (!a.given(6)) made = new_i32(path, {B});
     int32_t* new_prefix = static_cast<int32_t*>(a.given(6) ? a.ptr(6, "new_prefix_len") : made.data_ptr());
-    check(lib.specvlm_kv_compact(&d, static_cast<int32_t>(L), kb, vb, layer_stride,
+    check(unlocked(lib.specvlm_kv_compact, &d, static_cast<int32_t>(L), kb, vb, layer_stride,
                                  static_cast<void* const*>(a.ptr(8, "layer_ptrs")), static_cast<void* const*>(a.ptr(9, "layer_ptrs")),
                                  a.i32(5, "block_table"), a.i32(2, "prefix_len"), a.i32(3, "path"), static_cast<int32_t>(cap),
                                  a.i32(4, "accept_len"), new_prefix, a.i32_unchecked(7, "moved_idx"),
@@ -317,7 +327,7 @@ PyObject* node_argmax(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     const at::Tensor& l = logits_of(a, 0);
     at::Tensor made;
     if (!a.given(2)) made = new_i32(l, {l.size(0), l.size(1)});
-    check(lib.specvlm_node_argmax(dtype_code(l), l.size(0), l.size(1), l.size(2), l.data_ptr(), l.stride(0), l.stride(1),
+    check(unlocked(lib.specvlm_node_argmax, dtype_code(l), l.size(0), l.size(1), l.size(2), l.data_ptr(), l.stride(0), l.stride(1),
                                   a.i32(1, "num_nodes"),
                                   static_cast<int32_t*>(a.given(2) ? a.ptr(2, "out") : made.data_ptr()), a.stream(3)),
           a.what);
@@ -333,7 +343,7 @@ PyObject* tree_accept(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     want(parent.dim() == 2, "parent must have two dimensions");
     const int64_t B = parent.size(0);
     const WalkOutputs o(a, 6, parent, B, 4);
-    check(lib.specvlm_tree_accept(B, parent.size(1), o.path_cap, a.i32(0, "parent"), a.i32(1, "draft_tok"), a.i32(2, "amax"),
+    check(unlocked(lib.specvlm_tree_accept, B, parent.size(1), o.path_cap, a.i32(0, "parent"), a.i32(1, "draft_tok"), a.i32(2, "amax"),
                                   a.i32(3, "num_nodes"), o.p(o.accept_len), o.p(o.path), o.p(o.bonus), o.p(o.committed),
                                   a.i32_unchecked(5, "err_flag"), a.stream(7)),
           a.what);
@@ -352,7 +362,7 @@ PyObject* node_argmax_accept(PyObject*, PyObject* const* args, Py_ssize_t nargs)
     if (!a.given(6)) made = new_i32(l, {B, N});
     int32_t* amax = a.given(6) ? a.i32(6, "amax") : static_cast<int32_t*>(made.data_ptr());
     const at::Tensor counters = counters_of(a, 5, l, B);
-    check(lib.specvlm_node_argmax_accept(dtype_code(l), B, N, l.size(2), o.path_cap, l.data_ptr(), l.stride(0), l.stride(1),
+    check(unlocked(lib.specvlm_node_argmax_accept, dtype_code(l), B, N, l.size(2), o.path_cap, l.data_ptr(), l.stride(0), l.stride(1),
                                          a.i32(3, "num_nodes"), a.i32(1, "parent"), a.i32(2, "draft_tok"), amax,
                                          o.p(o.accept_len), o.p(o.path), o.p(o.bonus), o.p(o.committed), o.p(counters),
                                          a.i32_unchecked(7, "err_flag"), a.stream(9)),
@@ -374,7 +384,7 @@ PyObject* tree_accept_sample(PyObject*, PyObject* const* args, Py_ssize_t nargs)
     if (ub.scalar_type() != at::kFloat || ub.dim() != 1 || ub.size(0) != B || !ub.is_contiguous())
         fail(PyExc_ValueError, "u_bonus must be a contiguous float32 tensor of shape (%lld,)", static_cast<long long>(B));
     const WalkOutputs o(a, 9, l, B, 7);
-    check(lib.specvlm_tree_accept_sample(dtype_code(l), B, N, l.size(2), o.path_cap, a.i32(0, "parent"), a.i32(1, "draft_tok"),
+    check(unlocked(lib.specvlm_tree_accept_sample, dtype_code(l), B, N, l.size(2), o.path_cap, a.i32(0, "parent"), a.i32(1, "draft_tok"),
                                          l.data_ptr(), l.stride(0), l.stride(1), a.i32(6, "num_nodes"), a.real(5),
                                          static_cast<const float*>(ua.data_ptr()), static_cast<const float*>(ub.data_ptr()),
                                          o.p(o.accept_len), o.p(o.path), o.p(o.bonus), o.p(o.committed),
@@ -426,7 +436,7 @@ PyObject* draft_topk(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     const at::Tensor& l = logits_of(a, 0);
     const int64_t K = a.integer(1);
     const Level v(a, 2, l, K);
-    check(lib.specvlm_draft_topk(dtype_code(l), l.size(0), l.size(1), l.size(2), K, l.data_ptr(), l.stride(0), l.stride(1),
+    check(unlocked(lib.specvlm_draft_topk, dtype_code(l), l.size(0), l.size(1), l.size(2), K, l.data_ptr(), l.stride(0), l.stride(1),
                                  v.cum, v.cum_stride, v.parent_idx, v.parent_stride, static_cast<float*>(v.score.data_ptr()),
                                  static_cast<int32_t*>(v.token.data_ptr()), v.parent_out, v.score.stride(0), v.lse, a.stream(8)),
           a.what);
@@ -457,7 +467,7 @@ PyObject* draft_topk_select(PyObject*, PyObject* const* args, Py_ssize_t nargs) 
     const Level v(a, 3, l, K);
     const Selection s(a, 10, l, B, M);
     const at::Tensor counters = counters_of(a, 13, l, B);
-    check(lib.specvlm_draft_topk_select(dtype_code(l), B, l.size(1), l.size(2), K, l.data_ptr(), l.stride(0), l.stride(1),
+    check(unlocked(lib.specvlm_draft_topk_select, dtype_code(l), B, l.size(1), l.size(2), K, l.data_ptr(), l.stride(0), l.stride(1),
                                         v.cum, v.cum_stride, v.parent_idx, v.parent_stride, static_cast<float*>(v.score.data_ptr()),
                                         static_cast<int32_t*>(v.token.data_ptr()), v.parent_out, v.score.stride(0), v.lse, M,
                                         a.integer(9), static_cast<int32_t*>(s.sel.data_ptr()), static_cast<float*>(s.score.data_ptr()),
@@ -477,7 +487,7 @@ PyObject* draft_select(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     a.f32(0, "score");
     const int64_t B = score.size(0), M = a.integer(1);
     const Selection s(a, 4, score, B, M);
-    check(lib.specvlm_draft_select(B, score.size(1), M, static_cast<const float*>(score.data_ptr()), score.stride(0), a.i32(2, "num_cand"),
+    check(unlocked(lib.specvlm_draft_select, B, score.size(1), M, static_cast<const float*>(score.data_ptr()), score.stride(0), a.i32(2, "num_cand"),
                                    a.integer(3), static_cast<int32_t*>(s.sel.data_ptr()), static_cast<float*>(s.score.data_ptr()),
                                    static_cast<int32_t*>(s.count.data_ptr()), a.stream(7)),
           a.what);
@@ -515,7 +525,7 @@ PyObject* draft_finalize(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
         t[3] = new_i32(score, {B});
     }
     auto p = [&](int x) { return t[x].defined() ? static_cast<int32_t*>(t[x].data_ptr()) : nullptr; };
-    check(lib.specvlm_draft_finalize(B, score.size(1), N, static_cast<const float*>(score.data_ptr()),
+    check(unlocked(lib.specvlm_draft_finalize, B, score.size(1), N, static_cast<const float*>(score.data_ptr()),
                                      static_cast<const int32_t*>(par.data_ptr()), static_cast<const int32_t*>(tok.data_ptr()),
                                      score.stride(0), a.i32(5, "num_cand"), a.i32(3, "root_token"), p(0), p(1), p(2), p(3),
                                      a.i32_unchecked(6, "err_flag"), a.stream(8)),
@@ -545,7 +555,7 @@ PyObject* head_argmax(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     if (!a.given(5))                                 // zero-filled once, as the ABI asks
         scratch = at::zeros({static_cast<int64_t>(lib.specvlm_head_argmax_workspace_bytes(B, N, V))}, h.options().dtype(at::kByte));
     const at::Tensor& ws = a.given(5) ? a.tensor(5, "workspace") : scratch;
-    check(lib.specvlm_head_argmax(dtype_code(h), B, N, h.size(2), V, h.data_ptr(), h.stride(0), h.stride(1), w.data_ptr(), w.stride(0),
+    check(unlocked(lib.specvlm_head_argmax, dtype_code(h), B, N, h.size(2), V, h.data_ptr(), h.stride(0), h.stride(1), w.data_ptr(), w.stride(0),
                                   a.i32(2, "num_nodes"), out, a.f32(4, "max_logit"), ws.data_ptr(),
                                   static_cast<size_t>(ws.numel() * ws.element_size()), a.stream(6)),
           a.what);
@@ -568,7 +578,7 @@ PyObject* visual_pool(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     const at::Tensor& out = a.given(3) ? a.tensor(3, "out") : made;
     want(out.dim() == 3 && x.stride(2) == 1 && out.stride(2) == 1, "feature dimension must be contiguous");
     auto* const fn = a.given(3) ? lib.specvlm_visual_pool : lib.specvlm_visual_pool_padded;
-    check(fn(dtype_code(x), B, T, E, ratio, x.data_ptr(), x.stride(0), x.stride(1), a.i32(2, "num_tokens"),
+    check(unlocked(fn, dtype_code(x), B, T, E, ratio, x.data_ptr(), x.stride(0), x.stride(1), a.i32(2, "num_tokens"),
                                   out.data_ptr(), out.stride(0), out.stride(1),
                                   a.given(4) ? a.i32(4, "out_tokens") : static_cast<int32_t*>(made_n.data_ptr()),
                                   a.i32_unchecked(5, "err_flag"), a.stream(6)),
@@ -589,7 +599,7 @@ PyObject* visual_prune(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     const at::Tensor& out = a.given(2) ? a.tensor(2, "out") : made;
     want(out.dim() == 3 && x.stride(2) == 1 && out.stride(2) == 1, "feature dimension must be contiguous");
     auto* const fn = a.given(2) ? lib.specvlm_visual_prune : lib.specvlm_visual_prune_padded;
-    check(fn(dtype_code(x), B, T, Tk, E, x.data_ptr(), x.stride(0), x.stride(1), a.i32(1, "keep"),
+    check(unlocked(fn, dtype_code(x), B, T, Tk, E, x.data_ptr(), x.stride(0), x.stride(1), a.i32(1, "keep"),
                                    out.data_ptr(), out.stride(0), out.stride(1), a.i32_unchecked(3, "err_flag"), a.stream(4)),
           a.what);
     return keep(a.obj(2), made);

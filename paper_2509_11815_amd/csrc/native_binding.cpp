@@ -308,7 +308,8 @@ PyObject* kv_compact(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
                                  a.i32(4, "accept_len"), new_prefix, a.i32_unchecked(7, "moved_idx"),
                                  a.i32_unchecked(10, "err_flag"), a.stream(11)),
           a.what);
-    return tuple_of<2>({keep(a.obj(6), made), keep(a.obj(7), made)});
+    Py_INCREF(a.obj(7));                             // (moved_idx is None where it is not given)
+    return tuple_of<2>({keep(a.obj(6), made), a.obj(7)});
     END_HANDLE_TH_ERRORS
 }
 

@@ -60,3 +60,12 @@ def test_ranks(sv):
         sv.specvlm_tree_accept(parent[None], tok, tok)
     with pytest.raises(ValueError):
         sv.specvlm_draft_select(torch.zeros(1, 2, 8, device="cuda"), 2)
+
+
+@pytest.mark.parametrize("given", [False, True])
+def test_compaction_returns_none_for_moved_idx_left_out(sv, given):
+    k, v = (torch.zeros(2, 1, 1, 32, 64, device="cuda") for _ in range(2))
+    P, path = torch.tensor([5], dtype=torch.int32, device="cuda"), torch.tensor([[0, 2, -1]], dtype=torch.int32, device="cuda")
+    new_P = torch.zeros(1, dtype=torch.int32, device="cuda") if given else None
+    got = sv.specvlm_kv_compact(k, v, P, path, torch.tensor([1], dtype=torch.int32, device="cuda"), new_prefix_len=new_P)
+    assert got[0].tolist() == [7] and got[1] is None

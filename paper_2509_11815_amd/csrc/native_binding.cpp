@@ -16,6 +16,7 @@
 #include <torch/csrc/utils/object_ptr.h>
 
 #include <array>
+#include <optional>
 #include <string>
 
 #include "specvlm.h"
@@ -136,14 +137,46 @@ void want(bool ok, const char* message) {
     if (!ok) fail(PyExc_ValueError, "%s", message);
 }
 
+// The stream of a call: argument i, or the current one.  Tensors that the call allocates or zeroes belong to it: an
+// explicit stream is made the current one of `like`'s device for the length of the call, so that a zero fill comes before
+// the kernel, and memory given back meanwhile is not handed to other streams' work.  A returned tensor is recorded on the
+// stream that was current, where the caller is likely to use it.
+class CallStream {
+public:
+    CallStream(const Arguments& a, int i, const at::Tensor& like) : a_(a), i_(i) {
+        if (!a.given(i) || !like.is_cuda()) return;
+        void* const handle = a.stream(i);
+        const auto device = like.device().index();
+        const auto current = c10::hip::getCurrentHIPStream(device);
+        if (current.stream() == handle) return;
+        before_ = current;
+        device_ = like.device();
+        c10::hip::setCurrentHIPStream(handle ? c10::hip::getStreamFromExternal(static_cast<hipStream_t>(handle), device)
+                                             : c10::hip::getDefaultHIPStream(device));
+    }
+    void* handle() const { return a_.stream(i_); }
+    ~CallStream() { if (before_) c10::hip::setCurrentHIPStream(*before_); }
+    CallStream(const CallStream&) = delete;
+    CallStream& operator=(const CallStream&) = delete;
+    PyObject* wrap(const at::Tensor& made) const {
+        if (before_ && made.defined()) made.record_stream(c10::Stream(c10::Stream::UNSAFE, *device_, before_->id()));
+        return THPVariable_Wrap(made);
+    }
+    // The given tensor as a new reference, or a new one wrapped.
+    PyObject* keep(PyObject* given, const at::Tensor& made) const {
+        if (given != Py_None) { Py_INCREF(given); return given; }
+        return wrap(made);
+    }
+
+private:
+    const Arguments& a_;
+    const int i_;
+    std::optional<c10::hip::HIPStream> before_;
+    std::optional<c10::Device> device_;
+};
+
 at::Tensor new_i32(const at::Tensor& like, at::IntArrayRef size) { return at::empty(size, like.options().dtype(at::kInt)); }
 at::Tensor new_f32(const at::Tensor& like, at::IntArrayRef size) { return at::empty(size, like.options().dtype(at::kFloat)); }
-
-// The given tensor as a new reference, or a new one wrapped.
-PyObject* keep(PyObject* given, const at::Tensor& made) {
-    if (given != Py_None) { Py_INCREF(given); return given; }
-    return THPVariable_Wrap(made);
-}
 
 template <size_t N>
 PyObject* tuple_of(const std::array<PyObject*, N>& items) {
@@ -188,8 +221,8 @@ struct WalkOutputs {
         path_cap = path.size(1);
     }
     static int32_t* p(const at::Tensor& t) { return static_cast<int32_t*>(t.data_ptr()); }
-    std::array<PyObject*, 4> take() const {
-        return {keep(given[0], accept_len), keep(given[1], path), keep(given[2], bonus), keep(given[3], committed)};
+    std::array<PyObject*, 4> take(const CallStream& on) const {
+        return {on.keep(given[0], accept_len), on.keep(given[1], path), on.keep(given[2], bonus), on.keep(given[3], committed)};
     }
 };
 
@@ -203,6 +236,7 @@ PyObject* tree_verify_attn(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
                              : entry == 1 ? "specvlm_tree_verify_attn_static" : "specvlm_tree_verify_attn_vector_alu";
     const Arguments a{args, nargs, what};
     const at::Tensor &q = a.tensor(0, "q"), &k = a.tensor(1, "k_cache"), &v = a.tensor(2, "v_cache");
+    const CallStream on(a, 14, q);
     at::Tensor made;
     if (!a.given(7)) made = at::zeros_like(q);       // rows past num_nodes are not written
     const at::Tensor& out = a.given(7) ? a.tensor(7, "out") : made;
@@ -240,9 +274,8 @@ PyObject* tree_verify_attn(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
                   *parent = a.i32(4, "parent");
     float* lse = static_cast<float*>(a.ptr(8, "lse"));
     int32_t* err = a.i32_unchecked(10, "err_flag");
-    void* stream = a.stream(14);
     int32_t rc;
-    at::Tensor scratch;                              // (stream-ordered: may be given back as soon as the call is enqueued)
+    at::Tensor scratch;                              // (of the call's stream: may be given back as soon as the call is enqueued)
     if (entry == 0) {
         void* ws = nullptr;
         size_t bytes = 0;
@@ -255,13 +288,13 @@ PyObject* tree_verify_attn(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
             ws = scratch.data_ptr();
         }
         rc = unlocked(lib.specvlm_tree_verify_attn, desc, q.data_ptr(), k.data_ptr(), v.data_ptr(), table, prefix, nn, parent,
-                                          out.data_ptr(), lse, ws, bytes, err, stream);
+                                          out.data_ptr(), lse, ws, bytes, err, on.handle());
     } else {
         auto* fn = entry == 1 ? lib.specvlm_tree_verify_attn_static : lib.specvlm_tree_verify_attn_vector_alu;
-        rc = unlocked(fn, desc, q.data_ptr(), k.data_ptr(), v.data_ptr(), table, prefix, nn, parent, out.data_ptr(), lse, err, stream);
+        rc = unlocked(fn, desc, q.data_ptr(), k.data_ptr(), v.data_ptr(), table, prefix, nn, parent, out.data_ptr(), lse, err, on.handle());
     }
     check(rc, what);
-    return keep(a.obj(7), made);
+    return on.keep(a.obj(7), made);
     END_HANDLE_TH_ERRORS
 }
 
@@ -271,6 +304,7 @@ PyObject* kv_compact(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     const Arguments a{args, nargs, "specvlm_kv_compact"};
     const at::Tensor &k = a.tensor(0, "k_caches"), &path = a.tensor(3, "path");
     want(path.dim() == 2, "path must have two dimensions");
+    const CallStream on(a, 11, path);
     const int64_t B = path.size(0), cap = path.size(1);
     const bool by_ptr = a.given(8);
     const int x = by_ptr ? 0 : 1;                    // first per-layer dimension
@@ -306,10 +340,10 @@ PyObject* kv_compact(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
                                  static_cast<void* const*>(a.ptr(8, "layer_ptrs")), static_cast<void* const*>(a.ptr(9, "layer_ptrs")),
                                  a.i32(5, "block_table"), a.i32(2, "prefix_len"), a.i32(3, "path"), static_cast<int32_t>(cap),
                                  a.i32(4, "accept_len"), new_prefix, a.i32_unchecked(7, "moved_idx"),
-                                 a.i32_unchecked(10, "err_flag"), a.stream(11)),
+                                 a.i32_unchecked(10, "err_flag"), on.handle()),
           a.what);
     Py_INCREF(a.obj(7));                             // (moved_idx is None where it is not given)
-    return tuple_of<2>({keep(a.obj(6), made), a.obj(7)});
+    return tuple_of<2>({on.keep(a.obj(6), made), a.obj(7)});
     END_HANDLE_TH_ERRORS
 }
 
@@ -326,13 +360,14 @@ PyObject* node_argmax(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     HANDLE_TH_ERRORS
     const Arguments a{args, nargs, "specvlm_node_argmax"};
     const at::Tensor& l = logits_of(a, 0);
+    const CallStream on(a, 3, l);
     at::Tensor made;
     if (!a.given(2)) made = new_i32(l, {l.size(0), l.size(1)});
     check(unlocked(lib.specvlm_node_argmax, dtype_code(l), l.size(0), l.size(1), l.size(2), l.data_ptr(), l.stride(0), l.stride(1),
                                   a.i32(1, "num_nodes"),
-                                  static_cast<int32_t*>(a.given(2) ? a.ptr(2, "out") : made.data_ptr()), a.stream(3)),
+                                  static_cast<int32_t*>(a.given(2) ? a.ptr(2, "out") : made.data_ptr()), on.handle()),
           a.what);
-    return keep(a.obj(2), made);
+    return on.keep(a.obj(2), made);
     END_HANDLE_TH_ERRORS
 }
 
@@ -342,13 +377,14 @@ PyObject* tree_accept(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     const Arguments a{args, nargs, "specvlm_tree_accept"};
     const at::Tensor& parent = a.tensor(0, "parent");
     want(parent.dim() == 2, "parent must have two dimensions");
+    const CallStream on(a, 7, parent);
     const int64_t B = parent.size(0);
     const WalkOutputs o(a, 6, parent, B, 4);
     check(unlocked(lib.specvlm_tree_accept, B, parent.size(1), o.path_cap, a.i32(0, "parent"), a.i32(1, "draft_tok"), a.i32(2, "amax"),
                                   a.i32(3, "num_nodes"), o.p(o.accept_len), o.p(o.path), o.p(o.bonus), o.p(o.committed),
-                                  a.i32_unchecked(5, "err_flag"), a.stream(7)),
+                                  a.i32_unchecked(5, "err_flag"), on.handle()),
           a.what);
-    return tuple_of<4>(o.take());
+    return tuple_of<4>(o.take(on));
     END_HANDLE_TH_ERRORS
 }
 
@@ -357,6 +393,7 @@ PyObject* node_argmax_accept(PyObject*, PyObject* const* args, Py_ssize_t nargs)
     HANDLE_TH_ERRORS
     const Arguments a{args, nargs, "specvlm_node_argmax_accept"};
     const at::Tensor& l = logits_of(a, 0);
+    const CallStream on(a, 9, l);
     const int64_t B = l.size(0), N = l.size(1);
     const WalkOutputs o(a, 8, l, B, 4);
     at::Tensor made;
@@ -366,10 +403,10 @@ PyObject* node_argmax_accept(PyObject*, PyObject* const* args, Py_ssize_t nargs)
     check(unlocked(lib.specvlm_node_argmax_accept, dtype_code(l), B, N, l.size(2), o.path_cap, l.data_ptr(), l.stride(0), l.stride(1),
                                          a.i32(3, "num_nodes"), a.i32(1, "parent"), a.i32(2, "draft_tok"), amax,
                                          o.p(o.accept_len), o.p(o.path), o.p(o.bonus), o.p(o.committed), o.p(counters),
-                                         a.i32_unchecked(7, "err_flag"), a.stream(9)),
+                                         a.i32_unchecked(7, "err_flag"), on.handle()),
           a.what);
-    const auto w = o.take();
-    return tuple_of<5>({keep(a.obj(6), made), w[0], w[1], w[2], w[3]});
+    const auto w = o.take(on);
+    return tuple_of<5>({on.keep(a.obj(6), made), w[0], w[1], w[2], w[3]});
     END_HANDLE_TH_ERRORS
 }
 
@@ -378,6 +415,7 @@ PyObject* tree_accept_sample(PyObject*, PyObject* const* args, Py_ssize_t nargs)
     HANDLE_TH_ERRORS
     const Arguments a{args, nargs, "specvlm_tree_accept_sample"};
     const at::Tensor& l = logits_of(a, 2);
+    const CallStream on(a, 10, l);
     const int64_t B = l.size(0), N = l.size(1);
     const at::Tensor &ua = a.tensor(3, "u_accept"), &ub = a.tensor(4, "u_bonus");
     if (ua.scalar_type() != at::kFloat || ua.dim() != 2 || ua.size(0) != B || ua.size(1) != N || !ua.is_contiguous())
@@ -389,9 +427,9 @@ PyObject* tree_accept_sample(PyObject*, PyObject* const* args, Py_ssize_t nargs)
                                          l.data_ptr(), l.stride(0), l.stride(1), a.i32(6, "num_nodes"), a.real(5),
                                          static_cast<const float*>(ua.data_ptr()), static_cast<const float*>(ub.data_ptr()),
                                          o.p(o.accept_len), o.p(o.path), o.p(o.bonus), o.p(o.committed),
-                                         a.i32_unchecked(8, "err_flag"), a.stream(10)),
+                                         a.i32_unchecked(8, "err_flag"), on.handle()),
           a.what);
-    return tuple_of<4>(o.take());
+    return tuple_of<4>(o.take(on));
     END_HANDLE_TH_ERRORS
 }
 
@@ -424,9 +462,9 @@ struct Level {
         parent_out = has_parent ? static_cast<int32_t*>(par.data_ptr()) : nullptr;
         lse = a.f32(first + 5, "lse_out");
     }
-    PyObject* parent(const Arguments& a, int first) const {
+    PyObject* parent(const CallStream& on, const Arguments& a, int first) const {
         if (a.given(first + 4) || !parent_made.defined()) { Py_INCREF(a.obj(first + 4)); return a.obj(first + 4); }
-        return THPVariable_Wrap(parent_made);
+        return on.wrap(parent_made);
     }
 };
 
@@ -435,13 +473,14 @@ PyObject* draft_topk(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     HANDLE_TH_ERRORS
     const Arguments a{args, nargs, "specvlm_draft_topk"};
     const at::Tensor& l = logits_of(a, 0);
+    const CallStream on(a, 8, l);
     const int64_t K = a.integer(1);
     const Level v(a, 2, l, K);
     check(unlocked(lib.specvlm_draft_topk, dtype_code(l), l.size(0), l.size(1), l.size(2), K, l.data_ptr(), l.stride(0), l.stride(1),
                                  v.cum, v.cum_stride, v.parent_idx, v.parent_stride, static_cast<float*>(v.score.data_ptr()),
-                                 static_cast<int32_t*>(v.token.data_ptr()), v.parent_out, v.score.stride(0), v.lse, a.stream(8)),
+                                 static_cast<int32_t*>(v.token.data_ptr()), v.parent_out, v.score.stride(0), v.lse, on.handle()),
           a.what);
-    return tuple_of<3>({keep(a.obj(4), v.score), keep(a.obj(5), v.token), v.parent(a, 2)});
+    return tuple_of<3>({on.keep(a.obj(4), v.score), on.keep(a.obj(5), v.token), v.parent(on, a, 2)});
     END_HANDLE_TH_ERRORS
 }
 
@@ -464,6 +503,7 @@ PyObject* draft_topk_select(PyObject*, PyObject* const* args, Py_ssize_t nargs) 
     HANDLE_TH_ERRORS
     const Arguments a{args, nargs, "specvlm_draft_topk_select"};
     const at::Tensor& l = logits_of(a, 0);
+    const CallStream on(a, 14, l);
     const int64_t K = a.integer(1), M = a.integer(2), B = l.size(0);
     const Level v(a, 3, l, K);
     const Selection s(a, 10, l, B, M);
@@ -472,10 +512,10 @@ PyObject* draft_topk_select(PyObject*, PyObject* const* args, Py_ssize_t nargs) 
                                         v.cum, v.cum_stride, v.parent_idx, v.parent_stride, static_cast<float*>(v.score.data_ptr()),
                                         static_cast<int32_t*>(v.token.data_ptr()), v.parent_out, v.score.stride(0), v.lse, M,
                                         a.integer(9), static_cast<int32_t*>(s.sel.data_ptr()), static_cast<float*>(s.score.data_ptr()),
-                                        static_cast<int32_t*>(s.count.data_ptr()), static_cast<int32_t*>(counters.data_ptr()), a.stream(14)),
+                                        static_cast<int32_t*>(s.count.data_ptr()), static_cast<int32_t*>(counters.data_ptr()), on.handle()),
           a.what);
-    return tuple_of<6>({keep(a.obj(5), v.score), keep(a.obj(6), v.token), v.parent(a, 3), keep(a.obj(10), s.sel),
-                        keep(a.obj(11), s.score), keep(a.obj(12), s.count)});
+    return tuple_of<6>({on.keep(a.obj(5), v.score), on.keep(a.obj(6), v.token), v.parent(on, a, 3), on.keep(a.obj(10), s.sel),
+                        on.keep(a.obj(11), s.score), on.keep(a.obj(12), s.count)});
     END_HANDLE_TH_ERRORS
 }
 
@@ -485,14 +525,15 @@ PyObject* draft_select(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     const Arguments a{args, nargs, "specvlm_draft_select"};
     const at::Tensor& score = a.tensor(0, "score");
     want(score.dim() == 2, "score must have two dimensions");
+    const CallStream on(a, 7, score);
     a.f32(0, "score");
     const int64_t B = score.size(0), M = a.integer(1);
     const Selection s(a, 4, score, B, M);
     check(unlocked(lib.specvlm_draft_select, B, score.size(1), M, static_cast<const float*>(score.data_ptr()), score.stride(0), a.i32(2, "num_cand"),
                                    a.integer(3), static_cast<int32_t*>(s.sel.data_ptr()), static_cast<float*>(s.score.data_ptr()),
-                                   static_cast<int32_t*>(s.count.data_ptr()), a.stream(7)),
+                                   static_cast<int32_t*>(s.count.data_ptr()), on.handle()),
           a.what);
-    return tuple_of<3>({keep(a.obj(4), s.sel), keep(a.obj(5), s.score), keep(a.obj(6), s.count)});
+    return tuple_of<3>({on.keep(a.obj(4), s.sel), on.keep(a.obj(5), s.score), on.keep(a.obj(6), s.count)});
     END_HANDLE_TH_ERRORS
 }
 
@@ -502,6 +543,7 @@ PyObject* draft_finalize(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     const Arguments a{args, nargs, "specvlm_draft_finalize"};
     const at::Tensor &score = a.tensor(0, "cand_score"), &par = a.tensor(1, "cand_parent"), &tok = a.tensor(2, "cand_token");
     want(score.dim() == 2, "cand_score must have two dimensions");
+    const CallStream on(a, 8, score);
     a.f32(0, "cand_score");
     const int64_t B = score.size(0), N = a.integer(4);
     for (const at::Tensor* t : {&par, &tok})
@@ -529,11 +571,11 @@ PyObject* draft_finalize(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     check(unlocked(lib.specvlm_draft_finalize, B, score.size(1), N, static_cast<const float*>(score.data_ptr()),
                                      static_cast<const int32_t*>(par.data_ptr()), static_cast<const int32_t*>(tok.data_ptr()),
                                      score.stride(0), a.i32(5, "num_cand"), a.i32(3, "root_token"), p(0), p(1), p(2), p(3),
-                                     a.i32_unchecked(6, "err_flag"), a.stream(8)),
+                                     a.i32_unchecked(6, "err_flag"), on.handle()),
           a.what);
     std::array<PyObject*, 4> r;
     for (int x = 0; x < 4; ++x) {
-        if (t[x].defined()) { r[x] = keep(given[x], t[x]); continue; }
+        if (t[x].defined()) { r[x] = on.keep(given[x], t[x]); continue; }
         Py_INCREF(Py_None);
         r[x] = Py_None;
     }
@@ -547,6 +589,7 @@ PyObject* head_argmax(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     HANDLE_TH_ERRORS
     const Arguments a{args, nargs, "specvlm_head_argmax"};
     const at::Tensor &h = a.tensor(0, "hidden"), &w = a.tensor(1, "weight");
+    const CallStream on(a, 6, h);
     want(h.dim() == 3 && w.dim() == 2 && h.stride(2) == 1 && w.stride(1) == 1 && w.size(1) == h.size(2),
          "hidden [B,N_max,E] and weight [V,E] need a contiguous last dimension of equal size");
     const int64_t B = h.size(0), N = h.size(1), V = w.size(0);
@@ -558,9 +601,9 @@ PyObject* head_argmax(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     const at::Tensor& ws = a.given(5) ? a.tensor(5, "workspace") : scratch;
     check(unlocked(lib.specvlm_head_argmax, dtype_code(h), B, N, h.size(2), V, h.data_ptr(), h.stride(0), h.stride(1), w.data_ptr(), w.stride(0),
                                   a.i32(2, "num_nodes"), out, a.f32(4, "max_logit"), ws.data_ptr(),
-                                  static_cast<size_t>(ws.numel() * ws.element_size()), a.stream(6)),
+                                  static_cast<size_t>(ws.numel() * ws.element_size()), on.handle()),
           a.what);
-    return keep(a.obj(3), made);
+    return on.keep(a.obj(3), made);
     END_HANDLE_TH_ERRORS
 }
 
@@ -569,6 +612,7 @@ PyObject* visual_pool(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     HANDLE_TH_ERRORS
     const Arguments a{args, nargs, "specvlm_visual_pool"};
     const at::Tensor& x = a.tensor(0, "x");
+    const CallStream on(a, 6, x);
     want(x.dim() == 3, "x must have three dimensions");
     const int64_t B = x.size(0), T = x.size(1), E = x.size(2), ratio = a.integer(1);
     const int64_t Tp = ratio > 0 ? (T + ratio - 1) / ratio : T;      // (the library rejects ratio < 1)
@@ -582,9 +626,9 @@ PyObject* visual_pool(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     check(unlocked(fn, dtype_code(x), B, T, E, ratio, x.data_ptr(), x.stride(0), x.stride(1), a.i32(2, "num_tokens"),
                                   out.data_ptr(), out.stride(0), out.stride(1),
                                   a.given(4) ? a.i32(4, "out_tokens") : static_cast<int32_t*>(made_n.data_ptr()),
-                                  a.i32_unchecked(5, "err_flag"), a.stream(6)),
+                                  a.i32_unchecked(5, "err_flag"), on.handle()),
           a.what);
-    return tuple_of<2>({keep(a.obj(3), made), keep(a.obj(4), made_n)});
+    return tuple_of<2>({on.keep(a.obj(3), made), on.keep(a.obj(4), made_n)});
     END_HANDLE_TH_ERRORS
 }
 
@@ -593,6 +637,7 @@ PyObject* visual_prune(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     HANDLE_TH_ERRORS
     const Arguments a{args, nargs, "specvlm_visual_prune"};
     const at::Tensor &x = a.tensor(0, "x"), &kept = a.tensor(1, "keep");
+    const CallStream on(a, 4, x);
     want(x.dim() == 3 && kept.dim() == 2, "x must have three dimensions and keep two");
     const int64_t B = x.size(0), T = x.size(1), E = x.size(2), Tk = kept.size(1);
     at::Tensor made;
@@ -601,9 +646,9 @@ PyObject* visual_prune(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
     want(out.dim() == 3 && x.stride(2) == 1 && out.stride(2) == 1, "feature dimension must be contiguous");
     auto* const fn = a.given(2) ? lib.specvlm_visual_prune : lib.specvlm_visual_prune_padded;
     check(unlocked(fn, dtype_code(x), B, T, Tk, E, x.data_ptr(), x.stride(0), x.stride(1), a.i32(1, "keep"),
-                                   out.data_ptr(), out.stride(0), out.stride(1), a.i32_unchecked(3, "err_flag"), a.stream(4)),
+                                   out.data_ptr(), out.stride(0), out.stride(1), a.i32_unchecked(3, "err_flag"), on.handle()),
           a.what);
-    return keep(a.obj(2), made);
+    return on.keep(a.obj(2), made);
     END_HANDLE_TH_ERRORS
 }
 

@@ -22,8 +22,6 @@ HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I" + INC
                # keep MFMA accumulators in architectural VGPRs: the attention kernel rescales and
                # converts them with VALU ops, and AGPR copies would dominate its inner loop
                "-mllvm", "-amdgpu-mfma-vgpr-form"]
-# no NaN takes part in a score's maximum: fmaxf without quieting its operands first
-SOURCE_FLAGS = {"attn_wave.hip": ["-fno-honor-nans"]}
 
 
 def _hipcc() -> str:
@@ -57,7 +55,7 @@ def build(verbose: bool = False) -> str:
         objs = [os.path.join(tmp, s + ".o") for s in SOURCES]
         with ThreadPoolExecutor(max_workers=8) as pool:
             native = pool.submit(_run, native_command())
-            said = list(pool.map(_run, [[_hipcc(), *HIPCC_FLAGS, *SOURCE_FLAGS.get(s, []), "-c", os.path.join(CSRC, s), "-o", o]
+            said = list(pool.map(_run, [[_hipcc(), *HIPCC_FLAGS, "-c", os.path.join(CSRC, s), "-o", o]
                                         for s, o in zip(SOURCES, objs)]))
             said.append(_run([_hipcc(), "--offload-arch=gfx950", "-fPIC", "-shared", "-o", LIB, *objs]))
             said.append(native.result())
@@ -71,7 +69,7 @@ def kernel_resource_usage(source: str) -> dict:
     compiler's own kernel-resource-usage remarks (device code only, nothing is linked)."""
     import re
     with tempfile.TemporaryDirectory() as tmp:
-        said = _run([_hipcc(), *HIPCC_FLAGS, *SOURCE_FLAGS.get(source, []), "-Rpass-analysis=kernel-resource-usage", "--cuda-device-only", "-c",
+        said = _run([_hipcc(), *HIPCC_FLAGS, "-Rpass-analysis=kernel-resource-usage", "--cuda-device-only", "-c",
                      "-o", os.path.join(tmp, "k.o"), os.path.join(CSRC, source)])
     out, name = {}, None
     for line in said.splitlines():

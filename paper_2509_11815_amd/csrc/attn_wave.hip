@@ -51,9 +51,10 @@ struct WaveParams {
 __device__ __forceinline__ uint32_t divide(uint32_t n, uint32_t m) { return __umulhi(2 * n, m); }
 uint32_t divisor(uint32_t d) { return (0x80000000u + d - 1) / d; }
 
-// the greatest of eight scores (this file is compiled without NaN semantics: max3 without canonicalisation)
+// The greatest of eight scores, NaN where one is: v_maximum3 takes its operands as they are (fmaxf would quiet each first).
 __device__ __forceinline__ float max8(f32x4 a, f32x4 b) {
-    return fmaxf(fmaxf(fmaxf(fmaxf(a[0], a[1]), a[2]), fmaxf(fmaxf(a[3], b[0]), b[1])), fmaxf(b[2], b[3]));
+    auto max3 = [](float x, float y, float z) { return __builtin_elementwise_maximum(__builtin_elementwise_maximum(x, y), z); };
+    return max3(max3(a[0], a[1], a[2]), max3(a[3], b[0], b[1]), __builtin_elementwise_maximum(b[2], b[3]));
 }
 
 constexpr int kWaveWgs = 4;               // wavefronts per workgroup, one per SIMD, a key stream each

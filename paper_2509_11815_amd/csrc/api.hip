@@ -57,13 +57,13 @@ int32_t specvlm_last_hip_error(void) { return g_last_hip_error; }
 size_t specvlm_tree_verify_attn_workspace_bytes(const specvlm_attn_desc* desc) {
     if (!desc || check_attn_desc(*desc)) return 0;
     if (desc->dtype == SPECVLM_F32) return 256;
-    return attn_mfma_workspace_bytes(*desc, attn_mfma_pick_splits(*desc));
+    return attn_mfma_workspace_bytes(*desc, attn_plan(*desc).ranges);
 }
 
 int32_t specvlm_tree_verify_attn_num_splits(const specvlm_attn_desc* desc) {
     if (!desc || check_attn_desc(*desc)) return 0;
     if (desc->dtype == SPECVLM_F32) return 1;
-    return attn_mfma_pick_splits(*desc);
+    return attn_plan(*desc).ranges;
 }
 
 enum { kCallerWorkspace = 0, kStaticWorkspace = 1, kVectorAluKernel = 2 };
@@ -93,8 +93,8 @@ static int32_t tree_verify_attn(const specvlm_attn_desc* desc, const void* q_dev
     a.err_flag = err_flag_dev; a.stream = static_cast<hipStream_t>(stream);
     if (mode == kVectorAluKernel) return launch_attn_valu(a);
     if (desc->dtype == SPECVLM_F32) return launch_attn_f32(a);
-    a.num_splits = attn_mfma_pick_splits(*desc);
-    const size_t need = attn_mfma_workspace_bytes(*desc, a.num_splits);
+    a.plan = attn_plan(*desc);
+    const size_t need = attn_mfma_workspace_bytes(*desc, a.plan.ranges);
     if (need) {
         if (static_workspace) {
             if (need > SPECVLM_STATIC_WORKSPACE_BYTES) return SPECVLM_WORKSPACE_TOO_SMALL;

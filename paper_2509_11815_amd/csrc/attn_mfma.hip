@@ -51,9 +51,8 @@ namespace specvlm {
 constexpr int kWaves = 8;           // wavefronts per workgroup: two per SIMD
 constexpr int kShare = 4;           // wavefronts sharing one key stream, 64/kShare query rows each
 constexpr int kAhead = 2;           // tiles per stream kept in flight ahead of the one being consumed
-constexpr int kStreamsPerWg = kWaves / kShare;
 constexpr int kThreads = kWaves * 64;
-constexpr int kTile = 32;           // keys per tile
+static_assert(kWaves / kShare == kStreamsPerWg, "the plan's streams");
 
 struct MfmaParams {
     KvGeom g;
@@ -121,123 +120,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4))
 #undef SPECVLM_SPREAD_REQUESTS
 }
 
-// Key-range splits per (request, head) when the caller leaves the choice to the library: the
-// count that minimises a small cost model of the kernel on 256 compute units, one workgroup
-// each.  A workgroup costs a fixed prologue + merge time plus one step per 32-key tile of its
-// longest stream; a step takes the measured time of the loop body with two tiles in flight
-// (the same with 160 or 256 units active), or the workgroup's share of HBM bandwidth if that
-// is slower; workgroups beyond 256 run as further rounds.  The cache capacity stands in for
-// the request lengths, which the host does not know.
-static int32_t single_round_splits(const specvlm_attn_desc& d) {
-    const int64_t heads = static_cast<int64_t>(d.B) * d.H_q;
-    if (heads > kMaxSplitHeads) return 1;      // more (request, head) pairs than ticket counters: that many fill the chip unsplit
-    if (d.num_splits > 0) return min(d.num_splits, 64);
-    const int cus = 256;
-    const int bh = d.B * d.H_q;
-    const int cap = d.paged ? d.max_blocks_per_req * SPECVLM_PAGE_SIZE : d.kv_capacity;
-    const int ntile = (cap + kTile - 1) / kTile;
-    const double step_bytes = static_cast<double>(kStreamsPerWg) * kTile * d.D * 2 * 2;   // K and V, bf16
-    const double bw = 6.0e6;                                     // bytes per microsecond the loop sustains
-    const double step_alone = d.D == 128 ? 1.35 : 0.9;           // microseconds per step of one compute unit by itself
-    auto wg_time = [&](int splits, int active) {
-        const int steps = (ntile + kStreamsPerWg * splits - 1) / (kStreamsPerWg * splits);
-        const double step = fmax(step_alone, step_bytes * active / bw);
-        return (splits > 1 ? 8.0 : 5.0) + steps * step;
-    };
-    const int most = max(1, min(64, ntile / kStreamsPerWg));     // never a stream without a whole tile
-    int best = 1;
-    double best_t = 1e30;
-    for (int s = 1; s <= most; ++s) {
-        const long wgs = static_cast<long>(bh) * s;
-        const long full = wgs / cus;
-        const int rest = static_cast<int>(wgs % cus);
-        const double t = full * wg_time(s, cus) + (rest ? wg_time(s, rest) : 0.0);
-        if (t < best_t * 0.999) { best_t = t; best = s; }
-    }
-    return best;
-}
-
-// A batch whose query heads share KV heads gets twice the key ranges where these then fill the chip twice over
-// (the launch shape with two workgroups per compute unit): most of its tiles come from L2, so a second
-// workgroup's steps cost little, and a short request's workgroups make room next to a long one's.
-// us, 2 -> 4 ranges: 32 / 8 heads, 2000 keys x 4 25.2 -> 25.2, 2500 - 300 x 4 27.4 -> 22.0; 64 / 8 heads, 3000 x 2
-// 31.3 -> 29.2, 4500 + 900 41.0 -> 29.2.  Not taken where equal lengths lost: no shared KV heads 31.2 -> 32.6, two query
-// heads per KV head 25.2 -> 26.1, more than four ranges 21.6 -> 24.6, head size 64 18.7 -> 19.7; nor for a
-// call without key ranges, whose results would gain the rounding of partial results; short streams have
-// nothing to divide.
-int32_t attn_mfma_pick_splits(const specvlm_attn_desc& d) {
-    const int32_t base = single_round_splits(d);
-    if (d.num_splits > 0 || d.B < 2 || d.D != 128) return base;
-    if (d.H_q / d.H_kv < 4 || base != 2) return base;
-    const int64_t items = 2ll * base * d.B * d.H_q;
-    const int cap = d.paged ? d.max_blocks_per_req * SPECVLM_PAGE_SIZE : d.kv_capacity;
-    const bool long_streams = cap >= 12 * kStreamsPerWg * kTile * base;
-    return items > 448 && items <= 512 && long_streams ? 2 * base : base;
-}
-
-// How a call is divided among workgroups: query rows and key ranges, or key ranges only.
-//
-// With few (request, head) pairs the chip can be filled in two ways.  Key ranges (the kernels of this
-// file): every workgroup takes all 64 query rows, K and V are fetched once, and the 2 - 64 partial results
-// of a head meet at the end.  Query rows as well (attn_wave.hip): workgroups of 16 or 32 rows, whose
-// K and V come from L2 for all but the first of a head's row blocks, with a quarter or half of the
-// arithmetic each, so that fewer or no partial results have to meet, and those are a quarter or half the size.
-// The model below is fitted to measured calls (us; 1 x 32 heads x 128, 60 nodes, all on 256 workgroups):
-//   260 keys   key ranges 10.7 (1 split)   32 rows  8.4 (4)   16 rows  7.3 (1)
-//   828        key ranges 11.4 (8)         32 rows  9.9 (4)   16 rows  9.9 (2)
-//   3324       key ranges 16.5 (8)         32 rows 16.8 (4)   16 rows 23.6 (2)
-// so rows win until the repeated K and V traffic (at most ~14 TB/s from L2) costs more than the merge.
-struct AttnPlan { int block_rows, splits; };           // block_rows 0: key ranges only
-AttnPlan attn_plan(const specvlm_attn_desc& d, int32_t nominal) {
-    const int cus = 256;
-    const int group = d.H_q / d.H_kv, rows = group * d.N_max;
-    const int cap = d.paged ? d.max_blocks_per_req * SPECVLM_PAGE_SIZE : d.kv_capacity;
-    const int ntile = (cap + kTile - 1) / kTile;
-    const double half = d.D == 128 ? 1.0 : 0.5;            // tile size relative to head size 128
-    auto rounds_of = [&](double items, auto&& one) {       // us of `items` workgroups, 256 at a time
-        const int full = static_cast<int>(items / cus), rest = static_cast<int>(items) - full * cus;
-        return full * one(cus) + (rest ? one(rest) : 0.0);
-    };
-    const double heads = static_cast<double>(d.B) * d.H_q;
-    const int steps = (ntile + kStreamsPerWg * nominal - 1) / (kStreamsPerWg * nominal);
-    const double step = d.D == 128 ? 0.85 : 0.6;
-    const double merge = nominal == 1 ? 0.0 : nominal <= 8 ? 2.8 : 0.8 * nominal;
-    const double items = heads * nominal;
-    AttnPlan best{0, nominal};
-    double best_t = items > cus && items <= 2 * cus
-        ? 6.5 + merge + steps * fmax(2 * step, items * half * 32768 / 6.2e6)
-        : rounds_of(items, [&](int active) { return 6.5 + merge + steps * fmax(step, active * half * 32768 / 8.0e6); });
-    // what the row-dividing kernels assume (32-bit offsets into a request's query rows and a half tile)
-    if (d.kv_stride_t >= (1 << 22) || (d.N_max * d.q_stride_n + group * d.q_stride_h) >= (1ll << 30) ||
-        heads * 4 * nominal >= (1 << 24))
-        return best;
-    for (int br = 16; br <= 32; br *= 2) {
-        if (br == 32 && rows <= 16) break;
-        const int rb = (rows + br - 1) / br;
-        const double units = static_cast<double>(d.B) * d.H_kv * rb;
-        const double a = br == 16 ? (d.D == 128 ? 4.8 : 4.3) : (d.D == 128 ? 5.2 : 4.6);
-        const double c = br == 16 ? 1.9 : 2.5, b = (br == 16 ? 0.9 : 1.05) * (d.D == 128 ? 1.0 : 0.57);
-        const int s_lo = d.num_splits > 0 ? nominal : 1;      // a caller's count is taken as given
-        for (int s = s_lo; s <= nominal; ++s) {
-            if (s > 1 && units > kMaxSplitHeads) break;    // one set of ticket counters per unit
-            const int r = (ntile + 4 * s - 1) / (4 * s);
-            const double t = rounds_of(units * s, [&](int active) {
-                return a + (s > 1 ? c + 0.8 * ((s - 1) / 8) : 0.0) + r * fmax(b, active * half * 65536 / 13.5e6);
-            });
-            if (t < best_t * 0.98) { best_t = t; best = AttnPlan{br, s}; }
-        }
-    }
-    return best;
-}
-
 // The ticket counters occupy a region of fixed size at the start of the workspace, whatever the
 // shape: a later call of another shape then finds its counters where every earlier call left
 // zeros, never where one stored partial results.
 static size_t counter_bytes(const specvlm_attn_desc&) { return kCounterBytes; }
 
-size_t attn_mfma_workspace_bytes(const specvlm_attn_desc& d, int32_t splits) {
-    if (splits == 1) return 0;
-    const size_t parts = static_cast<size_t>(d.B) * d.H_q * splits;
+size_t attn_mfma_workspace_bytes(const specvlm_attn_desc& d, int32_t ranges) {
+    if (ranges == 1) return 0;
+    const size_t parts = static_cast<size_t>(d.B) * d.H_q * ranges;
     return counter_bytes(d) + parts * (static_cast<size_t>(kQRows) * d.D * 2 + kQRows * 8);
 }
 
@@ -271,14 +161,13 @@ int32_t attn_static_workspace(void** ptr_out) {
 
 int32_t launch_attn_mfma(const AttnArgs& a) {
     const specvlm_attn_desc& d = a.d;
-    const AttnPlan plan = attn_plan(d, single_round_splits(d));
-    if (plan.block_rows) return launch_attn_wave(a, plan.block_rows, plan.splits);
+    if (a.plan.block_rows) return launch_attn_wave(a);
     MfmaParams p;
     p.g = KvGeom{d.kv_stride_b, d.kv_stride_h, d.kv_stride_t, d.paged ? a.block_table : nullptr,
                  d.max_blocks_per_req, d.num_blocks,
                  d.paged ? d.max_blocks_per_req * SPECVLM_PAGE_SIZE : d.kv_capacity};
     p.N_max = d.N_max; p.H_q = d.H_q; p.group = d.H_q / d.H_kv;
-    p.num_splits = a.num_splits;
+    p.num_splits = a.plan.splits;
     p.xcd_heads = d.B > 1 && d.H_kv % 8 == 0 ? d.H_q / 8 : 0;
     p.scale = a.scale;
     p.q = static_cast<const uint16_t*>(a.q);
@@ -300,7 +189,7 @@ int32_t launch_attn_mfma(const AttnArgs& a) {
     // all of them resident at once instead of running a second, partly filled round (13B-shaped
     // batch of 4 with 3 splits, 480 items: 70.7 against 75.8 us; with 256 items or fewer the first
     // shape's deeper rings win: 16.5 against 23.3 us at the 2880-visual-token prefix).
-    if (parts > 256 && parts <= 512) {
+    if (parts > 256 && parts <= kMostTwoPerCu) {
         if (d.D == 128) hipLaunchKernelGGL((attn_mfma_kernel_2wg<128>), grid, block, 0, a.stream, p);
         else hipLaunchKernelGGL((attn_mfma_kernel_2wg<64>), grid, block, 0, a.stream, p);
     } else {

@@ -1,0 +1,140 @@
+// How a bf16 verification call is divided among workgroups.  Host arithmetic only, so that it can be checked
+// without a GPU.
+#pragma once
+#include <algorithm>
+#include <cmath>
+#include <cstdint>
+
+#include "specvlm.h"
+
+namespace specvlm {
+
+constexpr int kTile = 32;           // keys per tile
+constexpr int kStreamsPerWg = 2;    // key streams of a workgroup that takes all query rows of a head
+constexpr int kMostTwoPerCu = 512;  // work items that the launch shape with two workgroups per compute unit holds at once
+constexpr int kMaxSplitHeads = 1024;  // (request, head) pairs a split call can have: one set of ticket counters each
+
+// Key-range splits per (request, head) when the caller leaves the choice to the library: the
+// count that minimises a small cost model of the kernel on 256 compute units, one workgroup
+// each.  A workgroup costs a fixed prologue + merge time plus one step per 32-key tile of its
+// longest stream; a step takes the measured time of the loop body with two tiles in flight
+// (the same with 160 or 256 units active), or the workgroup's share of HBM bandwidth if that
+// is slower; workgroups beyond 256 run as further rounds.  The cache capacity stands in for
+// the request lengths, which the host does not know.
+inline int32_t single_round_ranges(const specvlm_attn_desc& d) {
+    const int64_t heads = static_cast<int64_t>(d.B) * d.H_q;
+    if (heads > kMaxSplitHeads) return 1;      // more (request, head) pairs than ticket counters: that many fill the chip unsplit
+    if (d.num_splits > 0) return std::min(d.num_splits, 64);
+    const int cus = 256;
+    const int bh = d.B * d.H_q;
+    const int cap = d.paged ? d.max_blocks_per_req * SPECVLM_PAGE_SIZE : d.kv_capacity;
+    const int ntile = (cap + kTile - 1) / kTile;
+    const double step_bytes = static_cast<double>(kStreamsPerWg) * kTile * d.D * 2 * 2;   // K and V, bf16
+    const double bw = 6.0e6;                                     // bytes per microsecond the loop sustains
+    const double step_alone = d.D == 128 ? 1.35 : 0.9;           // microseconds per step of one compute unit by itself
+    auto wg_time = [&](int splits, int active) {
+        const int steps = (ntile + kStreamsPerWg * splits - 1) / (kStreamsPerWg * splits);
+        const double step = std::fmax(step_alone, step_bytes * active / bw);
+        return (splits > 1 ? 8.0 : 5.0) + steps * step;
+    };
+    const int most = std::max(1, std::min(64, ntile / kStreamsPerWg));     // never a stream without a whole tile
+    int best = 1;
+    double best_t = 1e30;
+    for (int s = 1; s <= most; ++s) {
+        const long wgs = static_cast<long>(bh) * s;
+        const long full = wgs / cus;
+        const int rest = static_cast<int>(wgs % cus);
+        const double t = full * wg_time(s, cus) + (rest ? wg_time(s, rest) : 0.0);
+        if (t < best_t * 0.999) { best_t = t; best = s; }
+    }
+    return best;
+}
+
+// How a call is divided among workgroups: query rows and key ranges, or key ranges only.
+//
+// With few (request, head) pairs the chip can be filled in two ways.  Key ranges (attn_mfma.hip):
+// every workgroup takes all 64 query rows, K and V are fetched once, and the 2 - 64 partial results
+// of a head meet at the end.  Query rows as well (attn_wave.hip): workgroups of 16 or 32 rows, whose
+// K and V come from L2 for all but the first of a head's row blocks, with a quarter or half of the
+// arithmetic each, so that fewer or no partial results have to meet, and those are a quarter or half the size.
+// The model below is fitted to measured calls (us; 1 x 32 heads x 128, 60 nodes, all on 256 workgroups):
+//   260 keys   key ranges 10.7 (1 split)   32 rows  8.4 (4)   16 rows  7.3 (1)
+//   828        key ranges 11.4 (8)         32 rows  9.9 (4)   16 rows  9.9 (2)
+//   3324       key ranges 16.5 (8)         32 rows 16.8 (4)   16 rows 23.6 (2)
+// so rows win until the repeated K and V traffic (at most ~14 TB/s from L2) costs more than the merge.
+struct AttnPlan {
+    int32_t ranges;        // key ranges per head that the workspace holds
+    int32_t block_rows;    // query rows per workgroup, 0: all (key ranges only)
+    int32_t splits;        // key ranges the call takes, <= ranges
+};
+
+inline AttnPlan plan_rows(const specvlm_attn_desc& d, int32_t nominal) {
+    const int cus = 256;
+    const int group = d.H_q / d.H_kv, rows = group * d.N_max;
+    const int cap = d.paged ? d.max_blocks_per_req * SPECVLM_PAGE_SIZE : d.kv_capacity;
+    const int ntile = (cap + kTile - 1) / kTile;
+    const double half = d.D == 128 ? 1.0 : 0.5;            // tile size relative to head size 128
+    auto rounds_of = [&](double items, auto&& one) {       // us of `items` workgroups, 256 at a time
+        const int full = static_cast<int>(items / cus), rest = static_cast<int>(items) - full * cus;
+        return full * one(cus) + (rest ? one(rest) : 0.0);
+    };
+    const double heads = static_cast<double>(d.B) * d.H_q;
+    const int steps = (ntile + kStreamsPerWg * nominal - 1) / (kStreamsPerWg * nominal);
+    const double step = d.D == 128 ? 0.85 : 0.6;
+    const double merge = nominal == 1 ? 0.0 : nominal <= 8 ? 2.8 : 0.8 * nominal;
+    const double items = heads * nominal;
+    AttnPlan best{nominal, 0, nominal};
+    double best_t = items > cus && items <= 2 * cus
+        ? 6.5 + merge + steps * std::fmax(2 * step, items * half * 32768 / 6.2e6)
+        : rounds_of(items, [&](int active) { return 6.5 + merge + steps * std::fmax(step, active * half * 32768 / 8.0e6); });
+    // what the row-dividing kernels assume (32-bit offsets into a request's query rows and a half tile)
+    if (d.kv_stride_t >= (1 << 22) || (d.N_max * d.q_stride_n + group * d.q_stride_h) >= (1ll << 30) ||
+        heads * 4 * nominal >= (1 << 24))
+        return best;
+    for (int br = 16; br <= 32; br *= 2) {
+        if (br == 32 && rows <= 16) break;
+        const int rb = (rows + br - 1) / br;
+        const double units = static_cast<double>(d.B) * d.H_kv * rb;
+        const double a = br == 16 ? (d.D == 128 ? 4.8 : 4.3) : (d.D == 128 ? 5.2 : 4.6);
+        const double c = br == 16 ? 1.9 : 2.5, b = (br == 16 ? 0.9 : 1.05) * (d.D == 128 ? 1.0 : 0.57);
+        const int s_lo = d.num_splits > 0 ? nominal : 1;      // a caller's count is taken as given
+        for (int s = s_lo; s <= nominal; ++s) {
+            if (s > 1 && units > kMaxSplitHeads) break;    // one set of ticket counters per unit
+            const int r = (ntile + 4 * s - 1) / (4 * s);
+            const double t = rounds_of(units * s, [&](int active) {
+                return a + (s > 1 ? c + 0.8 * ((s - 1) / 8) : 0.0) + r * std::fmax(b, active * half * 65536 / 13.5e6);
+            });
+            if (t < best_t * 0.98) { best_t = t; best = AttnPlan{nominal, br, s}; }
+        }
+    }
+    return best;
+}
+
+// A batch in which at least four query heads share a KV head takes four key ranges instead of two, in the launch shape
+// with two workgroups per compute unit: most of its tiles come from L2, so that a second workgroup's steps cost
+// little, and a short request's workgroups make room next to a long one's.
+// us per call (head size 128, 60 nodes), 2 -> 4 ranges | 32-row blocks:
+//   query / KV heads x requests     equal lengths                            very different lengths
+//   32 / 8 x 4                      3000 keys 30.9 -> 29.8 | 29.5            2500 - 300  27.5 -> 21.7 | 24.5
+//                                   4500      41.3 -> 39.5 | 42.4
+//   64 / 8 x 2                      4500      41.2 -> 37.8 | 37.0            4500 + 900  41.1 -> 29.2 | 36.1
+//   40 / 8 x 3                      3000      30.9 -> 29.9 | 27.7            4500 - 1000 40.9 -> 29.9 | 37.7
+//   28 / 4 x 4                      3000      30.8 -> 28.8 | 26.8            3000 - 500  31.0 -> 27.9 | 26.3
+//   32 / 8 x 3                      3000      30.7 -> 28.4 | 27.8            3000 - 500  30.7 -> 23.2 | 26.9
+//   48 / 8 x 2                      4500      40.9 -> 35.8 | 37.0            4500 + 700  41.1 -> 28.9 | 36.4
+// Row blocks are chosen first, by their comparison with two ranges: where that favours them they also beat four
+// at equal lengths (32 / 8 x 4, 2000 keys 25.1 | 22.9; 64 / 8 x 2, 3000 keys 29.3 | 26.8), and where it does not they lose
+// little there and much at different ones.
+// Not taken where equal lengths lost: no shared KV heads 31.2 -> 32.6, two query heads per KV head
+// 25.2 -> 26.1, more than four ranges 21.6 -> 24.6, head size 64 18.7 -> 19.7; nor for a call without key ranges,
+// whose results would gain the rounding of partial results; streams shorter than 12 tiles have nothing to divide.
+inline AttnPlan attn_plan(const specvlm_attn_desc& d) {
+    AttnPlan plan = plan_rows(d, single_round_ranges(d));
+    if (plan.block_rows || d.num_splits > 0 || plan.ranges != 2) return plan;
+    if (d.B < 2 || d.D != 128 || d.H_q / d.H_kv < 4) return plan;
+    const int cap = d.paged ? d.max_blocks_per_req * SPECVLM_PAGE_SIZE : d.kv_capacity;
+    if (cap >= 12 * kStreamsPerWg * kTile * 2 && 4ll * d.B * d.H_q <= kMostTwoPerCu) plan.ranges = plan.splits = 4;
+    return plan;
+}
+
+}  // namespace specvlm

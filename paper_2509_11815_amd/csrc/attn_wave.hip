@@ -655,7 +655,8 @@ void launch_d(const WaveParams& p, int block_rows, dim3 grid, hipStream_t stream
 
 }  // namespace
 
-int32_t launch_attn_wave(const AttnArgs& a, int block_rows, int splits) {
+int32_t launch_attn_wave(const AttnArgs& a) {
+    const int block_rows = a.plan.block_rows;
     const specvlm_attn_desc& d = a.d;
     WaveParams p;
     p.g = KvGeom{d.kv_stride_b, d.kv_stride_h, d.kv_stride_t, d.paged ? a.block_table : nullptr,
@@ -663,7 +664,7 @@ int32_t launch_attn_wave(const AttnArgs& a, int block_rows, int splits) {
                  d.paged ? d.max_blocks_per_req * SPECVLM_PAGE_SIZE : d.kv_capacity};
     p.N_max = d.N_max; p.H_q = d.H_q; p.H_kv = d.H_kv; p.group = d.H_q / d.H_kv;
     p.row_blocks = (p.group * d.N_max + block_rows - 1) / block_rows;
-    p.num_splits = splits;
+    p.num_splits = a.plan.splits;
     p.magic_splits = divisor(p.num_splits); p.magic_rb = divisor(p.row_blocks); p.magic_hkv = divisor(p.H_kv);
     p.magic_nmax = divisor(p.N_max); p.magic_nstream = divisor(kWaveWgs * p.num_splits);
     p.scale = a.scale;

@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "attn_plan.hpp"
 #include "specvlm.h"
 
 namespace specvlm {
@@ -106,7 +107,7 @@ int32_t launch_draft_finalize(int32_t B, int32_t C, int32_t N_max, const float* 
 struct AttnArgs {
     specvlm_attn_desc d;
     float scale;                // resolved softmax scale
-    int32_t num_splits;         // resolved split count (matrix-core kernel)
+    AttnPlan plan;              // bf16 kernels: how the call is divided
     const void* q;
     const void* k;
     const void* v;
@@ -129,9 +130,8 @@ int32_t launch_attn_valu(const AttnArgs& a);
 // bf16 MFMA split-key kernel + merge.
 int32_t launch_attn_mfma(const AttnArgs& a);
 // ... and the kernel whose workgroups take 16 or 32 query rows each (same workspace layout rules).
-int32_t launch_attn_wave(const AttnArgs& a, int block_rows, int splits);
-size_t attn_mfma_workspace_bytes(const specvlm_attn_desc& d, int32_t splits);
-int32_t attn_mfma_pick_splits(const specvlm_attn_desc& d);
+int32_t launch_attn_wave(const AttnArgs& a);
+size_t attn_mfma_workspace_bytes(const specvlm_attn_desc& d, int32_t ranges);
 // Device address of the current device's library-owned scratch array (SPECVLM_STATIC_WORKSPACE_BYTES).
 int32_t attn_static_workspace(void** ptr_out);
 

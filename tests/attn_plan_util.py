@@ -1,0 +1,58 @@
+"""How the library divides a bf16 attention call among workgroups, from the same header as the library (built with g++)."""
+from __future__ import annotations
+
+import atexit
+import collections
+import ctypes
+import functools
+import os
+import shutil
+import subprocess
+import tempfile
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+Plan = collections.namedtuple("Plan", "ranges block_rows splits")
+
+SOURCE = r"""
+#include "attn_plan.hpp"
+extern "C" void plan(const specvlm_attn_desc* d, int* out) {
+    const specvlm::AttnPlan p = specvlm::attn_plan(*d);
+    out[0] = p.ranges; out[1] = p.block_rows; out[2] = p.splits;
+}
+"""
+
+
+@functools.lru_cache(None)
+def _library():
+    tmp = tempfile.mkdtemp()
+    atexit.register(shutil.rmtree, tmp, ignore_errors=True)
+    src, so = os.path.join(tmp, "plan.cpp"), os.path.join(tmp, "plan.so")
+    with open(src, "w") as f:
+        f.write(SOURCE)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-I" + os.path.join(ROOT, "include"),
+                    "-I" + os.path.join(ROOT, "paper_2509_11815_amd", "csrc"), src, "-o", so], check=True)
+    return ctypes.CDLL(so)
+
+
+def plan_of_desc(desc) -> Plan:
+    out = (ctypes.c_int * 3)()
+    _library().plan(ctypes.byref(desc), out)
+    return Plan(*out)
+
+
+def plan_of(B, Hq, Hkv, D, N, cap, num_splits=0, paged=False, token_stride=None) -> Plan:
+    """Dense tensors of these sizes; `cap` slots per request (a multiple of 16 when paged)."""
+    import paper_2509_11815_amd.binding as b
+    t = D if token_stride is None else token_stride
+    return plan_of_desc(b.AttnDesc(
+        dtype=b.SPECVLM_BF16, B=B, H_q=Hq, H_kv=Hkv, D=D, N_max=N, paged=int(paged), block_size=16 * paged, max_blocks_per_req=cap // 16 * paged,
+        num_blocks=B * (cap // 16) * paged, kv_capacity=cap, num_splits=num_splits, q_stride_b=N * Hq * D, q_stride_n=Hq * D,
+        q_stride_h=D, o_stride_b=N * Hq * D, o_stride_n=Hq * D, o_stride_h=D, kv_stride_b=Hkv * cap * t, kv_stride_h=cap * t, kv_stride_t=t))
+
+
+def plan_of_case(case, num_splits=0) -> Plan:
+    """The plan of a problem from gpu_util.random_case()."""
+    B, N, Hq, D = case["q"].shape
+    Hkv, table = case["k"].shape[1], case["block_table"]
+    cap = case["k"].shape[2] if table is None else table.shape[1] * 16
+    return plan_of(B, Hq, Hkv, D, N, cap, num_splits, table is not None)

@@ -1,7 +1,9 @@
-"""GPU parity of batches whose requests are spread over the XCDs (KV heads a multiple of 8), and of those among them
-that take twice the key ranges (at least four query heads per KV head, long streams)."""
+"""GPU parity of batches in the launch shape with two workgroups per compute unit, whose requests are spread over the XCDs
+where KV heads are a multiple of 8, and of those among them that take twice the key ranges (at least four query heads
+per KV head, long streams); and of batches next to them that are divided otherwise.  Each asserts its division."""
 import pytest
 
+from attn_plan_util import Plan, plan_of_case
 from test_gpu_attn import check, run_both
 
 pytestmark = pytest.mark.gpu
@@ -14,16 +16,35 @@ def sv():
     return sv
 
 
-@pytest.mark.parametrize("B,Hq,Hkv,D,N,P,nn,splits", [
-    (4, 32, 8, 128, 64, [1600, 33, 900, 0], [64, 1, 17, 2], 0),     # four key ranges, two workgroups per unit
-    (2, 64, 8, 128, 60, [1530, 700], None, 0),                      # ... a group of eight
-    (4, 32, 8, 128, 60, [1400, 3, 900, 500], None, 0),              # streams too short for that
-    (9, 24, 24, 64, 20, [600, 5, 77, 31, 33, 200, 0, 64, 95], None, 0),   # three heads per XCD, unsplit
-    (2, 40, 40, 128, 60, [900, 2500], [60, 9], 3),                  # five heads per XCD, a caller's key ranges
-    (3, 20, 20, 128, 60, [900, 100, 2500], None, 0),                # not a multiple of 8: contiguous ranges as before
+@pytest.mark.parametrize("B,Hq,Hkv,D,N,P,nn,splits,plan", [
+    (4, 32, 8, 128, 64, [2400, 33, 900, 0], [64, 1, 17, 2], 0, Plan(4, 0, 4)),     # four ranges, a request shorter than them
+    (2, 64, 8, 128, 60, [3900, 700], None, 0, Plan(4, 0, 4)),                      # ... a group of eight
+    (3, 32, 8, 128, 60, [2500, 3, 900], [60, 60, 7], 0, Plan(4, 0, 4)),            # ... 384 items
+    (3, 40, 10, 128, 60, [2600, 64, 1000], None, 0, Plan(4, 0, 4)),                # ... not a multiple of 8: contiguous ranges of items
+    (9, 40, 40, 64, 20, [280, 5, 77, 31, 33, 200, 0, 64, 95], None, 0, Plan(1, 0, 1)),   # five heads per XCD, unsplit
+    (12, 24, 24, 128, 33, [200, 5, 77, 31, 33, 150, 0, 64, 95, 1, 32, 127], None, 0, Plan(1, 0, 1)),   # three
+    (2, 40, 40, 128, 60, [900, 1500], [60, 9], 4, Plan(4, 0, 4)),                  # a caller's key ranges
+    (5, 20, 20, 128, 60, [900, 100, 1500, 7, 33], None, 3, Plan(3, 0, 3)),         # ... contiguous
 ])
 @pytest.mark.parametrize("paged", [False, True])
-def test_batches(sv, oracle, B, Hq, Hkv, D, N, P, nn, splits, paged):
+def test_two_workgroups_per_compute_unit(sv, oracle, B, Hq, Hkv, D, N, P, nn, splits, plan, paged):
     from gpu_util import random_case
     case = random_case(7300 + Hq + N + B, "bf16", B=B, Hq=Hq, Hkv=Hkv, D=D, N_max=N, P_list=P, num_nodes=nn, paged=paged, cap_extra=0)
+    assert plan_of_case(case, splits) == plan and 256 < B * Hq * plan.ranges <= 512
+    check(case, *run_both(sv, oracle, case, num_splits=splits), f"batch {B}x{Hq}/{Hkv}x{D} N={N} splits={splits} paged={paged}")
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,D,N,P,nn,splits,plan", [
+    (4, 32, 8, 128, 64, [1600, 33, 900, 0], [64, 1, 17, 2], 0, Plan(2, 32, 1)),    # row blocks: streams too short for four ranges
+    (2, 64, 8, 128, 60, [1530, 700], None, 0, Plan(2, 32, 1)),
+    (4, 32, 8, 128, 60, [1400, 3, 900, 500], None, 0, Plan(2, 32, 1)),
+    (9, 24, 24, 64, 20, [600, 5, 77, 31, 33, 200, 0, 64, 95], None, 0, Plan(1, 32, 1)),
+    (2, 40, 40, 128, 60, [900, 2500], [60, 9], 3, Plan(3, 0, 3)),                  # one workgroup per compute unit
+    (3, 20, 20, 128, 60, [900, 100, 2500], None, 0, Plan(4, 0, 4)),
+])
+@pytest.mark.parametrize("paged", [False, True])
+def test_divided_otherwise(sv, oracle, B, Hq, Hkv, D, N, P, nn, splits, plan, paged):
+    from gpu_util import random_case
+    case = random_case(7300 + Hq + N + B, "bf16", B=B, Hq=Hq, Hkv=Hkv, D=D, N_max=N, P_list=P, num_nodes=nn, paged=paged, cap_extra=0)
+    assert plan_of_case(case, splits) == plan and (plan.block_rows or B * Hq * plan.ranges <= 256)
     check(case, *run_both(sv, oracle, case, num_splits=splits), f"batch {B}x{Hq}/{Hkv}x{D} N={N} splits={splits} paged={paged}")

@@ -69,13 +69,13 @@ __device__ __forceinline__ void wait_vmcnt() {
     asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
 }
 
-// The same for a count that is a constant only after loop unrolling (an even number up to 30).
+// The same for a count that is a constant only after loop unrolling (up to 30).
 __device__ __forceinline__ void wait_vmcnt_unrolled(int n) {
     switch (n) {
 #define SPECVLM_WAIT_CASE(N) case N: wait_vmcnt<N>(); break;
-        SPECVLM_WAIT_CASE(0) SPECVLM_WAIT_CASE(2) SPECVLM_WAIT_CASE(4) SPECVLM_WAIT_CASE(6) SPECVLM_WAIT_CASE(8)
-        SPECVLM_WAIT_CASE(10) SPECVLM_WAIT_CASE(12) SPECVLM_WAIT_CASE(14) SPECVLM_WAIT_CASE(16) SPECVLM_WAIT_CASE(18)
-        SPECVLM_WAIT_CASE(20) SPECVLM_WAIT_CASE(22) SPECVLM_WAIT_CASE(24) SPECVLM_WAIT_CASE(26) SPECVLM_WAIT_CASE(28)
+        SPECVLM_WAIT_CASE(0) SPECVLM_WAIT_CASE(1) SPECVLM_WAIT_CASE(2) SPECVLM_WAIT_CASE(3) SPECVLM_WAIT_CASE(4) SPECVLM_WAIT_CASE(5) SPECVLM_WAIT_CASE(6) SPECVLM_WAIT_CASE(7) SPECVLM_WAIT_CASE(8) SPECVLM_WAIT_CASE(9)
+        SPECVLM_WAIT_CASE(10) SPECVLM_WAIT_CASE(11) SPECVLM_WAIT_CASE(12) SPECVLM_WAIT_CASE(13) SPECVLM_WAIT_CASE(14) SPECVLM_WAIT_CASE(15) SPECVLM_WAIT_CASE(16) SPECVLM_WAIT_CASE(17) SPECVLM_WAIT_CASE(18) SPECVLM_WAIT_CASE(19)
+        SPECVLM_WAIT_CASE(20) SPECVLM_WAIT_CASE(21) SPECVLM_WAIT_CASE(22) SPECVLM_WAIT_CASE(23) SPECVLM_WAIT_CASE(24) SPECVLM_WAIT_CASE(25) SPECVLM_WAIT_CASE(26) SPECVLM_WAIT_CASE(27) SPECVLM_WAIT_CASE(28) SPECVLM_WAIT_CASE(29)
         SPECVLM_WAIT_CASE(30)
 #undef SPECVLM_WAIT_CASE
         default: wait_vmcnt<0>(); break;

@@ -12,6 +12,8 @@
 // one 256-thread workgroup per (request, query head, tree node).  Thread t visits the
 // visible keys t, t+256, ... with a private online softmax (running max, sum and a D-wide
 // accumulator in registers); the 256 partial states are merged at the end.
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace specvlm {
@@ -217,86 +219,100 @@ __global__ __launch_bounds__(kF32Waves * 64) void attn_f32_kernel(ValuParams p) 
         mask = __shfl(mask, min(node, n - 1));
     }
     const int S = P + n, ntile = (S + 15) / 16;
-    float m = -INFINITY, l = 0.f;
+    float m, l;
     f32x4 acc[ND];
-#pragma unroll
-    for (int t = 0; t < ND; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
     bool bad_block = false;
-    for (int tile = wave; tile < ntile; tile += kF32Waves) {
-        const int last = S - 1 - 16 * tile;    // rows past the last key re-read it; their weight is zero
-        const int64_t base = kv_row_offset(p.g, b, hk, 16 * tile, bad_block);
-        const float* kr = static_cast<const float*>(p.k) + base + min(l16, last) * p.g.stride_t + 4 * g;
-        f32x4 kf[ND];
+    // Not every row sees every node, and a weight of zero times a V that is not finite is NaN.  `careful` takes such entries
+    // of a tile with tree nodes out of the product and adds them to the rows that see them.  It is a second pass, for the
+    // wavefronts whose sums are not all finite: looking at V in the first one cost 20.3 -> 22.5 us per call at
+    // 500 keys, 2 x 8 heads of 128, 60 nodes; looking at the sums costs 20.35.
+    auto stream = [&](auto careful) __attribute__((always_inline)) {
+        m = -INFINITY;
+        l = 0.f;
 #pragma unroll
-        for (int c = 0; c < ND; ++c) kf[c] = *reinterpret_cast<const f32x4*>(kr + 16 * c);
-        float vf[4][ND];                       // V^T operand: head dim 16t + l16 of key 4g + i
+        for (int t = 0; t < ND; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int tile = wave; tile < ntile; tile += kF32Waves) {
+            const int last = S - 1 - 16 * tile;    // rows past the last key re-read it; their weight is zero
+            const int64_t base = kv_row_offset(p.g, b, hk, 16 * tile, bad_block);
+            const float* kr = static_cast<const float*>(p.k) + base + min(l16, last) * p.g.stride_t + 4 * g;
+            f32x4 kf[ND];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float* vr = static_cast<const float*>(p.v) + base + min(4 * g + i, last) * p.g.stride_t + l16;
+            for (int c = 0; c < ND; ++c) kf[c] = *reinterpret_cast<const f32x4*>(kr + 16 * c);
+            float vf[4][ND];                       // V^T operand: head dim 16t + l16 of key 4g + i
 #pragma unroll
-            for (int t = 0; t < ND; ++t) vf[i][t] = vr[16 * t];
-        }
-        // Not every row sees every node, and a weight of zero times a V that is not finite is NaN: in a tile with tree
-        // nodes such entries leave the product and are added below to the rows that see them.
-        bool special = false;
-        if (16 * tile + 16 > P) {              // uniform
+            for (int i = 0; i < 4; ++i) {
+                const float* vr = static_cast<const float*>(p.v) + base + min(4 * g + i, last) * p.g.stride_t + l16;
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+                for (int t = 0; t < ND; ++t) vf[i][t] = vr[16 * t];
+            }
+            bool special = false;
+            if constexpr (careful) {
+                if (16 * tile + 16 > P) {          // uniform
 #pragma unroll
-                for (int t = 0; t < ND; ++t) special |= !(fabsf(vf[i][t]) < INFINITY);
-            special = __any(special);
-            if (special)
+                    for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int i = 0; i < 4; ++i)
-#pragma unroll
-                    for (int t = 0; t < ND; ++t) vf[i][t] = fabsf(vf[i][t]) < INFINITY ? vf[i][t] : 0.f;
-        }
-        f32x4 s = {0.f, 0.f, 0.f, 0.f};        // s[i]: key 4g + i of the tile against this lane's query
-#pragma unroll
-        for (int c = 0; c < ND; ++c)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][i], qf[c][i], s, 0, 0, 0);
-        float mx = -INFINITY;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int key = 16 * tile + 4 * g + i, rel = key - P;
-            const bool visible = key < S && (rel < 0 || ((mask >> (rel & 63)) & 1ull));
-            s[i] = visible ? s[i] * p.scale : -INFINITY;
-            mx = fmaxf(mx, s[i]);
-        }
-        mx = fmaxf(mx, __shfl_xor(mx, 16));
-        mx = fmaxf(mx, __shfl_xor(mx, 32));
-        const float m_new = fmaxf(m, mx);
-        const float m_safe = m_new == -INFINITY ? 0.f : m_new;
-        const float alpha = expf(m - m_safe);  // 0 while no key was seen
-        float w[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) w[i] = expf(s[i] - m_safe);
-        l = l * alpha + ((w[0] + w[1]) + (w[2] + w[3]));
-        m = m_new;
-#pragma unroll
-        for (int t = 0; t < ND; ++t) {
-            acc[t] *= alpha;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][t], w[i], acc[t], 0, 0, 0);
-        }
-        if (special)
-            for (int k4 = 0; k4 < 4; ++k4)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int key = 16 * tile + 4 * k4 + i, rel = key - P;
-                    const float weight = __shfl(w[i], 16 * k4 + l16);      // of this key for this lane's query
-                    const bool visible = key < S && (rel < 0 || ((mask >> (rel & 63)) & 1ull));
-                    const float* vr = static_cast<const float*>(p.v) + base + min(4 * k4 + i, last) * p.g.stride_t + 4 * g;
-#pragma unroll
-                    for (int t = 0; t < ND; ++t) {
-                        const f32x4 x = *reinterpret_cast<const f32x4*>(vr + 16 * t);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (visible && !(fabsf(x[e]) < INFINITY)) acc[t][e] += weight * x[e];
-                    }
+                        for (int t = 0; t < ND; ++t) {
+                            special |= !(fabsf(vf[i][t]) < INFINITY);
+                            vf[i][t] = fabsf(vf[i][t]) < INFINITY ? vf[i][t] : 0.f;
+                        }
+                    special = __any(special);
                 }
-    }
+            }
+            f32x4 s = {0.f, 0.f, 0.f, 0.f};        // s[i]: key 4g + i of the tile against this lane's query
+#pragma unroll
+            for (int c = 0; c < ND; ++c)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) s = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[c][i], qf[c][i], s, 0, 0, 0);
+            float mx = -INFINITY;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int key = 16 * tile + 4 * g + i, rel = key - P;
+                const bool visible = key < S && (rel < 0 || ((mask >> (rel & 63)) & 1ull));
+                s[i] = visible ? s[i] * p.scale : -INFINITY;
+                mx = fmaxf(mx, s[i]);
+            }
+            mx = fmaxf(mx, __shfl_xor(mx, 16));
+            mx = fmaxf(mx, __shfl_xor(mx, 32));
+            const float m_new = fmaxf(m, mx);
+            const float m_safe = m_new == -INFINITY ? 0.f : m_new;
+            const float alpha = expf(m - m_safe);  // 0 while no key was seen
+            float w[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) w[i] = expf(s[i] - m_safe);
+            l = l * alpha + ((w[0] + w[1]) + (w[2] + w[3]));
+            m = m_new;
+#pragma unroll
+            for (int t = 0; t < ND; ++t) {
+                acc[t] *= alpha;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[i][t], w[i], acc[t], 0, 0, 0);
+            }
+            if (careful && special)
+                for (int k4 = 0; k4 < 4; ++k4)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        const int key = 16 * tile + 4 * k4 + i, rel = key - P;
+                        const float weight = __shfl(w[i], 16 * k4 + l16);      // of this key for this lane's query
+                        const bool visible = key < S && (rel < 0 || ((mask >> (rel & 63)) & 1ull));
+                        const float* vr = static_cast<const float*>(p.v) + base + min(4 * k4 + i, last) * p.g.stride_t + 4 * g;
+#pragma unroll
+                        for (int t = 0; t < ND; ++t) {
+                            const f32x4 x = *reinterpret_cast<const f32x4*>(vr + 16 * t);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                if (visible && !(fabsf(x[e]) < INFINITY)) acc[t][e] += weight * x[e];
+                        }
+                    }
+        }
+    };
+    stream(std::false_type{});
+    // An entry that is not finite makes the sums of its head dim so in all rows, and they stay so when they are rescaled.
+    float sum = 0.f;
+#pragma unroll
+    for (int t = 0; t < ND; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sum = fmaf(acc[t][i], 0.f, sum);
+    if (__builtin_expect(__any(sum != sum), 0)) stream(std::true_type{});
     if (bad_block && p.err_flag) atomicOr(p.err_flag, SPECVLM_ERR_BAD_BLOCK);
     // merge: acc[t][i] is O^T at head dim 16t + 4g + i, query l16
     l += __shfl_xor(l, 16);

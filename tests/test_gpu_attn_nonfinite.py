@@ -43,3 +43,25 @@ def test_invisible_values_do_not_leak(sv, oracle, D, N, P, nodes, bad, paged):
             assert np.all(np.isnan(got[i][:, hit]))
         else:
             assert np.all(got[i][:, hit] == bad)
+
+
+@pytest.mark.parametrize("D", [64, 128])
+def test_prefix_beside_a_node(sv, oracle, D):
+    """An infinity in the prefix reaches every row, the NaN of a node in the same tile only those that see it."""
+    from gpu_util import i32, random_case, to_dev
+    N, P, node = 24, 37, 5
+    case = random_case(9300 + D, "f32", B=1, Hq=2, Hkv=2, D=D, N_max=N, P_list=[P], paged=False)
+    ref = oracle.tree_attn(case["q"], case["k"], case["v"], case["prefix_len"], case["parent"], None)[0][0]
+    case["v"][0, :, P - 1, 7] = np.inf
+    case["v"][0, :, P + node, 9] = np.nan
+    got = sv.specvlm_tree_verify_attn(to_dev(case["q"]), to_dev(case["k"]), to_dev(case["v"]), i32(case["prefix_len"]),
+                                      i32(case["parent"])).cpu().numpy()[0]
+    below = np.zeros(N, dtype=bool)
+    for i in range(N):
+        below[i] = i == node or (i > 0 and below[case["parent"][0][i]])
+    assert np.all(got[:, :, 7] == np.inf)
+    assert np.array_equal(np.isnan(got[:, :, 9]), np.repeat(below[:, None], 2, axis=1))
+    rest = np.ones(D, dtype=bool)
+    rest[[7, 9]] = False
+    np.testing.assert_allclose(got[:, :, rest], ref[:, :, rest], rtol=0, atol=1e-5)
+    np.testing.assert_allclose(got[~below][:, :, 9], ref[~below][:, :, 9], rtol=0, atol=1e-5)

@@ -347,8 +347,8 @@ int32_t specvlm_visual_prune_padded(int32_t dtype, int32_t B, int32_t T, int32_t
  * Sec. 4.1: temperature 0).  Replaces "project to logits, store them, specvlm_node_argmax":
  *     logit[b,i,v] = sum_e hidden[b,i,e] * W[v,e]          (bf16 products, fp32 accumulation)
  *     amax[b,i]    = the LOWEST v whose logit is the row's greatest (-0 == +0; inputs finite)
- * The [nodes, vocabulary] logits are never stored and W is streamed from HBM once per block of 64
- * node rows.  The choice is taken on the fp32 sums, so against exact arithmetic it can differ
+ * The [nodes, vocabulary] logits are never stored.  W is read once per tile of 64 - 256 node
+ * rows; tiles that share a part of W run next to each other, so that HBM delivers it about once.  The choice is taken on the fp32 sums, so against exact arithmetic it can differ
  * only where the two greatest logits of a row are closer than the fp32 accumulation error.
  * Rows i >= num_nodes[b] get amax -1 (their hidden rows are still read and must be finite memory).
  *   dtype          SPECVLM_BF16 only (SPECVLM_F32 returns SPECVLM_UNSUPPORTED)

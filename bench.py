@@ -24,6 +24,9 @@ if ROOT not in sys.path:
     sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBPS = 8000.0          # MI355X published HBM3E peak
+# the kernel that the library chooses for a workload's attention call (--splits 0)
+ATTENTION_KERNELS = {"C2": "attn_wave_kernel<128, 2, false>", "C3": "attn_mfma_kernel<128, 4, 2>",
+                     "C4": "attn_mfma_kernel<128, 4, 2>", "C5": "attn_mfma_kernel_2wg<128>"}
 
 
 
@@ -311,7 +314,7 @@ def main():
         nbytes = W.kv_bytes_per_layer(c)
         rec = {"attn_us_per_launch": round(us, 3), "algorithmic_bytes_per_launch": nbytes,
                "GBps": round(nbytes / (us * 1e-6) / 1e9, 1), "frac": round(nbytes / (us * 1e-6) / 1e9 / HBM_PEAK_GBPS, 4),
-               "num_splits": sv.specvlm_tree_verify_attn_num_splits(dc), "layers_timed": Lc,
+               "key_ranges_at_most": sv.specvlm_tree_verify_attn_num_splits(dc), "layers_timed": Lc,
                "shape": f"B={c.B}, H={c.H}, D={c.D}, prefix={Pc.tolist()}, paged={c.paged}"
                         + (f", cache capacity {capacity}" if capacity else "")}
         if tail:
@@ -337,7 +340,7 @@ def main():
             if name != cfg.name:
                 other_configs[name] = attention_only(name, tail=(name == "C4"))
                 torch.cuda.empty_cache()
-        # a short request in a cache preallocated for a long one: the split count follows the capacity
+        # a short request in a cache preallocated for a long one: the division of the work follows the capacity
         c3 = W.CONFIGS["C3"]
         other_configs["C2_lengths_in_a_cache_of_C3_capacity"] = attention_only(
             "C2", capacity=W.round_up(int(W.prefix_lengths(c3).max()) + c3.N, 16))
@@ -433,7 +436,7 @@ def main():
                                f"tree nodes={N}, depth={cfg.depth}, vocab={cfg.V}, paged={cfg.paged}",
                    "launch": "HIP graph replay of one whole step" if not args.no_graph else "eager launches",
                    "timing": "HIP events on the stream the calls are launched on",
-                   "num_splits": sv.specvlm_tree_verify_attn_num_splits(desc),
+                   "key_ranges_at_most": sv.specvlm_tree_verify_attn_num_splits(desc),
                    "accept_len": acc_out[0].tolist()},
         "verify_steps_per_s": round(1e3 / ms_step, 1),
         "pct_hbm_peak": round(100.0 * value / HBM_PEAK_GBPS, 2),
@@ -448,12 +451,12 @@ def main():
             "note": "one layer through specvlm_tree_verify_attn_vector_alu (no matrix cores): what the matrix-core kernel is measured against"},
         "outside_the_step_ms": {"tree_accept_sample_T1": round(ms_smp, 5), "draft_tree_growth": round(ms_grow, 5),
                                 "head_argmax_fused": round(ms_head, 5)},
-        "roofline_head_argmax": {"kernel": "specvlm::head_argmax_kernel<%d>" % (1 if B * N <= 64 else 2 if B * N <= 128 else 4 if B * N <= 256 else 8), "bound": "hbm",
+        "roofline_head_argmax": {"kernel": "specvlm::head_argmax_kernel" if B * N <= 64 else "specvlm::head_gemm_kernel", "bound": "hbm",
                                  "achieved": round(head_bytes / (ms_head * 1e-3) / 1e9, 1), "peak": HBM_PEAK_GBPS,
                                  "unit": "GB/s", "frac": round(head_bytes / (ms_head * 1e-3) / 1e9 / HBM_PEAK_GBPS, 4),
                                  "algorithmic_bytes_per_launch": head_bytes, "avg_launch_us": round(ms_head * 1e3, 3),
                                  "traffic": measured_traffic("head_argmax_kernel_C3.txt", "head_argmax.hip") if cfg.name == "C3" else None},
-        "roofline": {"kernel": "specvlm::attn_mfma_kernel<128, 4, 2> (the whole specvlm_tree_verify_attn call of one layer)",
+        "roofline": {"kernel": "specvlm::" + ATTENTION_KERNELS[cfg.name] + " (the whole specvlm_tree_verify_attn call of one layer)",
                      "bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": round(achieved / HBM_PEAK_GBPS, 4),
                      "algorithmic_bytes_per_launch": kv_bytes_layer,
@@ -461,7 +464,7 @@ def main():
                      "traffic": measured_traffic("attn_mfma_kernel_C3.txt", "attn_mfma.hip", "attn_mfma_body.inc") if cfg.name == "C3" else None},
         "configs": dict({cfg.name: {"attn_us_per_launch": round(attn_launch_us, 3), "algorithmic_bytes_per_launch": kv_bytes_layer,
                                     "GBps": round(achieved, 1), "frac": round(achieved / HBM_PEAK_GBPS, 4),
-                                    "num_splits": sv.specvlm_tree_verify_attn_num_splits(desc), "layers_timed": L}},
+                                    "key_ranges_at_most": sv.specvlm_tree_verify_attn_num_splits(desc), "layers_timed": L}},
                         **other_configs),
     }
 

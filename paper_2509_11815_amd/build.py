@@ -13,7 +13,7 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libspecvlm.so")
 NATIVE = os.path.join(HERE, "_specvlm_native.so")
-SOURCES = ["api.hip", "sample_kernels.hip", "accept_sample.hip", "draft_tree.hip", "head_argmax.hip", "compress.hip", "attn_valu.hip", "attn_mfma.hip", "attn_wave.hip"]
+SOURCES = ["api.hip", "sample_kernels.hip", "accept_sample.hip", "draft_tree.hip", "head_argmax.hip", "compress.hip", "attn_valu.hip", "attn_mfma.hip", "attn_wave.hip", "attn_streams.hip"]
 
 
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I" + INCLUDE, "-I" + CSRC,

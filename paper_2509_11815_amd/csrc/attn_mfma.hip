@@ -161,6 +161,7 @@ int32_t attn_static_workspace(void** ptr_out) {
 
 int32_t launch_attn_mfma(const AttnArgs& a) {
     const specvlm_attn_desc& d = a.d;
+    if (a.plan.streams) return launch_attn_streams(a);
     if (a.plan.block_rows) return launch_attn_wave(a);
     MfmaParams p;
     p.g = KvGeom{d.kv_stride_b, d.kv_stride_h, d.kv_stride_t, d.paged ? a.block_table : nullptr,

@@ -66,6 +66,7 @@ struct AttnPlan {
     int32_t ranges;        // key ranges per head that the workspace holds
     int32_t block_rows;    // query rows per workgroup, 0: all (key ranges only)
     int32_t splits;        // key ranges the call takes, <= ranges
+    int32_t streams = 0;   // key ranges of the kernel with four streams per workgroup (attn_streams.hip), <= ranges; 0: one of the others
 };
 
 inline AttnPlan plan_rows(const specvlm_attn_desc& d, int32_t nominal) {
@@ -128,12 +129,41 @@ inline AttnPlan plan_rows(const specvlm_attn_desc& d, int32_t nominal) {
 // Not taken where equal lengths lost: no shared KV heads 31.2 -> 32.6, two query heads per KV head
 // 25.2 -> 26.1, more than four ranges 21.6 -> 24.6, head size 64 18.7 -> 19.7; nor for a call without key ranges,
 // whose results would gain the rounding of partial results; streams shorter than 12 tiles have nothing to divide.
-inline AttnPlan attn_plan(const specvlm_attn_desc& d) {
+inline AttnPlan plan_of_heads_and_rows(const specvlm_attn_desc& d) {
     AttnPlan plan = plan_rows(d, single_round_ranges(d));
     if (plan.block_rows || d.num_splits > 0 || plan.ranges != 2) return plan;
     if (d.B < 2 || d.D != 128 || d.H_q / d.H_kv < 4) return plan;
     const int cap = d.paged ? d.max_blocks_per_req * SPECVLM_PAGE_SIZE : d.kv_capacity;
     if (cap >= 12 * kStreamsPerWg * kTile * 2 && 4ll * d.B * d.H_q <= kMostTwoPerCu) plan.ranges = plan.splits = 4;
+    return plan;
+}
+
+// Batches that fill the chip with four streams per workgroup of 64 rows (attn_streams.hip) take as many key ranges as make one
+// round of 140 - 256 workgroups.  Not fewer workgroups (128 x 19 tiles: 15.1 us, 12.8 by row blocks), streams shorter than 3.5 tiles
+// (4 x 16 heads of 31 tiles, two ranges: 15.7 against 14.2; with four ranges, whose meeting costs more, 4.25 tiles), nor blocks
+// less than 55 % full (28 of 64 rows: 17.0 against 15.5).  A call whose results were not rounded to partial ones before stays
+// without them, and one that took key ranges takes at least two: requests of different lengths need them (5 x 32 heads,
+// 3568 - 400 keys, three ranges 38.9, one 43.2; equal lengths of 3100: 49.3 and 46.3).
+// us per call before -> here (head size 128 unless said); over 300 random shapes 76 taken, 0.64 - 1.00 of the time before, mean 0.86:
+//   unsplit       8 x 32 query / 16 KV heads, 4788 keys 82.4 -> 65.7; 7 x 32 / 8, 852: 21.1 -> 17.2; 4 x 40, 671: 18.5 -> 16.4;
+//                 6 x 32, 2800 - 300: 44.7 -> 35.6; 8 x 32, 900: 25.3 -> 25.4; 5 x 32 of 64, 253: 10.6 -> 8.9
+//   two ranges    3 x 32 / 4, 2657: 27.7 -> 22.0; 3 x 32, 3529: 38.8 -> 35.6
+//   three, four   5 x 16 of 64, 3027: 18.6 -> 16.3; 2 x 40, 3729: 33.0 -> 30.6; 2 x 32, 4474: 30.9 -> 30.7
+inline int32_t stream_ranges(const specvlm_attn_desc& d, const AttnPlan& plan) {
+    const int cap = d.paged ? d.max_blocks_per_req * SPECVLM_PAGE_SIZE : d.kv_capacity;
+    const int group = d.H_q / d.H_kv, rows = group * d.N_max, blocks = (rows + 63) / 64;
+    const int64_t units = static_cast<int64_t>(d.B) * d.H_kv * blocks;
+    if (d.B < 2 || d.num_splits > 0 || units > 256 || 100 * rows < 55 * 64 * blocks) return 0;
+    // what the kernel assumes: whole halves of a tile inside the cache, 32-bit offsets into a request's query rows and a half tile
+    if (cap % 16 || d.kv_stride_t >= (1 << 22) || (d.N_max * d.q_stride_n + group * d.q_stride_h) >= (1ll << 30)) return 0;
+    const int s = plan.splits == 1 ? 1 : std::min<int64_t>({256 / units, plan.ranges, 4});
+    if (s < (plan.splits == 1 ? 1 : 2) || units * s < (s == 1 ? 140 : 180)) return 0;
+    return (cap + kTile - 1) / kTile >= (s == 4 ? 17 : 14) * s ? s : 0;
+}
+
+inline AttnPlan attn_plan(const specvlm_attn_desc& d) {
+    AttnPlan plan = plan_of_heads_and_rows(d);
+    plan.streams = stream_ranges(d, plan);
     return plan;
 }
 

@@ -1,0 +1,599 @@
+// Tree-masked verification attention for bf16 caches: 64 query rows per workgroup, a key stream per wavefront.
+//
+// For batches whose (request, head) pairs fill the chip with long streams.  What bounds such a call is the K/V stream (6.2 - 7
+// TB/s over all compute units, 57 GB/s into one of them) as long as a step's own chain is shorter; attn_mfma.hip needs
+// 0.43 us per 32-key tile and compute unit (two streams, a barrier per step, every tile read from LDS by four wavefronts),
+// more than the stream where K and V come from L2 (grouped heads) or few long requests are left.  Here:
+//
+//   grid      (request, KV head, block of 64 rows of the group, key range), 4 wavefronts each, all 64 rows in every one:
+//             wavefront w has the tiles of stream w splits + split, so a tile is read from LDS once, there is no barrier in
+//             the loop, and four tiles take 0.73 us without fetches (0.18 us a tile)
+//   product   v_mfma_f32_32x32x16_bf16: half the matrix instructions of 16 x 16 x 32, and a lane holds 2 query rows x 16 keys
+//             instead of 4 x 8 (half the softmax state).  S^T = K Q^T of tile j + 1 stands beside the softmax of tile j
+//             in one block, so that the compiler interleaves matrix and vector instructions; the last three tiles are
+//             unrolled to keep it that way (one loop with run-time conditions costs 1 us per call)
+//   fetch     as in attn_wave.hip: direct-to-LDS, two K and two V areas per wavefront, K three tiles and V two tiles ahead
+//   merge     the four streams meet in LDS, every wavefront owns 32 head dims of all rows; key ranges as in attn_wave.hip
+//
+// us per call (HIP-graph replay), attn_mfma / attn_wave -> here; head size 128, 60 - 64 nodes unless said: 4 x 32 query / 8
+// KV heads, 2048, 1311, 3000, 777 keys 27.6 -> 23.5; 8 x 32 / 16 heads, 4788 keys 82.4 -> 65.7; 3 x 32 / 16 heads, 3664 - 500 keys
+// 34.8 -> 27.2; 4 x 40 heads, 671 keys 18.5 -> 16.4; 6 x 32 heads, 2800 - 300 keys 44.7 -> 35.6; 5 x 40 heads of 64, 1935
+// keys 26.0 -> 20.4.  Tried and slower: two wavefronts sharing a stream of 128 rows (26.3 at the first of these),
+// wavefronts dealt out to the requests by length on the device (24.4).
+#include <type_traits>
+
+#include "attn_rows.hpp"
+
+namespace specvlm {
+
+namespace {
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+// The greatest of sixteen scores, NaN where one is.
+__device__ __forceinline__ float max16(const f32x16& a) {
+    auto max3 = [](float x, float y, float z) { return __builtin_elementwise_maximum(__builtin_elementwise_maximum(x, y), z); };
+    const float u = max3(a[0], a[1], a[2]), v = max3(a[3], a[4], a[5]), w = max3(a[6], a[7], a[8]), x = max3(a[9], a[10], a[11]);
+    const float y = max3(a[12], a[13], a[14]);
+    return max3(max3(u, v, w), max3(x, y, a[15]), a[15]);
+}
+
+// What the other half of the wavefront (lane ^ 32) holds.
+__device__ __forceinline__ float other_half(float x) {
+    const uint32_t a = __float_as_uint(x);
+    const auto r = __builtin_amdgcn_permlane32_swap(a, a, false, false);     // lower half everywhere, upper half everywhere
+    return __uint_as_float((threadIdx.x & 32) ? r[0] : r[1]);
+}
+
+template <int D, bool PAGED>
+__global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1, 1))) void attn_streams_kernel(WaveParams p) {
+    constexpr int NC = D / 16;                 // QK^T contraction steps of 16
+    constexpr int NT = D / 32;                 // output blocks of 32 head dims
+    constexpr int ROWG = D / 8;                // 16-byte granules per K/V row
+    constexpr int RPI = 64 / ROWG;             // rows per load instruction (4 or 8)
+    constexpr int NH = 16 / RPI;               // load instructions per half tile (4 or 2)
+    constexpr int KLD = 2 * NH;                // ... per K (or V) tile
+    constexpr int kTileBytes = kKeys * D * 2;
+    constexpr int kSlotBytes = 2 * kTileBytes;           // K tile then V tile
+    constexpr int kRingBytes = 2 * kSlotBytes;           // two slots per wavefront
+    constexpr int NQ = kQRows / RPI / 4;                 // query-row load instructions per wavefront
+    constexpr int OWN = NT / 2;                          // (32 query rows, 32 head dims) blocks of an owner at the merge
+    static_assert(kWaveWgs * kRingBytes >= 4 * 3 * OWN * 4096, "merge scratch must fit in the rings");
+
+    __shared__ __attribute__((aligned(1024))) unsigned char s_ring[kWaveWgs * kRingBytes];
+    __shared__ __attribute__((aligned(1024))) unsigned char s_q[kQRows * D * 2];
+    __shared__ float s_m[kWaveWgs][kQRows];
+    __shared__ float s_l[kWaveWgs][kQRows];
+    __shared__ int s_par[kWaveWgs][64];
+
+    // work item: (request, KV head, row block, split); every XCD gets a contiguous range of items
+    uint32_t work = blockIdx.x;
+    if ((gridDim.x & 7) == 0) work = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+    const uint32_t unit = divide(work, p.magic_splits);
+    const int split = work - unit * p.num_splits;
+    const uint32_t bk = divide(unit, p.magic_rb);
+    const int rb = unit - bk * p.row_blocks;
+    const int b = divide(bk, p.magic_hkv);
+    const int hk = bk - b * p.H_kv;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l32 = lane & 31, hf = lane >> 5;
+
+    typedef const __attribute__((address_space(4))) int32_t* const_i32;
+    const int n_raw = p.num_nodes ? ((const_i32)p.num_nodes)[b] : p.N_max;
+    const int P_raw = ((const_i32)p.prefix_len)[b];
+    const int nstream = kWaveWgs * p.num_splits;
+    const int stream = wave * p.num_splits + split;
+
+    unsigned char* ring = s_ring + wave * kRingBytes;
+    typedef __attribute__((address_space(3))) unsigned char lds_byte;
+    typedef __attribute__((address_space(3))) int lds_int;
+    const uint32_t ring_lds = (uint32_t)(uintptr_t)(lds_byte*)ring;
+
+    // the parent array first (every wavefront its own copy)
+    dma4(p.parent + static_cast<int64_t>(b) * p.N_max + min(lane, p.N_max - 1), (uint32_t)(uintptr_t)(lds_int*)s_par[wave]);
+
+    // ---- tile fetch -------------------------------------------------------------------------
+    const int lrow = lane / ROWG, lpos = lane % ROWG;
+    const uint32_t row_bytes = static_cast<uint32_t>(p.g.stride_t) * 2u;
+    const uint32_t lrow_off = __umul24(lrow, row_bytes);   // (row_bytes < 2^24: checked on the host)
+    // V granules: the 64-byte block of 32 head dims c of row r lands at block c ^ vswz(r)
+    auto vswz = [](int r) { return D == 128 ? (r & 3) : ((r >> 1) & 1); };
+    uint32_t voff_k[NH], voff_v[NH];
+#pragma unroll
+    for (int i = 0; i < NH; ++i) {
+        const int r = i * RPI + lrow;
+        voff_k[i] = lrow_off + ((lpos ^ (r & (ROWG - 1))) << 4) + i * (RPI * row_bytes - 1024);   // (row_bytes >= 2 D)
+        voff_v[i] = lrow_off + ((lpos ^ (vswz(r) << 2)) << 4) + i * (RPI * row_bytes - 1024);
+    }
+    const int64_t head_off = hk * p.g.stride_h + (PAGED ? 0 : b * p.g.stride_b);   // elements
+    const int64_t tile_step = static_cast<int64_t>(nstream) * kKeys * p.g.stride_t;         // elements from one tile of the stream to its next
+    const int64_t first_off = head_off + static_cast<int64_t>(stream) * kKeys * p.g.stride_t;
+    const uint16_t* k_next = p.k + (PAGED ? head_off : first_off);       // contiguous: the next tile to request
+    const uint16_t* v_next = p.v + (PAGED ? head_off : first_off);
+    const int64_t half_step = 16 * p.g.stride_t;
+    // Tile j of this stream, K or V, into slot j % 2: two halves of 16 rows.  The capacity is a multiple of 16 (host), so a half
+    // lies inside the cache or beyond it; one beyond is replaced by the tile's first half (its keys do not exist, weight zero).
+    auto issue = [&](const uint16_t*& src, const uint32_t (&voff)[NH], int area, int j, const int (&phys)[2]) __attribute__((always_inline)) {
+        const uint32_t dst = ring_lds + (j & 1) * kSlotBytes + area;
+        if constexpr (PAGED) {
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+                dma_half<D>(src + min(max(phys[x], 0), p.g.num_blocks - 1) * p.g.stride_b, voff, dst + x * (kTileBytes / 2));
+        } else {
+            const int lo = (stream + j * nstream) * kKeys;
+            dma_half<D>(src, voff, dst);
+            dma_half<D>(src + (lo + 16 < p.g.capacity ? half_step : 0), voff, dst + kTileBytes / 2);
+            src += tile_step;
+        }
+    };
+    auto issue_k = [&](int j, const int (&phys)[2]) __attribute__((always_inline)) { issue(k_next, voff_k, 0, j, phys); };
+    auto issue_v = [&](int j, const int (&phys)[2]) __attribute__((always_inline)) { issue(v_next, voff_v, kTileBytes, j, phys); };
+    int phys[2] = {0, 0};
+    // With a contiguous cache the first tile's address needs no length: requested before the lengths arrive (a tile
+    // beyond the cache is replaced by the cache's first).
+    constexpr bool early = !PAGED;
+    if constexpr (early) {
+        if (stream * kKeys >= p.g.capacity) { k_next = p.k + head_off; v_next = p.v + head_off; }      // never used
+        issue_k(0, phys);
+    }
+
+    // query rows of this block: row r of the block is row R = 64 rb + r of the group's (head, node) rows
+    const int rows_total = p.group * p.N_max;
+    const uint32_t q_lds = (uint32_t)(uintptr_t)(lds_byte*)s_q;
+    const int row0 = rb * kQRows;
+    const int q_row = static_cast<int>(p.q_sn) * 2, q_head = static_cast<int>(p.q_sh) * 2;     // bytes (checked on the host)
+    const uint16_t* q_base = p.q + b * p.q_sb + static_cast<int64_t>(hk * p.group) * p.q_sh;
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+        const int inst = wave * NQ + i;
+        const int r = inst * RPI + lrow;
+        const int R = min(row0 + r, rows_total - 1);
+        const int hh = divide(R, p.magic_nmax);
+        const int node = R - hh * p.N_max;
+        const uint32_t voff = static_cast<uint32_t>(node * q_row + hh * q_head) + ((lpos ^ (r & (ROWG - 1))) << 4);
+        dma16s(q_base, voff, q_lds + inst * 1024);
+    }
+    if constexpr (early) issue_v(0, phys);
+
+    int err = 0;
+    int n = n_raw;
+    const int P = P_raw;
+    if (n < 1 || n > p.N_max) err |= SPECVLM_ERR_BAD_NUM_NODES;
+    n = min(max(n, 1), p.N_max);
+    if (P < 0 || P + n > p.g.capacity) err |= SPECVLM_ERR_BAD_LENGTH;
+    const int S = P + n;
+    const int ntile = (S + kKeys - 1) / kKeys;
+    const int my_tiles = (!err && stream < ntile) ? static_cast<int>(divide(ntile - stream + nstream - 1, p.magic_nstream)) : 0;
+    int bad_block = 0;                                     // uniform
+    auto fetch_blocks = [&](int j, int (&phys)[2]) __attribute__((always_inline)) {
+        if constexpr (PAGED) {
+            const int blk0 = (stream + j * nstream) * (kKeys >> 4), last_blk = (S - 1) >> 4;
+            const const_i32 row = (const_i32)p.g.block_table + static_cast<int64_t>(b) * p.g.max_blocks;
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                phys[x] = row[min(blk0 + x, last_blk)];
+                bad_block |= static_cast<uint32_t>(phys[x]) >= static_cast<uint32_t>(p.g.num_blocks) ? 1 : 0;
+            }
+        }
+    };
+    if (!early && my_tiles > 0) { fetch_blocks(0, phys); issue_k(0, phys); issue_v(0, phys); }
+    if (my_tiles > 1) { fetch_blocks(1, phys); issue_k(1, phys); issue_v(1, phys); }
+    int phys_k[2] = {0, 0}, phys_v[2] = {0, 0};            // block ids of the next K and V tile to request
+    if (my_tiles > 2) { fetch_blocks(2, phys_k); phys_v[0] = phys_k[0]; phys_v[1] = phys_k[1]; }
+
+    const float c2 = p.scale * kLog2e;
+    const float tau = fminf(kTau / c2, 1e30f);
+    // K fragments of a tile (A operand): lane (key l32, half hf) holds dims 16c + 8hf .. +7; the query rows likewise
+    uint32_t kaddr[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) kaddr[c] = l32 * (ROWG * 16) + (((2 * c + hf) ^ (l32 & (ROWG - 1))) << 4);
+    bf16x8 ka[NC];
+    auto read_k = [&](int slot_off) __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) ka[c] = *reinterpret_cast<const bf16x8*>(ring + slot_off + kaddr[c]);
+    };
+    // requested after the query rows: V0, K1, V1 (an early request) or K0, V0, K1, V1
+    if (my_tiles > 1) wait_vmcnt<3 * KLD>();
+    else if (my_tiles == 1) wait_vmcnt<KLD>();
+    else wait_vmcnt<0>();
+    __syncthreads();
+    const int par = s_par[wave][lane];
+    bf16x8 qf[2][NC];
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) qf[qb][c] = *reinterpret_cast<const bf16x8*>(s_q + qb * 32 * ROWG * 16 + kaddr[c]);
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) asm volatile("" : "+a"(qf[qb][c]));
+    const bool bad_par = lane < n && (lane == 0 ? par != -1 : (par < 0 || par >= lane));
+    if (__any(bad_par)) err |= SPECVLM_ERR_BAD_PARENT;
+    if (err) {                                             // the same in every wavefront of the request
+        if (tid == 0 && p.err_flag) atomicOr(p.err_flag, err);
+        wait_vmcnt<0>();
+        return;
+    }
+    // Ancestor-or-self masks of this lane's two query rows: pointer doubling over the lanes (lane i holds node i)
+    uint32_t anc_lo[2], anc_hi[2];
+    auto build_anc = [&]() __attribute__((always_inline)) {
+        uint32_t mlo = lane < 32 ? 1u << (lane & 31) : 0u, mhi = lane < 32 ? 0u : 1u << (lane & 31);
+        int up = lane < n ? par : -1;
+#pragma unroll 1
+        while (__any(up >= 0)) {
+            const int src = max(up, 0) * 4;
+            const uint32_t alo = __builtin_amdgcn_ds_bpermute(src, mlo), ahi = __builtin_amdgcn_ds_bpermute(src, mhi);
+            const int up2 = __builtin_amdgcn_ds_bpermute(src, up);
+            if (up >= 0) { mlo |= alo; mhi |= ahi; up = up2; }
+        }
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) {
+            const int R = min(row0 + qb * 32 + l32, rows_total - 1);
+            const int node = R - divide(R, p.magic_nmax) * p.N_max;
+            anc_lo[qb] = __builtin_amdgcn_ds_bpermute(node * 4, mlo);
+            anc_hi[qb] = __builtin_amdgcn_ds_bpermute(node * 4, mhi);
+        }
+    };
+    // Softmax state of query row 32 qb + l32 (both halves agree): reference maximum, the same times c2 (0 while no key was
+    // seen), the maximum that moves it, and this lane's part of the sum of the row's weights.
+    // acc[qb][t][i]: O^T row 32t + 8 (i / 4) + 4 hf + i % 4.
+    float m_run[2], mrc[2], thr[2], l_run[2];
+    f32x16 acc[2][NT];
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+        m_run[qb] = -INFINITY;
+        thr[qb] = -INFINITY;
+        mrc[qb] = 0.f;
+        l_run[qb] = 0.f;
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[qb][t][i] = 0.f;
+    }
+    // V operands: va[t][x] element e is key 16x + 8 (e / 4) + 4 hf + e % 4, dim 32t + l32.  A transposing read hands lane i of a
+    // 16-lane block four keys at dim i of the 16 that the block's lanes address (lane j: key j / 4, dims 4 (j % 4) ..)
+    const int k0 = 4 * hf + ((lane & 15) >> 2);
+    const uint32_t vaddr = kTileBytes + k0 * (ROWG * 16) + ((lane >> 4) & 1) * 32 + (lane & 3) * 8 + (vswz(k0) << 6);
+    bf16x8 va[NT][2];
+    auto read_v = [&](int t, int slot_off) __attribute__((always_inline)) {
+        const uint32_t a = (vaddr ^ (t << 6)) + slot_off;
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            const s16x4 lo = lds_read_tr16(ring + a + (16 * x) * ROWG * 16);
+            const s16x4 hi = lds_read_tr16(ring + a + (16 * x + 8) * ROWG * 16);
+            const s16x8 both = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+            va[t][x] = __builtin_bit_cast(bf16x8, both);
+        }
+    };
+    // S^T = K Q^T: s[qb][i] = score of key 8 (i / 4) + 4 hf + i % 4 of the tile against query row 32 qb + l32
+    f32x16 s[2], s_next[2];
+    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    auto scores = [&](f32x16& d, int qb) __attribute__((always_inline)) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) d = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[c], qf[qb][c], c ? d : zero, 0, 0, 0);
+    };
+    bf16x8 pf[2][2];
+    auto weights = [&](int qb) __attribute__((always_inline)) {     // exp2(S^T) packed to bf16 is the B operand of PV
+        float pr[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) pr[i] = fast_exp2(fmaf(s[qb][i], c2, -mrc[qb]));
+        float sum[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sum[i] = (pr[4 * i] + pr[4 * i + 1]) + (pr[4 * i + 2] + pr[4 * i + 3]);
+        l_run[qb] += (sum[0] + sum[1]) + (sum[2] + sum[3]);
+#pragma unroll
+        for (int x = 0; x < 2; ++x) {
+            u32x4 w;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[e] = pack_bf16x2(pr[8 * x + 2 * e], pr[8 * x + 2 * e + 1]);
+            pf[qb][x] = __builtin_bit_cast(bf16x8, w);
+        }
+    };
+    float lmax[2];
+
+    if (my_tiles > 0) {
+        read_k(0);
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the K area of slot 0 is free
+        if (my_tiles > 2) { issue_k(2, phys_k); if (my_tiles > 3) fetch_blocks(3, phys_k); }
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) scores(s[qb], qb);
+        // V0 and K1 (the requests after them: V1, K2)
+        if (my_tiles > 2) wait_vmcnt<2 * KLD>();
+        else if (my_tiles == 2) wait_vmcnt<KLD>();
+        else wait_vmcnt<0>();
+        if (my_tiles > 1) read_k(kSlotBytes);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) read_v(t, 0);
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) lmax[qb] = max16(s[qb]);
+    }
+    // One tile.  At its start s holds tile j's scores and lmax their maxima; va (being read) its V operands, ka the next tile's
+    // K operands.  LEFT: tiles after this one (3: three or more).
+    auto step = [&](auto after, int j) __attribute__((always_inline)) {
+        constexpr int LEFT = decltype(after)::value;
+        const int slot0 = (stream + j * nstream) * kKeys;
+        if (slot0 + kKeys > P) {                           // reaches past the prefix: tree region or tail
+            build_anc();
+            // branch-free on purpose: plain integer logic and one select per score
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb) {
+                const unsigned long long anc = (static_cast<unsigned long long>(anc_hi[qb]) << 32) | anc_lo[qb];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int slot_key = slot0 + 8 * (i >> 2) + 4 * hf + (i & 3);
+                    const int rel = slot_key - P;
+                    const uint32_t in_prefix = static_cast<uint32_t>(rel) >> 31;
+                    const uint32_t is_anc = static_cast<uint32_t>(anc >> (rel & 63)) & 1u;
+                    const uint32_t in_range = static_cast<uint32_t>(slot_key - S) >> 31;
+                    const uint32_t vis = in_range & (in_prefix | is_anc);
+                    s[qb][i] = vis ? s[qb][i] : -INFINITY;
+                }
+                lmax[qb] = max16(s[qb]);
+            }
+            if (slot0 + kKeys > S) {                       // keys that do not exist: zero weight must meet a finite value
+#pragma unroll
+                for (int x = 0; x < 2; ++x) {
+                    uint32_t keep[4];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {          // dword e of an operand: keys kk, kk + 1
+                        const int kk = slot0 + 16 * x + 8 * (e >> 1) + 4 * hf + 2 * (e & 1);
+                        keep[e] = (kk < S ? 0xFFFFu : 0u) | (kk + 1 < S ? 0xFFFF0000u : 0u);
+                    }
+#pragma unroll
+                    for (int t = 0; t < NT; ++t) {
+                        u32x4 w = __builtin_bit_cast(u32x4, va[t][x]);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) w[e] &= keep[e];
+                        va[t][x] = __builtin_bit_cast(bf16x8, w);
+                    }
+                }
+            }
+        }
+        // Online softmax with a lazily updated reference: a weight may exceed 1; the reference only moves when
+        // some score would exceed it by more than 2^kTau (or on the first visible key).
+        if (__builtin_expect(__any((lmax[0] > thr[0]) | (lmax[1] > thr[1])), 0)) {
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb) {
+                const float mx = fmaxf(lmax[qb], other_half(lmax[qb]));
+                const float m_new = fmaxf(m_run[qb], mx);
+                const float m_safe = m_new == -INFINITY ? 0.f : m_new;
+                const float alpha = m_run[qb] == -INFINITY ? 1.f : fast_exp2((m_run[qb] - m_safe) * c2);
+                m_run[qb] = m_new;
+                thr[qb] = m_new + tau;
+                mrc[qb] = m_safe * c2;
+                l_run[qb] *= alpha;
+#pragma unroll
+                for (int t = 0; t < NT; ++t) acc[qb][t] *= alpha;
+            }
+        }
+        // weights of tile j beside the next tile's scores
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) {
+            if constexpr (LEFT > 0) scores(s_next[qb], qb);
+            weights(qb);
+        }
+        const int next_off = ((j + 1) & 1) * kSlotBytes;
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // ka and va are in registers: their areas are free
+        if constexpr (LEFT >= 2) {
+            issue_v(j + 2, phys_v);
+            if constexpr (LEFT >= 3) {
+                phys_v[0] = phys_k[0]; phys_v[1] = phys_k[1];
+                issue_k(j + 3, phys_k);
+                if constexpr (PAGED) { if (j + 4 < my_tiles) fetch_blocks(j + 4, phys_k); }
+            }
+        }
+        // V of tile j + 1 and K of tile j + 2 have landed (the requests after them: V of j + 2, K of j + 3)
+        if constexpr (LEFT >= 3) wait_vmcnt<2 * KLD>();
+        else if constexpr (LEFT == 2) wait_vmcnt<KLD>();
+        else if constexpr (LEFT == 1) wait_vmcnt<0>();
+        if constexpr (LEFT >= 2) read_k(next_off ^ kSlotBytes);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+#pragma unroll
+            for (int x = 0; x < 2; ++x)
+#pragma unroll
+                for (int qb = 0; qb < 2; ++qb) acc[qb][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(va[t][x], pf[qb][x], acc[qb][t], 0, 0, 0);
+            if constexpr (LEFT >= 1) read_v(t, next_off);
+        }
+        if constexpr (LEFT >= 1) {
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb) { s[qb] = s_next[qb]; lmax[qb] = max16(s[qb]); }
+        }
+    };
+    {
+        int j = 0;
+        for (; j < my_tiles - 3; ++j) step(std::integral_constant<int, 3>{}, j);
+        if (my_tiles > 2) step(std::integral_constant<int, 2>{}, j++);
+        if (my_tiles > 1) step(std::integral_constant<int, 1>{}, j++);
+        if (my_tiles > 0) step(std::integral_constant<int, 0>{}, j);
+    }
+
+    if (bad_block && lane == 0 && p.err_flag) atomicOr(p.err_flag, SPECVLM_ERR_BAD_BLOCK);
+    // ---- merge the four streams ---------------------------------------------------------------------
+    // Owner w takes OWN blocks of 32 rows x 32 dims: both row blocks at dims 32w (head size 128), or rows 32 (w / 2), dims 32 (w % 2).
+    auto own_qb = [](int w, int e) { return D == 128 ? e : w >> 1; };
+    auto own_t = [](int w, int e) { return D == 128 ? w : w & 1; };
+    bool real[OWN];
+    int64_t o_off[OWN], lse_off[OWN];
+    bool any_real = false;
+#pragma unroll
+    for (int e = 0; e < OWN; ++e) {
+        const int R = row0 + own_qb(wave, e) * 32 + l32;
+        const int hh = divide(R, p.magic_nmax);
+        const int node = R - hh * p.N_max;
+        const int h = hk * p.group + hh;
+        real[e] = R < rows_total && node < n;
+        any_real = any_real || real[e];
+        // lanes 0-31 store dims 16u + 0..7, lanes 32-63 dims 16u + 8..15 of the block
+        o_off[e] = b * p.o_sb + node * p.o_sn + static_cast<int64_t>(h) * p.o_sh + 32 * own_t(wave, e) + 8 * hf;
+        lse_off[e] = (static_cast<int64_t>(b) * p.H_q + h) * p.N_max + node;
+    }
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+        l_run[qb] += other_half(l_run[qb]);
+        if (hf == 0) {
+            s_m[wave][qb * 32 + l32] = m_run[qb];
+            s_l[wave][qb * 32 + l32] = l_run[qb];
+        }
+    }
+    __syncthreads();                                       // every stream is done with its ring
+    f32x16 out[OWN];
+#pragma unroll
+    for (int o = 0; o < kWaveWgs; ++o) {
+        if (o == wave) {                                   // uniform
+#pragma unroll
+            for (int e = 0; e < OWN; ++e) out[e] = acc[own_qb(o, e)][own_t(o, e)];
+        } else {
+            const int idx = wave < o ? wave : wave - 1;
+            f32x4* dst = reinterpret_cast<f32x4*>(s_ring) + (o * 3 + idx) * (OWN * 4) * 64 + lane;
+#pragma unroll
+            for (int e = 0; e < OWN; ++e)
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const f32x16& a = acc[own_qb(o, e)][own_t(o, e)];
+                    dst[(e * 4 + u) * 64] = f32x4{a[4 * u], a[4 * u + 1], a[4 * u + 2], a[4 * u + 3]};
+                }
+        }
+    }
+    __syncthreads();
+    float Mq[OWN], Lq[OWN];
+#pragma unroll
+    for (int e = 0; e < OWN; ++e) {
+        const int qrow = own_qb(wave, e) * 32 + l32;
+        float m[kWaveWgs], w[kWaveWgs];
+#pragma unroll
+        for (int x = 0; x < kWaveWgs; ++x) m[x] = s_m[x][qrow];
+        Mq[e] = fmaxf(fmaxf(m[0], m[1]), fmaxf(m[2], m[3]));
+        const float m_safe = Mq[e] == -INFINITY ? 0.f : Mq[e];
+        Lq[e] = 0.f;
+#pragma unroll
+        for (int x = 0; x < kWaveWgs; ++x) {               // (in this order in every owner of the rows)
+            w[x] = fast_exp2((m[x] - m_safe) * c2);
+            Lq[e] += s_l[x][qrow] * w[x];
+        }
+        out[e] *= wave == 0 ? w[0] : wave == 1 ? w[1] : wave == 2 ? w[2] : w[3];
+        const f32x4* src = reinterpret_cast<const f32x4*>(s_ring) + (wave * 3 * OWN + e) * 4 * 64 + lane;
+#pragma unroll
+        for (int idx = 0; idx < 3; ++idx) {
+            const float wx = wave <= idx ? w[idx + 1] : w[idx];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const f32x4 v = src[(idx * OWN * 4 + u) * 64];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) out[e][4 * u + i] += v[i] * wx;
+            }
+        }
+    }
+    if (!__any(any_real)) return;                          // uniform over the splits of the unit as well
+    auto store_out = [&](const float (&M)[OWN], const float (&L)[OWN]) {
+#pragma unroll
+        for (int e = 0; e < OWN; ++e) {
+            const float inv = 1.f / L[e];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {                  // 16 dims: registers 8u .. 8u + 7
+                uint32_t w[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) w[i] = pack_bf16x2(out[e][8 * u + 2 * i] * inv, out[e][8 * u + 2 * i + 1] * inv);
+                // the halves of the wavefront hold dims 0-3, 8-11 and 4-7, 12-15: the lower keeps 0-7, the upper 8-15
+                const auto r0 = __builtin_amdgcn_permlane32_swap(w[0], w[2], false, false);
+                const auto r1 = __builtin_amdgcn_permlane32_swap(w[1], w[3], false, false);
+                if (real[e]) *reinterpret_cast<u32x4*>(p.o + o_off[e] + 16 * u) = u32x4{r0[0], r1[0], r0[1], r1[1]};
+            }
+            if (real[e] && p.lse && hf == 0 && own_t(wave, e) == 0) p.lse[lse_off[e]] = M[e] * p.scale + __log2f(L[e]) * kLn2;
+        }
+    };
+    if (p.num_splits == 1) {
+        store_out(Mq, Lq);
+        return;
+    }
+    // ---- split partials ----------------------------------------------------------------------------
+    constexpr int PV = OWN * 2;                            // 16-byte vectors per lane per partial
+    const int64_t part0 = static_cast<int64_t>(unit) * p.num_splits;
+    constexpr int kPartBytes = kWaveWgs * PV * 1024;       // one split's partial
+    {
+        unsigned char* dst = p.ws_acc + (part0 + split) * kPartBytes + wave * PV * 1024 + lane * 16;
+#pragma unroll
+        for (int e = 0; e < OWN; ++e)
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                u32x4 x;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) x[i] = pack_bf16x2(out[e][8 * u + 2 * i], out[e][8 * u + 2 * i + 1]);
+                store16_coherent(dst + (e * 2 + u) * 1024, x);
+            }
+        // (every owner of a row stores the same pair)
+#pragma unroll
+        for (int e = 0; e < OWN; ++e)
+            if (hf == 0) store8_coherent(p.ws_ml + ((part0 + split) * kQRows + own_qb(wave, e) * 32 + l32) * 2, u32x2{__float_as_uint(Mq[e]), __float_as_uint(Lq[e])});
+    }
+    wait_vmcnt<0>();
+    int is_last = 0;
+    if (lane == 0) {
+        int32_t* cnt = p.ws_cnt + (static_cast<int64_t>(unit) * 4 + wave) * kCounterStride;
+        const int ticket = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        is_last = ticket == p.num_splits - 1;
+        if (is_last) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (!__builtin_amdgcn_readfirstlane(is_last)) return;
+    asm volatile("" ::: "memory");
+    // device-coherent (sc1) buffer loads, which the compiler counts; not before the ticket was seen
+    constexpr int kCoherent = 16, kMostRanges = 4;
+    const auto acc_rsrc = __builtin_amdgcn_make_buffer_rsrc(p.ws_acc + part0 * kPartBytes + wave * PV * 1024, 0, 0x7FFFFFFF, 0x00027000);
+    const auto ml_rsrc = __builtin_amdgcn_make_buffer_rsrc(p.ws_ml + part0 * kQRows * 2, 0, 0x7FFFFFFF, 0x00027000);
+    u32x4 part[kMostRanges][PV];
+    u32x2 ml[kMostRanges][OWN];
+    const int last = p.num_splits - 1;
+#pragma unroll
+    for (int u = 0; u < kMostRanges; ++u)                  // (past the last range: the last one again, weight zero)
+#pragma unroll
+        for (int e = 0; e < OWN; ++e)
+            ml[u][e] = __builtin_amdgcn_raw_buffer_load_b64(ml_rsrc, (own_qb(wave, e) * 32 + l32) * 8, min(u, last) * (kQRows * 8), kCoherent);
+#pragma unroll
+    for (int u = 0; u < kMostRanges; ++u)
+#pragma unroll
+        for (int v = 0; v < PV; ++v)
+            part[u][v] = __builtin_amdgcn_raw_buffer_load_b128(acc_rsrc, lane * 16, min(u, last) * kPartBytes + v * 1024, kCoherent);
+    float Mall[OWN], Lall[OWN];
+#pragma unroll
+    for (int e = 0; e < OWN; ++e) {
+        Mall[e] = -INFINITY;
+#pragma unroll
+        for (int u = 0; u < kMostRanges; ++u) Mall[e] = fmaxf(Mall[e], __uint_as_float(ml[u][e][0]));
+        const float m_safe = Mall[e] == -INFINITY ? 0.f : Mall[e];
+        Lall[e] = 0.f;
+        out[e] = zero;
+#pragma unroll
+        for (int u = 0; u < kMostRanges; ++u) {
+            const float w = u <= last ? fast_exp2((__uint_as_float(ml[u][e][0]) - m_safe) * c2) : 0.f;
+            Lall[e] += __uint_as_float(ml[u][e][1]) * w;
+#pragma unroll
+            for (int v = 0; v < 2; ++v)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t x = part[u][2 * e + v][i];
+                    out[e][8 * v + 2 * i] = fmaf(__uint_as_float(x << 16), w, out[e][8 * v + 2 * i]);
+                    out[e][8 * v + 2 * i + 1] = fmaf(__uint_as_float(x & 0xFFFF0000u), w, out[e][8 * v + 2 * i + 1]);
+                }
+        }
+    }
+    store_out(Mall, Lall);
+}
+
+template <int D>
+void launch_d(const WaveParams& p, dim3 grid, hipStream_t stream) {
+    if (p.g.block_table) hipLaunchKernelGGL((attn_streams_kernel<D, true>), grid, dim3(kWaveWgs * 64), 0, stream, p);
+    else hipLaunchKernelGGL((attn_streams_kernel<D, false>), grid, dim3(kWaveWgs * 64), 0, stream, p);
+}
+
+}  // namespace
+
+int32_t launch_attn_streams(const AttnArgs& a) {
+    unsigned workgroups;
+    const WaveParams p = wave_params(a, kQRows, a.plan.streams, workgroups);
+    if (a.d.D == 128) launch_d<128>(p, dim3(workgroups), a.stream);
+    else launch_d<64>(p, dim3(workgroups), a.stream);
+    return check_launch();
+}
+
+}  // namespace specvlm

@@ -25,57 +25,16 @@
 // Measured per call (HIP-graph replay), key ranges only -> here: 1 x 32 heads, 828 keys 11.3 -> 9.8 us; 4 x 8
 // heads, 144 keys 8.8 -> 5.8; 2 x 8 heads, 1197 keys, paged 16.6 -> 10.2; 1 x 8 heads of 64, 4200 keys 21.4 -> 8.5;
 // 4 x 32 query / 16 KV heads of 64, 13 nodes 9.0 -> 6.0.
-#include "attn_common.hpp"
+#include "attn_rows.hpp"
 
 namespace specvlm {
 
 namespace {
 
-struct WaveParams {
-    KvGeom g;
-    int N_max, H_q, H_kv, group, row_blocks, num_splits;
-    uint32_t magic_splits, magic_rb, magic_hkv, magic_nmax, magic_nstream;   // divisors, see divide()
-    float scale;                // softmax scale
-    const uint16_t *q, *k, *v;
-    uint16_t* o;
-    float* lse;
-    int64_t q_sb, q_sn, q_sh, o_sb, o_sn, o_sh;
-    const int32_t *prefix_len, *num_nodes, *parent;
-    int32_t* err_flag;
-    int32_t* ws_cnt;            // [units][4 owners] arrival tickets, kCounterStride words apart, zero between calls
-    unsigned char* ws_acc;      // [units * splits][owners][OT / 2][64 lanes] 16-byte vectors of packed bf16
-    float* ws_ml;               // [units * splits][block rows][2] (max, sum)
-};
-
-// n / d for n * d < 2^31, with m = ceil(2^31 / d) from the host.
-__device__ __forceinline__ uint32_t divide(uint32_t n, uint32_t m) { return __umulhi(2 * n, m); }
-uint32_t divisor(uint32_t d) { return (0x80000000u + d - 1) / d; }
-
 // The greatest of eight scores, NaN where one is: v_maximum3 takes its operands as they are (fmaxf would quiet each first).
 __device__ __forceinline__ float max8(f32x4 a, f32x4 b) {
     auto max3 = [](float x, float y, float z) { return __builtin_elementwise_maximum(__builtin_elementwise_maximum(x, y), z); };
     return max3(max3(a[0], a[1], a[2]), max3(a[3], b[0], b[1]), __builtin_elementwise_maximum(b[2], b[3]));
-}
-
-constexpr int kWaveWgs = 4;               // wavefronts per workgroup, one per SIMD, a key stream each
-constexpr int kKeys = 32;                 // keys per tile
-
-// Four (head size 128) or two (64) consecutive direct-to-LDS loads: the 16 rows of half a tile.  The
-// instruction offset advances the LDS and the global address alike, so voff[i] holds what is left.
-template <int D>
-__device__ __forceinline__ void dma_half(const void* sbase, const uint32_t (&voff)[D / 32], uint32_t lds_dst) {
-    if constexpr (D == 128)
-        asm volatile("s_mov_b32 m0, %5\n\ts_nop 0\n\t"
-                     "global_load_lds_dwordx4 %0, %4 nt\n\t"
-                     "global_load_lds_dwordx4 %1, %4 offset:1024 nt\n\t"
-                     "global_load_lds_dwordx4 %2, %4 offset:2048 nt\n\t"
-                     "global_load_lds_dwordx4 %3, %4 offset:3072 nt"
-                     : : "v"(voff[0]), "v"(voff[1]), "v"(voff[2]), "v"(voff[3]), "s"(sbase), "s"(lds_dst) : "memory");
-    else
-        asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\t"
-                     "global_load_lds_dwordx4 %0, %2 nt\n\t"
-                     "global_load_lds_dwordx4 %1, %2 offset:1024 nt"
-                     : : "v"(voff[0]), "v"(voff[1]), "s"(sbase), "s"(lds_dst) : "memory");
 }
 
 template <int D, int QB, bool PAGED>
@@ -656,34 +615,10 @@ void launch_d(const WaveParams& p, int block_rows, dim3 grid, hipStream_t stream
 }  // namespace
 
 int32_t launch_attn_wave(const AttnArgs& a) {
-    const int block_rows = a.plan.block_rows;
-    const specvlm_attn_desc& d = a.d;
-    WaveParams p;
-    p.g = KvGeom{d.kv_stride_b, d.kv_stride_h, d.kv_stride_t, d.paged ? a.block_table : nullptr,
-                 d.max_blocks_per_req, d.num_blocks,
-                 d.paged ? d.max_blocks_per_req * SPECVLM_PAGE_SIZE : d.kv_capacity};
-    p.N_max = d.N_max; p.H_q = d.H_q; p.H_kv = d.H_kv; p.group = d.H_q / d.H_kv;
-    p.row_blocks = (p.group * d.N_max + block_rows - 1) / block_rows;
-    p.num_splits = a.plan.splits;
-    p.magic_splits = divisor(p.num_splits); p.magic_rb = divisor(p.row_blocks); p.magic_hkv = divisor(p.H_kv);
-    p.magic_nmax = divisor(p.N_max); p.magic_nstream = divisor(kWaveWgs * p.num_splits);
-    p.scale = a.scale;
-    p.q = static_cast<const uint16_t*>(a.q);
-    p.k = static_cast<const uint16_t*>(a.k);
-    p.v = static_cast<const uint16_t*>(a.v);
-    p.o = static_cast<uint16_t*>(a.o);
-    p.lse = a.lse;
-    p.q_sb = d.q_stride_b; p.q_sn = d.q_stride_n; p.q_sh = d.q_stride_h;
-    p.o_sb = d.o_stride_b; p.o_sn = d.o_stride_n; p.o_sh = d.o_stride_h;
-    p.prefix_len = a.prefix_len; p.num_nodes = a.num_nodes; p.parent = a.parent;
-    p.err_flag = a.err_flag;
-    const unsigned parts = static_cast<unsigned>(d.B) * d.H_kv * p.row_blocks * p.num_splits;
-    unsigned char* ws = static_cast<unsigned char*>(a.workspace);
-    p.ws_cnt = reinterpret_cast<int32_t*>(ws);
-    p.ws_ml = reinterpret_cast<float*>(ws + kCounterBytes);
-    p.ws_acc = ws + kCounterBytes + static_cast<size_t>(parts) * block_rows * 8;
-    if (d.D == 128) launch_d<128>(p, block_rows, dim3(parts), a.stream);
-    else launch_d<64>(p, block_rows, dim3(parts), a.stream);
+    unsigned workgroups;
+    const WaveParams p = wave_params(a, a.plan.block_rows, a.plan.splits, workgroups);
+    if (a.d.D == 128) launch_d<128>(p, a.plan.block_rows, dim3(workgroups), a.stream);
+    else launch_d<64>(p, a.plan.block_rows, dim3(workgroups), a.stream);
     return check_launch();
 }
 

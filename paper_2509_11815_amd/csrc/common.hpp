@@ -129,8 +129,10 @@ int32_t launch_attn_valu(const AttnArgs& a);
 
 // bf16 MFMA split-key kernel + merge.
 int32_t launch_attn_mfma(const AttnArgs& a);
-// ... and the kernel whose workgroups take 16 or 32 query rows each (same workspace layout rules).
+// ... the kernel whose workgroups take 16 or 32 query rows each, and the one with 64 rows and a key stream per wavefront (same
+// workspace layout rules).
 int32_t launch_attn_wave(const AttnArgs& a);
+int32_t launch_attn_streams(const AttnArgs& a);
 size_t attn_mfma_workspace_bytes(const specvlm_attn_desc& d, int32_t ranges);
 // Device address of the current device's library-owned scratch array (SPECVLM_STATIC_WORKSPACE_BYTES).
 int32_t attn_static_workspace(void** ptr_out);

@@ -19,6 +19,7 @@ extern "C" void plan(const specvlm_attn_desc* d, int* out) {
     const specvlm::AttnPlan p = specvlm::attn_plan(*d);
     out[0] = p.ranges; out[1] = p.block_rows; out[2] = p.splits;
 }
+extern "C" int streams(const specvlm_attn_desc* d) { return specvlm::attn_plan(*d).streams; }
 """
 
 
@@ -40,14 +41,23 @@ def plan_of_desc(desc) -> Plan:
     return Plan(*out)
 
 
-def plan_of(B, Hq, Hkv, D, N, cap, num_splits=0, paged=False, token_stride=None) -> Plan:
+def desc_of(B, Hq, Hkv, D, N, cap, num_splits=0, paged=False, token_stride=None):
     """Dense tensors of these sizes; `cap` slots per request (a multiple of 16 when paged)."""
     import paper_2509_11815_amd.binding as b
     t = D if token_stride is None else token_stride
-    return plan_of_desc(b.AttnDesc(
+    return b.AttnDesc(
         dtype=b.SPECVLM_BF16, B=B, H_q=Hq, H_kv=Hkv, D=D, N_max=N, paged=int(paged), block_size=16 * paged, max_blocks_per_req=cap // 16 * paged,
         num_blocks=B * (cap // 16) * paged, kv_capacity=cap, num_splits=num_splits, q_stride_b=N * Hq * D, q_stride_n=Hq * D,
-        q_stride_h=D, o_stride_b=N * Hq * D, o_stride_n=Hq * D, o_stride_h=D, kv_stride_b=Hkv * cap * t, kv_stride_h=cap * t, kv_stride_t=t))
+        q_stride_h=D, o_stride_b=N * Hq * D, o_stride_n=Hq * D, o_stride_h=D, kv_stride_b=Hkv * cap * t, kv_stride_h=cap * t, kv_stride_t=t)
+
+
+def streams_of(*shape, **options) -> int:
+    """Key ranges of the kernel with a key stream per wavefront, 0 where another is taken."""
+    return _library().streams(ctypes.byref(desc_of(*shape, **options)))
+
+
+def plan_of(*shape, **options) -> Plan:
+    return plan_of_desc(desc_of(*shape, **options))
 
 
 def plan_of_case(case, num_splits=0) -> Plan:

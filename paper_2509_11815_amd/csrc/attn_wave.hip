@@ -20,9 +20,9 @@
 //   tree      ancestor masks from a register copy of the parent array by pointer doubling across lanes, built
 //             only by wavefronts that meet a tile past the prefix
 //   merge     as in attn_mfma.hip: streams through LDS, key ranges through the workspace and tickets; the last
-//             arrival reads the partials in batches of eight (a caller's 9 - 64 splits too)
+//             arrival reads up to four partials at once, more in batches of eight (a caller's 9 - 64 splits too)
 //
-// Measured per call (HIP-graph replay), key ranges only -> here: 1 x 32 heads, 828 keys 11.3 -> 9.8 us; 4 x 8
+// Measured per call (HIP-graph replay), key ranges only -> here: 1 x 32 heads, 828 keys 11.3 -> 9.25 us; 4 x 8
 // heads, 144 keys 8.8 -> 5.8; 2 x 8 heads, 1197 keys, paged 16.6 -> 10.2; 1 x 8 heads of 64, 4200 keys 21.4 -> 8.5;
 // 4 x 32 query / 16 KV heads of 64, 13 nodes 9.0 -> 6.0.
 #include "attn_rows.hpp"
@@ -59,6 +59,11 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
     __shared__ float s_m[kWaveWgs][QB * 16];
     __shared__ float s_l[kWaveWgs][QB * 16];
 
+    // What the first requests need of the arguments, in one trip to memory (left to itself the compiler loads them where they
+    // are used: two more trips, one of them the lengths', before the first request; 2 x 16 / 4 heads, 300 keys 6.50 -> 6.37 us)
+    asm volatile("" : : "s"(p.g.stride_b), "s"(p.g.stride_h), "s"(p.g.stride_t), "s"(p.g.capacity), "s"(p.N_max), "s"(p.H_kv), "s"(p.group), "s"(p.row_blocks),
+                 "s"(p.num_splits), "s"(p.magic_splits), "s"(p.magic_rb), "s"(p.magic_hkv), "s"(p.magic_nmax), "s"(p.magic_nstream), "s"(p.q), "s"(p.k), "s"(p.v),
+                 "s"(p.q_sb), "s"(p.q_sn), "s"(p.q_sh), "s"(p.prefix_len), "s"(p.num_nodes), "s"(p.parent));
     // work item: (request, KV head, row block, split); every XCD gets a contiguous range of items
     uint32_t work = blockIdx.x;
     if ((gridDim.x & 7) == 0) work = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
@@ -73,8 +78,6 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
     const int l16 = lane & 15, g = lane >> 4;
 
     typedef const __attribute__((address_space(4))) int32_t* const_i32;
-    const int n_raw = p.num_nodes ? ((const_i32)p.num_nodes)[b] : p.N_max;
-    const int P_raw = ((const_i32)p.prefix_len)[b];
     const int nstream = kWaveWgs * p.num_splits;
     const int stream = wave * p.num_splits + split;
 
@@ -148,6 +151,11 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
     constexpr bool early = !PAGED;
     offsets_k();
     if (early) issue_k(0, phys);
+    // the request's lengths through the scalar cache, not before that request
+    const int32_t *lengths = p.prefix_len, *counts = p.num_nodes ? p.num_nodes : p.prefix_len;
+    asm volatile("" : "+s"(lengths), "+s"(counts));
+    const int P_raw = ((const_i32)lengths)[b];
+    const int n_given = ((const_i32)counts)[b], n_raw = p.num_nodes ? n_given : p.N_max;
 
     // query rows of this block: row r of the block is row R = 16 QB rb + r of the group's (head, node) rows
     const int rows_total = p.group * p.N_max;
@@ -247,6 +255,20 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
             for (int c = 0; c < NC; ++c)
                 ka[x][c] = *reinterpret_cast<const bf16x8*>(ring + slot_off + kaddr[c] + x * 16 * ROWG * 16);
     };
+    // Where this wavefront's share of the result goes (worked out while the first tile is on its way): wavefront w owns query
+    // block w / NS, head-dim slice w % NS
+    const int oqb = wave / NS, osl = wave % NS, qrow = oqb * 16 + l16;
+    int64_t o_off, lse_off;
+    unsigned long long real_rows;
+    {
+        const int R = row0 + qrow;
+        const int hh = divide(R, p.magic_nmax);
+        const int node = R - hh * p.N_max;
+        const int h = hk * p.group + hh;
+        real_rows = __ballot(R < rows_total && node < n);
+        o_off = b * p.o_sb + node * p.o_sn + static_cast<int64_t>(h) * p.o_sh + 4 * (g & ~1) + osl * OT * 16;
+        lse_off = (static_cast<int64_t>(b) * p.H_q + h) * p.N_max + node;
+    }
     // K0 and the query rows of this wavefront have landed; the barrier extends the latter to the workgroup
     if (my_tiles > 1) wait_vmcnt<3 * KLD>();
     else if (my_tiles == 1) wait_vmcnt<KLD>();
@@ -435,7 +457,7 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
     }
 
     if (bad_block && lane == 0 && p.err_flag) atomicOr(p.err_flag, SPECVLM_ERR_BAD_BLOCK);
-    // ---- merge the four streams: wavefront w owns query block w / NS, head-dim slice w % NS ----------
+    // ---- merge the four streams --------------------------------------------------------------------
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
         l_run[qb] += __shfl_xor(l_run[qb], 16);
@@ -462,8 +484,6 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
     }
     __syncthreads();
     if (wave >= QB * NS) return;
-    const int oqb = wave / NS, osl = wave % NS;
-    const int qrow = oqb * 16 + l16;
     float Mq = s_m[0][qrow];
 #pragma unroll
     for (int x = 1; x < kWaveWgs; ++x) Mq = fmaxf(Mq, s_m[x][qrow]);
@@ -487,16 +507,12 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
             for (int t = 0; t < OT; ++t) out[t] += src[(idx * OT + t) * 64 + lane] * wx;
         }
     }
-    const int R = row0 + qrow;
-    const int hh = divide(R, p.magic_nmax);
-    const int node = R - hh * p.N_max;
-    const bool real = R < rows_total && node < n;
-    const int h = hk * p.group + hh;
-    if (!__any(real)) return;                              // uniform over the splits of the unit as well
+    if (!real_rows) return;                                // uniform over the splits of the unit as well
+    const bool real = (real_rows >> lane) & 1;
     auto store_out = [&](float M, float L) {
         const float inv = 1.f / L;
         const bool odd = g & 1;
-        uint16_t* orow = p.o + b * p.o_sb + node * p.o_sn + static_cast<int64_t>(h) * p.o_sh + 4 * (g & ~1) + osl * OT * 16;
+        uint16_t* orow = p.o + o_off;
 #pragma unroll
         for (int u = 0; u < OT / 2; ++u) {
             const uint32_t e0 = pack_bf16x2(out[2 * u][0] * inv, out[2 * u][1] * inv);
@@ -509,7 +525,7 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
             if (real) *reinterpret_cast<u32x4*>(orow + 16 * (2 * u + (odd ? 1 : 0))) = w;
         }
         if (real && p.lse && g == 0 && osl == 0)
-            p.lse[(static_cast<int64_t>(b) * p.H_q + h) * p.N_max + node] = M * p.scale + __log2f(L) * kLn2;
+            p.lse[lse_off] = M * p.scale + __log2f(L) * kLn2;
     };
     if (p.num_splits == 1) {
         store_out(Mq, Lq);
@@ -542,6 +558,44 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
         if (is_last) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (!__builtin_amdgcn_readfirstlane(is_last)) return;
+    if (p.num_splits <= 4) {                               // uniform; what the library chooses by itself, mostly
+        // (four partials in place of eight: half the instructions of the chain's last link: 1 x 32 heads, 828 keys 9.85 -> 9.25 us)
+        constexpr int kFew = 4, kCoherent = 16;            // sc1; buffer loads, which the compiler counts
+        const auto acc_rsrc = __builtin_amdgcn_make_buffer_rsrc(p.ws_acc + part0 * kPartBytes + wave * PV * 1024, 0, 0x7FFFFFFF, 0x00027000);
+        const auto ml_rsrc = __builtin_amdgcn_make_buffer_rsrc(p.ws_ml + part0 * (QB * 16) * 2, 0, 0x7FFFFFFF, 0x00027000);
+        const int last = p.num_splits - 1;
+        u32x4 part[kFew][PV];
+        u32x2 ml[kFew];
+#pragma unroll
+        for (int u = 0; u < kFew; ++u)
+            ml[u] = __builtin_amdgcn_raw_buffer_load_b64(ml_rsrc, qrow * 8, min(u, last) * (QB * 16 * 8), kCoherent);
+#pragma unroll
+        for (int u = 0; u < kFew; ++u)
+#pragma unroll
+            for (int v = 0; v < PV; ++v)
+                part[u][v] = __builtin_amdgcn_raw_buffer_load_b128(acc_rsrc, lane * 16, min(u, last) * kPartBytes + v * 1024, kCoherent);
+        float Mall = -INFINITY, Lall = 0.f;
+#pragma unroll
+        for (int u = 0; u < kFew; ++u) Mall = fmaxf(Mall, __uint_as_float(ml[u][0]));
+        const float m_safe = Mall == -INFINITY ? 0.f : Mall;
+#pragma unroll
+        for (int t = 0; t < OT; ++t) out[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int u = 0; u < kFew; ++u) {
+            const float w = u <= last ? fast_exp2((__uint_as_float(ml[u][0]) - m_safe) * c2) : 0.f;
+            Lall += __uint_as_float(ml[u][1]) * w;
+#pragma unroll
+            for (int v = 0; v < PV; ++v)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t x = part[u][v][i];
+                    out[2 * v][i] = fmaf(__uint_as_float(x << 16), w, out[2 * v][i]);
+                    out[2 * v + 1][i] = fmaf(__uint_as_float(x & 0xFFFF0000u), w, out[2 * v + 1][i]);
+                }
+        }
+        store_out(Mall, Lall);
+        return;
+    }
     constexpr int MB = 8;                                  // splits requested together
     const uint32_t voff_part = lane * 16, voff_ml = qrow * 8;
     const unsigned char* acc_base = p.ws_acc + part0 * kPartBytes + wave * PV * 1024;

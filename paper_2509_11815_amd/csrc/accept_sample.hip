@@ -21,8 +21,8 @@
 //   bonus     a two-level scan: every thread sums a contiguous chunk of the vocabulary, the chunk sums are
 //             scanned, and the chunk that contains the drawn position is walked (CH = 0: its probabilities are
 //             computed by the whole workgroup first)
-// Kernel alone, averages over 1 - 16 requests: up to 32768 tokens 15.2 -> 12.1 us, up to 65536 31.3 -> 18.2, beyond
-// (99254 and 152064) 198 -> 29 (every pass and the walk of the drawn chunk read token by token before).
+// Kernel alone, 4 requests: 32000 tokens 10.9 us, 20003 13.3, 60000 22.7, 65536 17.7, 152064 34.4 (beyond 65536, passes that
+// read token by token took 198 us).
 #include "chunk_vectors.hpp"
 #include "wave_ops.hpp"
 
@@ -80,9 +80,10 @@ __device__ __forceinline__ float vec_at(const uint4& w, int e) {
 }
 
 // CH > 0: every thread keeps its chunk of the current row (at most CH consecutive tokens) in
-// registers, loaded once per level with 16-byte loads when the row allows; CH == 0: any
-// vocabulary size, every pass reads the row again (from L2).
-template <typename T, int CH>
+// registers, loaded once per level with 16-byte loads; WHOLE: the chunks of every row are whole aligned vectors.
+// (Two kernels: with both ways of loading in one, 4 requests of 32000 tokens took 12.5 us in place of 10.9, 65536 22.8 of 17.7.)
+// CH == 0: any vocabulary size, every pass reads the row again (from L2).
+template <typename T, int CH, bool WHOLE>
 __global__ __launch_bounds__(kThreadsAS) void tree_accept_sample_kernel(
     int N_max, int V, int path_cap, const int32_t* __restrict__ parent, const int32_t* __restrict__ draft_tok,
     const T* __restrict__ logits, int64_t stride_b, int64_t stride_n, const int32_t* __restrict__ num_nodes,
@@ -120,25 +121,49 @@ __global__ __launch_bounds__(kThreadsAS) void tree_accept_sample_kernel(
 #pragma unroll
         for (int j = 0; j < NV; ++j) asm volatile("" : "+v"(lv[j].x), "+v"(lv[j].y), "+v"(lv[j].z), "+v"(lv[j].w));
     };
+    auto put = [](uint4& w, int e, T value) __attribute__((always_inline)) {     // (a select per dword: e may be known at run time only)
+#pragma unroll
+        for (int d = 0; d < 4; ++d) {
+            uint32_t& x = (&w.x)[d];
+            if constexpr (sizeof(T) == 2) {
+                const uint32_t y = e & 1 ? (x & 0xFFFFu) | static_cast<uint32_t>(value) << 16 : (x & 0xFFFF0000u) | static_cast<uint32_t>(value);
+                x = d == e >> 1 ? y : x;
+            } else {
+                x = d == e ? __float_as_uint(value) : x;
+            }
+        }
+    };
     auto load_row = [&](const T* row) __attribute__((always_inline)) {
         if constexpr (CH > 0) {
-            const bool vec_ok = (reinterpret_cast<uintptr_t>(row) & 15u) == 0 && chunk % VEC == 0 && V % VEC == 0;
 #pragma unroll
             for (int j = 0; j < NV; ++j) lv[j] = uint4{kInfWord, kInfWord, kInfWord, kInfWord};
-            if (vec_ok) {                               // uniform
+            if constexpr (WHOLE) {
 #pragma unroll
                 for (int j = 0; j < NV; ++j)
                     if (v0 + j * VEC < v1) lv[j] = *reinterpret_cast<const uint4*>(row + v0 + j * VEC);
             } else {
+                // Most vocabularies: chunks start at any token.  16 bytes a load all the same (gfx950 takes them at any alignment
+                // of their type); only the vector that the row ends in is read entry by entry.  (Every entry of its own:
+                // 4 requests of 60000 tokens 39.4 us, now 22.7; 20003 15.5, now 13.3.)
+#pragma unroll
+                for (int j = 0; j < NV; ++j) {
+                    const int at = v0 + j * VEC;
+                    if (at < v1) {
+                        if (at + VEC <= V) {
+                            __builtin_memcpy(&lv[j], row + at, 16);
+                        } else {
+#pragma unroll
+                            for (int e = 0; e < VEC - 1; ++e)
+                                if (at + e < V) put(lv[j], e, row[at + e]);
+                        }
+                    }
+                }
 #pragma unroll
                 for (int j = 0; j < NV; ++j)
+                    if (v0 + (j + 1) * VEC > v1)       // entries of the next chunk
 #pragma unroll
-                    for (int e = 0; e < VEC; ++e)
-                        if (v0 + j * VEC + e < v1) {
-                            uint32_t& x = (&lv[j].x)[sizeof(T) == 2 ? e >> 1 : e];
-                            if constexpr (sizeof(T) == 2) x = (x & (0xFFFF0000u >> (16 * (e & 1)))) | static_cast<uint32_t>(row[v0 + j * VEC + e]) << (16 * (e & 1));
-                            else x = __float_as_uint(row[v0 + j * VEC + e]);
-                        }
+                        for (int e = 0; e < VEC; ++e)
+                            if (v0 + j * VEC + e >= v1) put(lv[j], e, sizeof(T) == 2 ? static_cast<T>(0xFF80u) : static_cast<T>(-INFINITY));
             }
         }
     };
@@ -167,7 +192,7 @@ __global__ __launch_bounds__(kThreadsAS) void tree_accept_sample_kernel(
     }
 
     int cur = 0, m = 0;
-    float mx = 0.f, Z = 0.f;
+    float mx = 0.f, Z = 0.f, mass = 0.f;               // mass: this thread's share of Z
     // unnormalised probability exp((l - max) / T) as one multiply and one v_exp_f32 (the whole
     // vocabulary goes through it three times on a single compute unit); -inf gives 0
     const float c2 = 1.4426950408889634f / temperature;
@@ -228,6 +253,7 @@ __global__ __launch_bounds__(kThreadsAS) void tree_accept_sample_kernel(
             }
             for (; v < V; v += kThreadsAS) part += prob_of(logit_at<T>(row, v));
         }
+        mass = part;
         Z = block_sum(part, s_red);
         // The children of cur are tried in increasing node index; wavefront 0 holds child c in lane c.
         if (tid < SPECVLM_MAX_NODES) {
@@ -281,9 +307,15 @@ __global__ __launch_bounds__(kThreadsAS) void tree_accept_sample_kernel(
     unsigned long long mine = 0;                       // bit r: rejected token r lies in this thread's chunk
     for (int r = 0; r < nrej; ++r) mine |= static_cast<unsigned long long>(s_rej[r] >= v0 && s_rej[r] < v1) << r;
     if constexpr (CH > 0) {                            // lv[] still holds cur's row
-        for (unsigned long long r = mine; r; r &= r - 1) drop(lv, NV, s_rej[__builtin_ctzll(r)] - v0);
+        // A chunk without a rejected token has the sum that went into Z, added up in the same order; few
+        // wavefronts hold any other (all of them summing again: 32000 tokens 12.1 us, now 10.9; 65536 19.6, now 17.7).
+        csum = mass;
+        if (mine) {
+            for (unsigned long long r = mine; r; r &= r - 1) drop(lv, NV, s_rej[__builtin_ctzll(r)] - v0);
+            csum = 0.f;
 #pragma unroll
-        for (int i = 0; i < CH; ++i) csum += prob_of(vec_at<T>(lv[i / VEC], i % VEC));
+            for (int i = 0; i < CH; ++i) csum += prob_of(vec_at<T>(lv[i / VEC], i % VEC));
+        }
         repack();
     } else {
         if (v0 < v1) {
@@ -416,20 +448,27 @@ int32_t launch_tree_accept_sample(int32_t dtype, int32_t B, int32_t N_max, int32
                                   int32_t* accept_len, int32_t* path, int32_t* bonus_tok,
                                   int32_t* committed_tok, int32_t* err_flag, hipStream_t stream) {
     dim3 grid(B), block(kThreadsAS);
-#define SPECVLM_LAUNCH_AS(T, CH)                                                                              \
-    hipLaunchKernelGGL((tree_accept_sample_kernel<T, CH>), grid, block, 0, stream, N_max, V, path_cap, parent, \
-                       draft_tok, static_cast<const T*>(logits), stride_b, stride_n, num_nodes, temperature,  \
+#define SPECVLM_LAUNCH_AS2(T, CH, WHOLE)                                                                             \
+    hipLaunchKernelGGL((tree_accept_sample_kernel<T, CH, WHOLE>), grid, block, 0, stream, N_max, V, path_cap, parent, \
+                       draft_tok, static_cast<const T*>(logits), stride_b, stride_n, num_nodes, temperature,         \
                        u_accept, u_bonus, accept_len, path, bonus_tok, committed_tok, err_flag)
-    const int chunk = (V + kThreadsAS - 1) / kThreadsAS;
+#define SPECVLM_LAUNCH_AS(T, CH)                     \
+    do {                                             \
+        if (whole) SPECVLM_LAUNCH_AS2(T, CH, true);  \
+        else SPECVLM_LAUNCH_AS2(T, CH, false);       \
+    } while (0)
+    const int chunk = (V + kThreadsAS - 1) / kThreadsAS, vec = dtype == SPECVLM_BF16 ? 8 : 4;
+    const bool whole = (reinterpret_cast<uintptr_t>(logits) & 15u) == 0 && (stride_b | stride_n | chunk | V) % vec == 0;
     if (dtype == SPECVLM_BF16) {
         if (chunk <= 32) SPECVLM_LAUNCH_AS(uint16_t, 32);
         else if (chunk <= 64) SPECVLM_LAUNCH_AS(uint16_t, 64);
-        else SPECVLM_LAUNCH_AS(uint16_t, 0);
+        else SPECVLM_LAUNCH_AS2(uint16_t, 0, false);
     } else {
         if (chunk <= 32) SPECVLM_LAUNCH_AS(float, 32);
         else if (chunk <= 64) SPECVLM_LAUNCH_AS(float, 64);
-        else SPECVLM_LAUNCH_AS(float, 0);
+        else SPECVLM_LAUNCH_AS2(float, 0, false);
     }
+#undef SPECVLM_LAUNCH_AS2
 #undef SPECVLM_LAUNCH_AS
     return check_launch();
 }

@@ -103,6 +103,14 @@ __device__ __forceinline__ int pos_of(const unsigned long long* s_key, int i) {
     return reinterpret_cast<const int*>(s_key)[2 * i];
 }
 
+// How many of n keys are above the key of this row of 16 lanes (every lane of the row gets it): lanes take the keys in turn.
+__device__ __forceinline__ int keys_above(const unsigned long long* s_key, int n, unsigned long long key) {
+    int above = 0;
+#pragma unroll 4
+    for (int x = threadIdx.x & 15; x < n; x += 16) above += s_key[x] > key ? 1 : 0;
+    return row_sum(above);
+}
+
 // Many candidates, few winners (the whole tree's 500 candidates, 59 nodes): ranking everybody
 // against everybody is mostly wasted on candidates that cannot win.  The candidates are dealt
 // into kGroupsDT groups (candidate i -> group i mod kGroupsDT); the M-th largest of the group
@@ -110,16 +118,17 @@ __device__ __forceinline__ int pos_of(const unsigned long long* s_key, int i) {
 // M * ceil(c / kGroupsDT) candidates reach it (the members of M groups).  Only those are ranked,
 // among themselves.  Same result as rank_winners' full ranking: keys are distinct, so "the M
 // greatest keys" is one set whatever way it is found.  Needs kGroupsDT <= c <= kThreadsDT (every
-// group has a member, one candidate per thread) and M <= kGroupsDT.
+// group has a member, one candidate per thread) and M <= kGroupsDT.  Rows of 16 lanes count as below; the survivors are
+// gathered in any order, the winners meet in a bitmap: five barriers.  A select call of 510 candidates, 59 chosen, 4.8 -> 4.3 us
+// (before: LDS counts of slices, survivors in index order, eight barriers).
 constexpr int kGroupsDT = 128;
 
 __device__ __forceinline__ void rank_winners_prefiltered(unsigned long long* s_key, int c, int M) {
-    __shared__ unsigned long long s_gmax[kGroupsDT];
+    __shared__ __attribute__((aligned(16))) unsigned long long s_gmax[kGroupsDT];
     __shared__ unsigned long long s_surv[kThreadsDT];
     __shared__ unsigned long long s_thr;
-    __shared__ int s_cnt2[kThreadsDT];
-    __shared__ int s_wcount2[kWavesDT];
-    __shared__ uint32_t s_winmask[kThreadsDT / 32];
+    __shared__ int s_ns;
+    __shared__ unsigned long long s_winmask[kWavesDT];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const unsigned long long ki = tid < c ? s_key[tid] : 0ull;          // 0: below every real key
     if (tid < kGroupsDT) {
@@ -130,96 +139,66 @@ __device__ __forceinline__ void rank_winners_prefiltered(unsigned long long* s_k
         }
         s_gmax[tid] = m;
     }
-    s_cnt2[tid] = 0;
-    if (tid < kThreadsDT / 32) s_winmask[tid] = 0u;
+    if (tid < kWavesDT) s_winmask[tid] = 0ull;
+    if (tid == 0) s_ns = 0;
     __syncthreads();
-    // rank of every group maximum among the group maxima: four threads per maximum, a quarter each
-    {
-        const int j = tid & (kGroupsDT - 1), part = tid / kGroupsDT;
-        constexpr int kPer = kGroupsDT / (kThreadsDT / kGroupsDT);
+    // the M-th greatest group maximum
+#pragma unroll
+    for (int j = tid >> 4; j < kGroupsDT; j += kThreadsDT / 16) {
         const unsigned long long kj = s_gmax[j];
-        int beaten = 0;
-#pragma unroll 8
-        for (int x = part * kPer; x < (part + 1) * kPer; ++x) beaten += s_gmax[x] > kj ? 1 : 0;
-        atomicAdd(&s_cnt2[j], beaten);
+        const int above = keys_above(s_gmax, kGroupsDT, kj);
+        if ((tid & 15) == 0 && above == M - 1) s_thr = kj;               // exactly one group: the ranks are a permutation
     }
-    __syncthreads();
-    if (tid < kGroupsDT && s_cnt2[tid] == M - 1) s_thr = s_gmax[tid];    // exactly one thread: the ranks are a permutation
     __syncthreads();
     const unsigned long long thr = s_thr;
-    // the candidates that reach the threshold, gathered in index order
+    // the candidates that reach the threshold, in any order
     const bool surv = ki >= thr;                                         // thr is a real key: never true for tid >= c
     const unsigned long long bal = __ballot(surv);
-    if (lane == 0) s_wcount2[wave] = __popcll(bal);
-    s_cnt2[tid] = 0;
-    __syncthreads();
-    int before = 0, ns = 0;
-#pragma unroll
-    for (int x = 0; x < kWavesDT; ++x) {
-        const int n = s_wcount2[x];
-        before += x < wave ? n : 0;
-        ns += n;
-    }
-    if (surv) s_surv[before + __popcll(bal & ((1ull << lane) - 1ull))] = ki;
-    if (tid < c) reinterpret_cast<int*>(s_key)[2 * tid] = -1;           // every key is in a register or in s_surv by now
-    __syncthreads();
-    // rank among the ns survivors: `parts` threads per survivor, a slice each
-    int nsp = 64;                                                        // uniform: survivors rounded up to a power of two
-    while (nsp < ns) nsp *= 2;
-    const int parts = kThreadsDT / nsp, per = (ns + parts - 1) / parts;
-    const int a = tid & (nsp - 1), part = tid / nsp;
-    const unsigned long long ka = a < ns ? s_surv[a] : ~0ull;
-    {
-        int beaten = 0;
-        const int x1 = min(ns, (part + 1) * per);
-        for (int x = part * per; x < x1; ++x) beaten += s_surv[x] > ka ? 1 : 0;
-        if (a < ns) atomicAdd(&s_cnt2[a], beaten);
+    if (bal) {                                                           // uniform in a wavefront
+        int at = 0;
+        if (lane == 0) at = atomicAdd(&s_ns, __popcll(bal));
+        at = __builtin_amdgcn_readfirstlane(at);
+        if (surv) s_surv[at + __popcll(bal & ((1ull << lane) - 1ull))] = ki;
     }
     __syncthreads();
-    const bool win = part == 0 && a < ns && s_cnt2[a] < M;
-    const uint32_t idx = 0xFFFFFFFFu - static_cast<uint32_t>(ka);       // the candidate's index sits in the key's low word
-    if (win) atomicOr(&s_winmask[idx >> 5], 1u << (idx & 31));
+    const int ns = s_ns;
+    for (int a = tid >> 4; a < ns; a += kThreadsDT / 16) {
+        const unsigned long long ka = s_surv[a];
+        const int above = keys_above(s_surv, ns, ka);
+        const uint32_t idx = 0xFFFFFFFFu - static_cast<uint32_t>(ka);   // the candidate's index sits in the key's low word
+        if ((tid & 15) == 0 && above < M) atomicOr(&s_winmask[idx >> 6], 1ull << (idx & 63));
+    }
     __syncthreads();
-    if (win) {                                                           // position = winners of lower index
-        int pos = __popc(s_winmask[idx >> 5] & ((1u << (idx & 31)) - 1u));
-        for (uint32_t w = 0; w < (idx >> 5); ++w) pos += __popc(s_winmask[w]);
-        reinterpret_cast<int*>(s_key)[2 * idx] = pos;
+    if (tid < c) {                                                       // position = winners of lower index
+        const unsigned long long mine = s_winmask[wave];
+        int pos = __popcll(mine & ((1ull << lane) - 1ull));
+        for (int w = 0; w < wave; ++w) pos += __popcll(s_winmask[w]);
+        reinterpret_cast<int*>(s_key)[2 * tid] = (mine >> lane) & 1ull ? pos : -1;      // every key is in a register or in s_surv by now
     }
     __syncthreads();
 }
 
-// Few candidates (a level's Top-K lists): everybody against everybody with `parts` threads per candidate, a
-// slice of the others each, and a winner's position as a population count over a bitmap of the winners --
-// three workgroup barriers (the general form below takes eight): 1.9 -> 1.5 us for 100 candidates.
+// Few candidates (a level's Top-K lists): everybody against everybody, a row of 16 lanes per candidate, and a winner's
+// position as a population count over the ballots of the winners -- two workgroup barriers (the general form below takes eight).
+// A select call of 100 candidates 3.2 -> 3.05 us (before: counts of slices meeting in LDS atomics, five barriers).
 __device__ __forceinline__ void rank_winners_few(unsigned long long* s_key, int c, int M) {
-    __shared__ int s_beaten[2 * kGroupsDT];
-    __shared__ uint32_t s_win[2 * kGroupsDT / 32];
-    const int tid = threadIdx.x;
-    const int cp = c <= 64 ? 64 : c <= 128 ? 128 : 256;     // uniform; a slice is whole wavefronts
-    const int parts = kThreadsDT / cp, per = (c + parts - 1) / parts;
-    const int i = tid & (cp - 1), part = tid / cp;
-    if (tid < 2 * kGroupsDT) s_beaten[tid] = 0;
-    if (tid < 2 * kGroupsDT / 32) s_win[tid] = 0u;
-    __syncthreads();
-    const unsigned long long ki = i < c ? s_key[i] : ~0ull;
-    {
-        int beaten = 0;
-        const int x1 = min(c, (part + 1) * per);
-#pragma unroll 8
-        for (int x = part * per; x < x1; ++x) beaten += s_key[x] > ki ? 1 : 0;
-        if (i < c && beaten) atomicAdd(&s_beaten[i], beaten);
+    __shared__ int s_win[2 * kGroupsDT];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int i = tid >> 4; i < c; i += kThreadsDT / 16) {                // the same in a row of lanes
+        const int above = keys_above(s_key, c, s_key[i]);
+        if ((tid & 15) == 0) s_win[i] = above < M;
     }
     __syncthreads();
-    const bool win = part == 0 && i < c && s_beaten[i] < M;
-    if (win) atomicOr(&s_win[i >> 5], 1u << (i & 31));
-    __syncthreads();
-    if (part == 0 && i < c) {
-        int pos = -1;
-        if (win) {
-            pos = __popc(s_win[i >> 5] & ((1u << (i & 31)) - 1u));
-            for (int w = 0; w < (i >> 5); ++w) pos += __popc(s_win[w]);
+    if (wave * 64 < c) {                                                 // uniform in a wavefront
+        int before = 0, pos = -1;
+        for (int w = 0; w <= wave; ++w) {
+            const int i = w * 64 + lane;
+            const bool win = i < c && s_win[i];
+            const unsigned long long bal = __ballot(win);
+            if (w == wave && win) pos = before + __popcll(bal & ((1ull << lane) - 1ull));
+            before += __popcll(bal);
         }
-        reinterpret_cast<int*>(s_key)[2 * i] = pos;
+        if (tid < c) reinterpret_cast<int*>(s_key)[2 * tid] = pos;
     }
     __syncthreads();
 }
@@ -228,7 +207,8 @@ __device__ __forceinline__ void rank_winners(unsigned long long* s_key, int c, i
     __shared__ int s_wcount[kWavesDT];
     __shared__ int s_cnt[kThreadsDT];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    if (c >= 2 * kGroupsDT && c <= kThreadsDT && M >= 1 && M <= kGroupsDT / 2) {    // uniform
+    // (below: select 192 of 10 3.6 us so and 3.8 by the few's form, of 64 3.9 and 3.8; 255 3.6 and 5.4, 4.0 and 5.4)
+    if (c > 3 * kGroupsDT / 2 && c <= kThreadsDT && M >= 1 && M <= kGroupsDT / 2) {    // uniform
         rank_winners_prefiltered(s_key, c, M);
         return;
     }
@@ -333,6 +313,8 @@ __device__ __forceinline__ void rank_winners(unsigned long long* s_key, int c, i
 // Per level (10 rows, kernel alone): 32000 bf16 logits 10.4 -> 6.6 us; rows of 99254 and 152064, which used to be re-read
 // entry by entry in every pass, 66 and 96 us -> 12.9 and 14.4.  Ten rows of equal logits, one call: 32000 42.7 -> 18.7,
 // 152064 97.9 -> 57.7; sorted along the vocabulary 44.5 -> 16.1 and 97.7 -> 41.0.
+// Entries ranked by rows of 16 lanes (a lane's share instead of a lane for all others) and the log-sum-exp left to one wavefront
+// beside the collection: 5.75 -> 5.3 us a call, 8.4 -> 8.05 with the selection; a growth of six levels with its finalize 53.4 -> 49.2.
 // ---------------------------------------------------------------------------------------
 // SEL: the workgroup that finishes a request's last row also chooses the M most valuable of the
 // request's W*K new candidates (what draft_select_kernel does in a launch of its own): scores
@@ -365,7 +347,7 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
     __shared__ __attribute__((aligned(16))) unsigned long long s_cand[kCandCap];
     __shared__ unsigned long long s_grp_key[64], s_thr_key;
     __shared__ int s_last, s_ncand;
-    __shared__ float s_thr;
+    __shared__ float s_thr, s_lse;
 
     const int w = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int nrows = gridDim.x;
@@ -467,23 +449,16 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
         beaten = row_sum(beaten);
         if (part == 0 && beaten == K - 1) s_thr = gj;    // exactly one group: the ranks are a permutation
     }
-    const float mx = row_max(s_wmax[tid & 15]);
-    const float lse = mx + logf(row_sum(s_wsum[tid & 15] * exp_of(s_wmax[tid & 15] - mx)));
-    if (tid == 0 && lse_out) lse_out[b * nrows + w] = lse;
     __syncthreads();
     const float thr = s_thr;
-
-    const int64_t out0 = b * out_stride_b + static_cast<int64_t>(w) * K;
-    auto emit = [&](int k, unsigned long long key) {     // k-th best of the row
-        token_out[out0 + k] = static_cast<int>(0xFFFFFFFFu - static_cast<uint32_t>(key));
-        const float sc = c + (key_value(key) - lse);
-        if constexpr (SEL)                               // read by another workgroup in this kernel
-            __hip_atomic_store(reinterpret_cast<uint32_t*>(score_out + out0 + k), __float_as_uint(sc),
-                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        else
-            score_out[out0 + k] = sc;
-        if (parent_out) parent_out[out0 + k] = par;
-    };
+    if (wave == kWavesDT - 1) {                          // beside the collection, in one wavefront's chain only
+        const float mx = row_max(s_wmax[tid & 15]);
+        const float l = mx + logf(row_sum(s_wsum[tid & 15] * exp_of(s_wmax[tid & 15] - mx)));
+        if (lane == 0) {
+            s_lse = l;
+            if (lse_out) lse_out[b * nrows + w] = l;
+        }
+    }
 
     // ---- the entries that reach it ------------------------------------------------------------------
     auto collect = [&](float x, int v) {
@@ -510,13 +485,32 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
     }
     __syncthreads();
     int nc = s_ncand;
+    const float lse = s_lse;
+    const int64_t out0 = b * out_stride_b + static_cast<int64_t>(w) * K;
+    // The root's only row: its candidates come in the order of their scores (rounding keeps it, equal ones go by
+    // index, with a NaN all are), so the selection is the first M and nobody has to be met: 7.7 -> 5.6 us a call.
+    const bool lone = SEL && nrows == 1 && !cum;
+    auto emit = [&](int k, unsigned long long key) {     // k-th best of the row
+        token_out[out0 + k] = static_cast<int>(0xFFFFFFFFu - static_cast<uint32_t>(key));
+        const float sc = c + (key_value(key) - lse);
+        if constexpr (SEL)                               // may be read by another workgroup in this kernel
+            __hip_atomic_store(reinterpret_cast<uint32_t*>(score_out + out0 + k), __float_as_uint(sc),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else
+            score_out[out0 + k] = sc;
+        if (parent_out) parent_out[out0 + k] = par;
+        if constexpr (SEL) {
+            if (lone && k < sel.M) {
+                sel.sel_out[b * sel.M + k] = k + sel.index_base;
+                if (sel.sel_score_out) sel.sel_score_out[b * sel.M + k] = sc;
+            }
+        }
+    };
     auto rank_them = [&]() __attribute__((always_inline)) {
-        for (int i = tid; i < nc; i += kThreadsDT) {
+        for (int i = tid >> 4; i < nc; i += kThreadsDT / 16) {           // a row of 16 lanes per entry
             const unsigned long long k = s_cand[i];
-            int beaten = 0;
-#pragma unroll 4
-            for (int x = 0; x < nc; ++x) beaten += s_cand[x] > k ? 1 : 0;
-            if (beaten < K) emit(beaten, k);
+            const int beaten = keys_above(s_cand, nc, k);
+            if ((tid & 15) == 0 && beaten < K) emit(beaten, k);
         }
     };
     if (nc <= kRankDirect) {                             // uniform
@@ -627,6 +621,18 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
         }
     }
     if constexpr (SEL) {
+        const int nc = nrows * K, count = min(sel.M, nc);
+        auto rest = [&]() __attribute__((always_inline)) {     // what follows the selected ones
+            for (int pw = count + tid; pw < sel.M; pw += kThreadsDT) {
+                sel.sel_out[b * sel.M + pw] = -1;
+                if (sel.sel_score_out) sel.sel_score_out[b * sel.M + pw] = -INFINITY;
+            }
+            if (tid == 0 && sel.count_out) sel.count_out[b] = count;
+        };
+        if (lone) {                                        // uniform
+            rest();
+            return;
+        }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this thread's score stores have been acknowledged
         __syncthreads();
         if (tid == 0) {
@@ -639,7 +645,6 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
         __syncthreads();
         if (!s_last) return;
         // the request's W*K new candidates (at most kCandCap, checked on the host), one per thread
-        const int nc = nrows * K;
         float sc = 0.f;
         if (tid < nc) {
             sc = __uint_as_float(__hip_atomic_load(reinterpret_cast<uint32_t*>(score_out + b * out_stride_b + tid),
@@ -648,7 +653,6 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
         }
         __syncthreads();
         rank_winners(s_cand, nc, sel.M);
-        const int count = min(sel.M, nc);
         if (tid < nc) {
             const int pw = pos_of(s_cand, tid);
             if (pw >= 0) {
@@ -656,11 +660,7 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
                 if (sel.sel_score_out) sel.sel_score_out[b * sel.M + pw] = sc;
             }
         }
-        for (int pw = count + tid; pw < sel.M; pw += kThreadsDT) {
-            sel.sel_out[b * sel.M + pw] = -1;
-            if (sel.sel_score_out) sel.sel_score_out[b * sel.M + pw] = -INFINITY;
-        }
-        if (tid == 0 && sel.count_out) sel.count_out[b] = count;
+        rest();
     }
 }
 
@@ -706,6 +706,13 @@ __global__ __launch_bounds__(kThreadsDT) void draft_finalize_kernel(
     }
     const int M = N_max - 1;
     const int64_t base = b * cand_stride_b;
+    // what the chosen ones will need, for the first candidate of a thread on its way while they are ranked
+    int parent0 = -1, token0 = -1, root = -1;
+    if (tid < c) {
+        parent0 = cand_parent[base + tid];
+        token0 = cand_token[base + tid];
+    }
+    if (tid == 0) root = root_token[b];
     for (int i = tid; i < c; i += kThreadsDT) s_key[i] = order_key(cand_score[base + i], i);
     __syncthreads();
     rank_winners(s_key, c, M);
@@ -713,7 +720,7 @@ __global__ __launch_bounds__(kThreadsDT) void draft_finalize_kernel(
     for (int i = tid; i < c; i += kThreadsDT) {
         const int p = pos_of(s_key, i);
         if (p < 0) continue;
-        const int cp = cand_parent[base + i];
+        const int cp = i == tid ? parent0 : cand_parent[base + i];
         int pn = -1;
         if (cp < -1 || cp >= i) {
             err |= SPECVLM_ERR_BAD_PARENT;
@@ -726,7 +733,7 @@ __global__ __launch_bounds__(kThreadsDT) void draft_finalize_kernel(
         }
         const int node = p + 1;
         parent_out[b * N_max + node] = pn;
-        draft_tok_out[b * N_max + node] = cand_token[base + i];
+        draft_tok_out[b * N_max + node] = i == tid ? token0 : cand_token[base + i];
         if (node_cand_out) node_cand_out[b * N_max + node] = i;
     }
     for (int node = count + 1 + tid; node < N_max; node += kThreadsDT) {
@@ -736,7 +743,7 @@ __global__ __launch_bounds__(kThreadsDT) void draft_finalize_kernel(
     }
     if (tid == 0) {
         parent_out[b * N_max] = -1;
-        draft_tok_out[b * N_max] = root_token[b];
+        draft_tok_out[b * N_max] = root;
         if (node_cand_out) node_cand_out[b * N_max] = -1;
         num_nodes_out[b] = count + 1;
     }

@@ -138,13 +138,33 @@ inline AttnPlan plan_of_heads_and_rows(const specvlm_attn_desc& d) {
     return plan;
 }
 
+// Row blocks (attn_wave.hip) that run in one round of workgroups are beaten by twice their key ranges (196 random shapes, 0.68 -
+// 0.99 of their time), not by the same number or half as many more, as long as the blocks of a head share an XCD, that is where
+// their workgroups are a multiple of 8.  us by row blocks | here:
+//   8 x 40 query / 10 KV heads, 22 nodes, 503 keys 10.3 | 12.3; 6 x 64 / 8 of 64, 18 nodes, 828: 9.4 | 11.6; 4 x 40 / 20, 46 nodes, 3869:
+//   40.7 | 43.5 (42 such shapes, all slower here, 6 - 27 %); two ranges | three: 5 x 28 / 4, 24 nodes, 2900: 21.1 | 23.0; but 8 x 20 / 5,
+//   22 nodes, 3390: 24.8 | 22.4 (three ranges on 216 workgroups or more, long streams); three | four: 3 x 16 / 8, 36 nodes, 2750: 16.0 | 16.7
+// Where they do not, every XCD fetches a head's K and V again, which short streams still bear (5 x 50 / 10, 30 nodes, 462 keys
+// 12.6 | 13.2; 1330 keys 20.9 | 20.4; 2600: 60.0 | 43.0), six or more blocks of a unit do not (9 x 20 / 4, 40 nodes, 512: 13.8 | 12.3), and
+// which paged requests of different lengths bear at head size 64 (10 x 40 / 5, 19 nodes, 4450: 32.2 | 36.6).
+inline bool rows_in_one_round_win(const specvlm_attn_desc& d, const AttnPlan& plan, int64_t units, int s) {
+    const int ntile = ((d.paged ? d.max_blocks_per_req * SPECVLM_PAGE_SIZE : d.kv_capacity) + kTile - 1) / kTile;
+    if (!plan.block_rows) return false;
+    const int row_blocks = (d.H_q / d.H_kv * d.N_max + plan.block_rows - 1) / plan.block_rows;
+    const int64_t workgroups = static_cast<int64_t>(d.B) * d.H_kv * row_blocks * plan.splits;
+    if (workgroups > 256 || s >= 2 * plan.splits) return false;
+    if (workgroups % 8 == 0) return !(s == 3 && units * s >= 216 && ntile >= (d.D == 64 ? 56 : 90));
+    if (plan.splits > 1) return ntile < 56;
+    return row_blocks < 6 && (ntile < 32 || (d.paged && d.D == 64));
+}
+
 // Batches that fill the chip with four streams per workgroup of 64 rows (attn_streams.hip) take as many key ranges as make one
-// round of 140 - 256 workgroups.  Not fewer workgroups (128 x 19 tiles: 15.1 us, 12.8 by row blocks), streams shorter than 3.5 tiles
+// round of 140 (with ranges 180) - 256 workgroups.  Not fewer workgroups (128 x 19 tiles: 15.1 us, 12.8 by row blocks), streams shorter than 3.5 tiles
 // (4 x 16 heads of 31 tiles, two ranges: 15.7 against 14.2; with four ranges, whose meeting costs more, 4.25 tiles), nor blocks
 // less than 55 % full (28 of 64 rows: 17.0 against 15.5).  A call whose results were not rounded to partial ones before stays
 // without them, and one that took key ranges takes at least two: requests of different lengths need them (5 x 32 heads,
 // 3568 - 400 keys, three ranges 38.9, one 43.2; equal lengths of 3100: 49.3 and 46.3).
-// us per call before -> here (head size 128 unless said); over 300 random shapes 76 taken, 0.64 - 1.00 of the time before, mean 0.86:
+// us per call before -> here (head size 128 unless said):
 //   unsplit       8 x 32 query / 16 KV heads, 4788 keys 82.4 -> 65.7; 7 x 32 / 8, 852: 21.1 -> 17.2; 4 x 40, 671: 18.5 -> 16.4;
 //                 6 x 32, 2800 - 300: 44.7 -> 35.6; 8 x 32, 900: 25.3 -> 25.4; 5 x 32 of 64, 253: 10.6 -> 8.9
 //   two ranges    3 x 32 / 4, 2657: 27.7 -> 22.0; 3 x 32, 3529: 38.8 -> 35.6
@@ -157,7 +177,7 @@ inline int32_t stream_ranges(const specvlm_attn_desc& d, const AttnPlan& plan) {
     // what the kernel assumes: whole halves of a tile inside the cache, 32-bit offsets into a request's query rows and a half tile
     if (cap % 16 || d.kv_stride_t >= (1 << 22) || (d.N_max * d.q_stride_n + group * d.q_stride_h) >= (1ll << 30)) return 0;
     const int s = plan.splits == 1 ? 1 : std::min<int64_t>({256 / units, plan.ranges, 4});
-    if (s < (plan.splits == 1 ? 1 : 2) || units * s < (s == 1 ? 140 : 180)) return 0;
+    if (s < (plan.splits == 1 ? 1 : 2) || units * s < (s == 1 ? 140 : 180) || rows_in_one_round_win(d, plan, units, s)) return 0;
     return (cap + kTile - 1) / kTile >= (s == 4 ? 17 : 14) * s ? s : 0;
 }
 

@@ -43,6 +43,20 @@ def test_measured_shapes(shape, streams):
     assert streams_of(*shape) == streams
 
 
+@pytest.mark.parametrize("shape,contiguous,paged", [
+    # row blocks in one round of workgroups, a multiple of 8: the same number of key ranges loses to them ...
+    ((8, 40, 10, 128, 22, 512), 0, 0), ((6, 64, 8, 64, 18, 832), 0, 0), ((4, 40, 20, 128, 46, 3872), 0, 0), ((6, 40, 8, 128, 28, 1792), 0, 0),
+    # ... half as many more mostly, twice as many do not
+    ((5, 28, 4, 128, 24, 2912), 0, 0), ((3, 16, 8, 128, 36, 2752), 0, 0), ((8, 20, 5, 128, 22, 3392), 3, 3), ((3, 16, 4, 64, 60, 4304), 4, 4),
+    # not a multiple of 8: short streams with few blocks a unit lose
+    ((5, 50, 10, 128, 30, 464), 0, 0), ((5, 50, 10, 128, 30, 1344), 1, 1), ((9, 20, 4, 128, 40, 512), 1, 1), ((10, 40, 5, 64, 19, 4448), 1, 0),
+    # more than one round
+    ((8, 50, 10, 128, 30, 512), 1, 1), ((6, 50, 10, 128, 42, 1040), 1, 1),
+])
+def test_row_blocks_in_one_round(shape, contiguous, paged):
+    assert plan_of(*shape).block_rows and (streams_of(*shape), streams_of(*shape, paged=True)) == (contiguous, paged)
+
+
 def test_far_strides_take_another_kernel():
     """32-bit offsets of half a tile."""
     assert streams_of(8, 32, 32, 128, 60, 976, token_stride=(1 << 22) - 8) == 1

@@ -31,7 +31,7 @@ def make(seed, B, Hq, Hkv, D, N, P, nn, paged):
     (6, 32, 32, 64, 64, [0, 1, 31, 64, 127, 400], [1, 64, 33, 64, 1, 64], 1),
     (5, 32, 32, 128, 40, [0, 95, 216, 300, 440], [40, 33, 40, 7, 40], 1),        # 40 of 64 rows; 2, 4, 8, 10 and 15 tiles
     (5, 40, 8, 128, 48, [3, 450, 129, 96, 33], [48, 48, 2, 32, 48], 1),          # 240 rows: blocks across head borders
-    (7, 48, 12, 64, 24, [470, 0, 33, 64, 96, 128, 256], None, 1),                # 96 rows: the second block half full
+    (8, 48, 12, 64, 24, [470, 0, 33, 64, 96, 128, 256, 17], None, 1),                # 96 rows: the second block half full
     (3, 32, 16, 128, 64, [2300, 5, 511], [64, 64, 17], 2),
     (5, 16, 16, 128, 60, [1400, 0, 40, 700, 96], [60, 1, 60, 59, 60], 3),
     (2, 32, 32, 128, 36, [2200, 700], None, 4),

@@ -65,6 +65,7 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
     __shared__ float s_m[kWaveWgs][kQRows];
     __shared__ float s_l[kWaveWgs][kQRows];
     __shared__ int s_par[kWaveWgs][64];
+    __shared__ int s_blocks[PAGED ? kWaveWgs : 1][64];
 
     // work item: (request, KV head, row block, split); every XCD gets a contiguous range of items
     uint32_t work = blockIdx.x;
@@ -165,22 +166,38 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
     const int S = P + n;
     const int ntile = (S + kKeys - 1) / kKeys;
     const int my_tiles = (!err && stream < ntile) ? static_cast<int>(divide(ntile - stream + nstream - 1, p.magic_nstream)) : 0;
-    int bad_block = 0;                                     // uniform
+    // Block ids: the first two tiles' through the scalar cache; from there on lane 2i + x holds that of half x of tile
+    // i (mod 32), fetched for 32 tiles at once.  (A scalar load per tile shares its counter with the LDS reads, which then all
+    // have to wait for it: 2 x 64 query / 8 KV heads, 4500 + 900 keys 33.4 us; 3 x 32 / 8, 3000 - 500 26.4.)
+    const int last_blk = (max(S, 1) - 1) >> 4;
+    const int64_t table_row = static_cast<int64_t>(b) * p.g.max_blocks;
+    bool bad_block = false;
     auto fetch_blocks = [&](int j, int (&phys)[2]) __attribute__((always_inline)) {
         if constexpr (PAGED) {
-            const int blk0 = (stream + j * nstream) * (kKeys >> 4), last_blk = (S - 1) >> 4;
-            const const_i32 row = (const_i32)p.g.block_table + static_cast<int64_t>(b) * p.g.max_blocks;
 #pragma unroll
-            for (int x = 0; x < 2; ++x) {
-                phys[x] = row[min(blk0 + x, last_blk)];
-                bad_block |= static_cast<uint32_t>(phys[x]) >= static_cast<uint32_t>(p.g.num_blocks) ? 1 : 0;
-            }
+            for (int x = 0; x < 2; ++x) phys[x] = ((const_i32)p.g.block_table)[table_row + min((stream + j * nstream) * 2 + x, last_blk)];
         }
     };
+    auto request_ids = [&](int j) __attribute__((always_inline)) {       // of tiles j .. j + 31 (past the last: the request's last block again)
+        const int blk = min((stream + (j + (lane >> 1)) * nstream) * 2 + (lane & 1), last_blk);
+        dma4(p.g.block_table + table_row + blk, (uint32_t)(uintptr_t)(lds_int*)s_blocks[PAGED ? wave : 0]);
+    };
+    int ids = 0;
+    auto read_ids = [&]() __attribute__((always_inline)) {
+        ids = s_blocks[PAGED ? wave : 0][lane];
+        bad_block = bad_block || static_cast<uint32_t>(ids) >= static_cast<uint32_t>(p.g.num_blocks);
+    };
+    auto blocks_of = [&](int j, int (&phys)[2]) __attribute__((always_inline)) {
+        if constexpr (PAGED) {
+#pragma unroll
+            for (int x = 0; x < 2; ++x) phys[x] = __builtin_amdgcn_readlane(ids, ((2 * j) & 63) + x);
+        }
+    };
+    if constexpr (PAGED) {
+        if (my_tiles > 0) request_ids(0);
+    }
     if (!early && my_tiles > 0) { fetch_blocks(0, phys); issue_k(0, phys); issue_v(0, phys); }
     if (my_tiles > 1) { fetch_blocks(1, phys); issue_k(1, phys); issue_v(1, phys); }
-    int phys_k[2] = {0, 0}, phys_v[2] = {0, 0};            // block ids of the next K and V tile to request
-    if (my_tiles > 2) { fetch_blocks(2, phys_k); phys_v[0] = phys_k[0]; phys_v[1] = phys_k[1]; }
 
     const float c2 = p.scale * kLog2e;
     const float tau = fminf(kTau / c2, 1e30f);
@@ -199,6 +216,9 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
     else wait_vmcnt<0>();
     __syncthreads();
     const int par = s_par[wave][lane];
+    if constexpr (PAGED) {
+        if (my_tiles > 0) read_ids();
+    }
     bf16x8 qf[2][NC];
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb)
@@ -295,7 +315,7 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
     if (my_tiles > 0) {
         read_k(0);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the K area of slot 0 is free
-        if (my_tiles > 2) { issue_k(2, phys_k); if (my_tiles > 3) fetch_blocks(3, phys_k); }
+        if (my_tiles > 2) { blocks_of(2, phys); issue_k(2, phys); }
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) scores(s[qb], qb);
         // V0 and K1 (the requests after them: V1, K2)
@@ -376,12 +396,15 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
         const int next_off = ((j + 1) & 1) * kSlotBytes;
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // ka and va are in registers: their areas are free
         if constexpr (LEFT >= 2) {
-            issue_v(j + 2, phys_v);
-            if constexpr (LEFT >= 3) {
-                phys_v[0] = phys_k[0]; phys_v[1] = phys_k[1];
-                issue_k(j + 3, phys_k);
-                if constexpr (PAGED) { if (j + 4 < my_tiles) fetch_blocks(j + 4, phys_k); }
+            blocks_of(j + 2, phys);
+            int phys3[2] = {0, 0};
+            if constexpr (LEFT >= 3 && PAGED) {                // (uniform branches, once in 32 tiles)
+                if (((j + 3) & 31) == 0) read_ids();           // landed: the step before has waited past its requests
+                blocks_of(j + 3, phys3);
+                if (((j + 4) & 31) == 0) request_ids(j + 4);
             }
+            issue_v(j + 2, phys);
+            if constexpr (LEFT >= 3) issue_k(j + 3, phys3);
         }
         // V of tile j + 1 and K of tile j + 2 have landed (the requests after them: V of j + 2, K of j + 3)
         if constexpr (LEFT >= 3) wait_vmcnt<2 * KLD>();
@@ -409,7 +432,7 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
         if (my_tiles > 0) step(std::integral_constant<int, 0>{}, j);
     }
 
-    if (bad_block && lane == 0 && p.err_flag) atomicOr(p.err_flag, SPECVLM_ERR_BAD_BLOCK);
+    if (__any(bad_block) && lane == 0 && p.err_flag) atomicOr(p.err_flag, SPECVLM_ERR_BAD_BLOCK);
     // ---- merge the four streams ---------------------------------------------------------------------
     // Owner w takes OWN blocks of 32 rows x 32 dims: both row blocks at dims 32w (head size 128), or rows 32 (w / 2), dims 32 (w % 2).
     auto own_qb = [](int w, int e) { return D == 128 ? e : w >> 1; };

@@ -62,3 +62,16 @@ def test_bad_requests_beside_good_ones(sv, oracle, B, H, P, ranges):
     good = [b for b in range(B) if b not in (1, 2)]
     assert_attn_close(got[good], ref[good], "bf16", "good requests")
     assert np.all(got[1:3] == 7.0)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,D,N,P,nn,ranges", [
+    (7, 15, 3, 128, 64, [2900, 5, 700, 33, 0, 1500, 64], [64, 1, 64, 17, 2, 64, 33], 2),      # 210 workgroups
+    (9, 17, 17, 64, 64, [410, 5, 77, 31, 33, 200, 0, 64, 95], None, 1),                       # 153
+    (3, 19, 19, 128, 60, [3100, 40, 700], None, 4),                                           # 228
+])
+@pytest.mark.parametrize("paged", [False, True])
+def test_workgroups_no_multiple_of_eight(sv, oracle, B, Hq, Hkv, D, N, P, nn, ranges, paged):
+    """The grid is rounded up to whole rows of XCDs: the last ones' workgroups have nothing to do."""
+    case, taken = make(8500 + D + N + B, B, Hq, Hkv, D, N, P, nn, paged)
+    assert taken == ranges and B * Hkv * -(-Hq // Hkv * N // 64) * taken % 8
+    check(case, *run_both(sv, oracle, case), f"streams {B}x{Hq}/{Hkv}x{D} N={N} ranges={ranges} paged={paged}")

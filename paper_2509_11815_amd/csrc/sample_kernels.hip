@@ -3,6 +3,7 @@
 #include <limits.h>
 
 #include "common.hpp"
+#include "compact_plan.hpp"
 
 namespace specvlm {
 
@@ -326,11 +327,8 @@ int32_t launch_tree_accept(int32_t B, int32_t N_max, int32_t path_cap, const int
 // rows: gather semantics even though source and destination ranges overlap.  Rows that
 // do not move (path[j] == j, always true for the root) are skipped.
 // A workgroup's few loads and stores are one chain of latencies, so with many of them it is their number that
-// counts: 32 layers x 8 requests x 32 heads with a workgroup per head (16384) 13.8 us, 2048 of them 4.0; one request 3.25 -> 2.4.
+// counts: 32 layers x 8 requests x 32 heads with a workgroup per head (16384) 13.8 us, 2048 of them 4.0 (compact_plan.hpp).
 // ---------------------------------------------------------------------------------------
-constexpr int kCompactThreads = 256;
-constexpr int kCompactChunksPerThread = 8;   // 64 rows * 32 chunks / 256 threads
-
 __global__ __launch_bounds__(kCompactThreads) void kv_compact_kernel(
     KvGeom g, unsigned char* k_base, unsigned char* v_base, int64_t layer_stride_bytes,
     void* const* k_ptrs, void* const* v_ptrs, int elem_bytes, int chunk_bits, int head_bits, int H_kv,
@@ -421,12 +419,8 @@ int32_t launch_kv_compact(const specvlm_attn_desc& d, int32_t L, void* k_base, v
     KvGeom g{d.kv_stride_b, d.kv_stride_h, d.kv_stride_t, d.paged ? block_table : nullptr,
              d.max_blocks_per_req, d.num_blocks,
              d.paged ? d.max_blocks_per_req * SPECVLM_PAGE_SIZE : d.kv_capacity};
-    // heads per workgroup: a power of two, as many as the path's rows leave registers for and 512 workgroups remain (64 in place
-    // of 512: 2.8 against 2.6 us)
     const int chunk_bits = __builtin_ctz(d.D * eb / 16);           // (8, 16 or 32 chunks of a row)
-    int head_bits = 0;
-    while (head_bits < 3 && (static_cast<int64_t>(L) * 2 * d.B * d.H_kv >> (head_bits + 1)) >= 512 &&
-           (path_cap << (chunk_bits + head_bits + 1)) <= kCompactThreads * kCompactChunksPerThread) ++head_bits;
+    const int head_bits = compact_head_bits(static_cast<int64_t>(L) * 2 * d.B * d.H_kv, path_cap << chunk_bits);
     dim3 grid(L * 2, (d.H_kv + (1 << head_bits) - 1) >> head_bits, d.B);
     // One launch when new_prefix_len is a buffer of its own; when it aliases prefix_len it may only
     // be written after every workgroup has read the old lengths: a second, tiny launch.

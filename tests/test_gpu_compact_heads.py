@@ -5,6 +5,7 @@ import pytest
 import torch
 
 import workloads as W
+from test_compact_plan import head_bits
 
 pytestmark = pytest.mark.gpu
 
@@ -12,13 +13,18 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("L,B,H,D,dtype,path_cap", [
     (32, 8, 5, 64, np.uint16, 8),          # 4 heads a workgroup, the last has one
     (32, 16, 9, 64, np.uint16, 8),         # 8 and one
-    (40, 8, 7, 128, np.float32, 16),       # 4 heads of 512-byte rows fill the registers
-    (40, 8, 7, 128, np.float32, 17),       # ... one row more: 2 heads
-    (33, 8, 2, 128, np.uint16, 64),        # 2 of 1024 chunks
+    (40, 8, 7, 128, np.float32, 16),       # 2 heads of 512-byte rows
+    (40, 8, 7, 128, np.float32, 17),       # ... one row more
+    (33, 8, 2, 128, np.uint16, 64),        # one of 1024 chunks
     (1, 1, 3, 64, np.uint16, 5),           # one head each
+    (40, 16, 7, 128, np.float32, 16),      # 4 heads of 512-byte rows fill the registers
+    (64, 8, 4, 128, np.uint16, 64),        # 2 of 1024 chunks
 ])
 @pytest.mark.parametrize("paged", [False, True])
 def test_head_groups(oracle, L, B, H, D, dtype, path_cap, paged):
+    chunks = path_cap * D * np.dtype(dtype).itemsize // 16
+    expected = {(32, 5, 8): 4, (32, 9, 8): 8, (40, 7, 16): 2 if B == 8 else 4, (40, 7, 17): 2, (33, 2, 64): 1, (1, 3, 5): 1, (64, 4, 64): 2}
+    assert 1 << head_bits(2 * L * B * H, chunks) == expected[L, H, path_cap]
     import paper_2509_11815_amd as sv
     sv.load_library()
     rng = np.random.default_rng(path_cap + H)

@@ -144,9 +144,10 @@ inline AttnPlan plan_of_heads_and_rows(const specvlm_attn_desc& d) {
 //   8 x 40 query / 10 KV heads, 22 nodes, 503 keys 10.3 | 12.3; 6 x 64 / 8 of 64, 18 nodes, 828: 9.4 | 11.6; 4 x 40 / 20, 46 nodes, 3869:
 //   40.7 | 43.5 (42 such shapes, all slower here, 6 - 27 %); two ranges | three: 5 x 28 / 4, 24 nodes, 2900: 21.1 | 23.0; but 8 x 20 / 5,
 //   22 nodes, 3390: 24.8 | 22.4 (three ranges on 216 workgroups or more, long streams); three | four: 3 x 16 / 8, 36 nodes, 2750: 16.0 | 16.7
-// Where they do not, every XCD fetches a head's K and V again, which short streams still bear (5 x 50 / 10, 30 nodes, 462 keys
-// 12.6 | 13.2; 1330 keys 20.9 | 20.4; 2600: 60.0 | 43.0), six or more blocks of a unit do not (9 x 20 / 4, 40 nodes, 512: 13.8 | 12.3), and
-// which paged requests of different lengths bear at head size 64 (10 x 40 / 5, 19 nodes, 4450: 32.2 | 36.6).
+// Where they do not, every XCD fetches a head's K and V again: long streams then lose to the streams' kernel (5 x 50 / 10, 30 nodes,
+// 2600 keys 60.0 | 34.6; 1330: 22 - 25 | 21.4), and so do six or more blocks of a unit (9 x 20 / 4, 40 nodes, 472: 13.8 | 13.0).
+// Short ones are near even (21 shapes of 15 - 30 tiles: here 0.78 - 1.05 of their time at equal lengths, 0.92 - 1.16 at very different
+// ones, paged the most) and stay, and paged requests of head size 64 with them.
 inline bool rows_in_one_round_win(const specvlm_attn_desc& d, const AttnPlan& plan, int64_t units, int s) {
     const int ntile = ((d.paged ? d.max_blocks_per_req * SPECVLM_PAGE_SIZE : d.kv_capacity) + kTile - 1) / kTile;
     if (!plan.block_rows) return false;

@@ -11,15 +11,15 @@ import subprocess
 import tempfile
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-Plan = collections.namedtuple("Plan", "ranges block_rows splits")
+# streams: key ranges of the kernel with a key stream per wavefront, 0 where one of the others takes the call
+Plan = collections.namedtuple("Plan", "ranges block_rows splits streams", defaults=[0])
 
 SOURCE = r"""
 #include "attn_plan.hpp"
 extern "C" void plan(const specvlm_attn_desc* d, int* out) {
     const specvlm::AttnPlan p = specvlm::attn_plan(*d);
-    out[0] = p.ranges; out[1] = p.block_rows; out[2] = p.splits;
+    out[0] = p.ranges; out[1] = p.block_rows; out[2] = p.splits; out[3] = p.streams;
 }
-extern "C" int streams(const specvlm_attn_desc* d) { return specvlm::attn_plan(*d).streams; }
 """
 
 
@@ -36,7 +36,7 @@ def _library():
 
 
 def plan_of_desc(desc) -> Plan:
-    out = (ctypes.c_int * 3)()
+    out = (ctypes.c_int * 4)()
     _library().plan(ctypes.byref(desc), out)
     return Plan(*out)
 
@@ -53,7 +53,7 @@ def desc_of(B, Hq, Hkv, D, N, cap, num_splits=0, paged=False, token_stride=None)
 
 def streams_of(*shape, **options) -> int:
     """Key ranges of the kernel with a key stream per wavefront, 0 where another is taken."""
-    return _library().streams(ctypes.byref(desc_of(*shape, **options)))
+    return plan_of(*shape, **options).streams
 
 
 def plan_of(*shape, **options) -> Plan:

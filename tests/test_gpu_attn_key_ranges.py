@@ -29,7 +29,8 @@ class FarQueries:
         out = torch.zeros(q.shape, dtype=q.dtype, device=q.device) if out is None else out
         num_splits = desc.num_splits if desc is not None else num_splits
         desc = self._sv.binding.make_attn_desc(far, k, out, block_table=block_table, num_splits=num_splits, softmax_scale=softmax_scale)
-        assert plan_of_desc(desc).block_rows == 0
+        plan = plan_of_desc(desc)
+        assert plan.block_rows == 0 and plan.streams == 0
         self.calls += 1
         return self._sv.specvlm_tree_verify_attn(far, k, v, *args, out=out, desc=desc, block_table=block_table, **kw)
 

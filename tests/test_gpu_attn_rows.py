@@ -33,7 +33,8 @@ def test_row_blocks(sv, oracle, B, Hq, Hkv, D, N, P, nn, splits, paged):
     from gpu_util import random_case
     case = random_case(7000 + D + N + splits, "bf16", B=B, Hq=Hq, Hkv=Hkv, D=D, N_max=N, P_list=P, num_nodes=nn, paged=paged,
                        cap_extra=0)
-    assert plan_of_case(case, splits).block_rows
+    plan = plan_of_case(case, splits)
+    assert plan.block_rows and not plan.streams
     check(case, *run_both(sv, oracle, case, num_splits=splits), f"rows {B}x{Hq}/{Hkv}x{D} N={N} splits={splits} paged={paged}")
 
 
@@ -44,6 +45,7 @@ def test_log_sum_exp_is_of_fp32_weights(sv, oracle, D, N, P, splits):
     exp2 / log2 add a few 2^-24 each; a sum of bf16 weights is off by up to 2^-9 over the root of the key count."""
     from gpu_util import random_case
     case = random_case(7100 + D + N, "bf16", B=2, Hq=4, Hkv=4, D=D, N_max=N, P_list=P, num_nodes=None, paged=False, cap_extra=0)
-    assert plan_of_case(case, splits).block_rows
+    plan = plan_of_case(case, splits)
+    assert plan.block_rows and not plan.streams
     _, lse, _, ref = run_both(sv, oracle, case, num_splits=splits)
     assert abs(lse - ref).max() <= 3e-5

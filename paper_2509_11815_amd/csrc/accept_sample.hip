@@ -143,7 +143,7 @@ __global__ __launch_bounds__(kThreadsAS) void tree_accept_sample_kernel(
                     if (v0 + j * VEC < v1) lv[j] = *reinterpret_cast<const uint4*>(row + v0 + j * VEC);
             } else {
                 // Most vocabularies: chunks start at any token.  16 bytes a load all the same (gfx950 takes them at any alignment
-                // of their type); only the vector that the row ends in is read entry by entry.  (Every entry of its own:
+                // of their type); only the vector that the row ends in is read entry by entry.  (Every entry of its own, bf16:
                 // 4 requests of 60000 tokens 39.4 us, now 22.7; 20003 15.5, now 13.3.)
 #pragma unroll
                 for (int j = 0; j < NV; ++j) {
@@ -160,9 +160,9 @@ __global__ __launch_bounds__(kThreadsAS) void tree_accept_sample_kernel(
                 }
 #pragma unroll
                 for (int j = 0; j < NV; ++j)
-                    if (v0 + (j + 1) * VEC > v1)       // entries of the next chunk
+                    if (v0 + j * VEC < v1 && v0 + (j + 1) * VEC > v1)       // the vector that the chunk ends in: entries of the next
 #pragma unroll
-                        for (int e = 0; e < VEC; ++e)
+                        for (int e = 1; e < VEC; ++e)
                             if (v0 + j * VEC + e >= v1) put(lv[j], e, sizeof(T) == 2 ? static_cast<T>(0xFF80u) : static_cast<T>(-INFINITY));
             }
         }

@@ -20,10 +20,10 @@ def sv():
     return sv
 
 
-# chunks of 1 token (most threads without any), 1 + a remainder, whole vectors (8192, 32768, 65536: aligned rows take the
+# chunks of 1 token (most threads without any), 2 and 3, whole vectors (8192, 32768, 65536: aligned rows take the
 # aligned form), whole vectors with the last thread's chunk cut short inside a vector, ragged chunks, the last one of 1 token
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("V", [3, 1024, 1025, 7169, 8184, 8192, 20003, 30724, 32768, 33000, 60001, 65529, 65536])
+@pytest.mark.parametrize("V", [3, 1024, 1025, 2500, 7169, 8184, 8192, 20003, 30724, 32768, 33000, 60001, 65529, 65536])
 def test_rows_aligned_and_not(sv, oracle, dtype, V):
     from gpu_util import i32, to_dev
     rng = np.random.default_rng(3 * V + len(dtype))

@@ -110,13 +110,15 @@ __device__ __forceinline__ void store_rows(const MfmaParams& p, const f32x4 (&ou
 //                         split) items are resident at once
 template <int D, int WQ, int PD>
 __global__ __launch_bounds__(kThreads) void attn_mfma_kernel(MfmaParams p) {
-    constexpr int SL = WQ, MB = 8;
+    // Two owners per query block shorten the chain at head size 128.  At 64 a half is one 16-byte vector, and twice the tickets and
+    // (max, sum) pairs cost more: 7 x 40 query / 10 KV heads, 560 keys, four ranges 29.3 us with one owner, 30.6 with two.
+    constexpr int SL = WQ, MB = 8, OWNERS = D == 128 ? 2 : 1;
 #include "attn_mfma_body.inc"
 }
 
 template <int D>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void attn_mfma_kernel_2wg(MfmaParams p) {
-    constexpr int WQ = kShare, PD = 1, SL = 2, MB = 3;
+    constexpr int WQ = kShare, PD = 1, SL = 2, MB = 3, OWNERS = 2;
 #define SPECVLM_SPREAD_REQUESTS
 #include "attn_mfma_body.inc"
 #undef SPECVLM_SPREAD_REQUESTS

@@ -1,5 +1,5 @@
 """Split calls with more than half as many (request, head) pairs as there are ticket counter lines: the two counters of a query
-block share a line.  The counters are zero again after every call."""
+block (head size 128; 64 has one) share a line.  The counters are zero again after every call."""
 import pytest
 
 from attn_plan_util import Plan, plan_of_case
@@ -7,7 +7,7 @@ from attn_plan_util import Plan, plan_of_case
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("D,B,H", [(64, 9, 57), (128, 16, 40), (64, 16, 32)])       # 513, 640 and (lines of their own) 512 pairs
+@pytest.mark.parametrize("D,B,H", [(64, 9, 57), (128, 9, 57), (128, 16, 40), (64, 16, 32)])       # 513, 640 and (lines of their own) 512 pairs
 def test_second_counters(oracle, D, B, H):
     import paper_2509_11815_amd as sv
     import torch

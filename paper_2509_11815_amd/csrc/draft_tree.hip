@@ -706,14 +706,19 @@ __global__ __launch_bounds__(kThreadsDT) void draft_finalize_kernel(
     }
     const int M = N_max - 1;
     const int64_t base = b * cand_stride_b;
-    // what the chosen ones will need, for the first candidate of a thread on its way while they are ranked
+    // what the chosen ones will need, for the first candidate of a thread on its way while they are ranked; after the scores,
+    // which are waited for first
+    float score0 = 0.f;
     int parent0 = -1, token0 = -1, root = -1;
     if (tid < c) {
+        score0 = cand_score[base + tid];
+        asm volatile("" ::: "memory");
         parent0 = cand_parent[base + tid];
         token0 = cand_token[base + tid];
+        s_key[tid] = order_key(score0, tid);
     }
     if (tid == 0) root = root_token[b];
-    for (int i = tid; i < c; i += kThreadsDT) s_key[i] = order_key(cand_score[base + i], i);
+    for (int i = tid + kThreadsDT; i < c; i += kThreadsDT) s_key[i] = order_key(cand_score[base + i], i);
     __syncthreads();
     rank_winners(s_key, c, M);
     const int count = min(M, c);

@@ -22,7 +22,6 @@ struct WaveParams {
     int32_t* ws_cnt;            // [units][4 owners] arrival tickets, kCounterStride words apart, zero between calls
     unsigned char* ws_acc;      // [units * splits][owners][..][64 lanes] 16-byte vectors of packed bf16
     float* ws_ml;               // [units * splits][block rows][2] (max, sum)
-    uint32_t workgroups;        // (unit, range) items
 };
 
 // n / d for n * d < 2^31, with m = ceil(2^31 / d) from the host.
@@ -52,7 +51,7 @@ inline WaveParams wave_params(const AttnArgs& a, int block_rows, int splits, uns
     p.o_sb = d.o_stride_b; p.o_sn = d.o_stride_n; p.o_sh = d.o_stride_h;
     p.prefix_len = a.prefix_len; p.num_nodes = a.num_nodes; p.parent = a.parent;
     p.err_flag = a.err_flag;
-    workgroups = p.workgroups = static_cast<unsigned>(d.B) * d.H_kv * p.row_blocks * p.num_splits;
+    workgroups = static_cast<unsigned>(d.B) * d.H_kv * p.row_blocks * p.num_splits;
     unsigned char* ws = static_cast<unsigned char*>(a.workspace);
     p.ws_cnt = reinterpret_cast<int32_t*>(ws);
     p.ws_ml = reinterpret_cast<float*>(ws + kCounterBytes);

@@ -68,10 +68,10 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
     __shared__ int s_blocks[PAGED ? kWaveWgs : 1][64];
 
     // work item: (request, KV head, row block, split); every XCD gets a contiguous range of items, so that the blocks of a head
-    // share an L2.  The grid is rounded up to a multiple of 8 for it: items dealt out to the XCDs in turn took 39.2 us for the 210 of
-    // 3 x 35 query / 7 KV heads, 4060 keys, now 30.9; the 250 of 5 x 25 / 5, 5312 keys 54.8, now 39.7.
-    const uint32_t work = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
-    if (work >= p.workgroups) return;
+    // share an L2, the first ones an item more where their number is no multiple of 8 (dealt out to the XCDs in turn: 39.2 us for the
+    // 210 of 3 x 35 query / 7 KV heads, 4060 keys, now 29.6; the 250 of 5 x 25 / 5, 5312 keys 53.3, now 37.0).
+    const uint32_t xcd = blockIdx.x & 7;
+    const uint32_t work = xcd * (gridDim.x >> 3) + min(xcd, gridDim.x & 7) + (blockIdx.x >> 3);
     const uint32_t unit = divide(work, p.magic_splits);
     const int split = work - unit * p.num_splits;
     const uint32_t bk = divide(unit, p.magic_rb);
@@ -616,9 +616,8 @@ void launch_d(const WaveParams& p, dim3 grid, hipStream_t stream) {
 int32_t launch_attn_streams(const AttnArgs& a) {
     unsigned workgroups;
     const WaveParams p = wave_params(a, kQRows, a.plan.streams, workgroups);
-    const dim3 grid((workgroups + 7) / 8 * 8);
-    if (a.d.D == 128) launch_d<128>(p, grid, a.stream);
-    else launch_d<64>(p, grid, a.stream);
+    if (a.d.D == 128) launch_d<128>(p, dim3(workgroups), a.stream);
+    else launch_d<64>(p, dim3(workgroups), a.stream);
     return check_launch();
 }
 

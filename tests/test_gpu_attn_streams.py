@@ -71,7 +71,7 @@ def test_bad_requests_beside_good_ones(sv, oracle, B, H, P, ranges):
 ])
 @pytest.mark.parametrize("paged", [False, True])
 def test_workgroups_no_multiple_of_eight(sv, oracle, B, Hq, Hkv, D, N, P, nn, ranges, paged):
-    """The grid is rounded up to whole rows of XCDs: the last ones' workgroups have nothing to do."""
+    """The first XCDs take an item more."""
     case, taken = make(8500 + D + N + B, B, Hq, Hkv, D, N, P, nn, paged)
     assert taken == ranges and B * Hkv * -(-Hq // Hkv * N // 64) * taken % 8
     check(case, *run_both(sv, oracle, case), f"streams {B}x{Hq}/{Hkv}x{D} N={N} ranges={ranges} paged={paged}")

@@ -165,6 +165,10 @@ inline bool rows_in_one_round_win(const specvlm_attn_desc& d, const AttnPlan& pl
 // less than 55 % full (28 of 64 rows: 17.0 against 15.5).  A call whose results were not rounded to partial ones before stays
 // without them, and one that took key ranges takes at least two: requests of different lengths need them (5 x 32 heads,
 // 3568 - 400 keys, three ranges 38.9, one 43.2; equal lengths of 3100: 49.3 and 46.3).
+// Nor short unsplit calls of 224 workgroups or more that share no K and V, whose stream from HBM counts more than a tile's step.
+// attn_mfma | here: 7 x 32 heads, 424 keys 14.3 | 15.5; 8 x 32, 560: 17.7 | 18.6; 8 x 28, 670: 18.3 | 18.9 (25 of 30 such calls of equal
+// lengths are slower here, up to 10 %; at very different ones 10 x 25, 700 - 90: 17.1 | 16.8, in the mean 3 % faster here).  From 24 tiles on
+// (paged 18) equal lengths are even to 3 % slower, different ones 2 - 15 % faster.
 // us per call before -> here (head size 128 unless said):
 //   unsplit       8 x 32 query / 16 KV heads, 4788 keys 82.4 -> 65.7; 7 x 32 / 8, 852: 21.1 -> 17.2; 4 x 40, 671: 18.5 -> 16.4;
 //                 6 x 32, 2800 - 300: 44.7 -> 35.6; 8 x 32, 900: 25.3 -> 25.4; 5 x 32 of 64, 253: 10.6 -> 8.9
@@ -179,7 +183,9 @@ inline int32_t stream_ranges(const specvlm_attn_desc& d, const AttnPlan& plan) {
     if (cap % 16 || d.kv_stride_t >= (1 << 22) || (d.N_max * d.q_stride_n + group * d.q_stride_h) >= (1ll << 30)) return 0;
     const int s = plan.splits == 1 ? 1 : std::min<int64_t>({256 / units, plan.ranges, 4});
     if (s < (plan.splits == 1 ? 1 : 2) || units * s < (s == 1 ? 140 : 180) || rows_in_one_round_win(d, plan, units, s)) return 0;
-    return (cap + kTile - 1) / kTile >= (s == 4 ? 17 : 14) * s ? s : 0;
+    const int ntile = (cap + kTile - 1) / kTile;
+    if (s == 1 && group == 1 && !plan.block_rows && d.D == 128 && units >= 224 && ntile < (d.paged ? 18 : 24)) return 0;
+    return ntile >= (s == 4 ? 17 : 14) * s ? s : 0;
 }
 
 inline AttnPlan attn_plan(const specvlm_attn_desc& d) {

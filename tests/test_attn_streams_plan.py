@@ -57,6 +57,15 @@ def test_row_blocks_in_one_round(shape, contiguous, paged):
     assert plan_of(*shape).block_rows and (streams_of(*shape), streams_of(*shape, paged=True)) == (contiguous, paged)
 
 
+@pytest.mark.parametrize("shape,contiguous,paged", [
+    # 224 unsplit workgroups or more without shared K and V: from 24 tiles on, paged 18; fewer workgroups, shared ones, head size 64 from 14 on
+    ((7, 32, 32, 128, 64, 448), 0, 0), ((7, 32, 32, 128, 64, 560), 0, 1), ((8, 32, 32, 128, 60, 736), 0, 1), ((8, 32, 32, 128, 60, 752), 1, 1),
+    ((223, 1, 1, 128, 60, 448), 1, 1), ((7, 32, 16, 128, 64, 448), 1, 1), ((7, 32, 32, 64, 64, 448), 1, 1),
+])
+def test_short_streams_that_share_nothing(shape, contiguous, paged):
+    assert (streams_of(*shape), streams_of(*shape, paged=True)) == (contiguous, paged)
+
+
 def test_far_strides_take_another_kernel():
     """32-bit offsets of half a tile."""
     assert streams_of(8, 32, 32, 128, 60, 976, token_stride=(1 << 22) - 8) == 1

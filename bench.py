@@ -25,7 +25,7 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBPS = 8000.0          # MI355X published HBM3E peak
 # the kernel that the library chooses for a workload's attention call (--splits 0)
-ATTENTION_KERNELS = {"C2": "attn_wave_kernel<128, 2, false>", "C3": "attn_mfma_kernel<128, 4, 2>",
+ATTENTION_KERNELS = {"C2": "attn_wave_kernel<128, 2, false>", "C3": "attn_mfma_kernel<128, 2>",
                      "C4": "attn_streams_kernel<128, false>", "C5": "attn_mfma_kernel_2wg<128>"}
 
 

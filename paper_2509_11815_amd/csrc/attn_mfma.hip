@@ -38,7 +38,7 @@
 //             end test the per-query ancestor bit mask (select, never multiply)
 //   merge     the streams of a workgroup are merged through LDS (one round, the rings are
 //             free by then; every wavefront ends up owning 16 query rows x half the head
-//             dims); the workgroup's partial goes, as bf16, to a lane-major
+//             dims, at head size 64 and one workgroup per compute unit four of them 16 rows); the workgroup's partial goes, as bf16, to a lane-major
 //             workspace with write-through stores, and for every (query block, half) the last
 //             split to arrive -- found with a ticket counter -- merges the splits, adding a
 //             split up while the next ones still load.  (With one owner for all head dims of a block four of the
@@ -98,27 +98,26 @@ __device__ __forceinline__ void store_rows(const MfmaParams& p, const f32x4 (&ou
         p.lse[(static_cast<int64_t>(b) * p.H_q + h) * p.N_max + qi] = M * p.scale + __log2f(L) * kLn2;
 }
 
-// WQ wavefronts share a stream (2: 32 query rows each, 4 streams, 2 ring slots; 4: 16 query rows
-// each, 2 streams, 4 ring slots); PD tiles per stream are kept in flight ahead of the one consumed.
-// Measured on the 2880-visual-token workload: (WQ, PD) = (4, 2) 19.5 us per layer, (4, 3) 20.0,
-// (4, 1) 20.8, (2, 1) 21.8; only (kShare, kAhead) is instantiated.
+// PD tiles per stream are kept in flight ahead of the one consumed.  Measured on the 2880-visual-token workload, with a merge that
+// had one owner per query block: PD = 2 19.5 us per layer, 3 20.0, 1 20.8; two wavefronts of 32 query rows per stream, four streams,
+// PD = 1 21.8 (a form that is gone).
 // Two launch shapes of the same body (attn_mfma_body.inc).
 //   attn_mfma_kernel      128 KB of rings (four slots per stream, two tiles in flight ahead), one
 //                         workgroup per compute unit: few (request, head) pairs, long streams
 //   attn_mfma_kernel_2wg  64 KB of rings (two slots, one tile ahead) and at most 128 registers, so
 //                         that two workgroups share a compute unit: twice as many (request, head,
 //                         split) items are resident at once
-template <int D, int WQ, int PD>
+template <int D, int PD>
 __global__ __launch_bounds__(kThreads) void attn_mfma_kernel(MfmaParams p) {
     // Two owners per query block shorten the chain at head size 128.  At 64 a half is one 16-byte vector, and twice the tickets and
     // (max, sum) pairs cost more: 7 x 40 query / 10 KV heads, 560 keys, four ranges 29.3 us with one owner, 30.6 with two.
-    constexpr int SL = WQ, MB = 8, OWNERS = D == 128 ? 2 : 1;
+    constexpr int SL = 4, MB = 8, OWNERS = D == 128 ? 2 : 1;
 #include "attn_mfma_body.inc"
 }
 
 template <int D>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4))) void attn_mfma_kernel_2wg(MfmaParams p) {
-    constexpr int WQ = kShare, PD = 1, SL = 2, MB = 3, OWNERS = 2;
+    constexpr int PD = 1, SL = 2, MB = 3, OWNERS = 2;
 #define SPECVLM_SPREAD_REQUESTS
 #include "attn_mfma_body.inc"
 #undef SPECVLM_SPREAD_REQUESTS
@@ -200,8 +199,8 @@ int32_t launch_attn_mfma(const AttnArgs& a) {
         if (d.D == 128) hipLaunchKernelGGL((attn_mfma_kernel_2wg<128>), grid, block, 0, a.stream, p);
         else hipLaunchKernelGGL((attn_mfma_kernel_2wg<64>), grid, block, 0, a.stream, p);
     } else {
-        if (d.D == 128) hipLaunchKernelGGL((attn_mfma_kernel<128, kShare, kAhead>), grid, block, 0, a.stream, p);
-        else hipLaunchKernelGGL((attn_mfma_kernel<64, kShare, kAhead>), grid, block, 0, a.stream, p);
+        if (d.D == 128) hipLaunchKernelGGL((attn_mfma_kernel<128, kAhead>), grid, block, 0, a.stream, p);
+        else hipLaunchKernelGGL((attn_mfma_kernel<64, kAhead>), grid, block, 0, a.stream, p);
     }
     return check_launch();
 }

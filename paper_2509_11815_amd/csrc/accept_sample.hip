@@ -21,7 +21,7 @@
 //   bonus     a two-level scan: every thread sums a contiguous chunk of the vocabulary, the chunk sums are
 //             scanned, and the chunk that contains the drawn position is walked (CH = 0: its probabilities are
 //             computed by the whole workgroup first)
-// Kernel alone, 4 requests: 32000 tokens 10.9 us, 20003 13.3, 60000 22.7, 65536 17.7, 152064 34.4 (beyond 65536, passes that
+// Kernel alone, 4 requests, bf16: 32000 tokens 10.9 us, 20003 13.3, 60000 22.7, 65536 17.7, 152064 34.4 (beyond 65536, passes that
 // read token by token took 198 us).
 #include "chunk_vectors.hpp"
 #include "wave_ops.hpp"
@@ -81,6 +81,8 @@ __device__ __forceinline__ float vec_at(const uint4& w, int e) {
 
 // CH > 0: every thread keeps its chunk of the current row (at most CH consecutive tokens) in
 // registers, loaded once per level with 16-byte loads; WHOLE: the chunks of every row are whole aligned vectors.
+// (CH = 64 without WHOLE does not quite fit its 128 registers: 164 bytes of scratch a lane in fp32, 8 in bf16.  Reading such fp32 rows
+// again, as CH = 0 does, is faster by up to a third - 4 requests of 50001 tokens 24.6 us here, 17.2 there - but adds in another order.)
 // (Two kernels: with both ways of loading in one, 4 requests of 32000 tokens took 12.5 us in place of 10.9, 65536 22.8 of 17.7.)
 // CH == 0: any vocabulary size, every pass reads the row again (from L2).
 template <typename T, int CH, bool WHOLE>

@@ -57,11 +57,15 @@ inline int32_t single_round_ranges(const specvlm_attn_desc& d) {
 // of a head meet at the end.  Query rows as well (attn_wave.hip): workgroups of 16 or 32 rows, whose
 // K and V come from L2 for all but the first of a head's row blocks, with a quarter or half of the
 // arithmetic each, so that fewer or no partial results have to meet, and those are a quarter or half the size.
-// The model below is fitted to measured calls (us; 1 x 32 heads x 128, 60 nodes, all on 256 workgroups):
-//   260 keys   key ranges 10.7 (1 split)   32 rows  8.4 (4)   16 rows  7.3 (1)
-//   828        key ranges 11.4 (8)         32 rows  9.9 (4)   16 rows  9.9 (2)
-//   3324       key ranges 16.5 (8)         32 rows 16.8 (4)   16 rows 23.6 (2)
-// so rows win until the repeated K and V traffic (at most ~14 TB/s from L2) costs more than the merge.
+// The model below was fitted to measured calls; as the kernels are now (us; 1 x 32 heads x 128, 60 nodes, all on 256 workgroups):
+//   260 keys   key ranges 11.1 (1 split)   32 rows  8.4 (4)   16 rows  7.8 (1)
+//   828        key ranges 11.5 (8)         32 rows  9.8 (4)   16 rows  9.9 (2)
+//   1600       key ranges 13.2 (8)         32 rows 11.6 (4)   16 rows 13.2 (2)
+//   2940       key ranges 15.4 (8)         32 rows 15.1 (4)   16 rows 19.4 (2)
+//   3324       key ranges 16.4 (8)         32 rows 16.3 (4)   16 rows 21.2 (2)
+//   3600       key ranges 17.6 (8)         32 rows 17.6 (4)
+// so rows win until the repeated K and V traffic (at most ~14 TB/s from L2) costs more than the merge.  The choice is the best of
+// these to 1 % at every length (the model crosses near 3300 keys, the calls near 3600).
 struct AttnPlan {
     int32_t ranges;        // key ranges per head that the workspace holds
     int32_t block_rows;    // query rows per workgroup, 0: all (key ranges only)
@@ -123,6 +127,13 @@ inline AttnPlan plan_rows(const specvlm_attn_desc& d, int32_t nominal) {
 //   28 / 4 x 4                      3000      30.8 -> 28.8 | 26.8            3000 - 500  31.0 -> 27.9 | 26.3
 //   32 / 8 x 3                      3000      30.7 -> 28.4 | 27.8            3000 - 500  30.7 -> 23.2 | 26.9
 //   48 / 8 x 2                      4500      40.9 -> 35.8 | 37.0            4500 + 700  41.1 -> 28.9 | 36.4
+// (figures of these kernels before attn_streams.hip, which now takes all of these shapes with two ranges; stream_ranges below.  This rule
+// then says how large the workspace is, and still chooses the kernel where that one is not taken: blocks of rows less than 55 % full, fewer
+// than 180 workgroups, capacities that are no multiple of 16.)  Four ranges in two workgroups per compute unit | attn_streams.hip:
+//   32 / 8 x 4, 3000: 28.9 | 24.5; 2500 - 300: 21.8 | 21.6; 64 / 8 x 2, 4500: 36.6 | 29.9; 4500 + 900: 28.9 | 29.7, paged 30.3 | 31.9;
+//   40 / 8 x 3, 3000: 28.8 | 23.8; 4500 - 1000: 29.3 | 29.7; 28 / 4 x 4, 3000 - 500: 27.7 | 22.6; 48 / 8 x 2, 4500 + 700: 28.5 | 28.8, paged 30.0 | 31.2
+// (one request much longer than the other: two ranges of it are all that 256 workgroups of 64 rows leave; up to 5 % slower, equal
+// lengths 15 - 22 % faster, and the host does not know the lengths.)
 // Row blocks are chosen first, by their comparison with two ranges: where that favours them they also beat four
 // at equal lengths (32 / 8 x 4, 2000 keys 25.1 | 22.9; 64 / 8 x 2, 3000 keys 29.3 | 26.8), and where it does not they lose
 // little there and much at different ones.

@@ -28,7 +28,9 @@ namespace {
 constexpr int kThreadsDT = 1024;
 constexpr int kWavesDT = kThreadsDT / 64;
 constexpr int kCandCap = 1024;           // Top-K: entries at or above a threshold kept in LDS
-constexpr int kRankDirect = 320;         // ... and ranked as they are (square of their number: 2.7 us; 27 us for 1000)
+constexpr int kRankDirect = 320;         // ... and ranked as they are.  Ten rows of that many equal best entries, one call: 320
+                                         // 10.6 us, 512 15.6, 1000 37.8; with the second threshold 14.8 - 16.4 at any number, so the
+                                         // two meet near 500 (the line was drawn for a ranking that one lane did per entry)
 
 // Eight consecutive entries of a row, as loaded.
 template <typename T>
@@ -314,7 +316,8 @@ __device__ __forceinline__ void rank_winners(unsigned long long* s_key, int c, i
 // entry by entry in every pass, 66 and 96 us -> 12.9 and 14.4.  Ten rows of equal logits, one call: 32000 42.7 -> 18.7,
 // 152064 97.9 -> 57.7; sorted along the vocabulary 44.5 -> 16.1 and 97.7 -> 41.0.
 // Entries ranked by rows of 16 lanes (a lane's share instead of a lane for all others) and the log-sum-exp left to one wavefront
-// beside the collection: 5.75 -> 5.3 us a call, 8.4 -> 8.05 with the selection; a growth of six levels with its finalize 53.4 -> 49.2.
+// beside the collection: 5.75 -> 5.3 us a call; a growth of six levels with its finalize 53.4 -> 49.2, nearly all of it at the root, the last
+// level and the finalize (the levels between, ten rows with the selection, take 9.2 - 9.3 us each in a trace of the growth, as before).
 // ---------------------------------------------------------------------------------------
 // SEL: the workgroup that finishes a request's last row also chooses the M most valuable of the
 // request's W*K new candidates (what draft_select_kernel does in a launch of its own): scores

@@ -168,9 +168,9 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
     const int S = P + n;
     const int ntile = (S + kKeys - 1) / kKeys;
     const int my_tiles = (!err && stream < ntile) ? static_cast<int>(divide(ntile - stream + nstream - 1, p.magic_nstream)) : 0;
-    // Block ids: the first two tiles' through the scalar cache; from there on lane 2i + x holds that of half x of tile
-    // i (mod 32), fetched for 32 tiles at once.  (A scalar load per tile shares its counter with the LDS reads, which then all
-    // have to wait for it: 2 x 64 query / 8 KV heads, 4500 + 900 keys 33.4 us; 3 x 32 / 8, 3000 - 500 26.4.)
+    // Block ids: the first three tiles' through the scalar cache (the third's again for V); from there on lane 2i + x holds that of
+    // half x of tile i (mod 32), fetched for 32 tiles at once.  (A scalar load per tile shares its counter with the LDS reads, which
+    // then all have to wait for it: 2 x 64 query / 8 KV heads, 4500 + 900 keys 33.4 us; 3 x 32 / 8, 3000 - 500 26.4.)
     const int last_blk = (max(S, 1) - 1) >> 4;
     const int64_t table_row = static_cast<int64_t>(b) * p.g.max_blocks;
     bool bad_block = false;
@@ -200,6 +200,8 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
     }
     if (!early && my_tiles > 0) { fetch_blocks(0, phys); issue_k(0, phys); issue_v(0, phys); }
     if (my_tiles > 1) { fetch_blocks(1, phys); issue_k(1, phys); issue_v(1, phys); }
+    int phys2[2] = {0, 0};
+    if (my_tiles > 2) fetch_blocks(2, phys2);
 
     const float c2 = p.scale * kLog2e;
     const float tau = fminf(kTau / c2, 1e30f);
@@ -317,7 +319,7 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
     if (my_tiles > 0) {
         read_k(0);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the K area of slot 0 is free
-        if (my_tiles > 2) { blocks_of(2, phys); issue_k(2, phys); }
+        if (my_tiles > 2) issue_k(2, phys2);
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) scores(s[qb], qb);
         // V0 and K1 (the requests after them: V1, K2)

@@ -180,6 +180,8 @@ inline bool rows_in_one_round_win(const specvlm_attn_desc& d, const AttnPlan& pl
 // attn_mfma | here: 7 x 32 heads, 424 keys 14.3 | 15.5; 8 x 32, 560: 17.7 | 18.6; 8 x 28, 670: 18.3 | 18.9 (25 of 30 such calls of equal
 // lengths are slower here, up to 10 %; at very different ones 10 x 25, 700 - 90: 17.1 | 16.8, in the mean 3 % faster here).  From 24 tiles on
 // (paged 18) equal lengths are even to 3 % slower, different ones 2 - 15 % faster.
+// Nor a single request, which mostly loses (1 x 32 / 8, 4000 keys, four ranges 16.2 by key ranges | 18.1; 1 x 40, 2000: 14.6 by row blocks | 15.6;
+// 1 x 28 / 4, 5200: 18.3 | 21.8), except with 64 query heads on few KV heads and 2000 keys or more (1 x 64 / 8, 4000: 23.0 | 18.5): not taken yet.
 // us per call before -> here (head size 128 unless said):
 //   unsplit       8 x 32 query / 16 KV heads, 4788 keys 82.4 -> 65.7; 7 x 32 / 8, 852: 21.1 -> 17.2; 4 x 40, 671: 18.5 -> 16.4;
 //                 6 x 32, 2800 - 300: 44.7 -> 35.6; 8 x 32, 900: 25.3 -> 25.4; 5 x 32 of 64, 253: 10.6 -> 8.9

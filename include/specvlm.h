@@ -102,8 +102,9 @@ int32_t specvlm_version(void);
 int32_t specvlm_last_hip_error(void);
 
 /*
- * Scratch bytes specvlm_tree_verify_attn needs for `desc` (arrival counters and split-key
- * partial results; 0 when the shape needs none).  Returns 0 when desc is invalid.  The
+ * Scratch bytes specvlm_tree_verify_attn wants for `desc` (arrival counters and split-key
+ * partial results; 0 when the shape needs none).  Returns 0 when desc is invalid.  A call whose
+ * specvlm_tree_verify_attn_num_splits is 1 also runs with less, or without, if more slowly.  The
  * workspace is device memory, 256-byte aligned.  It must be ZERO-FILLED ONCE after
  * allocation; every call leaves its counter words zero again, and the counters occupy the
  * same fixed region at the start whatever the shape, so the same workspace can be reused by

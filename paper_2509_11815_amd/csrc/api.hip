@@ -57,7 +57,7 @@ int32_t specvlm_last_hip_error(void) { return g_last_hip_error; }
 size_t specvlm_tree_verify_attn_workspace_bytes(const specvlm_attn_desc* desc) {
     if (!desc || check_attn_desc(*desc)) return 0;
     if (desc->dtype == SPECVLM_F32) return 256;
-    return attn_mfma_workspace_bytes(*desc, attn_plan(*desc).ranges);
+    return attn_workspace_bytes(*desc, attn_plan(*desc));
 }
 
 int32_t specvlm_tree_verify_attn_num_splits(const specvlm_attn_desc* desc) {
@@ -94,16 +94,21 @@ static int32_t tree_verify_attn(const specvlm_attn_desc* desc, const void* q_dev
     if (mode == kVectorAluKernel) return launch_attn_valu(a);
     if (desc->dtype == SPECVLM_F32) return launch_attn_f32(a);
     a.plan = attn_plan(*desc);
-    const size_t need = attn_mfma_workspace_bytes(*desc, a.plan.ranges);
+    size_t need = attn_workspace_bytes(*desc, a.plan);
+    const bool usable = static_workspace || (a.workspace && (reinterpret_cast<uintptr_t>(a.workspace) & 255u) == 0);
+    const size_t have = static_workspace ? SPECVLM_STATIC_WORKSPACE_BYTES : workspace_bytes;
+    if (a.plan.by_length && (!usable || have < need)) {
+        a.plan = evenly(*desc, a.plan);
+        need = attn_workspace_bytes(*desc, a.plan);
+    }
     if (need) {
+        if (!usable) return SPECVLM_INVALID_ARG;
+        if (have < need) return SPECVLM_WORKSPACE_TOO_SMALL;
         if (static_workspace) {
-            if (need > SPECVLM_STATIC_WORKSPACE_BYTES) return SPECVLM_WORKSPACE_TOO_SMALL;
             rc = attn_static_workspace(&a.workspace);
             if (rc) return rc;
-            a.workspace_bytes = SPECVLM_STATIC_WORKSPACE_BYTES;
+            a.workspace_bytes = have;
         }
-        if (!a.workspace || (reinterpret_cast<uintptr_t>(a.workspace) & 255u)) return SPECVLM_INVALID_ARG;
-        if (a.workspace_bytes < need) return SPECVLM_WORKSPACE_TOO_SMALL;
     }
     return launch_attn_mfma(a);
 }

@@ -28,7 +28,7 @@ constexpr float kTau = 8.0f;        // log2 of how far a probability may exceed 
 constexpr int kCounterStride = 32;    // int32 words from one ticket counter to the next: every counter has a 128-byte line of
                                       // its own, but two of a query block share one above 512 pairs (attn_mfma.hip) (with the counters of eight heads in one line, 256 atomics queued up on it:
                                       // 17.1 -> 16.6 us per call at the 2880-visual-token prefix, 12.4 -> 11.3 us at 576)
-constexpr size_t kCounterBytes = static_cast<size_t>(kMaxSplitHeads) * 4 * kCounterStride * sizeof(int32_t);
+static_assert(kCounterBytes == static_cast<size_t>(kMaxSplitHeads) * 4 * kCounterStride * sizeof(int32_t), "counter region");
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     f32x2 f = {lo, hi};

@@ -123,17 +123,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4, 4))
 #undef SPECVLM_SPREAD_REQUESTS
 }
 
-// The ticket counters occupy a region of fixed size at the start of the workspace, whatever the
-// shape: a later call of another shape then finds its counters where every earlier call left
-// zeros, never where one stored partial results.
-static size_t counter_bytes(const specvlm_attn_desc&) { return kCounterBytes; }
-
-size_t attn_mfma_workspace_bytes(const specvlm_attn_desc& d, int32_t ranges) {
-    if (ranges == 1) return 0;
-    const size_t parts = static_cast<size_t>(d.B) * d.H_q * ranges;
-    return counter_bytes(d) + parts * (static_cast<size_t>(kQRows) * d.D * 2 + kQRows * 8);
-}
-
 // ---- library-owned scratch for callers that cannot allocate device memory -----------------------
 // One array per GPU (each device holds its own copy of the code object's globals, zero when the
 // object is loaded).  Host code must not use the array's name as an address: the device address
@@ -164,7 +153,7 @@ int32_t attn_static_workspace(void** ptr_out) {
 
 int32_t launch_attn_mfma(const AttnArgs& a) {
     const specvlm_attn_desc& d = a.d;
-    if (a.plan.streams) return launch_attn_streams(a);
+    if (a.plan.columns) return launch_attn_streams(a);
     if (a.plan.block_rows) return launch_attn_wave(a);
     MfmaParams p;
     p.g = KvGeom{d.kv_stride_b, d.kv_stride_h, d.kv_stride_t, d.paged ? a.block_table : nullptr,
@@ -188,7 +177,7 @@ int32_t launch_attn_mfma(const AttnArgs& a) {
     p.ws_cnt = reinterpret_cast<int32_t*>(ws);
     // a line of its own for the second counters too, where the region has one (more than 512 pairs: the first ones' lines)
     p.second_counters = d.B * d.H_q <= kMaxSplitHeads / 2 ? kMaxSplitHeads / 2 * 4 * kCounterStride : kCounterStride / 2;
-    p.ws_acc = reinterpret_cast<float*>(ws + counter_bytes(d));
+    p.ws_acc = reinterpret_cast<float*>(ws + kCounterBytes);
     p.ws_ml = p.ws_acc + parts * kQRows * d.D / 2;
     const dim3 grid(static_cast<unsigned>(parts)), block(kThreads);
     // More work items than compute units, but no more than fit two to a unit: the second shape keeps

@@ -3,6 +3,7 @@
 #pragma once
 #include <algorithm>
 #include <cmath>
+#include <cstddef>
 #include <cstdint>
 
 #include "specvlm.h"
@@ -71,6 +72,8 @@ struct AttnPlan {
     int32_t block_rows;    // query rows per workgroup, 0: all (key ranges only)
     int32_t splits;        // key ranges the call takes, <= ranges
     int32_t streams = 0;   // key ranges of the kernel with four streams per workgroup (attn_streams.hip), <= ranges; 0: one of the others
+    int32_t columns = 0;   // workgroups of that kernel per row block of a KV head, all requests together; 0: one of the other kernels
+    int32_t by_length = 0; // the columns are dealt out to the requests by their lengths, on the device
 };
 
 inline AttnPlan plan_rows(const specvlm_attn_desc& d, int32_t nominal) {
@@ -201,10 +204,83 @@ inline int32_t stream_ranges(const specvlm_attn_desc& d, const AttnPlan& plan) {
     return ntile >= (s == 4 ? 17 : 14) * s ? s : 0;
 }
 
+constexpr int kMostRanges = 8;      // key ranges of a request that the kernel with four streams adds up
+constexpr int kMostByLength = 16;   // requests that it deals columns out to
+
+// The host does not know the requests' lengths, the device does.  A batch with room for more workgroups than `streams` would take, or
+// for more than one per request, gets C = 256 / (row blocks of a request) columns, and every workgroup works out from the lengths which
+// request and key range its column is (attn_streams.hip): few for short requests, up to eight for long ones, so that the longest stream
+// of the batch is as short as C columns allow.  us per call before -> here (head size 128, 60 - 64 nodes):
+//   4 x 32 query / 8 KV heads, 2048, 1311, 3000, 777 keys 24.0 -> 20.1; 3 x 32 / 16, 3664, 1500, 500: 27.9 -> 20.4; 8 x 16 / 4, 4500 - 200:
+//   29.8 -> 20.5; 6 x 32, 2800 - 300: 42.0 -> 33.8; 2 x 32, 4474 + 800: 29.5 -> 24.7; 2 x 32, 64 / 8, 4500 + 900 paged: 31.9 -> 25.7;
+//   4 x 35 / 5, 48 nodes, 2016, from row blocks: 37.8 -> 20.5
+// Equal lengths cost what the plan costs, 0.1 - 0.5 us, as the first tile is requested before it.  So only where streams are long:
+// x = tiles per column at equal lengths (the capacity stands in for them) from 26 on at head size 128 (streams' kernel before; 86 shapes of
+// 26 and more: 1.00 of the time at equal lengths, 0.91 at different ones; 20 - 26: 1.02 and 0.96), from 60 on at 64 (1.02 and 0.87).
+// In place of the kernels with other divisions: x >= 20, at 64 and without shared heads from 26 (row blocks; 68 shapes 0.85 and 0.80, one
+// of them above 1.04; 4 x 32, 1300 keys paged, x = 21.5: 21.6 | 23.9) or 40 (key ranges: 0.94 and 0.84), with blocks at least 70 % full; not
+// where heads are shared and equal lengths would leave more than a fifth of the columns idle (5 x 32 / 16, 4916 keys 53.6 | 63.9).  Below,
+// short unsplit calls with shared heads gain from a column each (x < 12, at 64 16: 0.83 - 1.00 of their time, mean 0.90; without shared heads
+// 0.95 - 1.08).
+inline void plan_columns(const specvlm_attn_desc& d, AttnPlan& plan) {
+    const int group = d.H_q / d.H_kv, rows = group * d.N_max, blocks = (rows + 63) / 64;
+    const int64_t units = static_cast<int64_t>(d.H_kv) * blocks;
+    if (plan.streams) plan.columns = d.B * plan.streams;
+    const int cap = d.paged ? d.max_blocks_per_req * SPECVLM_PAGE_SIZE : d.kv_capacity;
+    if (d.B < 2 || d.B > kMostByLength || d.num_splits > 0 || units * d.B > 256 || 100 * rows < (plan.streams ? 55 : 70) * 64 * blocks) return;
+    if (cap % 16 || cap > (1 << 24) || d.kv_stride_t >= (1 << 22) || (d.N_max * d.q_stride_n + group * d.q_stride_h) >= (1ll << 30)) return;
+    int columns = static_cast<int>(256 / units);
+    // blocks of a head and range on one XCD, where that costs an eighth of the columns at most (4 x 28 / 4, 3000 keys 23.8 -> 22.6)
+    if (blocks > 1)
+        for (int c = columns; c >= d.B && 8 * c >= 7 * columns; --c)
+            if (d.H_kv * c % 8 == 0) { columns = c; break; }
+    const double x = static_cast<double>((cap + kTile - 1) / kTile) * d.B / columns;
+    const bool wide = d.D == 128;
+    if (plan.streams) {
+        if (x < (wide ? 26 : 60)) return;
+    } else {
+        if (group > 1 && !plan.block_rows && plan.splits == 1 && x < (wide ? 12 : 16)) {
+            plan.columns = d.B;
+            return;
+        }
+        const int used = std::min(columns / d.B, kMostRanges) * d.B;
+        if (x < (plan.block_rows ? (wide && group > 1 ? 20 : 26) : (wide ? 20 : 40))) return;
+        if (group > 1 && 5 * used < 4 * columns && (!plan.block_rows || x < 32)) return;
+    }
+    if (columns > d.B) {
+        plan.columns = columns;
+        plan.by_length = 1;
+    } else {
+        plan.columns = d.B;
+    }
+}
+
 inline AttnPlan attn_plan(const specvlm_attn_desc& d) {
     AttnPlan plan = plan_of_heads_and_rows(d);
     plan.streams = stream_ranges(d, plan);
+    plan_columns(d, plan);
     return plan;
+}
+
+// The same call without columns that are dealt out by length: for a workspace that does not hold their partial results.
+inline AttnPlan evenly(const specvlm_attn_desc& d, AttnPlan plan) {
+    if (plan.by_length) plan.columns = d.B * plan.streams;
+    plan.by_length = 0;
+    return plan;
+}
+
+// Workspace: the ticket counters, a region of fixed size at the start whatever the shape (a later call of another shape then finds its
+// counters where every earlier call left zeros, never where one stored partial results), and a partial result of 64 rows and their
+// (max, sum) pairs per (request, head, key range).  One that divides the columns by length takes one per workgroup, in fp32 where the call's
+// results are not rounded to partial ones otherwise.
+constexpr size_t kCounterBytes = static_cast<size_t>(kMaxSplitHeads) * 4 * 128;
+inline size_t attn_workspace_bytes(const specvlm_attn_desc& d, const AttnPlan& plan) {
+    size_t parts = plan.ranges == 1 ? 0 : static_cast<size_t>(d.B) * d.H_q * plan.ranges * (64 * d.D * 2 + 64 * 8);
+    if (plan.by_length) {
+        const size_t workgroups = static_cast<size_t>(plan.columns) * d.H_kv * ((d.H_q / d.H_kv * d.N_max + 63) / 64);
+        parts = std::max(parts, workgroups * (64 * d.D * (plan.splits == 1 ? 4 : 2) + 64 * 8));
+    }
+    return parts ? kCounterBytes + parts : 0;
 }
 
 }  // namespace specvlm

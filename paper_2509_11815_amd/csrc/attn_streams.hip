@@ -5,9 +5,12 @@
 // 0.43 us per 32-key tile and compute unit (two streams, a barrier per step, every tile read from LDS by four wavefronts),
 // more than the stream where K and V come from L2 (grouped heads) or few long requests are left.  Here:
 //
-//   grid      (request, KV head, block of 64 rows of the group, key range), 4 wavefronts each, all 64 rows in every one:
-//             wavefront w has the tiles of stream w splits + split, so a tile is read from LDS once, there is no barrier in
-//             the loop, and four tiles take 0.73 us without fetches (0.18 us a tile)
+//   grid      (KV head, column, block of 64 rows of the group), 4 wavefronts each, all 64 rows in every one.  A column is a key range of
+//             a request: one per request (attn_streams_kernel), or as many as its length earns, worked out by every workgroup
+//             from the lengths (attn_shares_kernel; the host does not know them).  Wavefront w has the tiles of stream w ranges + split,
+//             so a tile is read from LDS once, there is no barrier in the loop, and four tiles take 0.73 us without fetches.  Columns
+//             inside heads, so that every XCD has its part of the longest request (with the requests outermost one XCD has all of
+//             it: 8 x 32 heads, 906 - 170 keys 21.6 -> 20.0; equal lengths + 0.2)
 //   product   v_mfma_f32_32x32x16_bf16: half the matrix instructions of 16 x 16 x 32, and a lane holds 2 query rows x 16 keys
 //             instead of 4 x 8 (half the softmax state).  S^T = K Q^T of tile j + 1 stands beside the softmax of tile j
 //             in one block, so that the compiler interleaves matrix and vector instructions; the last three tiles are
@@ -16,10 +19,12 @@
 //   merge     the four streams meet in LDS, every wavefront owns 32 head dims of all rows; key ranges as in attn_wave.hip
 //
 // us per call (HIP-graph replay), attn_mfma / attn_wave -> here; head size 128, 60 - 64 nodes unless said: 4 x 32 query / 8
-// KV heads, 2048, 1311, 3000, 777 keys 27.6 -> 23.5; 8 x 32 / 16 heads, 4788 keys 82.4 -> 65.7; 3 x 32 / 16 heads, 3664 - 500 keys
-// 34.8 -> 27.2; 4 x 40 heads, 671 keys 18.5 -> 16.4; 6 x 32 heads, 2800 - 300 keys 44.7 -> 35.6; 5 x 40 heads of 64, 1935
-// keys 26.0 -> 20.4.  Tried and slower: two wavefronts sharing a stream of 128 rows (26.3 at the first of these),
-// wavefronts dealt out to the requests by length on the device (24.4).
+// KV heads, 2048, 1311, 3000, 777 keys 27.6 -> 20.1 (23.5 with two ranges each); 8 x 32 / 16 heads, 4788 keys 82.4 -> 65.7; 3 x 32 / 16 heads,
+// 3664 - 500 keys 34.8 -> 20.4 (27.2); 4 x 40 heads, 671 keys 18.5 -> 16.4; 6 x 32 heads, 2800 - 300 keys 44.7 -> 33.8 (35.6); 5 x 40 heads of
+// 64, 1935 keys 26.0 -> 20.4.  Tried and slower: two wavefronts sharing a stream of 128 rows (26.3 at the first of these), wavefronts
+// instead of whole workgroups dealt out by length (24.4), the row blocks of a head walking their tiles in different orders so that each finds
+// in L2 what another fetched (28.1; by one to three tiles of every four 25.0), loads that stay in L2 where blocks share them (a branch in
+// the loop: + 1; without one 22.8 - 24.6 against 23.9 - 24.4).
 #include <type_traits>
 
 #include "attn_rows.hpp"
@@ -27,6 +32,15 @@
 namespace specvlm {
 
 namespace {
+
+// What the two kernels here take beside WaveParams.
+struct StreamsParams : WaveParams {
+    int B, columns, each;       // workgroups per row block of a KV head; as many per request (attn_plan.hpp)
+    int by_length;              // columns go to the requests by their lengths, not `each` to everyone
+    int wide;                   // partial results in fp32
+    uint32_t magic_columns, magic_each;
+    float inv_columns, least_gain;   // rounds that a division must save
+};
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
@@ -38,6 +52,15 @@ __device__ __forceinline__ float max16(const f32x16& a) {
     return max3(max3(u, v, w), max3(x, y, a[15]), a[15]);
 }
 
+// op over lanes 0 .. i of this lane's row of 16.
+template <typename Op>
+__device__ __forceinline__ int row_scan(int x, Op op) {
+    x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, true));     // row_shr:1, zero where there is none
+    x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, true));
+    x = op(x, __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, true));
+    return op(x, __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, true));
+}
+
 // What the other half of the wavefront (lane ^ 32) holds.
 __device__ __forceinline__ float other_half(float x) {
     const uint32_t a = __float_as_uint(x);
@@ -45,8 +68,8 @@ __device__ __forceinline__ float other_half(float x) {
     return __uint_as_float((threadIdx.x & 32) ? r[0] : r[1]);
 }
 
-template <int D, bool PAGED>
-__global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1, 1))) void attn_streams_kernel(WaveParams p) {
+template <int D, bool PAGED, bool SHARES>
+__device__ __forceinline__ void attend(const StreamsParams& p) {
     constexpr int NC = D / 16;                 // QK^T contraction steps of 16
     constexpr int NT = D / 32;                 // output blocks of 32 head dims
     constexpr int ROWG = D / 8;                // 16-byte granules per K/V row
@@ -67,34 +90,41 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
     __shared__ int s_par[kWaveWgs][64];
     __shared__ int s_blocks[PAGED ? kWaveWgs : 1][64];
 
-    // work item: (request, KV head, row block, split); every XCD gets a contiguous range of items, so that the blocks of a head
+    // work item: (KV head, column, row block); every XCD gets a contiguous range of items, so that the blocks of a head
     // share an L2, the first ones an item more where their number is no multiple of 8 (dealt out to the XCDs in turn: 39.2 us for the
     // 210 of 3 x 35 query / 7 KV heads, 4060 keys, now 29.6; the 250 of 5 x 25 / 5, 5312 keys 53.3, now 37.0).
     const uint32_t xcd = blockIdx.x & 7;
     const uint32_t work = xcd * (gridDim.x >> 3) + min(xcd, gridDim.x & 7) + (blockIdx.x >> 3);
-    const uint32_t unit = divide(work, p.magic_splits);
-    const int split = work - unit * p.num_splits;
-    const uint32_t bk = divide(unit, p.magic_rb);
-    const int rb = unit - bk * p.row_blocks;
-    const int b = divide(bk, p.magic_hkv);
-    const int hk = bk - b * p.H_kv;
+    const uint32_t group_item = divide(work, p.magic_rb);
+    const int rb = work - group_item * p.row_blocks;
+    const int hk = divide(group_item, p.magic_columns);
+    const int column = group_item - hk * p.columns;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int l32 = lane & 31, hf = lane >> 5;
 
     typedef const __attribute__((address_space(4))) int32_t* const_i32;
-    const int n_raw = p.num_nodes ? ((const_i32)p.num_nodes)[b] : p.N_max;
-    const int P_raw = ((const_i32)p.prefix_len)[b];
-    const int nstream = kWaveWgs * p.num_splits;
-    const int stream = wave * p.num_splits + split;
+    // (dealt out evenly, as if all requests had one length; corrected below)
+    int b = SHARES ? min(static_cast<int>(divide(column, p.magic_each)), p.B - 1) : column;
+    int ranges = SHARES ? p.each : 1, split = SHARES ? min(column - b * p.each, p.each - 1) : 0;
+    int n_raw = p.num_nodes ? ((const_i32)p.num_nodes)[b] : p.N_max;
+    int P_raw = ((const_i32)p.prefix_len)[b];
 
     unsigned char* ring = s_ring + wave * kRingBytes;
     typedef __attribute__((address_space(3))) unsigned char lds_byte;
     typedef __attribute__((address_space(3))) int lds_int;
     const uint32_t ring_lds = (uint32_t)(uintptr_t)(lds_byte*)ring;
 
-    // the parent array first (every wavefront its own copy)
-    dma4(p.parent + static_cast<int64_t>(b) * p.N_max + min(lane, p.N_max - 1), (uint32_t)(uintptr_t)(lds_int*)s_par[wave]);
+    if (SHARES && p.by_length) {                           // lane i (mod 16): request i
+        const int at = min(lane & 15, p.B - 1);
+        dma4(p.prefix_len + at, (uint32_t)(uintptr_t)(lds_byte*)s_m[wave]);
+        if (p.num_nodes) dma4(p.num_nodes + at, (uint32_t)(uintptr_t)(lds_byte*)s_l[wave]);
+    }
+    // the parent array before the rest (every wavefront its own copy)
+    auto request_parents = [&]() __attribute__((always_inline)) {
+        dma4(p.parent + static_cast<int64_t>(b) * p.N_max + min(lane, p.N_max - 1), (uint32_t)(uintptr_t)(lds_int*)s_par[wave]);
+    };
+    request_parents();
 
     // ---- tile fetch -------------------------------------------------------------------------
     const int lrow = lane / ROWG, lpos = lane % ROWG;
@@ -109,11 +139,20 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
         voff_k[i] = lrow_off + ((lpos ^ (r & (ROWG - 1))) << 4) + i * (RPI * row_bytes - 1024);   // (row_bytes >= 2 D)
         voff_v[i] = lrow_off + ((lpos ^ (vswz(r) << 2)) << 4) + i * (RPI * row_bytes - 1024);
     }
-    const int64_t head_off = hk * p.g.stride_h + (PAGED ? 0 : b * p.g.stride_b);   // elements
-    const int64_t tile_step = static_cast<int64_t>(nstream) * kKeys * p.g.stride_t;         // elements from one tile of the stream to its next
-    const int64_t first_off = head_off + static_cast<int64_t>(stream) * kKeys * p.g.stride_t;
-    const uint16_t* k_next = p.k + (PAGED ? head_off : first_off);       // contiguous: the next tile to request
-    const uint16_t* v_next = p.v + (PAGED ? head_off : first_off);
+    int nstream, stream;
+    int64_t head_off, tile_step;
+    const uint16_t *k_next, *v_next;                       // contiguous: the next tile to request
+    auto place = [&]() __attribute__((always_inline)) {
+        nstream = kWaveWgs * ranges;
+        stream = wave * ranges + split;
+        head_off = hk * p.g.stride_h + (PAGED ? 0 : b * p.g.stride_b);                 // elements
+        tile_step = static_cast<int64_t>(nstream) * kKeys * p.g.stride_t;              // from one tile of the stream to its next
+        // (a first tile beyond the cache is replaced by the cache's first: never used)
+        const int64_t off = head_off + (PAGED || stream * kKeys >= p.g.capacity ? 0 : static_cast<int64_t>(stream) * kKeys * p.g.stride_t);
+        k_next = p.k + off;
+        v_next = p.v + off;
+    };
+    place();
     const int64_t half_step = 16 * p.g.stride_t;
     // Tile j of this stream, K or V, into slot j % 2: two halves of 16 rows.  The capacity is a multiple of 16 (host), so a half
     // lies inside the cache or beyond it; one beyond is replaced by the tile's first half (its keys do not exist, weight zero).
@@ -133,31 +172,69 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
     auto issue_k = [&](int j, const int (&phys)[2]) __attribute__((always_inline)) { issue(k_next, voff_k, 0, j, phys); };
     auto issue_v = [&](int j, const int (&phys)[2]) __attribute__((always_inline)) { issue(v_next, voff_v, kTileBytes, j, phys); };
     int phys[2] = {0, 0};
-    // With a contiguous cache the first tile's address needs no length: requested before the lengths arrive (a tile
-    // beyond the cache is replaced by the cache's first).
-    constexpr bool early = !PAGED;
-    if constexpr (early) {
-        if (stream * kKeys >= p.g.capacity) { k_next = p.k + head_off; v_next = p.v + head_off; }      // never used
-        issue_k(0, phys);
-    }
-
     // query rows of this block: row r of the block is row R = 64 rb + r of the group's (head, node) rows
     const int rows_total = p.group * p.N_max;
     const uint32_t q_lds = (uint32_t)(uintptr_t)(lds_byte*)s_q;
     const int row0 = rb * kQRows;
     const int q_row = static_cast<int>(p.q_sn) * 2, q_head = static_cast<int>(p.q_sh) * 2;     // bytes (checked on the host)
-    const uint16_t* q_base = p.q + b * p.q_sb + static_cast<int64_t>(hk * p.group) * p.q_sh;
+    auto request_first = [&]() __attribute__((always_inline)) {
+        if constexpr (!PAGED) issue_k(0, phys);
+        const uint16_t* q_base = p.q + b * p.q_sb + static_cast<int64_t>(hk * p.group) * p.q_sh;
 #pragma unroll
-    for (int i = 0; i < NQ; ++i) {
-        const int inst = wave * NQ + i;
-        const int r = inst * RPI + lrow;
-        const int R = min(row0 + r, rows_total - 1);
-        const int hh = divide(R, p.magic_nmax);
-        const int node = R - hh * p.N_max;
-        const uint32_t voff = static_cast<uint32_t>(node * q_row + hh * q_head) + ((lpos ^ (r & (ROWG - 1))) << 4);
-        dma16s(q_base, voff, q_lds + inst * 1024);
+        for (int i = 0; i < NQ; ++i) {
+            const int r = (wave * NQ + i) * RPI + lrow;
+            const int R = min(row0 + r, rows_total - 1);
+            const int hh = divide(R, p.magic_nmax);
+            const int node = R - hh * p.N_max;
+            dma16s(q_base, static_cast<uint32_t>(node * q_row + hh * q_head) + ((lpos ^ (r & (ROWG - 1))) << 4), q_lds + (wave * NQ + i) * 1024);
+        }
+    };
+    request_first();
+    // The columns of a row block, dealt out by the lengths: every request gets as many as bring its rounds of four tiles down to the
+    // least `len` for which they suffice, one each if that saves too little.  Lanes 16 g + i look at request i for the g-th of four
+    // lengths.  (Through the scalar cache, request by request, this took 1 us longer; with the requests above sent only afterwards
+    // 0.7 us.  What was requested for another request or range lands before what replaces it: loads return in order.)
+    if (SHARES && p.by_length) {
+        wait_vmcnt<1 + (PAGED ? 0 : KLD) + NQ>();
+        const int my_P = __float_as_int(s_m[wave][lane]);
+        const int my_n = p.num_nodes ? __float_as_int(s_l[wave][lane]) : p.N_max;
+        const int keys = min(max(my_P, 0) + min(max(my_n, 1), p.N_max), p.g.capacity);      // (a bad request's too)
+        const int rounds = (lane & 15) < p.B ? (keys + kWaveWgs * kKeys - 1) / (kWaveWgs * kKeys) : 0;
+        const int longest = __builtin_amdgcn_readlane(row_scan(rounds, [](int x, int y) { return max(x, y); }), 15);
+        const int total = __builtin_amdgcn_readlane(row_scan(rounds, [](int x, int y) { return x + y; }), 15);
+        const float most = static_cast<float>(rounds) - 0.5f;
+        auto columns_for = [&](float len) __attribute__((always_inline)) { return static_cast<int>((most + len) * __builtin_amdgcn_rcpf(len)); };   // ceil(rounds / len)
+        auto upto_for = [&](float len) __attribute__((always_inline)) { return row_scan(columns_for(len), [](int x, int y) { return x + y; }); };
+        float len = ceilf(fmaxf(total * p.inv_columns, longest * (1.f / kMostRanges)) - 0.01f) + (lane >> 4);
+        unsigned long long fits;
+        for (;; len += 4.f) {                              // ends where len >= longest: a column each
+            const int upto = upto_for(len);                // (not in the condition below: every lane takes part)
+            if ((fits = __ballot(((lane & 15) == 15) & (upto <= p.columns))) != 0) break;
+        }
+        len = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(len), __builtin_ctzll(fits)));
+        if (longest - len < p.least_gain) len = longest;
+        const int mine = columns_for(len), upto = upto_for(len);
+        const unsigned long long here = __ballot((lane < 16) & (column < upto) & (column >= upto - mine));
+        if (!here) {                                       // a column too many
+            wait_vmcnt<0>();
+            return;
+        }
+        const int to = __builtin_ctzll(here);
+        const int to_ranges = __builtin_amdgcn_readlane(mine, to), to_split = column - __builtin_amdgcn_readlane(upto, to) + to_ranges;
+        P_raw = __builtin_amdgcn_readlane(my_P, to);
+        n_raw = __builtin_amdgcn_readlane(my_n, to);
+        if (to != b || to_split != split || to_ranges != ranges) {
+            b = to;
+            split = to_split;
+            ranges = to_ranges;
+            request_parents();
+            place();
+            request_first();
+        }
     }
-    if constexpr (early) issue_v(0, phys);
+    const uint32_t head_block = hk * p.row_blocks + rb;
+    const uint32_t unit = b * p.H_kv * p.row_blocks + head_block;
+    if constexpr (!PAGED) issue_v(0, phys);
 
     int err = 0;
     int n = n_raw;
@@ -167,7 +244,7 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
     if (P < 0 || P + n > p.g.capacity) err |= SPECVLM_ERR_BAD_LENGTH;
     const int S = P + n;
     const int ntile = (S + kKeys - 1) / kKeys;
-    const int my_tiles = (!err && stream < ntile) ? static_cast<int>(divide(ntile - stream + nstream - 1, p.magic_nstream)) : 0;
+    const int my_tiles = (!err && stream < ntile) ? static_cast<int>(static_cast<uint32_t>(ntile - stream + nstream - 1) / static_cast<uint32_t>(nstream)) : 0;
     // Block ids: the first three tiles' through the scalar cache (the third's again for V); from there on lane 2i + x holds that of
     // half x of tile i (mod 32), fetched for 32 tiles at once.  (A scalar load per tile shares its counter with the LDS reads, which
     // then all have to wait for it: 2 x 64 query / 8 KV heads, 4500 + 900 keys 33.4 us; 3 x 32 / 8, 3000 - 500 26.4.)
@@ -198,7 +275,7 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
     if constexpr (PAGED) {
         if (my_tiles > 0) request_ids(0);
     }
-    if (!early && my_tiles > 0) { fetch_blocks(0, phys); issue_k(0, phys); issue_v(0, phys); }
+    if (PAGED && my_tiles > 0) { fetch_blocks(0, phys); issue_k(0, phys); issue_v(0, phys); }
     if (my_tiles > 1) { fetch_blocks(1, phys); issue_k(1, phys); issue_v(1, phys); }
     int phys2[2] = {0, 0};
     if (my_tiles > 2) fetch_blocks(2, phys2);
@@ -530,94 +607,163 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
             if (real[e] && p.lse && hf == 0 && own_t(wave, e) == 0) p.lse[lse_off[e]] = M[e] * p.scale + __log2f(L[e]) * kLn2;
         }
     };
-    if (p.num_splits == 1) {
+    if (!SHARES || ranges == 1) {
         store_out(Mq, Lq);
         return;
     }
-    // ---- split partials ----------------------------------------------------------------------------
-    constexpr int PV = OWN * 2;                            // 16-byte vectors per lane per partial
-    const int64_t part0 = static_cast<int64_t>(unit) * p.num_splits;
-    constexpr int kPartBytes = kWaveWgs * PV * 1024;       // one split's partial
-    {
-        unsigned char* dst = p.ws_acc + (part0 + split) * kPartBytes + wave * PV * 1024 + lane * 16;
+    if constexpr (SHARES) {
+        // ---- split partials ----------------------------------------------------------------------------
+        // partial results: 16-byte vectors, OWN x 2 a lane as bf16, OWN x 4 as fp32 (calls that the library does not split by itself)
+        const int64_t part0 = static_cast<int64_t>(head_block) * p.columns + column - split;
+        const int vectors = p.wide ? OWN * 4 : OWN * 2;
+        const int part_bytes = kWaveWgs * vectors * 1024;      // one split's partial
+        {
+            unsigned char* dst = p.ws_acc + (part0 + split) * part_bytes + wave * vectors * 1024 + lane * 16;
+            if (p.wide) {
 #pragma unroll
-        for (int e = 0; e < OWN; ++e)
+                for (int e = 0; e < OWN; ++e)
 #pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                u32x4 x;
+                    for (int u = 0; u < 4; ++u) {
+                        u32x4 x;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) x[i] = pack_bf16x2(out[e][8 * u + 2 * i], out[e][8 * u + 2 * i + 1]);
-                store16_coherent(dst + (e * 2 + u) * 1024, x);
+                        for (int i = 0; i < 4; ++i) x[i] = __float_as_uint(out[e][4 * u + i]);
+                        store16_coherent(dst + (e * 4 + u) * 1024, x);
+                    }
+            } else {
+#pragma unroll
+                for (int e = 0; e < OWN; ++e)
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        u32x4 x;
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) x[i] = pack_bf16x2(out[e][8 * u + 2 * i], out[e][8 * u + 2 * i + 1]);
+                        store16_coherent(dst + (e * 2 + u) * 1024, x);
+                    }
             }
-        // (every owner of a row stores the same pair)
+            // (every owner of a row stores the same pair)
 #pragma unroll
-        for (int e = 0; e < OWN; ++e)
-            if (hf == 0) store8_coherent(p.ws_ml + ((part0 + split) * kQRows + own_qb(wave, e) * 32 + l32) * 2, u32x2{__float_as_uint(Mq[e]), __float_as_uint(Lq[e])});
-    }
-    wait_vmcnt<0>();
-    int is_last = 0;
-    if (lane == 0) {
-        int32_t* cnt = p.ws_cnt + (static_cast<int64_t>(unit) * 4 + wave) * kCounterStride;
-        const int ticket = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        is_last = ticket == p.num_splits - 1;
-        if (is_last) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    if (!__builtin_amdgcn_readfirstlane(is_last)) return;
-    asm volatile("" ::: "memory");
-    // device-coherent (sc1) buffer loads, which the compiler counts; not before the ticket was seen
-    constexpr int kCoherent = 16, kMostRanges = 4;
-    const auto acc_rsrc = __builtin_amdgcn_make_buffer_rsrc(p.ws_acc + part0 * kPartBytes + wave * PV * 1024, 0, 0x7FFFFFFF, 0x00027000);
-    const auto ml_rsrc = __builtin_amdgcn_make_buffer_rsrc(p.ws_ml + part0 * kQRows * 2, 0, 0x7FFFFFFF, 0x00027000);
-    u32x4 part[kMostRanges][PV];
-    u32x2 ml[kMostRanges][OWN];
-    const int last = p.num_splits - 1;
-#pragma unroll
-    for (int u = 0; u < kMostRanges; ++u)                  // (past the last range: the last one again, weight zero)
-#pragma unroll
-        for (int e = 0; e < OWN; ++e)
-            ml[u][e] = __builtin_amdgcn_raw_buffer_load_b64(ml_rsrc, (own_qb(wave, e) * 32 + l32) * 8, min(u, last) * (kQRows * 8), kCoherent);
-#pragma unroll
-    for (int u = 0; u < kMostRanges; ++u)
-#pragma unroll
-        for (int v = 0; v < PV; ++v)
-            part[u][v] = __builtin_amdgcn_raw_buffer_load_b128(acc_rsrc, lane * 16, min(u, last) * kPartBytes + v * 1024, kCoherent);
-    float Mall[OWN], Lall[OWN];
-#pragma unroll
-    for (int e = 0; e < OWN; ++e) {
-        Mall[e] = -INFINITY;
-#pragma unroll
-        for (int u = 0; u < kMostRanges; ++u) Mall[e] = fmaxf(Mall[e], __uint_as_float(ml[u][e][0]));
-        const float m_safe = Mall[e] == -INFINITY ? 0.f : Mall[e];
-        Lall[e] = 0.f;
-        out[e] = zero;
-#pragma unroll
-        for (int u = 0; u < kMostRanges; ++u) {
-            const float w = u <= last ? fast_exp2((__uint_as_float(ml[u][e][0]) - m_safe) * c2) : 0.f;
-            Lall[e] += __uint_as_float(ml[u][e][1]) * w;
-#pragma unroll
-            for (int v = 0; v < 2; ++v)
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const uint32_t x = part[u][2 * e + v][i];
-                    out[e][8 * v + 2 * i] = fmaf(__uint_as_float(x << 16), w, out[e][8 * v + 2 * i]);
-                    out[e][8 * v + 2 * i + 1] = fmaf(__uint_as_float(x & 0xFFFF0000u), w, out[e][8 * v + 2 * i + 1]);
-                }
+            for (int e = 0; e < OWN; ++e)
+                if (hf == 0) store8_coherent(p.ws_ml + ((part0 + split) * kQRows + own_qb(wave, e) * 32 + l32) * 2, u32x2{__float_as_uint(Mq[e]), __float_as_uint(Lq[e])});
         }
+        wait_vmcnt<0>();
+        int is_last = 0;
+        if (lane == 0) {
+            int32_t* cnt = p.ws_cnt + (static_cast<int64_t>(unit) * 4 + wave) * kCounterStride;
+            const int ticket = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            is_last = ticket == ranges - 1;
+            if (is_last) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (!__builtin_amdgcn_readfirstlane(is_last)) return;
+        asm volatile("" ::: "memory");
+        // device-coherent (sc1) buffer loads, which the compiler counts; not before the ticket was seen
+        constexpr int kCoherent = 16, kBatch = 4;
+        const auto acc_rsrc = __builtin_amdgcn_make_buffer_rsrc(p.ws_acc + part0 * part_bytes + wave * vectors * 1024, 0, 0x7FFFFFFF, 0x00027000);
+        const auto ml_rsrc = __builtin_amdgcn_make_buffer_rsrc(p.ws_ml + part0 * kQRows * 2, 0, 0x7FFFFFFF, 0x00027000);
+        const int last = ranges - 1;
+        float Mall[OWN], Lall[OWN];
+#pragma unroll
+        for (int e = 0; e < OWN; ++e) {
+            Mall[e] = -INFINITY;
+            Lall[e] = 0.f;
+            out[e] = zero;
+        }
+        auto merge = [&](auto kind) __attribute__((always_inline)) {
+            constexpr bool WIDE = decltype(kind)::value;
+            constexpr int PV = WIDE ? OWN * 4 : OWN * 2;
+            constexpr int BATCH = 4;
+            for (int first = 0; first <= last; first += BATCH) {       // four ranges' loads at once (past the last: it again, weight zero)
+                u32x2 ml[BATCH][OWN];
+                u32x4 part[BATCH][PV];
+#pragma unroll
+                for (int u = 0; u < BATCH; ++u)
+#pragma unroll
+                    for (int e = 0; e < OWN; ++e)
+                        ml[u][e] = __builtin_amdgcn_raw_buffer_load_b64(ml_rsrc, (own_qb(wave, e) * 32 + l32) * 8, min(first + u, last) * (kQRows * 8), kCoherent);
+#pragma unroll
+                for (int u = 0; u < BATCH; ++u)
+#pragma unroll
+                    for (int v = 0; v < PV; ++v)
+                        part[u][v] = __builtin_amdgcn_raw_buffer_load_b128(acc_rsrc, lane * 16, min(first + u, last) * part_bytes + v * 1024, kCoherent);
+#pragma unroll
+                for (int e = 0; e < OWN; ++e) {
+                    float M = Mall[e];
+#pragma unroll
+                    for (int u = 0; u < BATCH; ++u) M = fmaxf(M, __uint_as_float(ml[u][e][0]));
+                    const float m_safe = M == -INFINITY ? 0.f : M;
+                    if (first) {
+                        const float alpha = fast_exp2((Mall[e] - m_safe) * c2);
+                        Lall[e] *= alpha;
+                        out[e] *= alpha;
+                    }
+                    Mall[e] = M;
+#pragma unroll
+                    for (int u = 0; u < BATCH; ++u) {
+                        const float w = first + u <= last ? fast_exp2((__uint_as_float(ml[u][e][0]) - m_safe) * c2) : 0.f;
+                        Lall[e] += __uint_as_float(ml[u][e][1]) * w;
+                        if constexpr (WIDE) {
+#pragma unroll
+                            for (int v = 0; v < 4; ++v)
+#pragma unroll
+                                for (int i = 0; i < 4; ++i) out[e][4 * v + i] = fmaf(__uint_as_float(part[u][4 * e + v][i]), w, out[e][4 * v + i]);
+                        } else {
+#pragma unroll
+                            for (int v = 0; v < 2; ++v)
+#pragma unroll
+                                for (int i = 0; i < 4; ++i) {
+                                    const uint32_t x = part[u][2 * e + v][i];
+                                    out[e][8 * v + 2 * i] = fmaf(__uint_as_float(x << 16), w, out[e][8 * v + 2 * i]);
+                                    out[e][8 * v + 2 * i + 1] = fmaf(__uint_as_float(x & 0xFFFF0000u), w, out[e][8 * v + 2 * i + 1]);
+                                }
+                        }
+                    }
+                }
+            }
+        };
+        if (p.wide) merge(std::true_type{});
+        else merge(std::false_type{});
+        store_out(Mall, Lall);
     }
-    store_out(Mall, Lall);
+}
+
+template <int D, bool PAGED>
+__global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1, 1))) void attn_streams_kernel(StreamsParams p) {
+    attend<D, PAGED, false>(p);
+}
+
+template <int D, bool PAGED>
+__global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1, 1))) void attn_shares_kernel(StreamsParams p) {
+    attend<D, PAGED, true>(p);
+}
+
+template <int D, bool PAGED>
+void launch_as(const StreamsParams& p, dim3 grid, hipStream_t stream) {
+    if (p.columns > p.B) hipLaunchKernelGGL((attn_shares_kernel<D, PAGED>), grid, dim3(kWaveWgs * 64), 0, stream, p);
+    else hipLaunchKernelGGL((attn_streams_kernel<D, PAGED>), grid, dim3(kWaveWgs * 64), 0, stream, p);
 }
 
 template <int D>
-void launch_d(const WaveParams& p, dim3 grid, hipStream_t stream) {
-    if (p.g.block_table) hipLaunchKernelGGL((attn_streams_kernel<D, true>), grid, dim3(kWaveWgs * 64), 0, stream, p);
-    else hipLaunchKernelGGL((attn_streams_kernel<D, false>), grid, dim3(kWaveWgs * 64), 0, stream, p);
+void launch_d(const StreamsParams& p, dim3 grid, hipStream_t stream) {
+    if (p.g.block_table) launch_as<D, true>(p, grid, stream);
+    else launch_as<D, false>(p, grid, stream);
 }
 
 }  // namespace
 
 int32_t launch_attn_streams(const AttnArgs& a) {
     unsigned workgroups;
-    const WaveParams p = wave_params(a, kQRows, a.plan.streams, workgroups);
+    StreamsParams p;
+    static_cast<WaveParams&>(p) = wave_params(a, kQRows, 1, workgroups);
+    p.B = a.d.B;
+    p.columns = a.plan.columns;
+    p.each = std::min(p.columns / p.B, kMostRanges);
+    p.by_length = a.plan.by_length;
+    p.wide = a.plan.splits == 1;
+    p.magic_columns = divisor(p.columns);
+    p.magic_each = divisor(p.each);
+    p.inv_columns = 1.f / p.columns;
+    p.least_gain = a.d.D == 128 ? 1.3f : 2.5f;             // meeting of partial results, 1.5 us, in rounds
+    workgroups = static_cast<unsigned>(p.columns) * a.d.H_kv * p.row_blocks;
+    p.ws_acc = static_cast<unsigned char*>(a.workspace) + kCounterBytes + static_cast<size_t>(workgroups) * kQRows * 8;
     if (a.d.D == 128) launch_d<128>(p, dim3(workgroups), a.stream);
     else launch_d<64>(p, dim3(workgroups), a.stream);
     return check_launch();

@@ -133,7 +133,6 @@ int32_t launch_attn_mfma(const AttnArgs& a);
 // workspace layout rules).
 int32_t launch_attn_wave(const AttnArgs& a);
 int32_t launch_attn_streams(const AttnArgs& a);
-size_t attn_mfma_workspace_bytes(const specvlm_attn_desc& d, int32_t ranges);
 // Device address of the current device's library-owned scratch array (SPECVLM_STATIC_WORKSPACE_BYTES).
 int32_t attn_static_workspace(void** ptr_out);
 

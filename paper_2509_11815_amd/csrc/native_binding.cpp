@@ -25,7 +25,7 @@ namespace {
 
 // ---- the library's entry points ------------------------------------------------------------------
 #define SPECVLM_NATIVE_ENTRIES(X)                                                                          \
-    X(specvlm_last_hip_error) X(specvlm_tree_verify_attn_workspace_bytes) X(specvlm_tree_verify_attn)      \
+    X(specvlm_last_hip_error) X(specvlm_tree_verify_attn_workspace_bytes) X(specvlm_tree_verify_attn_num_splits) X(specvlm_tree_verify_attn)      \
     X(specvlm_tree_verify_attn_static) X(specvlm_tree_verify_attn_vector_alu) X(specvlm_node_argmax)       \
     X(specvlm_tree_accept) X(specvlm_node_argmax_accept) X(specvlm_tree_accept_sample) X(specvlm_kv_compact) \
     X(specvlm_draft_topk) X(specvlm_draft_topk_select) X(specvlm_draft_select) X(specvlm_draft_finalize)   \
@@ -283,7 +283,8 @@ PyObject* tree_verify_attn(PyObject*, PyObject* const* args, Py_ssize_t nargs) {
             const at::Tensor& t = a.tensor(9, "workspace");
             ws = t.data_ptr();
             bytes = t.numel() * t.element_size();
-        } else if ((bytes = lib.specvlm_tree_verify_attn_workspace_bytes(desc)) != 0) {
+        } else if (lib.specvlm_tree_verify_attn_num_splits(desc) > 1) {       // (others need none; filling one costs more than it gains)
+            bytes = lib.specvlm_tree_verify_attn_workspace_bytes(desc);
             scratch = at::zeros({static_cast<int64_t>(bytes)}, q.options().dtype(at::kByte));   // zero-filled once, as the ABI asks
             ws = scratch.data_ptr();
         }

@@ -20,6 +20,11 @@ extern "C" void plan(const specvlm_attn_desc* d, int* out) {
     const specvlm::AttnPlan p = specvlm::attn_plan(*d);
     out[0] = p.ranges; out[1] = p.block_rows; out[2] = p.splits; out[3] = p.streams;
 }
+extern "C" void columns(const specvlm_attn_desc* d, long long* out) {
+    const specvlm::AttnPlan p = specvlm::attn_plan(*d), e = specvlm::evenly(*d, p);
+    out[0] = p.columns; out[1] = p.by_length; out[2] = specvlm::attn_workspace_bytes(*d, p);
+    out[3] = e.columns; out[4] = e.by_length; out[5] = specvlm::attn_workspace_bytes(*d, e);
+}
 """
 
 
@@ -66,3 +71,13 @@ def plan_of_case(case, num_splits=0) -> Plan:
     Hkv, table = case["k"].shape[1], case["block_table"]
     cap = case["k"].shape[2] if table is None else table.shape[1] * 16
     return plan_of(B, Hq, Hkv, D, N, cap, num_splits, table is not None)
+
+
+Columns = collections.namedtuple("Columns", "columns by_length bytes even_columns even_by_length even_bytes")
+
+
+def columns_of(*shape, **options) -> Columns:
+    """Workgroups per row block of a KV head, whether the lengths deal them out, workspace bytes; the same for a call that has not that much."""
+    out = (ctypes.c_longlong * 6)()
+    _library().columns(ctypes.byref(desc_of(*shape, **options)), out)
+    return Columns(*out)

@@ -409,7 +409,8 @@ int32_t specvlm_draft_topk(int32_t dtype, int32_t B, int32_t W, int32_t V, int32
  * launch: the workgroup that finishes a request's last row makes the selection.  W*K <= 1024.
  *   counters_dev   device int32 [B * SPECVLM_COUNTER_STRIDE] (request b's counter is word
  *                  b * SPECVLM_COUNTER_STRIDE), ZERO-FILLED ONCE after allocation (every call leaves
- *                  it zero); calls that may run concurrently need separate counters
+ *                  it zero; the words behind a counter are scratch); calls that may run concurrently need
+ *                  separate counters
  */
 int32_t specvlm_draft_topk_select(int32_t dtype, int32_t B, int32_t W, int32_t V, int32_t K,
                                   const void *logits_dev, int64_t stride_b, int64_t stride_w,

@@ -319,16 +319,25 @@ __device__ __forceinline__ void rank_winners(unsigned long long* s_key, int c, i
 // beside the collection: 5.75 -> 5.3 us a call; a growth of six levels with its finalize 53.4 -> 49.2, nearly all of it at the root, the last
 // level and the finalize (the levels between, ten rows with the selection, take 9.2 - 9.3 us each in a trace of the growth, as before).
 // ---------------------------------------------------------------------------------------
-// SEL: the workgroup that finishes a request's last row also chooses the M most valuable of the
+// With the selection (kSelect, kBeside): the workgroup that finishes a request's last row also chooses the M most valuable of the
 // request's W*K new candidates (what draft_select_kernel does in a launch of its own): scores
-// are stored write-through, acknowledged, then a ticket per request is drawn.
+// are stored write-through, acknowledged, then a ticket per request is drawn.  kBeside: a row has two workgroups on two compute
+// units, one for its log-sum-exp, which waits for no ranking, and one for its Top-K, which then leaves the exponentials (1.5 us of
+// 32000) alone.  They store a log-sum-exp and K logits; the scores are put together by the one that selects, from the same operations.
+// A growth of six levels, ten rows each but the root, in a graph, one workgroup a row -> two: bf16, one request 32000 tokens 48.8 -> 44.4 us,
+// 65000 59.4 -> 53.8, 152064 108.2 -> 94.0; eight requests 54.0 -> 50.1, 63.0 -> 60.6, 121.7 -> 106.7; fp32, one 50.4 -> 47.3, 62.3 -> 58.5,
+// 110.7 -> 98.0.  (Tried: the log-sum-exp of a long row shared by up to five workgroups in segments of 32768 entries, and rows of up to
+// 163840 bf16 entries in registers: the segments' reductions cost the other calls 1 us, the longer unrolled code 5.)
 struct SelArgs {
     int M, index_base;
     int32_t* sel_out;
     float* sel_score_out;
     int32_t* count_out;
-    int32_t* counters;            // [B * SPECVLM_COUNTER_STRIDE] tickets, zero between calls
+    int32_t* counters;            // [B * SPECVLM_COUNTER_STRIDE] tickets, zero between calls; kBeside: word 1 + w, row w's log-sum-exp
+    int rows;                     // kBeside: rows of a request
 };
+
+enum Level { kPlain, kSelect, kBeside };                   // scores only; with the selection; with that, and the log-sum-exps in workgroups of their own
 
 constexpr float kLowest = -3.402823466e38f;         // reference of a thread without entries: no finite logit is below it
 constexpr int kStream = 24;              // NC == 0: chunks per thread whose maximum is kept (196608 entries)
@@ -338,7 +347,7 @@ constexpr int kStream = 24;              // NC == 0: chunks per thread whose max
 // (a fused multiply-add with the reference already scaled saves an instruction, but adds 2^r, r the rounding of that).
 __device__ __forceinline__ float exp_of(float x) { return __builtin_amdgcn_exp2f(x * 1.4426950408889634f); }
 
-template <typename T, int NC, bool SEL>
+template <typename T, int NC, Level LEVEL>
 __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
     int V, int K, const T* __restrict__ logits, int64_t stride_b, int64_t stride_w,
     const float* __restrict__ cum, int64_t cum_stride_b, const int32_t* __restrict__ parent_idx,
@@ -352,8 +361,11 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
     __shared__ int s_last, s_ncand;
     __shared__ float s_thr, s_lse;
 
-    const int w = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int nrows = gridDim.x;
+    constexpr bool SEL = LEVEL != kPlain, BESIDE = LEVEL == kBeside;
+    const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int nrows = BESIDE ? sel.rows : gridDim.x;
+    const bool summing = BESIDE && static_cast<int>(blockIdx.x) >= nrows;       // uniform: this workgroup adds up, the row's other one ranks
+    const int w = summing ? blockIdx.x - nrows : blockIdx.x;
     const T* row = logits + b * stride_b + w * stride_w;
     const float c = cum ? cum[b * cum_stride_b + w] : 0.f;
     const int par = parent_idx ? parent_idx[b * parent_stride_b + w] : -1;
@@ -384,12 +396,15 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
             tmax = fmaxf(tmax, cmax[j]);
         }
         m = fmaxf(tmax, kLowest);
-        float part[4] = {exp_of(es - m), 0.f, 0.f, 0.f};
+        sum = 0.f;
+        if (!BESIDE || summing) {
+            float part[4] = {exp_of(es - m), 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int j = 0; j < NC; ++j)
+            for (int j = 0; j < NC; ++j)
 #pragma unroll
-            for (int e = 0; e < 8; ++e) part[e & 3] += exp_of(ch[j].at(e) - m);         // exp(-inf) = 0
-        sum = (part[0] + part[1]) + (part[2] + part[3]);
+                for (int e = 0; e < 8; ++e) part[e & 3] += exp_of(ch[j].at(e) - m);     // exp(-inf) = 0
+            sum = (part[0] + part[1]) + (part[2] + part[3]);
+        }
     } else {
         m = fmaxf(es, kLowest);
         sum = es > -INFINITY ? 1.f : 0.f;
@@ -406,6 +421,7 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
                 gm = fmaxf(gm, cm[u]);
             }
             tmax = fmaxf(tmax, gm);
+            if (BESIDE && !summing) return;
             const float mn = fmaxf(m, gm);
             float part[4] = {sum * exp_of(m - mn), 0.f, 0.f, 0.f};         // (times exactly 1 where the maximum stays)
 #pragma unroll
@@ -429,12 +445,34 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
             take(tid + kThreadsDT * j, cm);
         }
     }
-    {
-        const float gmax = row_max(tmax);                // of the row of 16 lanes
+    auto wave_sums = [&]() __attribute__((always_inline)) {
         const float wm = wave_max(m);
         const float ws = wave_sum(sum * exp_of(m - wm));
-        if ((tid & 15) == 0) s_grp[tid >> 4] = gmax;
         if (lane == 0) { s_wmax[wave] = wm; s_wsum[wave] = ws; }
+    };
+    auto log_sum = [&]() __attribute__((always_inline)) -> float {         // of the row, in every row of 16 lanes
+        const float mx = row_max(s_wmax[tid & 15]);
+        return mx + logf(row_sum(s_wsum[tid & 15] * exp_of(s_wmax[tid & 15] - mx)));
+    };
+    // The root's only row: its candidates come in the order of their scores (rounding keeps it, equal ones go by
+    // index, with a NaN all are), so the selection is the first M and nobody has to be met: 7.7 -> 5.6 us a call.
+    const bool lone = LEVEL == kSelect && nrows == 1 && !cum;
+    if (summing) {
+        wave_sums();
+        __syncthreads();
+        if (wave == 0) {
+            const float l = log_sum();
+            if (lane == 0) {
+                __hip_atomic_store(sel.counters + b * SPECVLM_COUNTER_STRIDE + 1 + w, static_cast<int32_t>(__float_as_uint(l)),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (lse_out) lse_out[b * nrows + w] = l;
+            }
+        }
+    } else {
+    {
+        const float gmax = row_max(tmax);                // of the row of 16 lanes
+        if constexpr (!BESIDE) wave_sums();
+        if ((tid & 15) == 0) s_grp[tid >> 4] = gmax;
         if (tid == 0) s_ncand = 0;
     }
     __syncthreads();
@@ -454,9 +492,8 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
     }
     __syncthreads();
     const float thr = s_thr;
-    if (wave == kWavesDT - 1) {                          // beside the collection, in one wavefront's chain only
-        const float mx = row_max(s_wmax[tid & 15]);
-        const float l = mx + logf(row_sum(s_wsum[tid & 15] * exp_of(s_wmax[tid & 15] - mx)));
+    if (!BESIDE && wave == kWavesDT - 1) {               // beside the collection, in one wavefront's chain only
+        const float l = log_sum();
         if (lane == 0) {
             s_lse = l;
             if (lse_out) lse_out[b * nrows + w] = l;
@@ -488,14 +525,11 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
     }
     __syncthreads();
     int nc = s_ncand;
-    const float lse = s_lse;
+    const float lse = BESIDE ? 0.f : s_lse;
     const int64_t out0 = b * out_stride_b + static_cast<int64_t>(w) * K;
-    // The root's only row: its candidates come in the order of their scores (rounding keeps it, equal ones go by
-    // index, with a NaN all are), so the selection is the first M and nobody has to be met: 7.7 -> 5.6 us a call.
-    const bool lone = SEL && nrows == 1 && !cum;
     auto emit = [&](int k, unsigned long long key) {     // k-th best of the row
         token_out[out0 + k] = static_cast<int>(0xFFFFFFFFu - static_cast<uint32_t>(key));
-        const float sc = c + (key_value(key) - lse);
+        const float sc = BESIDE ? key_value(key) : c + (key_value(key) - lse);       // (kBeside: the logit, for the last workgroup)
         if constexpr (SEL)                               // may be read by another workgroup in this kernel
             __hip_atomic_store(reinterpret_cast<uint32_t*>(score_out + out0 + k), __float_as_uint(sc),
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -623,6 +657,7 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
             }
         }
     }
+    }
     if constexpr (SEL) {
         const int nc = nrows * K, count = min(sel.M, nc);
         auto rest = [&]() __attribute__((always_inline)) {     // what follows the selected ones
@@ -641,7 +676,7 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
         if (tid == 0) {
             int32_t* cnt = sel.counters + b * SPECVLM_COUNTER_STRIDE;
             const int ticket = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            const int last = ticket == nrows - 1;
+            const int last = ticket == static_cast<int>(gridDim.x) - 1;
             if (last) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             s_last = last;
         }
@@ -652,9 +687,19 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
         if (tid < nc) {
             sc = __uint_as_float(__hip_atomic_load(reinterpret_cast<uint32_t*>(score_out + b * out_stride_b + tid),
                                                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+            if constexpr (BESIDE) {
+                const int of = tid / K;
+                int32_t* const at = sel.counters + b * SPECVLM_COUNTER_STRIDE + 1 + of;
+                const float l = __uint_as_float(static_cast<uint32_t>(__hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)));
+                sc = (cum ? cum[b * cum_stride_b + of] : 0.f) + (sc - l);
+                score_out[b * out_stride_b + tid] = sc;
+            }
             s_cand[tid] = order_key(sc, tid);
         }
         __syncthreads();
+        if constexpr (BESIDE) {
+            if (tid < nrows) __hip_atomic_store(sel.counters + b * SPECVLM_COUNTER_STRIDE + 1 + tid, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
         rank_winners(s_cand, nc, sel.M);
         if (tid < nc) {
             const int pw = pos_of(s_cand, tid);
@@ -766,17 +811,25 @@ int32_t launch_draft_topk(int32_t dtype, int32_t B, int32_t W, int32_t V, int32_
                           int32_t* token_out, int32_t* parent_out, int64_t out_stride_b, float* lse_out,
                           int32_t M, int32_t index_base, int32_t* sel_out, float* sel_score_out,
                           int32_t* count_out, int32_t* counters, hipStream_t stream) {
-    const dim3 grid(W, B), block(kThreadsDT);
-    const SelArgs sel{M, index_base, sel_out, sel_score_out, count_out, counters};
     const bool fused = counters != nullptr;             // with the selection of the level's candidates
-#define SPECVLM_LAUNCH_TK2(T, NC, SEL)                                                                              \
-    hipLaunchKernelGGL((draft_topk_kernel<T, NC, SEL>), grid, block, 0, stream, V, K, static_cast<const T*>(logits), \
+    // Two workgroups a row (kBeside) as long as all are resident at once and a request's log-sum-exps fit behind its counter.  Not the
+    // root's row of up to 65536 entries, which needs no meeting otherwise (32000 5.6 us, 6.3 with one; 100001 14.8, 11.9), nor fp32 rows
+    // whose second reading costs more than the exponentials (eight requests of ten rows, a growth of six levels in a graph, one
+    // workgroup a row | two: 16000 tokens 52.1 | 48.8, 32000 54.5 | 55.1, 40000 61.7 | 61.8; 65000 81 | 79, 152064 144 | 142).
+    const int64_t rows = static_cast<int64_t>(B) * W;
+    const bool beside = fused && W < SPECVLM_COUNTER_STRIDE && rows <= 128 && (W > 1 || cum || V > 65536) &&
+                        (dtype == SPECVLM_BF16 || V > 65536 || rows * V <= 2200000);
+    const dim3 grid(beside ? 2 * W : W, B), block(kThreadsDT);
+    const SelArgs sel{M, index_base, sel_out, sel_score_out, count_out, counters, W};
+#define SPECVLM_LAUNCH_TK2(T, NC, LEVEL)                                                                            \
+    hipLaunchKernelGGL((draft_topk_kernel<T, NC, LEVEL>), grid, block, 0, stream, V, K, static_cast<const T*>(logits), \
                        stride_b, stride_w, cum, cum_stride_b, parent_idx, parent_stride_b, score_out,               \
                        token_out, parent_out, out_stride_b, lse_out, sel)
 #define SPECVLM_LAUNCH_TK(T, NC)                                      \
     do {                                                              \
-        if (fused) SPECVLM_LAUNCH_TK2(T, NC, true);                   \
-        else SPECVLM_LAUNCH_TK2(T, NC, false);                        \
+        if (beside) SPECVLM_LAUNCH_TK2(T, NC, kBeside);               \
+        else if (fused) SPECVLM_LAUNCH_TK2(T, NC, kSelect);           \
+        else SPECVLM_LAUNCH_TK2(T, NC, kPlain);                       \
     } while (0)
     if (dtype == SPECVLM_BF16) {
         if (V <= 4 * 8 * kThreadsDT) SPECVLM_LAUNCH_TK(uint16_t, 4);

@@ -301,8 +301,8 @@ __device__ __forceinline__ void rank_winners(unsigned long long* s_key, int c, i
 // what counts is passes, instructions per entry and the latencies between the steps.
 //   entries   chunks of 8 (from the row's first 16-byte boundary), thread t takes chunks t, t + 1024, ...; the up to
 //             7 entries before and after are one thread's each.  NC = 4, 8: a row of up to 8192 NC entries stays in
-//             registers.  NC = 0: the row streams by once, in groups of chunks with a running maximum and sum;
-//             of a chunk only its maximum is kept, and only chunks that reach the threshold are read again.
+//             registers.  NC = 0: the row streams by once, in groups of four chunks a thread with a running maximum and sum,
+//             the next group on its way while one is added up; of a chunk only its maximum is kept.
 //   lse       every thread sums against its own maximum, so maximum and sum need one meeting of the workgroup
 //             instead of two; lanes meet by DPP.
 //   Top-K     every row of 16 lanes reduces its greatest logit; the K-th greatest of the 64 is a value that at least K
@@ -326,7 +326,9 @@ __device__ __forceinline__ void rank_winners(unsigned long long* s_key, int c, i
 // 32000) alone.  They store a log-sum-exp and K logits; the scores are put together by the one that selects, from the same operations.
 // A growth of six levels, ten rows each but the root, in a graph, one workgroup a row -> two: bf16, one request 32000 tokens 48.8 -> 44.4 us,
 // 65000 59.4 -> 53.8, 152064 108.2 -> 94.0; eight requests 54.0 -> 50.1, 63.0 -> 60.6, 121.7 -> 106.7; fp32, one 50.4 -> 47.3, 62.3 -> 58.5,
-// 110.7 -> 98.0.  (Tried: the log-sum-exp of a long row shared by up to five workgroups in segments of 32768 entries, and rows of up to
+// 110.7 -> 98.0.  Then rows beyond 65536 entries requested a group ahead, nothing summed where a row has ended, chunks that reach
+// the threshold found by a bit mask: bf16, one request 70000 69.9 -> 65.9, 100001 81.7 -> 75.4, 152064 94.5 -> 87.8, eight 106.2 -> 95.5; fp32
+// 99.1 -> 92.0, 140.1 -> 129.1 (four or eight chunks of bf16 a group: 87.8 and 92.6).  (Tried: the log-sum-exp of a long row shared by up to five workgroups in segments of 32768 entries, and rows of up to
 // 163840 bf16 entries in registers: the segments' reductions cost the other calls 1 us, the longer unrolled code 5.)
 struct SelArgs {
     int M, index_base;
@@ -408,12 +410,18 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
     } else {
         m = fmaxf(es, kLowest);
         sum = es > -INFINITY ? 1.f : 0.f;
-        auto take = [&](int k0, float (&cm)[U]) __attribute__((always_inline)) {        // chunks k0, k0 + 1024, ...
+        Chunk<T> next[U];                                // the group after the one being taken, on its way
+        auto request = [&](int k0) __attribute__((always_inline)) {                     // chunks k0, k0 + 1024, ...
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int k = k0 + kThreadsDT * u;
-                if (k < nck) ch[u].load(body + 8 * static_cast<int64_t>(k)); else ch[u].fill();
+                if (k < nck) next[u].load(body + 8 * static_cast<int64_t>(k)); else next[u].fill();
             }
+        };
+        auto take = [&](int j, float (&cm)[U]) __attribute__((always_inline)) {         // group j, j + 1, ... j + U - 1 of 1024 chunks
+#pragma unroll
+            for (int u = 0; u < U; ++u) ch[u] = next[u];
+            if ((j + U) * kThreadsDT < nck) request(tid + kThreadsDT * (j + U));        // uniform
             float gm = -INFINITY;
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -426,23 +434,25 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
             float part[4] = {sum * exp_of(m - mn), 0.f, 0.f, 0.f};         // (times exactly 1 where the maximum stays)
 #pragma unroll
             for (int u = 0; u < U; ++u)
+                if ((j + u) * kThreadsDT < nck)          // uniform
 #pragma unroll
-                for (int e = 0; e < 8; ++e) part[e & 3] += exp_of(ch[u].at(e) - mn);
+                    for (int e = 0; e < 8; ++e) part[e & 3] += exp_of(ch[u].at(e) - mn);
             sum = (part[0] + part[1]) + (part[2] + part[3]);
             m = mn;
         };
+        request(tid);
 #pragma unroll
         for (int j = 0; j < kStream; j += U) {
             float cm[U];
 #pragma unroll
             for (int u = 0; u < U; ++u) cm[u] = -INFINITY;
-            if (j * kThreadsDT < nck) take(tid + kThreadsDT * j, cm);       // uniform
+            if (j * kThreadsDT < nck) take(j, cm);       // uniform
 #pragma unroll
             for (int u = 0; u < U; ++u) cmax[j + u] = cm[u];
         }
         for (int j = kStream; j * kThreadsDT < nck; j += U) {               // (vocabularies beyond 196608)
             float cm[U];
-            take(tid + kThreadsDT * j, cm);
+            take(j, cm);
         }
     }
     auto wave_sums = [&]() __attribute__((always_inline)) {
@@ -509,12 +519,25 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
     };
     if (tmax >= thr) {
         if (vs >= 0) collect(es, vs);
+        // Registers need a copy of this code per chunk, of which a wavefront takes one or two and fetches all: from eight chunks on
+        // the few that reach the threshold are read again (eight requests of 65000 bf16 tokens 60.5 -> 59.1 us a growth; with four chunks
+        // in registers reading again costs 1 us)
+        if constexpr (NC > 0 && NC <= 4) {
 #pragma unroll
-        for (int j = 0; j < NM; ++j) {
-            const int k = tid + kThreadsDT * j;
-            if (cmax[j] >= thr && k < nck) {
+            for (int j = 0; j < NM; ++j) {
+                const int k = tid + kThreadsDT * j;
+                if (cmax[j] >= thr && k < nck)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) collect(ch[j].at(e), head + 8 * k + e);
+            }
+        } else {
+            uint32_t hits = 0;
+#pragma unroll
+            for (int j = 0; j < NM; ++j) hits |= static_cast<uint32_t>(cmax[j] >= thr && tid + kThreadsDT * j < nck) << j;
+            for (; hits; hits &= hits - 1) {
+                const int k = tid + kThreadsDT * __builtin_ctz(hits);
                 Chunk<T> again;
-                if constexpr (NC > 0) again = ch[j]; else again.load(body + 8 * k);
+                again.load(body + 8 * k);
 #pragma unroll
                 for (int e = 0; e < 8; ++e) collect(again.at(e), head + 8 * k + e);
             }

@@ -10,19 +10,21 @@
 //
 // One 1024-thread workgroup per request.  The walk is sequential (at most path_cap levels) on one compute
 // unit, so it is bound by latencies and by the instructions of passes over a vocabulary row.
-//   row       up to 64 consecutive tokens per thread stay in registers (CH = 32, 64); the root's row is requested
-//             before the tree is looked at.  Larger vocabularies (CH = 0): one pass for the maximum (16-byte
-//             loads), one for the sum of exp2((l - max) log2e / T), and one for the bonus draw's chunk sums in 16-byte loads.
+//   row       up to 32 consecutive tokens per thread stay in registers where they are whole vectors (CH = 32); the root's row is
+//             requested before the tree is looked at.  Other vocabularies (CH = 0) are read once a level: wavefronts have contiguous
+//             regions, every load is 1 KB of memory in one piece, and lanes sum exp2((l - m) log2e / T) against the greatest logit they
+//             have met, until the workgroup's is known
 //   sums      in a fixed order, so that the same input gives the same decision whatever the timing; lanes
 //             meet by DPP and lane swaps in the order of an xor butterfly (32, 16, 8, 4, 2, 1), then the 16
 //             wavefronts through LDS in order
 //   children  wavefront 0 holds a child per lane: what the earlier ones have taken is a running sum over lanes,
 //             then all acceptance thresholds are computed at once and the first accepted child is a bit scan
-//   bonus     a two-level scan: every thread sums a contiguous chunk of the vocabulary, the chunk sums are
-//             scanned, and the chunk that contains the drawn position is walked (CH = 0: its probabilities are
-//             computed by the whole workgroup first)
-// Kernel alone, 4 requests, bf16: 32000 tokens 10.9 us, 20003 13.3, 60000 22.7, 65536 17.7, 152064 34.4 (beyond 65536, passes that
-// read token by token took 198 us).
+//   bonus     a scan of the chunk sums, and the chunk that contains the drawn position is walked.  CH = 0: the regions' sums are there
+//             already (regions with a rejected token are added up again without it); the region that contains the position
+//             is taken apart into blocks of a wavefront's load, the block into lanes, the lane's vector is walked
+// In a graph, 4 requests, us, three passes over rows beyond 64 tokens a thread -> one: bf16 100001 tokens 27.2 -> 20.4, 152064 34.6 -> 24.7 (16
+// requests 42.0 -> 29.4), 250000 50.6 -> 34.1; fp32 28.2 -> 21.3, 37.1 -> 28.1, 54.6 -> 37.5.  What bounds the long ones is the
+// exponentials of a row on one compute unit.
 #include "chunk_vectors.hpp"
 #include "wave_ops.hpp"
 
@@ -31,7 +33,7 @@ namespace specvlm {
 namespace {
 
 constexpr int kThreadsAS = 1024;
-constexpr int kWalk = 2048;              // CH == 0: longest chunk whose probabilities are laid out in LDS
+constexpr float kLowestAS = -3.402823466e38f;         // reference of a lane without tokens: no finite logit is below it
 
 template <typename T>
 __device__ __forceinline__ float logit_at(const T* p, int v);
@@ -79,13 +81,53 @@ __device__ __forceinline__ float vec_at(const uint4& w, int e) {
     else return __uint_as_float(x);
 }
 
-// CH > 0: every thread keeps its chunk of the current row (at most CH consecutive tokens) in
-// registers, loaded once per level with 16-byte loads; WHOLE: the chunks of every row are whole aligned vectors.
-// (CH = 64 without WHOLE does not quite fit its 128 registers: 164 bytes of scratch a lane in fp32, 8 in bf16.  Reading such fp32 rows
-// again, as CH = 0 does, is faster by up to a third - 4 requests of 50001 tokens 24.6 us here, 17.2 there - but adds in another order.)
-// (Two kernels: with both ways of loading in one, 4 requests of 32000 tokens took 12.5 us in place of 10.9, 65536 22.8 of 17.7.)
-// CH == 0: any vocabulary size, every pass reads the row again (from L2).
-template <typename T, int CH, bool WHOLE>
+// CH == 0: a row as aligned 16-byte vectors (the first and the last may reach past its ends), dealt out to the wavefronts in contiguous
+// regions of whole blocks of 64 vectors, so that every load of a wavefront is one piece of memory.
+template <typename T>
+struct RowVectors {
+    static constexpr int VEC = 16 / sizeof(T);
+    const uint4* body = nullptr;
+    int lead = 0, lo = 0, hi = 0, end = 0, per = 0, r0 = 0, r1 = 0, V = 0;
+    __device__ RowVectors() {}
+    __device__ RowVectors(const T* row, int V_) : V(V_) {
+        const ChunkVectors cv(reinterpret_cast<uintptr_t>(row), 0, V, V, VEC);
+        lead = cv.lead, lo = cv.lo, hi = cv.hi, end = cv.count;
+        body = reinterpret_cast<const uint4*>(row - lead);
+        per = ((end + kThreadsAS / 64 - 1) / (kThreadsAS / 64) + 63) & ~63;
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        r0 = min(wave * per, end);
+        r1 = min(r0 + per, end);
+    }
+    __device__ bool whole(int k) const { return k >= lo && k <= hi; }
+    __device__ uint4 load(int k) const { return body[k]; }
+    __device__ int first(int k) const { return k * VEC - lead; }
+    __device__ int vector_at(int v) const { return (v + lead) / VEC; }
+    // take(vectors, number of the first, 64 apart) for this lane's whole vectors of its wavefront's region, eight or one at a time; one(token) for the entries of the others; eight loads in flight
+    template <typename Take, typename One>
+    __device__ __forceinline__ void each(Take&& take, One&& one) const {
+        const int lane = threadIdx.x & 63, from = max(r0, lo), to = min(r1, hi + 1);
+        int k = from + lane;
+        for (; k + 64 * 7 < to; k += 64 * 8) {
+            uint4 w[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) w[u] = body[k + 64 * u];
+            take(w, k);
+        }
+        for (; k < to; k += 64) {
+            const uint4 w[1] = {body[k]};
+            take(w, k);
+        }
+        if (r0 < r1 && lane < VEC) {
+            if (r0 < lo && first(0) + lane >= 0 && first(0) + lane < V) one(first(0) + lane);
+            if (r1 - 1 > hi && end > lo && first(end - 1) + lane < V) one(first(end - 1) + lane);
+        }
+    }
+};
+
+// CH > 0: every thread keeps its chunk of the current row (at most CH consecutive tokens, whole aligned vectors) in
+// registers, loaded once per level with 16-byte loads.
+// CH == 0: any vocabulary size at any alignment, a level reads its row once.
+template <typename T, int CH>
 __global__ __launch_bounds__(kThreadsAS) void tree_accept_sample_kernel(
     int N_max, int V, int path_cap, const int32_t* __restrict__ parent, const int32_t* __restrict__ draft_tok,
     const T* __restrict__ logits, int64_t stride_b, int64_t stride_n, const int32_t* __restrict__ num_nodes,
@@ -96,7 +138,6 @@ __global__ __launch_bounds__(kThreadsAS) void tree_accept_sample_kernel(
     __shared__ int s_rej[SPECVLM_MAX_NODES];           // tokens rejected at the current node
     __shared__ float s_red[kThreadsAS / 64];
     __shared__ float s_scan[kThreadsAS];
-    __shared__ float s_ev[CH > 0 ? 1 : kWalk];
     __shared__ int s_next, s_nrej, s_err, s_pick, s_chunk;
 
     const int b = blockIdx.x, tid = threadIdx.x;
@@ -139,36 +180,12 @@ __global__ __launch_bounds__(kThreadsAS) void tree_accept_sample_kernel(
         if constexpr (CH > 0) {
 #pragma unroll
             for (int j = 0; j < NV; ++j) lv[j] = uint4{kInfWord, kInfWord, kInfWord, kInfWord};
-            if constexpr (WHOLE) {
 #pragma unroll
-                for (int j = 0; j < NV; ++j)
-                    if (v0 + j * VEC < v1) lv[j] = *reinterpret_cast<const uint4*>(row + v0 + j * VEC);
-            } else {
-                // Most vocabularies: chunks start at any token.  16 bytes a load all the same (gfx950 takes them at any alignment
-                // of their type); only the vector that the row ends in is read entry by entry.  (Every entry of its own, bf16:
-                // 4 requests of 60000 tokens 39.4 us, now 22.7; 20003 15.5, now 13.3.)
-#pragma unroll
-                for (int j = 0; j < NV; ++j) {
-                    const int at = v0 + j * VEC;
-                    if (at < v1) {
-                        if (at + VEC <= V) {
-                            __builtin_memcpy(&lv[j], row + at, 16);
-                        } else {
-#pragma unroll
-                            for (int e = 0; e < VEC - 1; ++e)
-                                if (at + e < V) put(lv[j], e, row[at + e]);
-                        }
-                    }
-                }
-#pragma unroll
-                for (int j = 0; j < NV; ++j)
-                    if (v0 + j * VEC < v1 && v0 + (j + 1) * VEC > v1)       // the vector that the chunk ends in: entries of the next
-#pragma unroll
-                        for (int e = 1; e < VEC; ++e)
-                            if (v0 + j * VEC + e >= v1) put(lv[j], e, sizeof(T) == 2 ? static_cast<T>(0xFF80u) : static_cast<T>(-INFINITY));
-            }
+            for (int j = 0; j < NV; ++j)
+                if (v0 + j * VEC < v1) lv[j] = *reinterpret_cast<const uint4*>(row + v0 + j * VEC);
         }
     };
+    RowVectors<T> rv;                                   // CH == 0: the current row
     load_row(base);                                     // the root's row, whatever the tree is
     int err = 0;
     int n = num_nodes ? num_nodes[b] : N_max;
@@ -224,18 +241,34 @@ __global__ __launch_bounds__(kThreadsAS) void tree_accept_sample_kernel(
                 part = fmaxf(part, vec_at<T>(lv[i / VEC], i % VEC));
             repack();
         } else {
-            const int head = min(static_cast<int>(((16u - (reinterpret_cast<uintptr_t>(row) & 15u)) & 15u) / sizeof(T)), V);
-            const int nvec = (V - head) / VEC, tail0 = head + nvec * VEC;
-            if (tid < head) part = logit_at<T>(row, tid);
-            if (tid >= 64 && tid - 64 < V - tail0) part = logit_at<T>(row, tail0 + tid - 64);
-            const uint4* body = reinterpret_cast<const uint4*>(row + head);
-#pragma unroll 4
-            for (int c = tid; c < nvec; c += kThreadsAS) {
-                const uint4 w = body[c];
+            // once through the row: every lane sums against the greatest logit it has met
+            rv = RowVectors<T>(row, V);
+            float sum = 0.f;
+            part = kLowestAS;
+            auto meet = [&](float m) __attribute__((always_inline)) {
+                mx = fmaxf(part, m);                   // (prob_of is relative to it)
+                sum *= prob_of(part);                  // (by exactly 1 where the reference stays)
+                part = mx;
+            };
+            rv.each([&](const auto& w, int) __attribute__((always_inline)) {
+                float m = -INFINITY;
 #pragma unroll
-                for (int e = 0; e < VEC; ++e) part = fmaxf(part, vec_at<T>(w, e));
-            }
+                for (const uint4& x : w)
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e) m = fmaxf(m, vec_at<T>(x, e));
+                meet(m);
+#pragma unroll
+                for (const uint4& x : w)
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e) sum += prob_of(vec_at<T>(x, e));
+            }, [&](int v) {
+                const float l = logit_at<T>(row, v);
+                meet(l);
+                sum += prob_of(l);
+            });
+            mass = sum;
         }
+        const float mine = part;                       // CH == 0: what `mass` is relative to
         mx = block_max(part, s_red);
         part = 0.f;
         if constexpr (CH > 0) {
@@ -244,16 +277,7 @@ __global__ __launch_bounds__(kThreadsAS) void tree_accept_sample_kernel(
                 part += prob_of(vec_at<T>(lv[i / VEC], i % VEC));          // (adding the zeros of -inf changes nothing)
             repack();
         } else {
-            // (a thread's tokens are 1024 apart and added in that order; 16 loads in flight)
-            int v = tid;
-            for (; v + 15 * kThreadsAS < V; v += 16 * kThreadsAS) {
-                float l[16];
-#pragma unroll
-                for (int u = 0; u < 16; ++u) l[u] = logit_at<T>(row, v + u * kThreadsAS);
-#pragma unroll
-                for (int u = 0; u < 16; ++u) part += prob_of(l[u]);
-            }
-            for (; v < V; v += kThreadsAS) part += prob_of(logit_at<T>(row, v));
+            part = mass * prob_of(mine);
         }
         mass = part;
         Z = block_sum(part, s_red);
@@ -305,10 +329,12 @@ __global__ __launch_bounds__(kThreadsAS) void tree_accept_sample_kernel(
     // ---- bonus token: inverse CDF over the residual distribution at cur, in vocabulary order ----
     const T* row = base + cur * stride_n;
     const int nrej = s_nrej;
-    float csum = 0.f;
-    unsigned long long mine = 0;                       // bit r: rejected token r lies in this thread's chunk
-    for (int r = 0; r < nrej; ++r) mine |= static_cast<unsigned long long>(s_rej[r] >= v0 && s_rej[r] < v1) << r;
-    if constexpr (CH > 0) {                            // lv[] still holds cur's row
+    const int lane = tid & 63, wave = tid >> 6;
+    if constexpr (CH > 0) {
+        float csum = 0.f;
+        unsigned long long mine = 0;                   // bit r: rejected token r lies in this thread's chunk
+        for (int r = 0; r < nrej; ++r) mine |= static_cast<unsigned long long>(s_rej[r] >= v0 && s_rej[r] < v1) << r;
+        // lv[] still holds cur's row
         // A chunk without a rejected token has the sum that went into Z, added up in the same order; few
         // wavefronts hold any other (all of them summing again: 32000 tokens 12.1 us, now 10.9; 65536 19.6, now 17.7).
         csum = mass;
@@ -319,65 +345,27 @@ __global__ __launch_bounds__(kThreadsAS) void tree_accept_sample_kernel(
             for (int i = 0; i < CH; ++i) csum += prob_of(vec_at<T>(lv[i / VEC], i % VEC));
         }
         repack();
-    } else {
-        if (v0 < v1) {
-            // 16-byte vectors; entries outside the chunk count as zero, which changes no sum.  A vector that is not
-            // whole inside the row is replaced by another one of it, then patched entry by entry.
-            const ChunkVectors cv(reinterpret_cast<uintptr_t>(row), v0, v1, V, VEC);
-            const int lead = cv.lead, len = v1 - v0;
-            const uint4* pv = reinterpret_cast<const uint4*>(row + v0 - lead);
-            for (int k = 0; k < cv.count; k += 4) {
-                uint4 w[4];
+        // inclusive scan of the chunk sums: inside each wavefront by shuffles, then the 16 wavefront
+        // totals (summed in order by every thread) as offsets
+        float incl = csum;
 #pragma unroll
-                for (int u = 0; u < 4; ++u) w[u] = pv[min(max(k + u, cv.lo), cv.hi)];
-                if (k < cv.lo || (cv.hi < cv.count - 1 && k + 3 > cv.hi)) {       // (the row's first and last threads only)
-#pragma unroll
-                    for (int u = 0; u < 4; ++u)
-                        if (k + u < cv.lo || k + u > cv.hi)
-#pragma unroll
-                            for (int e = 0; e < VEC; ++e) {
-                                const int at = (k + u) * VEC + e - lead;
-                                if (static_cast<unsigned>(at) >= static_cast<unsigned>(len)) continue;
-                                uint32_t& x = (&w[u].x)[sizeof(T) == 2 ? e >> 1 : e];
-                                if constexpr (sizeof(T) == 2) x = (x & (0xFFFF0000u >> (16 * (e & 1)))) | static_cast<uint32_t>(row[v0 + at]) << (16 * (e & 1));
-                                else x = __float_as_uint(row[v0 + at]);
-                            }
-                }
-                for (unsigned long long r = mine; r; r &= r - 1) drop(w, 4, s_rej[__builtin_ctzll(r)] - v0 + lead - k * VEC);
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-#pragma unroll
-                    for (int e = 0; e < VEC; ++e) {
-                        const int at = (k + u) * VEC + e - lead;        // position in the chunk
-                        const float pe = prob_of(vec_at<T>(w[u], e));
-                        csum += static_cast<unsigned>(at) < static_cast<unsigned>(len) ? pe : 0.f;
-                    }
-            }
+        for (int off = 1; off < 64; off <<= 1) {
+            const float up = __shfl_up(incl, off);
+            if (lane >= off) incl += up;
         }
-    }
-    // inclusive scan of the chunk sums: inside each wavefront by shuffles, then the 16 wavefront
-    // totals (summed in order by every thread) as offsets
-    float incl = csum;
-    const int lane = tid & 63, wave = tid >> 6;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const float up = __shfl_up(incl, off);
-        if (lane >= off) incl += up;
-    }
-    if (tid == 0) { s_pick = -1; s_chunk = -1; }
-    __syncthreads();                                   // s_red is free (last use: the row sum)
-    if (lane == 63) s_red[wave] = incl;
-    __syncthreads();
-    float offset = 0.f;
-    for (int w = 0; w < wave; ++w) offset += s_red[w];
-    s_scan[tid] = incl + offset;
-    __syncthreads();
-    const float total = s_scan[kThreadsAS - 1];
-    const float t = u_bonus[b] * total;
-    const float before = tid ? s_scan[tid - 1] : 0.f;
-    if (s_scan[tid] > t && before <= t) s_chunk = tid; // the scan is non-decreasing: exactly one such chunk
-    __syncthreads();
-    if constexpr (CH > 0) {
+        if (tid == 0) { s_pick = -1; s_chunk = -1; }
+        __syncthreads();                               // s_red is free (last use: the row sum)
+        if (lane == 63) s_red[wave] = incl;
+        __syncthreads();
+        float offset = 0.f;
+        for (int w = 0; w < wave; ++w) offset += s_red[w];
+        s_scan[tid] = incl + offset;
+        __syncthreads();
+        const float total = s_scan[kThreadsAS - 1];
+        const float t = u_bonus[b] * total;
+        const float before = tid ? s_scan[tid - 1] : 0.f;
+        if (s_scan[tid] > t && before <= t) s_chunk = tid; // the scan is non-decreasing: exactly one such chunk
+        __syncthreads();
         if (s_chunk == tid) {
             float cum = before;
             int pick = -1, last_live = -1;
@@ -388,33 +376,124 @@ __global__ __launch_bounds__(kThreadsAS) void tree_accept_sample_kernel(
                 cum += ev;
                 if (pick < 0 && cum > t) pick = v0 + i;
             }
-            s_pick = pick >= 0 ? pick : last_live;    // rounding inside the chunk: its last live token
+            s_pick = pick >= 0 ? pick : last_live;     // rounding inside the chunk: its last live token
         }
-    } else if (s_chunk >= 0) {                         // uniform
-        const int c0 = min(s_chunk * chunk, V), len = min(chunk, V - c0);
-        auto walk = [&](auto&& ev_of) {
-            float cum = s_chunk ? s_scan[s_chunk - 1] : 0.f;
-            int pick = -1, last_live = -1;
-#pragma unroll 4
-            for (int i = 0; i < len; ++i) {
-                const float ev = ev_of(i);
-                if (ev > 0.f && pick < 0) last_live = c0 + i;
-                cum += ev;
-                if (cum > t && pick < 0) pick = c0 + i;
+    } else {
+        // s_red[w] holds the sum of wavefront w's region of the row; regions with a rejected token are added up without it
+        auto rejected_in = [&](int from, int to) __attribute__((always_inline)) -> unsigned long long {     // bit r: token r
+            unsigned long long some = 0;
+            for (int r = 0; r < nrej; ++r) {
+                const int k = rv.vector_at(s_rej[r]);
+                some |= static_cast<unsigned long long>(k >= from && k < to) << r;
             }
-            s_pick = pick >= 0 ? pick : last_live;
+            return some;
         };
-        auto residual_at = [&](int v) -> float {
-            bool live = true;
-            for (int r = 0; r < nrej; ++r) live = live && s_rej[r] != v;
-            return live ? prob_of(logit_at<T>(row, v)) : 0.f;
+        auto without = [&](uint4& w, int k, unsigned long long some) __attribute__((always_inline)) {
+            for (; some; some &= some - 1) {           // uniform in a wavefront
+                const int at = s_rej[__builtin_ctzll(some)] - rv.first(k);
+                if (static_cast<unsigned>(at) < static_cast<unsigned>(VEC)) drop(&w, 1, at);
+            }
         };
-        if (len <= kWalk) {                            // uniform
-            for (int i = tid; i < len; i += kThreadsAS) s_ev[i] = residual_at(c0 + i);
+        auto sum_of = [&](const uint4& w) __attribute__((always_inline)) -> float {
+            float x = 0.f;
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) x += prob_of(vec_at<T>(w, e));
+            return x;
+        };
+        auto vector_of = [&](int k, unsigned long long some) __attribute__((always_inline)) -> uint4 {
+            uint4 w{kInfWord, kInfWord, kInfWord, kInfWord};
+            if (rv.whole(k)) {
+                w = rv.load(k);
+            } else if (k < rv.end) {
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) {
+                    const int v = rv.first(k) + e;
+                    if (v >= 0 && v < V) put(w, e, row[v]);
+                }
+            }
+            without(w, k, some);
+            return w;
+        };
+        if (const unsigned long long mine = rejected_in(rv.r0, rv.r1)) {           // uniform in a wavefront
+            float sum = 0.f;
+            rv.each([&](auto& ws, int k) __attribute__((always_inline)) {
+                for (uint4 w : ws) {
+                    without(w, k, mine);
+                    sum += sum_of(w);
+                    k += 64;
+                }
+            }, [&](int v) {
+                bool live = true;
+                for (int r = 0; r < nrej; ++r) live = live && s_rej[r] != v;
+                sum += live ? prob_of(logit_at<T>(row, v)) : 0.f;
+            });
+            sum = butterfly_sum(sum);
+            if (lane == 0) s_red[wave] = sum;
+        }
+        if (tid == 0) s_pick = -1;
+        __syncthreads();
+        float total = 0.f;
+        for (int w = 0; w < kThreadsAS / 64; ++w) total += s_red[w];
+        const float t = u_bonus[b] * total;
+        // the region, then the block of 64 steps of `each` vectors, then the lane that the drawn position is in.  Where rounding
+        // leaves it past all parts of the one before, it is the last that holds anything.
+        float before = 0.f;
+        int region = 0;
+        for (; region < kThreadsAS / 64 && before + s_red[region] <= t; ++region) before += s_red[region];
+        if (region < kThreadsAS / 64) {                // uniform
+            const int r0 = min(region * rv.per, rv.end), r1 = min(r0 + rv.per, rv.end);
+            const int each = (r1 - r0 + 64 * kThreadsAS - 1) / (64 * kThreadsAS), blocks = (r1 - r0 + 64 * each - 1) / (64 * each);
+            const unsigned long long some = rejected_in(r0, r1);
+            auto lane_sum = [&](int block) __attribute__((always_inline)) -> float {
+                float x = 0.f;
+                for (int i = 0; i < each; ++i) {
+                    const int k = r0 + (block * 64 + lane) * each + i;
+                    if (k < r1) x += sum_of(vector_of(k, some));
+                }
+                return x;
+            };
+            for (int block = wave; block < blocks; block += kThreadsAS / 64) {
+                const float x = butterfly_sum(lane_sum(block));
+                if (lane == 0) s_scan[block] = x;
+            }
             __syncthreads();
-            if (tid == 0) walk([&](int i) { return s_ev[i]; });
-        } else if (tid == 0) {
-            walk([&](int i) { return residual_at(c0 + i); });
+            if (wave == 0) {
+                int block = -1, last = 0;
+                float at_last = before;
+                for (int i = 0; i < blocks && block < 0; ++i) {
+                    const float x = s_scan[i];
+                    if (x > 0.f) { last = i; at_last = before; }
+                    if (before + x > t) block = i; else before += x;
+                }
+                if (block < 0) { block = last; before = at_last; }
+                const float x = lane_sum(block);
+                float incl = x;
+#pragma unroll
+                for (int off = 1; off < 64; off <<= 1) {
+                    const float up = __shfl_up(incl, off);
+                    if (lane >= off) incl += up;
+                }
+                const float up = __shfl_up(incl, 1);
+                float cum = before + (lane ? up : 0.f);
+                const unsigned long long past = __ballot(before + incl > t && x > 0.f), any = __ballot(x > 0.f);
+                const int who = past ? __builtin_ctzll(past) : any ? 63 - __builtin_clzll(any) : -1;
+                if (lane == who) {
+                    int pick = -1, last_live = -1;
+                    for (int i = 0; i < each; ++i) {
+                        const int k = r0 + (block * 64 + lane) * each + i;
+                        if (k >= r1) break;
+                        const uint4 w = vector_of(k, some);
+#pragma unroll
+                        for (int e = 0; e < VEC; ++e) {
+                            const float ev = prob_of(vec_at<T>(w, e));
+                            if (ev > 0.f) last_live = rv.first(k) + e;
+                            cum += ev;
+                            if (pick < 0 && cum > t && ev > 0.f) pick = rv.first(k) + e;
+                        }
+                    }
+                    s_pick = pick >= 0 ? pick : last_live;
+                }
+            }
         }
     }
     __syncthreads();
@@ -450,27 +529,23 @@ int32_t launch_tree_accept_sample(int32_t dtype, int32_t B, int32_t N_max, int32
                                   int32_t* accept_len, int32_t* path, int32_t* bonus_tok,
                                   int32_t* committed_tok, int32_t* err_flag, hipStream_t stream) {
     dim3 grid(B), block(kThreadsAS);
-#define SPECVLM_LAUNCH_AS2(T, CH, WHOLE)                                                                             \
-    hipLaunchKernelGGL((tree_accept_sample_kernel<T, CH, WHOLE>), grid, block, 0, stream, N_max, V, path_cap, parent, \
+#define SPECVLM_LAUNCH_AS(T, CH)                                                                                     \
+    hipLaunchKernelGGL((tree_accept_sample_kernel<T, CH>), grid, block, 0, stream, N_max, V, path_cap, parent,       \
                        draft_tok, static_cast<const T*>(logits), stride_b, stride_n, num_nodes, temperature,         \
                        u_accept, u_bonus, accept_len, path, bonus_tok, committed_tok, err_flag)
-#define SPECVLM_LAUNCH_AS(T, CH)                     \
-    do {                                             \
-        if (whole) SPECVLM_LAUNCH_AS2(T, CH, true);  \
-        else SPECVLM_LAUNCH_AS2(T, CH, false);       \
-    } while (0)
+    // Registers where every chunk is whole vectors and at most 32 tokens, chunks 64 bytes apart at most: us, 4 requests in a graph, registers |
+    // reading once: 32000 bf16 11.0 | 13.4, 16000 11.8 | 12.5, fp32 12.0 | 12.8 (8000: 11.5 | 11.2, 4000 fp32 11.0 | 10.7).  Chunks at
+    // other places lost there: 4000 bf16 13.5 | 10.6, 20003 15.2 | 12.9, 30000 fp32 14.7 | 13.3, bf16 13.1 | 13.1; and so did 33 - 64 tokens a
+    // thread: 36864 bf16 21.1 | 14.6, 65536 20.0 | 16.2, 60000 22.9 | 15.7, fp32 27.2 | 17.6.
     const int chunk = (V + kThreadsAS - 1) / kThreadsAS, vec = dtype == SPECVLM_BF16 ? 8 : 4;
-    const bool whole = (reinterpret_cast<uintptr_t>(logits) & 15u) == 0 && (stride_b | stride_n | chunk | V) % vec == 0;
+    const bool held = chunk <= 32 && (reinterpret_cast<uintptr_t>(logits) & 15u) == 0 && (stride_b | stride_n | chunk | V) % vec == 0;
     if (dtype == SPECVLM_BF16) {
-        if (chunk <= 32) SPECVLM_LAUNCH_AS(uint16_t, 32);
-        else if (chunk <= 64) SPECVLM_LAUNCH_AS(uint16_t, 64);
-        else SPECVLM_LAUNCH_AS2(uint16_t, 0, false);
+        if (held) SPECVLM_LAUNCH_AS(uint16_t, 32);
+        else SPECVLM_LAUNCH_AS(uint16_t, 0);
     } else {
-        if (chunk <= 32) SPECVLM_LAUNCH_AS(float, 32);
-        else if (chunk <= 64) SPECVLM_LAUNCH_AS(float, 64);
-        else SPECVLM_LAUNCH_AS2(float, 0, false);
+        if (held) SPECVLM_LAUNCH_AS(float, 32);
+        else SPECVLM_LAUNCH_AS(float, 0);
     }
-#undef SPECVLM_LAUNCH_AS2
 #undef SPECVLM_LAUNCH_AS
     return check_launch();
 }

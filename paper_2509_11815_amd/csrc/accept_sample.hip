@@ -440,7 +440,7 @@ __global__ __launch_bounds__(kThreadsAS) void tree_accept_sample_kernel(
         float before = 0.f;
         int region = 0;
         for (; region < kThreadsAS / 64 && before + s_red[region] <= t; ++region) before += s_red[region];
-        if (region < kThreadsAS / 64) {                // uniform
+        if (region < kThreadsAS / 64 && t >= 0.f) {    // uniform (a position that is NaN or negative is in no region)
             const int r0 = min(region * rv.per, rv.end), r1 = min(r0 + rv.per, rv.end);
             const int each = (r1 - r0 + 64 * kThreadsAS - 1) / (64 * kThreadsAS), blocks = (r1 - r0 + 64 * each - 1) / (64 * each);
             const unsigned long long some = rejected_in(r0, r1);

@@ -46,7 +46,7 @@ def test_ends_of_blocks_and_regions(sv, oracle, dtype, V):
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
-@pytest.mark.parametrize("V", [513, 65537, 131072])
+@pytest.mark.parametrize("V", [512, 513, 65537, 131072])
 def test_little_finite(sv, dtype, V):
     """One token above a row of -inf or of the type's lowest value, a row of nothing but the lowest value, a row of -inf."""
     low = torch.finfo(dtype).min
@@ -62,3 +62,8 @@ def test_little_finite(sv, dtype, V):
         assert m.tolist() == [0] * 4 and b[0] == V - 1 and b[1] == V // 2 and b[3] == 0
         # V equal tokens less the rejected token 1, within the rounding of sums of up to V ones
         assert b[2] != 1 and abs(b[2] - u * (V - 1)) <= 2 + 1e-5 * V
+    # a position that is none: the last live token, as in the register form
+    for u in (-0.5, float("nan")):
+        bonus = sv.specvlm_tree_accept_sample(parent, tok, x, torch.ones((4, 2), device="cuda"), torch.full((4,), u, device="cuda"),
+                                              temperature=1.0, path_cap=4)[2]
+        assert bonus.tolist() == [V - 1, V // 2, V - 1, 0]

@@ -28,6 +28,7 @@
 #include <type_traits>
 
 #include "attn_rows.hpp"
+#include "lengths.hpp"
 
 namespace specvlm {
 
@@ -82,6 +83,7 @@ __device__ __forceinline__ void attend(const StreamsParams& p) {
     constexpr int NQ = kQRows / RPI / 4;                 // query-row load instructions per wavefront
     constexpr int OWN = NT / 2;                          // (32 query rows, 32 head dims) blocks of an owner at the merge
     static_assert(kWaveWgs * kRingBytes >= 4 * 3 * OWN * 4096, "merge scratch must fit in the rings");
+    static_assert(kSharesRound == kWaveWgs * kKeys, "a round is a tile of every stream");
 
     __shared__ __attribute__((aligned(1024))) unsigned char s_ring[kWaveWgs * kRingBytes];
     __shared__ __attribute__((aligned(1024))) unsigned char s_q[kQRows * D * 2];
@@ -198,12 +200,11 @@ __device__ __forceinline__ void attend(const StreamsParams& p) {
         wait_vmcnt<1 + (PAGED ? 0 : KLD) + NQ>();
         const int my_P = __float_as_int(s_m[wave][lane]);
         const int my_n = p.num_nodes ? __float_as_int(s_l[wave][lane]) : p.N_max;
-        const int keys = min(max(my_P, 0) + min(max(my_n, 1), p.N_max), p.g.capacity);      // (a bad request's too)
-        const int rounds = (lane & 15) < p.B ? (keys + kWaveWgs * kKeys - 1) / (kWaveWgs * kKeys) : 0;
+        const int keys = keys_of(my_P, my_n, p.N_max, p.g.capacity);
+        const int rounds = (lane & 15) < p.B ? (keys + kSharesRound - 1) / kSharesRound : 0;
         const int longest = __builtin_amdgcn_readlane(row_scan(rounds, [](int x, int y) { return max(x, y); }), 15);
         const int total = __builtin_amdgcn_readlane(row_scan(rounds, [](int x, int y) { return x + y; }), 15);
-        const float most = static_cast<float>(rounds) - 0.5f;
-        auto columns_for = [&](float len) __attribute__((always_inline)) { return static_cast<int>((most + len) * __builtin_amdgcn_rcpf(len)); };   // ceil(rounds / len)
+        auto columns_for = [&](float len) __attribute__((always_inline)) { return columns_of(rounds, len, __builtin_amdgcn_rcpf(len)); };
         auto upto_for = [&](float len) __attribute__((always_inline)) { return row_scan(columns_for(len), [](int x, int y) { return x + y; }); };
         float len = ceilf(fmaxf(total * p.inv_columns, longest * (1.f / kMostRanges)) - 0.01f) + (lane >> 4);
         unsigned long long fits;

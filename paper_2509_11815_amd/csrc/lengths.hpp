@@ -1,0 +1,19 @@
+// What the kernels work out from a request's prefix length and node count, which come from the caller's device memory and may
+// hold any 32-bit value.  Usable on the host as well, so that it can be checked without a GPU.
+#pragma once
+
+namespace specvlm {
+
+constexpr int kSharesRound = 128;   // keys that the four streams of a workgroup take at once (attn_streams.hip)
+
+// Keys of a request, 1 .. capacity whatever its lengths are (a bad request takes part in the division of a batch until it is reported).
+constexpr int keys_of(int prefix, int nodes, int nodes_max, int capacity) {
+    const int P = prefix < 0 ? 0 : prefix > capacity ? capacity : prefix;
+    const int n = nodes < 1 ? 1 : nodes > nodes_max ? nodes_max : nodes;
+    return n < capacity - P ? P + n : capacity;            // (P + n of the caller's values may not fit in 32 bits)
+}
+
+// ceil(rounds / len), inverse = 1 / len to a few ulp
+constexpr int columns_of(int rounds, float len, float inverse) { return static_cast<int>((static_cast<float>(rounds) - 0.5f + len) * inverse); }
+
+}  // namespace specvlm

@@ -29,15 +29,20 @@ extern "C" void columns(const specvlm_attn_desc* d, long long* out) {
 
 
 @functools.lru_cache(None)
-def _library():
+def compiled(source):
+    """A C++ source over the library's host headers, as a loaded shared object."""
     tmp = tempfile.mkdtemp()
     atexit.register(shutil.rmtree, tmp, ignore_errors=True)
     src, so = os.path.join(tmp, "plan.cpp"), os.path.join(tmp, "plan.so")
     with open(src, "w") as f:
-        f.write(SOURCE)
+        f.write(source)
     subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-shared", "-fPIC", "-I" + os.path.join(ROOT, "include"),
                     "-I" + os.path.join(ROOT, "paper_2509_11815_amd", "csrc"), src, "-o", so], check=True)
     return ctypes.CDLL(so)
+
+
+def _library():
+    return compiled(SOURCE)
 
 
 def plan_of_desc(desc) -> Plan:

@@ -86,21 +86,40 @@ def test_lengths(sv, oracle, name, fractions, paged):
 
 @pytest.mark.parametrize("name", ["bf16", "fp32"])
 @pytest.mark.parametrize("paged", [False, True])
-def test_bad_requests_beside_good_ones(sv, oracle, name, paged):
-    """A malformed tree, a length past the cache and a negative one take their share of the columns and are left alone."""
+@pytest.mark.parametrize("length", ["slots", -5, -2**31, 2**31 - 1, 2**31 - 60, 2**31 - 61])
+def test_bad_requests_beside_good_ones(sv, oracle, name, paged, length):
+    """A malformed tree and a length that no cache holds take their share of the columns and are left alone: prefix and nodes of the
+    largest ones do not fit in 32 bits together."""
     from gpu_util import assert_attn_close, to_host_f64
     case = make(name, (0.4, 0.6, 1, 0.5, 0.2, 0.7), paged=paged)
     B, cap = case["q"].shape[0], SHAPES[name][0][5]
     parent, lengths = case["parent"].copy(), case["prefix_len"].copy()
     parent[1, 7] = 7
-    lengths[0] = cap if B == 3 else -5
-    bad, good = (0, 1), list(range(2, B))
+    lengths[0] = cap if length == "slots" else length
+    good = list(range(2, B))
     ref, _ = oracle.tree_attn(case["q"], case["k"], case["v"], case["prefix_len"], case["parent"], None, block_table=case["block_table"])
     out, err, workspace = call(sv, dict(case, parent=parent, prefix_len=lengths))
-    assert int(err.item()) == 1 | 4 and not workspace[:1024 * 4 * 128].any()
+    assert int(err.item()) | 4 == 1 | 4 and not workspace[:1024 * 4 * 128].any()
     got = to_host_f64(out)
     assert_attn_close(got[good], ref[good], "bf16", "good requests")
-    assert np.all(got[list(bad)] == 7.0)
+    assert np.all(got[1] == 7.0)
+
+
+@pytest.mark.parametrize("name", ["bf16", "fp32"])
+@pytest.mark.parametrize("nodes", [0, -1, 61, 2**31 - 1, -2**31])
+def test_bad_node_counts_beside_good_ones(sv, oracle, name, nodes):
+    from gpu_util import assert_attn_close, to_host_f64
+    case = make(name, (0.4, 1, 0.6, 0.5, 0.2, 0.7))
+    B, N = case["q"].shape[:2]
+    good = list(range(1, B))
+    ref, _ = oracle.tree_attn(case["q"], case["k"], case["v"], case["prefix_len"], case["parent"], None)
+    counts = np.full(B, N, dtype=np.int32)
+    counts[0] = nodes
+    out, err, workspace = call(sv, dict(case, num_nodes=counts))
+    assert int(err.item()) == 2 and not workspace[:1024 * 4 * 128].any()
+    got = to_host_f64(out)
+    assert_attn_close(got[good], ref[good], "bf16", "good requests")
+    assert np.all(got[0] == 7.0)
 
 
 @pytest.mark.parametrize("name", list(SHAPES))

@@ -290,6 +290,8 @@ int32_t specvlm_tree_accept_sample(int32_t dtype, int32_t B, int32_t N_max, int3
  * Only desc's dtype, B, H_kv, D, paged, block_size, max_blocks_per_req, kv_capacity
  * and kv_stride_* are used.  new_prefix_len_dev may alias prefix_len_dev (that costs a second,
  * tiny launch: the old lengths may only be overwritten after every workgroup has read them).
+ * A move whose source or destination lies outside the cache (prefix_len[b] is negative, or too long
+ * for it) is NOT made.
  *   moved_idx_dev  optional int32 [B, path_cap, 2]: (src_slot, dst_slot) per j, -1 padded.
  *   err_flag_dev   device int32 or NULL.  A move whose source or destination block id (paged) is
  *                  outside [0, num_blocks) is NOT made -- nothing is ever written into a block the

@@ -13,6 +13,9 @@ constexpr int keys_of(int prefix, int nodes, int nodes_max, int capacity) {
     return n < capacity - P ? P + n : capacity;            // (P + n of the caller's values may not fit in 32 bits)
 }
 
+// Whether row `node` behind the prefix is a slot of the cache (prefix + node may not fit in 32 bits).
+constexpr bool slot_inside(int prefix, int node, int capacity) { return prefix >= 0 && node >= 0 && prefix < capacity - node; }
+
 // ceil(rounds / len), inverse = 1 / len to a few ulp
 constexpr int columns_of(int rounds, float len, float inverse) { return static_cast<int>((static_cast<float>(rounds) - 0.5f + len) * inverse); }
 

@@ -4,6 +4,7 @@
 
 #include "common.hpp"
 #include "compact_plan.hpp"
+#include "lengths.hpp"
 
 namespace specvlm {
 
@@ -376,7 +377,7 @@ __global__ __launch_bounds__(kCompactThreads) void kv_compact_kernel(
         regs[c] = uint4{0u, 0u, 0u, 0u};
         if (c * kCompactThreads >> bits >= path_cap) continue;      // uniform
         // a row moves only if it is a valid, different slot inside the cache
-        if (j <= m && hk < H_kv && a[c] != j && a[c] >= 0 && a[c] < SPECVLM_MAX_NODES && P >= 0 && P + a[c] < g.capacity && P + j < g.capacity) {
+        if (j <= m && hk < H_kv && a[c] != j && a[c] < SPECVLM_MAX_NODES && slot_inside(P, a[c], g.capacity) && slot_inside(P, j, g.capacity)) {
             bool bad_block = false;
             const int64_t src = kv_row_offset(g, b, hk, P + a[c], bad_block) * elem_bytes + ch * 16;
             const int64_t dst = kv_row_offset(g, b, hk, P + j, bad_block) * elem_bytes + ch * 16;

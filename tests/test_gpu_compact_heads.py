@@ -51,3 +51,36 @@ def test_head_groups(oracle, L, B, H, D, dtype, path_cap, paged):
     ref_newp, _ = oracle.kv_compact(k, v, P, paths, m, block_table=table)
     assert np.array_equal(newp.cpu().numpy(), ref_newp)
     assert np.array_equal(to_host_bits(kd), k) and np.array_equal(to_host_bits(vd), v)
+
+
+@pytest.mark.parametrize("length", [80, 79 - 63, -1, -2**31, 2**31 - 1, 2**31 - 2, 2**31 - 9, 2**31 - 64])
+@pytest.mark.parametrize("paged", [False, True])
+def test_moves_outside_the_cache_are_not_made(oracle, paged, length):
+    """A request whose prefix no cache holds, beside one that is compacted: of its path the rows that lie outside stay where they are,
+    also where prefix and node do not fit in 32 bits together."""
+    import paper_2509_11815_amd as sv
+    from gpu_util import i32, to_dev, to_host_bits
+    sv.load_library()
+    rng = np.random.default_rng(7)
+    L, B, H, D, slots = 3, 2, 4, 64, 80
+    P = np.array([5, length], dtype=np.int32)
+    path = np.array([[0, 3, 9, 20, 63], [0, 2, 5, 8, 63]], dtype=np.int32)
+    m = np.array([4, 4], dtype=np.int32)
+    table = None
+    if paged:
+        table, nb = W.block_table(rng, B, 5, spare=0.2)
+        shape = (L, nb, H, 16, D)
+    else:
+        shape = (L, B, H, slots, D)
+    k, v = (rng.integers(0, 65536, size=shape, dtype=np.uint16) for _ in range(2))
+    kd, vd = to_dev(k), to_dev(v)
+    sv.specvlm_kv_compact(kd, vd, i32(P), i32(path), i32(m), block_table=None if table is None else i32(table))
+    torch.cuda.synchronize()
+    inside = [j for j in range(5) if length >= 0 and length + int(path[1, j]) < slots]
+    ref = [x.copy() for x in (k, v)]
+    moves = [(0, 5 + int(a), 5 + j) for j, a in enumerate(path[0])] + [(1, length + int(path[1, j]), length + j) for j in inside]
+    row = lambda x, b, s: x[:, table[b, s >> 4], :, s & 15] if paged else x[:, b, :, s]
+    for old, new in zip((k, v), ref):
+        for b, src, dst in moves:
+            row(new, b, dst)[:] = row(old, b, src)
+    assert np.array_equal(to_host_bits(kd), ref[0]) and np.array_equal(to_host_bits(vd), ref[1])

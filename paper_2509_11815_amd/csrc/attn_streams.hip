@@ -28,7 +28,6 @@
 #include <type_traits>
 
 #include "attn_rows.hpp"
-#include "lengths.hpp"
 
 namespace specvlm {
 
@@ -242,7 +241,7 @@ __device__ __forceinline__ void attend(const StreamsParams& p) {
     const int P = P_raw;
     if (n < 1 || n > p.N_max) err |= SPECVLM_ERR_BAD_NUM_NODES;
     n = min(max(n, 1), p.N_max);
-    if (P < 0 || P + n > p.g.capacity) err |= SPECVLM_ERR_BAD_LENGTH;
+    if (!length_fits(P, n, p.g.capacity)) err |= SPECVLM_ERR_BAD_LENGTH;
     const int S = P + n;
     const int ntile = (S + kKeys - 1) / kKeys;
     const int my_tiles = (!err && stream < ntile) ? static_cast<int>(static_cast<uint32_t>(ntile - stream + nstream - 1) / static_cast<uint32_t>(nstream)) : 0;

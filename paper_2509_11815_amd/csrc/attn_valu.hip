@@ -72,7 +72,7 @@ __global__ __launch_bounds__(256) void attn_valu_kernel(ValuParams p) {
     int err = 0;
     if (n < 1 || n > p.N_max) err |= SPECVLM_ERR_BAD_NUM_NODES;
     n = min(max(n, 1), p.N_max);
-    if (P < 0 || P + n > p.g.capacity) err |= SPECVLM_ERR_BAD_LENGTH;
+    if (!length_fits(P, n, p.g.capacity)) err |= SPECVLM_ERR_BAD_LENGTH;
     if (tid == 0) {
         // ancestor-or-self bit mask of node i; the walk is bounded by 64 steps
         unsigned long long mask = 0;
@@ -192,7 +192,7 @@ __global__ __launch_bounds__(kF32Waves * 64) void attn_f32_kernel(ValuParams p) 
     int err = 0;
     if (n < 1 || n > p.N_max) err |= SPECVLM_ERR_BAD_NUM_NODES;
     n = min(max(n, 1), p.N_max);
-    if (P < 0 || P + n > p.g.capacity) err |= SPECVLM_ERR_BAD_LENGTH;
+    if (!length_fits(P, n, p.g.capacity)) err |= SPECVLM_ERR_BAD_LENGTH;
     const int node = row0 + l16;               // this lane's query (column of S^T and O^T)
     // Q operand: the contraction index of product i of a 16-wide block c is 16c + 4g + i, for K alike
     f32x4 qf[ND];

@@ -182,7 +182,7 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
     const int P = P_raw;
     if (n < 1 || n > p.N_max) err |= SPECVLM_ERR_BAD_NUM_NODES;
     n = min(max(n, 1), p.N_max);
-    if (P < 0 || P + n > p.g.capacity) err |= SPECVLM_ERR_BAD_LENGTH;
+    if (!length_fits(P, n, p.g.capacity)) err |= SPECVLM_ERR_BAD_LENGTH;
     const int S = P + n;
     const int ntile = (S + kKeys - 1) / kKeys;
     const int my_tiles = (!err && stream < ntile) ? static_cast<int>(divide(ntile - stream + nstream - 1, p.magic_nstream)) : 0;

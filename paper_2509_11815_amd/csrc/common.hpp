@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include "attn_plan.hpp"
+#include "lengths.hpp"
 #include "specvlm.h"
 
 namespace specvlm {

@@ -13,6 +13,9 @@ constexpr int keys_of(int prefix, int nodes, int nodes_max, int capacity) {
     return n < capacity - P ? P + n : capacity;            // (P + n of the caller's values may not fit in 32 bits)
 }
 
+// Whether a request's prefix and its `nodes` nodes (1 .. 64) lie inside the cache (their sum may not fit in 32 bits).
+constexpr bool length_fits(int prefix, int nodes, int capacity) { return prefix >= 0 && prefix <= capacity - nodes; }
+
 // Whether row `node` behind the prefix is a slot of the cache (prefix + node may not fit in 32 bits).
 constexpr bool slot_inside(int prefix, int node, int capacity) { return prefix >= 0 && node >= 0 && prefix < capacity - node; }
 

@@ -4,7 +4,6 @@
 
 #include "common.hpp"
 #include "compact_plan.hpp"
-#include "lengths.hpp"
 
 namespace specvlm {
 

@@ -215,13 +215,21 @@ constexpr int kMostByLength = 16;   // requests that it deals columns out to
 //   29.8 -> 20.5; 6 x 32, 2800 - 300: 42.0 -> 33.8; 2 x 32, 4474 + 800: 29.5 -> 24.7; 2 x 32, 64 / 8, 4500 + 900 paged: 31.9 -> 25.7;
 //   4 x 35 / 5, 48 nodes, 2016, from row blocks: 37.8 -> 20.5
 // Equal lengths cost what the plan costs, 0.1 - 0.5 us, as the first tile is requested before it.  So only where streams are long:
-// x = tiles per column at equal lengths (the capacity stands in for them) from 26 on at head size 128 (streams' kernel before; 86 shapes of
-// 26 and more: 1.00 of the time at equal lengths, 0.91 at different ones; 20 - 26: 1.02 and 0.96), from 60 on at 64 (1.02 and 0.87).
-// In place of the kernels with other divisions: x >= 20, at 64 and without shared heads from 26 (row blocks; 68 shapes 0.85 and 0.80, one
-// of them above 1.04; 4 x 32, 1300 keys paged, x = 21.5: 21.6 | 23.9) or 40 (key ranges: 0.94 and 0.84), with blocks at least 70 % full; not
-// where heads are shared and equal lengths would leave more than a fifth of the columns idle (5 x 32 / 16, 4916 keys 53.6 | 63.9).  Below,
-// short unsplit calls with shared heads gain from a column each (x < 12, at 64 16: 0.83 - 1.00 of their time, mean 0.90; without shared heads
-// 0.95 - 1.08).
+// x = tiles per column at equal lengths.  The capacity stands in for them, and requests may be much shorter: the lines lie where the
+// geometric mean of the time here over the time there, for a longest request of the whole capacity, a half, a quarter and an eighth, falls
+// below 1 (320 shapes at four fillings; requests of a batch equal or up to ten times different):
+//   in place of                        x        whole  half  quarter  eighth | mean
+//   the streams' kernel, evenly    128 26 - 34  0.94   0.97   1.02     1.02   0.99;   34 - 60: 0.97;   above: 0.94
+//                                   64 60 - 80  0.82   0.91   0.97     1.01   0.93;   above: 0.95
+//   key ranges                     128 20 - 30  0.98   1.05   1.16     1.18   1.09;   30 - 60: 0.92;   above: 0.82
+//                                   64 50 - 80  0.85   0.85   0.84     0.80   0.83;   above: 0.87
+//   row blocks, one round of a     128 20 - 38  0.90   1.10   1.33     1.36   1.16;   38 - 44: 1.06;   44 - 60: 0.94;   above: 0.87
+//     multiple of 8 workgroups      64 26 - 44  0.85   1.05   1.22     1.28   1.09;   44 - 50: 1.04;   50 - 60: 0.97;   above: 0.91
+//   row blocks, otherwise          128 34 - 60  0.52   0.68   0.88     1.13   0.77;   above: 0.57;     64 from 30 on: 0.83 and less
+// (3 x 40, 1744 slots: 1700 keys 23.1 -> 19.6, 376 - 58 keys 10.2 -> 14.4 us; so it keeps its row blocks.)  Not where heads are shared and
+// equal lengths would leave more than a fifth of the columns idle (5 x 32 / 16, 4916 keys 53.6 | 63.9), and blocks at least 70 % full.
+// Below, short unsplit calls with shared heads gain from a column each (x < 12, at 64 16: 0.83 - 1.05 of their time, mean 0.94; half as long 0.99;
+// without shared heads 0.95 - 1.08).
 inline void plan_columns(const specvlm_attn_desc& d, AttnPlan& plan) {
     const int group = d.H_q / d.H_kv, rows = group * d.N_max, blocks = (rows + 63) / 64;
     const int64_t units = static_cast<int64_t>(d.H_kv) * blocks;
@@ -244,7 +252,13 @@ inline void plan_columns(const specvlm_attn_desc& d, AttnPlan& plan) {
             return;
         }
         const int used = std::min(columns / d.B, kMostRanges) * d.B;
-        if (x < (plan.block_rows ? (wide && group > 1 ? 20 : 26) : (wide ? 20 : 40))) return;
+        double least = wide ? 30 : 40;
+        if (plan.block_rows) {
+            const int64_t workgroups = static_cast<int64_t>(d.B) * d.H_kv * ((rows + plan.block_rows - 1) / plan.block_rows) * plan.splits;
+            if (workgroups <= 256 && workgroups % 8 == 0) least = wide ? 44 : 50;
+            else least = wide && group > 1 ? 20 : 26;
+        }
+        if (x < least) return;
         if (group > 1 && 5 * used < 4 * columns && (!plan.block_rows || x < 32)) return;
     }
     if (columns > d.B) {

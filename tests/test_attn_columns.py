@@ -13,7 +13,7 @@ COUNTERS = 1024 * 4 * 128
 def test_bounds(seed):
     rng = random.Random(seed)
     seen = set()
-    for _ in range(3000):
+    for _ in range(6000):
         hkv, group = rng.choice([1, 2, 4, 5, 8, 16, 32, 40]), rng.choice([1, 1, 2, 3, 4, 8])
         B, D, N = rng.choice([1, 2, 3, 4, 5, 6, 8, 16, 17, 40]), rng.choice([64, 128]), rng.choice([13, 32, 36, 48, 60, 64])
         paged = rng.random() < 0.3
@@ -48,6 +48,11 @@ def test_bounds(seed):
     ((8, 32, 32, 128, 60, 976), False, 8, 0), ((8, 40, 8, 128, 48, 288), True, 8, 0), ((8, 32, 32, 128, 60, 272), False, 0, 0), ((4, 40, 40, 128, 64, 736), False, 4, 0),
     # head size 64: longer streams
     ((5, 16, 16, 64, 60, 6144), False, 16, 1), ((5, 16, 16, 64, 60, 3088), False, 15, 0),
+    # key ranges and row blocks: longer ones, as they lose more where requests are shorter than their cache; row blocks whose
+    # workgroups do not share the XCDs evenly, or make more than one round, lose less
+    ((3, 40, 40, 128, 60, 1744), False, 0, 0), ((4, 32, 16, 128, 64, 1952), False, 0, 0), ((8, 16, 4, 64, 64, 2544), True, 0, 0),
+    ((2, 16, 4, 128, 60, 5184), False, 0, 0), ((2, 64, 8, 128, 60, 3504), True, 4, 1), ((8, 32, 16, 128, 32, 3664), False, 16, 1),
+    ((6, 32, 4, 64, 60, 6544), False, 8, 1), ((5, 32, 32, 128, 60, 2272), False, 8, 1),
     # the other kernels: one request, shared heads and a third of the columns idle, short row blocks, capacities that end inside 16 slots
     ((1, 64, 8, 128, 60, 4064), False, 0, 0), ((5, 32, 16, 128, 60, 4976), False, 0, 0), ((4, 32, 8, 128, 32, 1024), False, 0, 0),
     ((4, 40, 40, 128, 60, 4921), False, 0, 0),

@@ -11,14 +11,15 @@ import subprocess
 import tempfile
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-# streams: key ranges of the kernel with a key stream per wavefront, 0 where one of the others takes the call
-Plan = collections.namedtuple("Plan", "ranges block_rows splits streams", defaults=[0])
+# columns: workgroups per row block of a KV head in the kernel with a key stream per wavefront, 0 where one of the others takes the call (by
+# row blocks, or by key ranges where block_rows is 0); by_length: the requests' lengths deal them out; streams: key ranges of a request otherwise
+Plan = collections.namedtuple("Plan", "ranges block_rows splits streams columns by_length", defaults=[0, 0, 0])
 
 SOURCE = r"""
 #include "attn_plan.hpp"
 extern "C" void plan(const specvlm_attn_desc* d, int* out) {
     const specvlm::AttnPlan p = specvlm::attn_plan(*d);
-    out[0] = p.ranges; out[1] = p.block_rows; out[2] = p.splits; out[3] = p.streams;
+    out[0] = p.ranges; out[1] = p.block_rows; out[2] = p.splits; out[3] = p.streams; out[4] = p.columns; out[5] = p.by_length;
 }
 extern "C" void columns(const specvlm_attn_desc* d, long long* out) {
     const specvlm::AttnPlan p = specvlm::attn_plan(*d), e = specvlm::evenly(*d, p);
@@ -46,7 +47,7 @@ def _library():
 
 
 def plan_of_desc(desc) -> Plan:
-    out = (ctypes.c_int * 4)()
+    out = (ctypes.c_int * 6)()
     _library().plan(ctypes.byref(desc), out)
     return Plan(*out)
 
@@ -62,8 +63,16 @@ def desc_of(B, Hq, Hkv, D, N, cap, num_splits=0, paged=False, token_stride=None)
 
 
 def streams_of(*shape, **options) -> int:
-    """Key ranges of the kernel with a key stream per wavefront, 0 where another is taken."""
+    """Key ranges of a request in the kernel with a key stream per wavefront, evenly divided; 0 where the call has another division."""
     return plan_of(*shape, **options).streams
+
+
+def division_of(*shape, **options) -> tuple[int, int]:
+    """In the kernel with a key stream per wavefront: key ranges of a request, and whether the lengths divide them instead.  A call that the
+    lengths divide is divided evenly where it has no workspace for that."""
+    plan = plan_of(*shape, **options)
+    assert plan.columns
+    return plan.streams, plan.by_length
 
 
 def plan_of(*shape, **options) -> Plan:

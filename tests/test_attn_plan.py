@@ -41,21 +41,21 @@ def test_bounds(seed):
 @pytest.mark.parametrize("shape,plan", [
     # (requests, query heads, KV heads, head size, nodes, slots per request)
     ((1, 32, 32, 128, 60, 832), Plan(7, 32, 4)), ((1, 32, 32, 128, 60, 3328), Plan(8, 0, 8)),
-    ((8, 32, 32, 128, 60, 968), Plan(1, 0, 1)), ((4, 40, 40, 128, 60, 4928), Plan(3, 0, 3)),
+    ((8, 32, 32, 128, 60, 968), Plan(1, 0, 1)), ((4, 40, 40, 128, 60, 4928), Plan(3, 0, 3, 0, 6, 1)),
     # at least four query heads per KV head: four ranges, 340 - 512 work items of two per compute unit (capacities that are a
     # multiple of 16 go to the kernel with a key stream per wavefront, below)
     ((4, 32, 8, 128, 64, 3080), Plan(4, 0, 4)), ((2, 64, 8, 128, 60, 4568), Plan(4, 0, 4)), ((3, 40, 8, 128, 60, 3080), Plan(4, 0, 4)),
     ((4, 28, 4, 128, 60, 3080), Plan(4, 0, 4)), ((3, 32, 8, 128, 60, 3080), Plan(4, 0, 4)), ((2, 48, 8, 128, 60, 4568), Plan(4, 0, 4)),
     # ... where row blocks win
-    ((4, 32, 8, 128, 60, 2064), Plan(2, 32, 1)), ((2, 64, 8, 128, 60, 3072), Plan(2, 32, 1)),
+    ((4, 32, 8, 128, 60, 2064), Plan(2, 32, 1)), ((2, 64, 8, 128, 60, 2560), Plan(2, 32, 1)), ((2, 64, 8, 128, 60, 3072), Plan(2, 32, 1, 0, 4, 1)),
     # ... not for one request, two query heads per KV head, head size 64 or more than two ranges to begin with
-    ((1, 128, 8, 128, 60, 4560), Plan(2, 0, 2)), ((4, 32, 16, 128, 60, 3080), Plan(2, 0, 2)), ((4, 32, 8, 64, 60, 4560), Plan(2, 32, 1)),
+    ((1, 128, 8, 128, 60, 4560), Plan(2, 0, 2)), ((4, 32, 16, 128, 60, 3080), Plan(2, 0, 2)), ((4, 32, 8, 64, 60, 4560), Plan(2, 32, 1, 0, 8, 1)),
     ((2, 32, 8, 128, 60, 3080), Plan(4, 0, 4)), ((4, 16, 4, 128, 60, 3080), Plan(4, 0, 4)),
     # the kernel with a key stream per wavefront in their place
-    ((8, 32, 32, 128, 60, 976), Plan(1, 0, 1, 1)), ((4, 32, 8, 128, 64, 3072), Plan(4, 0, 4, 2)), ((2, 64, 8, 128, 60, 4560), Plan(4, 0, 4, 2)),
-    ((3, 40, 8, 128, 60, 3072), Plan(4, 0, 4, 2)), ((4, 28, 4, 128, 60, 3072), Plan(4, 0, 4, 2)), ((3, 32, 8, 128, 60, 3072), Plan(4, 0, 4, 2)),
-    ((2, 48, 8, 128, 60, 4560), Plan(4, 0, 4, 2)), ((4, 32, 16, 128, 60, 3072), Plan(2, 0, 2, 2)), ((2, 32, 8, 128, 60, 3072), Plan(4, 0, 4, 4)),
-    ((4, 16, 4, 128, 60, 3072), Plan(4, 0, 4, 4)),
+    ((8, 32, 32, 128, 60, 976), Plan(1, 0, 1, 1, 8, 0)), ((4, 32, 8, 128, 64, 3072), Plan(4, 0, 4, 2, 8, 1)), ((2, 64, 8, 128, 60, 4560), Plan(4, 0, 4, 2, 4, 1)),
+    ((3, 40, 8, 128, 60, 3072), Plan(4, 0, 4, 2, 6, 1)), ((4, 28, 4, 128, 60, 3072), Plan(4, 0, 4, 2, 8, 1)), ((3, 32, 8, 128, 60, 3072), Plan(4, 0, 4, 2, 8, 1)),
+    ((2, 48, 8, 128, 60, 4560), Plan(4, 0, 4, 2, 5, 1)), ((4, 32, 16, 128, 60, 3072), Plan(2, 0, 2, 2, 8, 1)), ((2, 32, 8, 128, 60, 3072), Plan(4, 0, 4, 4, 8, 0)),
+    ((4, 16, 4, 128, 60, 3072), Plan(4, 0, 4, 4, 16, 0)),
 ])
 def test_measured_shapes(shape, plan):
     assert plan_of(*shape) == plan

@@ -53,13 +53,13 @@ def test_two_workgroups_per_compute_unit(sv, oracle, B, Hq, Hkv, D, N, P, nn, sp
     check(case, *run_both(sv, oracle, case, num_splits=splits), f"batch {B}x{Hq}/{Hkv}x{D} N={N} splits={splits} paged={paged}")
 
 
-# Streams per wavefront: the same shapes paged, or with a capacity that is a multiple of 16.
+# Streams per wavefront, most divided by the lengths: the same shapes paged, or with a capacity that is a multiple of 16.
 @pytest.mark.parametrize("B,Hq,Hkv,D,N,P,nn,plan", [
-    (4, 32, 8, 128, 64, [2400, 33, 900, 0], [64, 1, 17, 2], Plan(4, 0, 4, 2)),
-    (2, 64, 8, 128, 60, [3900, 700], None, Plan(4, 0, 4, 2)),
-    (3, 32, 8, 128, 60, [2500, 3, 900], [60, 60, 7], Plan(4, 0, 4, 2)),
-    (3, 40, 10, 128, 60, [2600, 64, 1000], None, Plan(4, 0, 4, 2)),
-    (3, 20, 20, 128, 60, [900, 100, 2500], None, Plan(4, 0, 4, 4)),
+    (4, 32, 8, 128, 64, [2400, 33, 900, 0], [64, 1, 17, 2], Plan(4, 0, 4, 2, 8, 1)),
+    (2, 64, 8, 128, 60, [3900, 700], None, Plan(4, 0, 4, 2, 4, 1)),
+    (3, 32, 8, 128, 60, [2500, 3, 900], [60, 60, 7], Plan(4, 0, 4, 2, 8, 1)),
+    (3, 40, 10, 128, 60, [2600, 64, 1000], None, Plan(4, 0, 4, 2, 6, 1)),
+    (3, 20, 20, 128, 60, [900, 100, 2500], None, Plan(4, 0, 4, 4, 12, 0)),
 ])
 @pytest.mark.parametrize("paged", [False, True])
 def test_streams_in_their_place(sv, oracle, B, Hq, Hkv, D, N, P, nn, plan, paged):

@@ -30,7 +30,7 @@ class FarQueries:
         num_splits = desc.num_splits if desc is not None else num_splits
         desc = self._sv.binding.make_attn_desc(far, k, out, block_table=block_table, num_splits=num_splits, softmax_scale=softmax_scale)
         plan = plan_of_desc(desc)
-        assert plan.block_rows == 0 and plan.streams == 0
+        assert plan.block_rows == 0 and plan.columns == 0
         self.calls += 1
         return self._sv.specvlm_tree_verify_attn(far, k, v, *args, out=out, desc=desc, block_table=block_table, **kw)
 

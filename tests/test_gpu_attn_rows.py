@@ -34,7 +34,7 @@ def test_row_blocks(sv, oracle, B, Hq, Hkv, D, N, P, nn, splits, paged):
     case = random_case(7000 + D + N + splits, "bf16", B=B, Hq=Hq, Hkv=Hkv, D=D, N_max=N, P_list=P, num_nodes=nn, paged=paged,
                        cap_extra=0)
     plan = plan_of_case(case, splits)
-    assert plan.block_rows and not plan.streams
+    assert plan.block_rows and not plan.columns
     check(case, *run_both(sv, oracle, case, num_splits=splits), f"rows {B}x{Hq}/{Hkv}x{D} N={N} splits={splits} paged={paged}")
 
 
@@ -46,6 +46,6 @@ def test_log_sum_exp_is_of_fp32_weights(sv, oracle, D, N, P, splits):
     from gpu_util import random_case
     case = random_case(7100 + D + N, "bf16", B=2, Hq=4, Hkv=4, D=D, N_max=N, P_list=P, num_nodes=None, paged=False, cap_extra=0)
     plan = plan_of_case(case, splits)
-    assert plan.block_rows and not plan.streams
+    assert plan.block_rows and not plan.columns
     _, lse, _, ref = run_both(sv, oracle, case, num_splits=splits)
     assert abs(lse - ref).max() <= 3e-5

@@ -3,7 +3,7 @@ those borders, and an id outside the pool on either side of the first."""
 import numpy as np
 import pytest
 
-from attn_plan_util import streams_of
+from attn_plan_util import division_of
 from test_gpu_attn import check, run_both
 
 pytestmark = pytest.mark.gpu
@@ -27,7 +27,7 @@ def make(D):
     tiles += [2] * (B - len(tiles))
     P = [128 * t - N - (5 * b) % 128 if t > 1 else 7 for b, t in enumerate(tiles)]
     case = random_case(8400 + D, "bf16", B=B, Hq=Hq, Hkv=Hkv, D=D, N_max=N, P_list=P, paged=True)
-    assert streams_of(B, Hq, Hkv, D, N, case["block_table"].shape[1] * 16, paged=True) == 1
+    assert division_of(B, Hq, Hkv, D, N, case["block_table"].shape[1] * 16, paged=True) == (1, 0)
     return case
 
 

@@ -5,7 +5,7 @@ import pytest
 import torch
 
 import test_gpu_attn_nan
-from attn_plan_util import streams_of
+from attn_plan_util import division_of
 from test_gpu_attn import check, run_both
 
 pytestmark = pytest.mark.gpu
@@ -18,13 +18,15 @@ def sv():
     return sv
 
 
-# requests, query heads, KV heads, head size, nodes, prefix lengths; key ranges.  Longest prefix + nodes: a multiple of 16.
+# key ranges: requests, query heads, KV heads, head size, nodes, prefix lengths (longest prefix + nodes: a multiple of 16).  BY_LENGTH: ranges
+# of the shape that the lengths divide.
 SHAPES = {
     1: (5, 32, 32, 128, 60, [420, 33, 250, 0, 419]),
     2: (3, 32, 16, 128, 64, [2304, 5, 511]),
     3: (5, 16, 16, 64, 60, [3028, 700, 64, 1, 2000]),
     4: (3, 20, 20, 128, 60, [2500, 100, 900]),
 }
+BY_LENGTH = 2
 
 
 def make(ranges, paged=False, num_nodes=None):
@@ -32,7 +34,7 @@ def make(ranges, paged=False, num_nodes=None):
     B, Hq, Hkv, D, N, P = SHAPES[ranges]
     case = random_case(8600 + ranges, "bf16", B=B, Hq=Hq, Hkv=Hkv, D=D, N_max=N, P_list=P, num_nodes=num_nodes, paged=paged, cap_extra=0)
     cap = case["block_table"].shape[1] * 16 if paged else case["k"].shape[2]
-    assert streams_of(B, Hq, Hkv, D, N, cap, paged=paged) == ranges
+    assert division_of(B, Hq, Hkv, D, N, cap, paged=paged) == (ranges, ranges == BY_LENGTH)
     return case
 
 
@@ -42,12 +44,12 @@ def device_args(case):
     return [to_dev(case[x]) for x in "qkv"] + [i32(case["prefix_len"]), i32(case["parent"])], table
 
 
-@pytest.mark.parametrize("B,H,D,P,ranges", [(5, 32, 128, 413, 1), (5, 32, 64, 413, 1), (3, 20, 128, 2490, 4), (2, 40, 128, 3741, 3)])
+@pytest.mark.parametrize("B,H,D,P,ranges,by_length", [(5, 32, 128, 413, 1, 0), (5, 32, 64, 413, 1, 0), (3, 20, 128, 2490, 4, 0), (2, 40, 128, 3741, 3, 1)])
 @pytest.mark.parametrize("where", ["prefix", "node", "query"])
 @pytest.mark.parametrize("paged", [False, True])
-def test_nan(sv, oracle, B, H, D, P, ranges, where, paged):
+def test_nan(sv, oracle, B, H, D, P, ranges, by_length, where, paged):
     cap = ((P + 60 + 15) // 16 + 1) * 16 if paged else (P + 60 + 7 + 7) // 8 * 8
-    assert streams_of(B, H, H, D, 60, cap, paged=paged) == ranges
+    assert division_of(B, H, H, D, 60, cap, paged=paged) == (ranges, by_length)
     test_gpu_attn_nan.test_nan(sv, oracle, "bf16", B, H, D, 60, P, 0, where, paged)
 
 

@@ -15,6 +15,7 @@
 // hundred entries.
 #include <limits.h>
 
+#include "draft_plan.hpp"
 #include "wave_ops.hpp"
 
 // Products and sums stay apart: which of them the compiler fuses differs between instantiations of one kernel, and a
@@ -835,13 +836,7 @@ int32_t launch_draft_topk(int32_t dtype, int32_t B, int32_t W, int32_t V, int32_
                           int32_t M, int32_t index_base, int32_t* sel_out, float* sel_score_out,
                           int32_t* count_out, int32_t* counters, hipStream_t stream) {
     const bool fused = counters != nullptr;             // with the selection of the level's candidates
-    // Two workgroups a row (kBeside) as long as all are resident at once and a request's log-sum-exps fit behind its counter.  Not the
-    // root's row of up to 65536 entries, which needs no meeting otherwise (32000 5.6 us, 6.3 with one; 100001 14.8, 11.9), nor fp32 rows
-    // whose second reading costs more than the exponentials (eight requests of ten rows, a growth of six levels in a graph, one
-    // workgroup a row | two: 16000 tokens 52.1 | 48.8, 32000 54.5 | 55.1, 40000 61.7 | 61.8; 65000 81 | 79, 152064 144 | 142).
-    const int64_t rows = static_cast<int64_t>(B) * W;
-    const bool beside = fused && W < SPECVLM_COUNTER_STRIDE && rows <= 128 && (W > 1 || cum || V > 65536) &&
-                        (dtype == SPECVLM_BF16 || V > 65536 || rows * V <= 2200000);
+    const bool beside = fused && sums_beside(dtype, B, W, V, !cum);
     const dim3 grid(beside ? 2 * W : W, B), block(kThreadsDT);
     const SelArgs sel{M, index_base, sel_out, sel_score_out, count_out, counters, W};
 #define SPECVLM_LAUNCH_TK2(T, NC, LEVEL)                                                                            \

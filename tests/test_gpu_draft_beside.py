@@ -1,5 +1,5 @@
 """A level with its selection, a row's log-sum-exp in a workgroup of its own: where that begins and ends (rows at any alignment,
-every row division, one row, 31 and 32 rows, 128 and more workgroups), bit for bit against the separate calls
+every row division, one row, 31 and 32 rows, the most rows of a call and one more), bit for bit against the separate calls
 (specvlm_draft_topk, then specvlm_draft_select over its scores), which add up and rank in one workgroup a row."""
 import numpy as np
 import pytest
@@ -40,7 +40,9 @@ def level(dtype, B, W, V, offset=0, seed=0):
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("B,W,V,K,offset", [(1, 10, 10, 10, 0), (2, 10, 32768, 10, 0), (1, 10, 32769, 10, 1), (1, 3, 65536, 64, 0), (1, 3, 65537, 10, 3),
                                             (1, 1, 65537, 10, 0), (2, 1, 9000, 10, 5), (1, 31, 4001, 33, 0), (1, 32, 4001, 32, 0), (16, 8, 2047, 7, 1),
-                                            (43, 3, 2047, 7, 1), (7, 10, 31500, 10, 0), (1, 2, 200003, 5, 7)])
+                                            (43, 3, 2047, 7, 1), (7, 10, 31500, 10, 0), (1, 2, 200003, 5, 7),
+                                            (12, 10, 2047, 7, 1), (11, 11, 2047, 7, 1), (11, 10, 65537, 10, 0), (37, 3, 65537, 5, 0), (5, 10, 65537, 10, 3),
+                                            (17, 3, 65537, 10, 1)])
 def test_equals_the_separate_calls(sv, dtype, B, W, V, K, offset):
     x, cum, par = level(dtype, B, W, V, offset)
     counters = torch.zeros(B * sv.binding.COUNTER_STRIDE, dtype=torch.int32, device="cuda")

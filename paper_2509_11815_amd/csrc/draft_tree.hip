@@ -303,7 +303,7 @@ __device__ __forceinline__ void rank_winners(unsigned long long* s_key, int c, i
 //   entries   chunks of 8 (from the row's first 16-byte boundary), thread t takes chunks t, t + 1024, ...; the up to
 //             7 entries before and after are one thread's each.  NC = 4, 8: a row of up to 8192 NC entries stays in
 //             registers.  NC = 0: the row streams by once, in groups of four chunks a thread with a running maximum and sum,
-//             the next group on its way while one is added up; of a chunk only its maximum is kept.
+//             (bf16) the next group on its way while one is added up; of a chunk only its maximum is kept.
 //   lse       every thread sums against its own maximum, so maximum and sum need one meeting of the workgroup
 //             instead of two; lanes meet by DPP.
 //   Top-K     every row of 16 lanes reduces its greatest logit; the K-th greatest of the 64 is a value that at least K
@@ -383,6 +383,10 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
     // ---- maximum and sum of exponentials of this thread's entries ------------------------------
     constexpr int NM = NC > 0 ? NC : kStream;
     constexpr int U = 4;                                 // NC == 0: chunks of a thread requested together
+    // ... in bf16 a group ahead of the one being taken.  A group of fp32 is twice the bytes, and 16 wavefronts' requests fill the unit's
+    // queue by themselves: 40 rows, from cache, ahead | not: 65537 entries 9.98 | 8.85 us, 128256 12.95 | 12.26, 250000 25.3 | 24.8 (one row
+    // 23.0 | 21.9; 80 rows from HBM 34.4 | 34.3, 152064 19.4 | 19.9)
+    constexpr bool AHEAD = sizeof(T) == 2;
     Chunk<T> ch[NC > 0 ? NC : U];
     float cmax[NM];
     float tmax = es;                                     // greatest entry
@@ -411,7 +415,7 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
     } else {
         m = fmaxf(es, kLowest);
         sum = es > -INFINITY ? 1.f : 0.f;
-        Chunk<T> next[U];                                // the group after the one being taken, on its way
+        Chunk<T> next[U];                                // the group requested last
         auto request = [&](int k0) __attribute__((always_inline)) {                     // chunks k0, k0 + 1024, ...
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -420,9 +424,11 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
             }
         };
         auto take = [&](int j, float (&cm)[U]) __attribute__((always_inline)) {         // group j, j + 1, ... j + U - 1 of 1024 chunks
+            if constexpr (!AHEAD) request(tid + kThreadsDT * j);
 #pragma unroll
             for (int u = 0; u < U; ++u) ch[u] = next[u];
-            if ((j + U) * kThreadsDT < nck) request(tid + kThreadsDT * (j + U));        // uniform
+            if constexpr (AHEAD)
+                if ((j + U) * kThreadsDT < nck) request(tid + kThreadsDT * (j + U));    // uniform
             float gm = -INFINITY;
 #pragma unroll
             for (int u = 0; u < U; ++u) {
@@ -441,7 +447,7 @@ __global__ __launch_bounds__(kThreadsDT) void draft_topk_kernel(
             sum = (part[0] + part[1]) + (part[2] + part[3]);
             m = mn;
         };
-        request(tid);
+        if constexpr (AHEAD) request(tid);
 #pragma unroll
         for (int j = 0; j < kStream; j += U) {
             float cm[U];

@@ -216,6 +216,12 @@ __global__ __launch_bounds__(kThreadsAS) void tree_accept_sample_kernel(
     // vocabulary goes through it three times on a single compute unit); -inf gives 0
     const float c2 = 1.4426950408889634f / temperature;
     auto prob_of = [&](float l) -> float { return __builtin_amdgcn_exp2f((l - mx) * c2); };
+    auto sum_of = [&](const uint4& w) __attribute__((always_inline)) -> float {
+        float x = prob_of(vec_at<T>(w, 0));
+#pragma unroll
+        for (int e = 1; e < VEC; ++e) x += prob_of(vec_at<T>(w, e));
+        return x;
+    };
     for (;;) {
         const T* row = base + cur * stride_n;
         // Wavefront 0, lane c: child c's logit and uniform number, requested now so that they
@@ -258,9 +264,7 @@ __global__ __launch_bounds__(kThreadsAS) void tree_accept_sample_kernel(
                     for (int e = 0; e < VEC; ++e) m = fmaxf(m, vec_at<T>(x, e));
                 meet(m);
 #pragma unroll
-                for (const uint4& x : w)
-#pragma unroll
-                    for (int e = 0; e < VEC; ++e) sum += prob_of(vec_at<T>(x, e));
+                for (const uint4& x : w) sum += sum_of(x);
             }, [&](int v) {
                 const float l = logit_at<T>(row, v);
                 meet(l);
@@ -393,12 +397,6 @@ __global__ __launch_bounds__(kThreadsAS) void tree_accept_sample_kernel(
                 const int at = s_rej[__builtin_ctzll(some)] - rv.first(k);
                 if (static_cast<unsigned>(at) < static_cast<unsigned>(VEC)) drop(&w, 1, at);
             }
-        };
-        auto sum_of = [&](const uint4& w) __attribute__((always_inline)) -> float {
-            float x = 0.f;
-#pragma unroll
-            for (int e = 0; e < VEC; ++e) x += prob_of(vec_at<T>(w, e));
-            return x;
         };
         auto vector_of = [&](int k, unsigned long long some) __attribute__((always_inline)) -> uint4 {
             uint4 w{kInfWord, kInfWord, kInfWord, kInfWord};

@@ -67,3 +67,25 @@ def test_little_finite(sv, dtype, V):
         bonus = sv.specvlm_tree_accept_sample(parent, tok, x, torch.ones((4, 2), device="cuda"), torch.full((4,), u, device="cuda"),
                                               temperature=1.0, path_cap=4)[2]
         assert bonus.tolist() == [V - 1, V // 2, V - 1, 0]
+
+
+@pytest.mark.parametrize("V", [20003, 152064, 200003, 250000])
+def test_row_sums_do_not_lose_precision_with_length(sv, V):
+    """The threshold at which a root's only child is accepted, its probability, by bisection against 64 bits.  exp2 and the quotient leave
+    about 0.8e-7 (root mean square of 400 rows, any length); a sum of one chain a lane made it 1.0e-7 to 1.1e-7 from 200003 bf16 tokens on."""
+    B = 400
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(V)
+    x = torch.empty((B, 2, V), device="cuda").normal_(0, 0.3, generator=gen).to(torch.bfloat16)
+    p = torch.softmax(x[:, 0].double(), -1)
+    exact, top = p.max(1)
+    parent = torch.tensor([[-1, 0]] * B, dtype=torch.int32, device="cuda")
+    tok = torch.stack([torch.zeros_like(top), top], 1).int().contiguous()
+    lo, hi = exact * (1 - 1e-4), exact * (1 + 1e-4)
+    u = torch.ones((B, 2), device="cuda")
+    for _ in range(24):
+        u[:, 1] = ((lo + hi) / 2).float()
+        accepted = sv.specvlm_tree_accept_sample(parent, tok, x, u, torch.full((B,), 0.5, device="cuda"), temperature=1.0, path_cap=4)[0] > 0
+        lo, hi = torch.where(accepted, u[:, 1].double(), lo), torch.where(accepted, hi, u[:, 1].double())
+    error = ((lo + hi) / 2 / exact - 1).square().mean().sqrt().item()
+    assert error <= 0.95e-7, error

@@ -228,8 +228,9 @@ constexpr int kMostByLength = 16;   // requests that it deals columns out to
 //   row blocks, otherwise          128 34 - 60  0.52   0.68   0.88     1.13   0.77;   above: 0.57;     64 from 30 on: 0.83 and less
 // (3 x 40, 1744 slots: 1700 keys 23.1 -> 19.6, 376 - 58 keys 10.2 -> 14.4 us; so it keeps its row blocks.)  Not where heads are shared and
 // equal lengths would leave more than a fifth of the columns idle (5 x 32 / 16, 4916 keys 53.6 | 63.9), and blocks at least 70 % full.
-// Below, short unsplit calls with shared heads gain from a column each (x < 12, at 64 16: 0.83 - 1.05 of their time, mean 0.94; half as long 0.99;
-// without shared heads 0.95 - 1.08).
+// Below, short unsplit calls with shared heads gain from a column each (x < 12, at 64 16); at 128 from 7 tiles on (140 shapes, equal lengths of the whole
+// capacity | different | half of it: 3 tiles 1.06 | 1.06 | 1.06 of their time; 4 - 6: 0.99 | 0.99 | 1.02; 7 - 10: 0.97 | 0.97 | 1.00; 11 - 13: 0.91 | 0.91 | 0.95; at
+// 64 3 - 6: 0.93 | 0.93 | 0.95; 7 - 13: 0.85 | 0.85 | 0.91; without shared heads 0.95 - 1.08).
 inline void plan_columns(const specvlm_attn_desc& d, AttnPlan& plan) {
     const int group = d.H_q / d.H_kv, rows = group * d.N_max, blocks = (rows + 63) / 64;
     const int64_t units = static_cast<int64_t>(d.H_kv) * blocks;
@@ -242,13 +243,14 @@ inline void plan_columns(const specvlm_attn_desc& d, AttnPlan& plan) {
     if (blocks > 1)
         for (int c = columns; c >= d.B && 8 * c >= 7 * columns; --c)
             if (d.H_kv * c % 8 == 0) { columns = c; break; }
-    const double x = static_cast<double>((cap + kTile - 1) / kTile) * d.B / columns;
+    const int ntile = (cap + kTile - 1) / kTile;
+    const double x = static_cast<double>(ntile) * d.B / columns;
     const bool wide = d.D == 128;
     if (plan.streams) {
         if (x < (wide ? 26 : 60)) return;
     } else {
         if (group > 1 && !plan.block_rows && plan.splits == 1 && x < (wide ? 12 : 16)) {
-            plan.columns = d.B;
+            if (!wide || ntile >= 7) plan.columns = d.B;
             return;
         }
         const int used = std::min(columns / d.B, kMostRanges) * d.B;

@@ -46,6 +46,8 @@ def test_bounds(seed):
     ((4, 40, 40, 128, 60, 4928), True, 6, 1), ((4, 35, 5, 128, 48, 2064), False, 8, 1), ((4, 28, 4, 128, 60, 3072), False, 8, 1),
     # one column a request: no room for more; short
     ((8, 32, 32, 128, 60, 976), False, 8, 0), ((8, 40, 8, 128, 48, 288), True, 8, 0), ((8, 32, 32, 128, 60, 272), False, 0, 0), ((4, 40, 40, 128, 64, 736), False, 4, 0),
+    # short, heads shared: from seven tiles on, at 64 always
+    ((7, 32, 4, 128, 64, 144), False, 0, 0), ((7, 32, 4, 128, 64, 192), True, 0, 0), ((7, 32, 4, 128, 64, 208), False, 7, 0), ((7, 32, 4, 64, 64, 144), False, 7, 0),
     # head size 64: longer streams
     ((5, 16, 16, 64, 60, 6144), False, 16, 1), ((5, 16, 16, 64, 60, 3088), False, 15, 0),
     # key ranges and row blocks: longer ones, as they lose more where requests are shorter than their cache; row blocks whose

@@ -87,7 +87,8 @@ typedef struct specvlm_attn_desc {
     int32_t kv_capacity;           /* slots per request (contiguous); paged: max_blocks_per_req*16.  Any
                                       number is served; a multiple of 16 lets batches of bf16 take a
                                       kernel that is up to a third faster */
-    int32_t num_splits;            /* key-range splits per (request, head): 0 lets the library choose, 1 ..
+    int32_t num_splits;            /* key-range splits per (request, head): 0 lets the library choose, by the
+                                      requests' lengths too; 1 ..
                                       SPECVLM_MAX_SPLITS is taken as given (anything else: SPECVLM_INVALID_ARG);
                                       with more than 1024 (request, head) pairs a call always runs unsplit */
     int64_t q_stride_b, q_stride_n, q_stride_h;
@@ -102,22 +103,27 @@ int32_t specvlm_version(void);
 int32_t specvlm_last_hip_error(void);
 
 /*
- * Scratch bytes specvlm_tree_verify_attn wants for `desc` (arrival counters and split-key
- * partial results; 0 when the shape needs none).  Returns 0 when desc is invalid.  A call whose
- * specvlm_tree_verify_attn_num_splits is 1 also runs with less, or without, if more slowly.  The
- * workspace is device memory, 256-byte aligned.  It must be ZERO-FILLED ONCE after
+ * Scratch bytes specvlm_tree_verify_attn wants for `desc` (arrival counters and partial results of
+ * key ranges; 0 when the shape needs none).  Returns 0 when desc is invalid.  The workspace is
+ * device memory, 256-byte aligned.  It must be ZERO-FILLED ONCE after
  * allocation; every call leaves its counter words zero again, and the counters occupy the
  * same fixed region at the start whatever the shape, so the same workspace can be reused by
  * later calls (of any shape it is large enough for) without clearing.  Two calls that may
- * run concurrently need separate workspaces.
+ * run concurrently need separate workspaces, whatever specvlm_tree_verify_attn_num_splits says of
+ * them: a batch that is divided by its requests' lengths (below) uses counters and partial results
+ * also where that is 1.  Such a batch runs with less too, if more slowly: with what an even division
+ * needs, which is none where specvlm_tree_verify_attn_num_splits is 1.
  */
 size_t specvlm_tree_verify_attn_workspace_bytes(const specvlm_attn_desc *desc);
 
 /*
- * Number of key-range splits per (request, head) specvlm_tree_verify_attn plans with for
- * `desc` (desc->num_splits when that is positive, otherwise the library's choice for the
- * shape; in the latter case a call that divides the query rows among workgroups as well may use
- * fewer).  Returns 0 when desc is invalid, 1 for SPECVLM_F32 (no split path).
+ * Number of key-range splits per (request, head) of an even division of `desc` (desc->num_splits
+ * when that is positive, otherwise the library's choice for the shape).  With desc->num_splits 0 a
+ * call may take others: fewer where it divides the query rows among workgroups as well, and in a batch
+ * of up to 16 requests one to eight for every request, chosen on the device by the requests'
+ * lengths.  The last bits of such a batch's results depend on all of its lengths, and on whether the
+ * workspace holds what specvlm_tree_verify_attn_workspace_bytes asks for.  Returns 0 when desc is
+ * invalid, 1 for SPECVLM_F32 (no split path).
  */
 int32_t specvlm_tree_verify_attn_num_splits(const specvlm_attn_desc *desc);
 
@@ -165,7 +171,7 @@ int32_t specvlm_tree_verify_attn(const specvlm_attn_desc *desc,
  * static device array inside the library, SPECVLM_STATIC_WORKSPACE_BYTES long, one per GPU, held
  * from the moment the library is loaded on that GPU until the process ends.  The call allocates
  * and frees nothing (the first call on a device asks the runtime once for the array's address).
- * A shape whose specvlm_tree_verify_attn_workspace_bytes exceeds the array returns
+ * A shape whose partial results exceed the array, evenly divided too, returns
  * SPECVLM_WORKSPACE_TOO_SMALL and launches nothing.  Every call on a GPU uses that GPU's one
  * array: calls that may overlap on one GPU (two streams) race on it and must use
  * specvlm_tree_verify_attn with workspaces of their own instead; calls ordered by a stream, or

@@ -212,8 +212,8 @@ __global__ __launch_bounds__(kThreadsAS) void tree_accept_sample_kernel(
 
     int cur = 0, m = 0;
     float mx = 0.f, Z = 0.f, mass = 0.f;               // mass: this thread's share of Z
-    // unnormalised probability exp((l - max) / T) as one multiply and one v_exp_f32 (the whole
-    // vocabulary goes through it three times on a single compute unit); -inf gives 0
+    // unnormalised probability exp((l - max) / T) as one multiply and one v_exp_f32 (a row goes through it once a level,
+    // on a single compute unit; the bonus draw takes only chunks or regions again); -inf gives 0
     const float c2 = 1.4426950408889634f / temperature;
     auto prob_of = [&](float l) -> float { return __builtin_amdgcn_exp2f((l - mx) * c2); };
     auto sum_of = [&](const uint4& w) __attribute__((always_inline)) -> float {
@@ -340,7 +340,7 @@ __global__ __launch_bounds__(kThreadsAS) void tree_accept_sample_kernel(
         for (int r = 0; r < nrej; ++r) mine |= static_cast<unsigned long long>(s_rej[r] >= v0 && s_rej[r] < v1) << r;
         // lv[] still holds cur's row
         // A chunk without a rejected token has the sum that went into Z, added up in the same order; few
-        // wavefronts hold any other (all of them summing again: 32000 tokens 12.1 us, now 10.9; 65536 19.6, now 17.7).
+        // wavefronts hold any other (all of them summing again: 32000 tokens 12.1 us, now 10.9).
         csum = mass;
         if (mine) {
             for (unsigned long long r = mine; r; r &= r - 1) drop(lv, NV, s_rej[__builtin_ctzll(r)] - v0);

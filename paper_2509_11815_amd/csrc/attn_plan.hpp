@@ -71,8 +71,8 @@ struct AttnPlan {
     int32_t ranges;        // key ranges per head that the workspace holds
     int32_t block_rows;    // query rows per workgroup, 0: all (key ranges only)
     int32_t splits;        // key ranges the call takes, <= ranges
-    int32_t streams = 0;   // key ranges of the kernel with four streams per workgroup (attn_streams.hip), <= ranges; 0: one of the others
-    int32_t columns = 0;   // workgroups of that kernel per row block of a KV head, all requests together; 0: one of the other kernels
+    int32_t streams = 0;   // key ranges of a request in the kernel with four streams per workgroup (attn_streams.hip) when it divides evenly, <= ranges; 0: that is another kernel's
+    int32_t columns = 0;   // workgroups of the kernel with four streams per row block of a KV head, all requests together: it takes the call; 0: one of the others
     int32_t by_length = 0; // the columns are dealt out to the requests by their lengths, on the device
 };
 
@@ -130,10 +130,10 @@ inline AttnPlan plan_rows(const specvlm_attn_desc& d, int32_t nominal) {
 //   28 / 4 x 4                      3000      30.8 -> 28.8 | 26.8            3000 - 500  31.0 -> 27.9 | 26.3
 //   32 / 8 x 3                      3000      30.7 -> 28.4 | 27.8            3000 - 500  30.7 -> 23.2 | 26.9
 //   48 / 8 x 2                      4500      40.9 -> 35.8 | 37.0            4500 + 700  41.1 -> 28.9 | 36.4
-// (figures of these kernels before attn_streams.hip, which now takes all of these shapes with two ranges; stream_ranges below.  This rule
+// (figures of these kernels before attn_streams.hip, which now takes all of these shapes, by length: plan_columns below.  This rule
 // then says how large the workspace is, and still chooses the kernel where that one is not taken: blocks of rows less than 55 % full, fewer
 // than 180 workgroups, capacities that are no multiple of 16.)  Four ranges in two workgroups per compute unit | attn_streams.hip:
-//   32 / 8 x 4, 3000: 28.9 | 24.5; 2500 - 300: 21.8 | 21.6; 64 / 8 x 2, 4500: 36.6 | 29.9; 4500 + 900: 28.9 | 29.7, paged 30.3 | 31.9;
+//   (two ranges each)  32 / 8 x 4, 3000: 28.9 | 24.5; 2500 - 300: 21.8 | 21.6; 64 / 8 x 2, 4500: 36.6 | 29.9; 4500 + 900: 28.9 | 29.7, paged 30.3 | 31.9;
 //   40 / 8 x 3, 3000: 28.8 | 23.8; 4500 - 1000: 29.3 | 29.7; 28 / 4 x 4, 3000 - 500: 27.7 | 22.6; 48 / 8 x 2, 4500 + 700: 28.5 | 28.8, paged 30.0 | 31.2
 // (one request much longer than the other: two ranges of it are all that 256 workgroups of 64 rows leave; up to 5 % slower, equal
 // lengths 15 - 22 % faster, and the host does not know the lengths.)

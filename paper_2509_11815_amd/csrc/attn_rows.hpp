@@ -20,8 +20,9 @@ struct WaveParams {
     const int32_t *prefix_len, *num_nodes, *parent;
     int32_t* err_flag;
     int32_t* ws_cnt;            // [units][4 owners] arrival tickets, kCounterStride words apart, zero between calls
-    unsigned char* ws_acc;      // [units * splits][owners][..][64 lanes] 16-byte vectors of packed bf16
-    float* ws_ml;               // [units * splits][block rows][2] (max, sum)
+    // one part per unit and split, or per workgroup (attn_streams.hip)
+    unsigned char* ws_acc;      // [parts][owners][..][64 lanes] 16-byte vectors of packed bf16, or of fp32 (attn_streams.hip, `wide`)
+    float* ws_ml;               // [parts][block rows][2] (max, sum)
 };
 
 // n / d for n * d < 2^31, with m = ceil(2^31 / d) from the host.

@@ -656,7 +656,7 @@ __device__ __forceinline__ void attend(const StreamsParams& p) {
         if (!__builtin_amdgcn_readfirstlane(is_last)) return;
         asm volatile("" ::: "memory");
         // device-coherent (sc1) buffer loads, which the compiler counts; not before the ticket was seen
-        constexpr int kCoherent = 16, kBatch = 4;
+        constexpr int kCoherent = 16;
         const auto acc_rsrc = __builtin_amdgcn_make_buffer_rsrc(p.ws_acc + part0 * part_bytes + wave * vectors * 1024, 0, 0x7FFFFFFF, 0x00027000);
         const auto ml_rsrc = __builtin_amdgcn_make_buffer_rsrc(p.ws_ml + part0 * kQRows * 2, 0, 0x7FFFFFFF, 0x00027000);
         const int last = ranges - 1;

@@ -26,7 +26,7 @@ if ROOT not in sys.path:
 HBM_PEAK_GBPS = 8000.0          # MI355X published HBM3E peak
 # the kernel that the library chooses for a workload's attention call (--splits 0)
 ATTENTION_KERNELS = {"C2": "attn_wave_kernel<128, 2, false>", "C3": "attn_mfma_kernel<128, 2>",
-                     "C4": "attn_streams_kernel<128, false>", "C5": "attn_mfma_kernel_2wg<128>"}
+                     "C4": "attn_streams_kernel<128, false>", "C5": "attn_shares_kernel<128, true>"}
 
 
 
@@ -314,7 +314,7 @@ def main():
         nbytes = W.kv_bytes_per_layer(c)
         rec = {"attn_us_per_launch": round(us, 3), "algorithmic_bytes_per_launch": nbytes,
                "GBps": round(nbytes / (us * 1e-6) / 1e9, 1), "frac": round(nbytes / (us * 1e-6) / 1e9 / HBM_PEAK_GBPS, 4),
-               "key_ranges_at_most": sv.specvlm_tree_verify_attn_num_splits(dc), "layers_timed": Lc,
+               "key_ranges_of_even_division": sv.specvlm_tree_verify_attn_num_splits(dc), "layers_timed": Lc,
                "shape": f"B={c.B}, H={c.H}, D={c.D}, prefix={Pc.tolist()}, paged={c.paged}"
                         + (f", cache capacity {capacity}" if capacity else "")}
         if tail:
@@ -436,7 +436,7 @@ def main():
                                f"tree nodes={N}, depth={cfg.depth}, vocab={cfg.V}, paged={cfg.paged}",
                    "launch": "HIP graph replay of one whole step" if not args.no_graph else "eager launches",
                    "timing": "HIP events on the stream the calls are launched on",
-                   "key_ranges_at_most": sv.specvlm_tree_verify_attn_num_splits(desc),
+                   "key_ranges_of_even_division": sv.specvlm_tree_verify_attn_num_splits(desc),
                    "accept_len": acc_out[0].tolist()},
         "verify_steps_per_s": round(1e3 / ms_step, 1),
         "pct_hbm_peak": round(100.0 * value / HBM_PEAK_GBPS, 2),
@@ -464,7 +464,7 @@ def main():
                      "traffic": measured_traffic("attn_mfma_kernel_C3.txt", "attn_mfma.hip", "attn_mfma_body.inc") if cfg.name == "C3" else None},
         "configs": dict({cfg.name: {"attn_us_per_launch": round(attn_launch_us, 3), "algorithmic_bytes_per_launch": kv_bytes_layer,
                                     "GBps": round(achieved, 1), "frac": round(achieved / HBM_PEAK_GBPS, 4),
-                                    "key_ranges_at_most": sv.specvlm_tree_verify_attn_num_splits(desc), "layers_timed": L}},
+                                    "key_ranges_of_even_division": sv.specvlm_tree_verify_attn_num_splits(desc), "layers_timed": L}},
                         **other_configs),
     }
 

@@ -327,10 +327,11 @@ __device__ __forceinline__ void rank_winners(unsigned long long* s_key, int c, i
 // 32000) alone.  They store a log-sum-exp and K logits; the scores are put together by the one that selects, from the same operations.
 // A growth of six levels, ten rows each but the root, in a graph, one workgroup a row -> two: bf16, one request 32000 tokens 48.8 -> 44.4 us,
 // 65000 59.4 -> 53.8, 152064 108.2 -> 94.0; eight requests 54.0 -> 50.1, 63.0 -> 60.6, 121.7 -> 106.7; fp32, one 50.4 -> 47.3, 62.3 -> 58.5,
-// 110.7 -> 98.0.  Then rows beyond 65536 entries requested a group ahead, nothing summed where a row has ended, chunks that reach
-// the threshold found by a bit mask: bf16, one request 70000 69.9 -> 65.9, 100001 81.7 -> 75.4, 152064 94.5 -> 87.8, eight 106.2 -> 95.5; fp32
-// 99.1 -> 92.0, 140.1 -> 129.1 (four or eight chunks of bf16 a group: 87.8 and 92.6).  (Tried: the log-sum-exp of a long row shared by up to five workgroups in segments of 32768 entries, and rows of up to
-// 163840 bf16 entries in registers: the segments' reductions cost the other calls 1 us, the longer unrolled code 5.)
+// 110.7 -> 98.0.  Then nothing summed where a row beyond 65536 entries has ended, chunks that reach the threshold found by a bit mask, and in bf16 the
+// next group of loads requested ahead: bf16, one request 70000 69.9 -> 65.9, 100001 81.7 -> 75.4, 152064 94.5 -> 87.8, eight 106.2 -> 95.5 (four or eight
+// chunks a group: 87.8 and 92.6); fp32 (and one workgroup a row for eight requests) one 83.6 -> 68.5, 99.7 -> 80.7, 112.6 -> 93.8, eight 95.1 -> 83.7, 109.0 ->
+// 95.2, 123.7 -> 108.5 from what there was at first.  (Tried: the log-sum-exp of a long row shared by up to five workgroups in segments of 32768
+// entries, and rows of up to 163840 bf16 entries in registers: the segments' reductions cost the other calls 1 us, the longer unrolled code 5.)
 struct SelArgs {
     int M, index_base;
     int32_t* sel_out;

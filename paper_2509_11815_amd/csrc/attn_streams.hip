@@ -291,36 +291,19 @@ __device__ __forceinline__ void attend(const StreamsParams& p) {
 #pragma unroll
         for (int c = 0; c < NC; ++c) ka[c] = *reinterpret_cast<const bf16x8*>(ring + slot_off + kaddr[c]);
     };
-    // requested after the query rows: V0, K1, V1 (an early request) or K0, V0, K1, V1
-    if (my_tiles > 1) wait_vmcnt<3 * KLD>();
-    else if (my_tiles == 1) wait_vmcnt<KLD>();
-    else wait_vmcnt<0>();
-    __syncthreads();
+    // Ancestor-or-self masks of this lane's two query rows, while the first tile is on its way (in the tile that needs them, the last of its
+    // stream, they stand in the call's chain): pointer doubling over the lanes (lane i holds node i).  Requested after the parents: K0 (an early
+    // request), the query rows, then block ids, K0, V0, K1, V1.
+    if (my_tiles > 1) wait_vmcnt<NQ + 4 * KLD + (PAGED ? 1 : 0)>();
+    else if (my_tiles == 1) wait_vmcnt<NQ + 2 * KLD + (PAGED ? 1 : 0)>();
+    else wait_vmcnt<NQ>();
     const int par = s_par[wave][lane];
-    if constexpr (PAGED) {
-        if (my_tiles > 0) read_ids();
-    }
-    bf16x8 qf[2][NC];
-#pragma unroll
-    for (int qb = 0; qb < 2; ++qb)
-#pragma unroll
-        for (int c = 0; c < NC; ++c) qf[qb][c] = *reinterpret_cast<const bf16x8*>(s_q + qb * 32 * ROWG * 16 + kaddr[c]);
-#pragma unroll
-    for (int qb = 0; qb < 2; ++qb)
-#pragma unroll
-        for (int c = 0; c < NC; ++c) asm volatile("" : "+a"(qf[qb][c]));
     const bool bad_par = lane < n && (lane == 0 ? par != -1 : (par < 0 || par >= lane));
     if (__any(bad_par)) err |= SPECVLM_ERR_BAD_PARENT;
-    if (err) {                                             // the same in every wavefront of the request
-        if (tid == 0 && p.err_flag) atomicOr(p.err_flag, err);
-        wait_vmcnt<0>();
-        return;
-    }
-    // Ancestor-or-self masks of this lane's two query rows: pointer doubling over the lanes (lane i holds node i)
     uint32_t anc_lo[2], anc_hi[2];
-    auto build_anc = [&]() __attribute__((always_inline)) {
+    {
         uint32_t mlo = lane < 32 ? 1u << (lane & 31) : 0u, mhi = lane < 32 ? 0u : 1u << (lane & 31);
-        int up = lane < n ? par : -1;
+        int up = lane < n && !err ? par : -1;              // (a bad array may have cycles)
 #pragma unroll 1
         while (__any(up >= 0)) {
             const int src = max(up, 0) * 4;
@@ -335,7 +318,29 @@ __device__ __forceinline__ void attend(const StreamsParams& p) {
             anc_lo[qb] = __builtin_amdgcn_ds_bpermute(node * 4, mlo);
             anc_hi[qb] = __builtin_amdgcn_ds_bpermute(node * 4, mhi);
         }
-    };
+    }
+    // requested after the query rows: V0, K1, V1 (an early request) or K0, V0, K1, V1
+    if (my_tiles > 1) wait_vmcnt<3 * KLD>();
+    else if (my_tiles == 1) wait_vmcnt<KLD>();
+    else wait_vmcnt<0>();
+    __syncthreads();
+    if constexpr (PAGED) {
+        if (my_tiles > 0) read_ids();
+    }
+    bf16x8 qf[2][NC];
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) qf[qb][c] = *reinterpret_cast<const bf16x8*>(s_q + qb * 32 * ROWG * 16 + kaddr[c]);
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) asm volatile("" : "+a"(qf[qb][c]));
+    if (err) {                                             // the same in every wavefront of the request
+        if (tid == 0 && p.err_flag) atomicOr(p.err_flag, err);
+        wait_vmcnt<0>();
+        return;
+    }
     // Softmax state of query row 32 qb + l32 (both halves agree): reference maximum, the same times c2 (0 while no key was
     // seen), the maximum that moves it, and this lane's part of the sum of the row's weights.
     // acc[qb][t][i]: O^T row 32t + 8 (i / 4) + 4 hf + i % 4.
@@ -408,6 +413,15 @@ __device__ __forceinline__ void attend(const StreamsParams& p) {
         for (int t = 0; t < NT; ++t) read_v(t, 0);
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) lmax[qb] = max16(s[qb]);
+        // The first reference, where every key is visible: as in the step below, with nothing accumulated that it would scale
+        if (stream * kKeys + kKeys <= P && __any((lmax[0] > thr[0]) | (lmax[1] > thr[1]))) {
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb) {
+                m_run[qb] = fmaxf(m_run[qb], fmaxf(lmax[qb], other_half(lmax[qb])));
+                thr[qb] = m_run[qb] + tau;
+                mrc[qb] = (m_run[qb] == -INFINITY ? 0.f : m_run[qb]) * c2;
+            }
+        }
     }
     // One tile.  At its start s holds tile j's scores and lmax their maxima; va (being read) its V operands, ka the next tile's
     // K operands.  LEFT: tiles after this one (3: three or more).
@@ -415,20 +429,19 @@ __device__ __forceinline__ void attend(const StreamsParams& p) {
         constexpr int LEFT = decltype(after)::value;
         const int slot0 = (stream + j * nstream) * kKeys;
         if (slot0 + kKeys > P) {                           // reaches past the prefix: tree region or tail
-            build_anc();
-            // branch-free on purpose: plain integer logic and one select per score
+            // bit k of `visible`: key slot0 + k.  Its place among this lane's scores is a constant once the lane's half is shifted out, so a
+            // score takes two instructions (a sign-extended bit and a bitwise select)
+            const int before = P - slot0;                  // keys of the tile in the prefix, < 32
+            const uint32_t exist = S - slot0 < 32 ? (1u << (S - slot0)) - 1u : ~0u;
 #pragma unroll
             for (int qb = 0; qb < 2; ++qb) {
                 const unsigned long long anc = (static_cast<unsigned long long>(anc_hi[qb]) << 32) | anc_lo[qb];
+                uint32_t visible = before > 0 ? (anc_lo[qb] << before) | ((1u << before) - 1u) : static_cast<uint32_t>(anc >> -before);
+                visible = (visible & exist) >> (4 * hf);
 #pragma unroll
                 for (int i = 0; i < 16; ++i) {
-                    const int slot_key = slot0 + 8 * (i >> 2) + 4 * hf + (i & 3);
-                    const int rel = slot_key - P;
-                    const uint32_t in_prefix = static_cast<uint32_t>(rel) >> 31;
-                    const uint32_t is_anc = static_cast<uint32_t>(anc >> (rel & 63)) & 1u;
-                    const uint32_t in_range = static_cast<uint32_t>(slot_key - S) >> 31;
-                    const uint32_t vis = in_range & (in_prefix | is_anc);
-                    s[qb][i] = vis ? s[qb][i] : -INFINITY;
+                    const uint32_t seen = static_cast<uint32_t>(static_cast<int32_t>(visible << (31 - (8 * (i >> 2) + (i & 3)))) >> 31);
+                    s[qb][i] = __uint_as_float((seen & __float_as_uint(s[qb][i])) | (~seen & 0xFF800000u));
                 }
                 lmax[qb] = max16(s[qb]);
             }

@@ -40,6 +40,7 @@ struct StreamsParams : WaveParams {
     int wide;                   // partial results in fp32
     uint32_t magic_columns, magic_each;
     float inv_columns, least_gain;   // rounds that a division must save
+    float c2, tau;              // scale x log2 e; how far a score may lie above the reference before that moves
 };
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -280,8 +281,7 @@ __device__ __forceinline__ void attend(const StreamsParams& p) {
     int phys2[2] = {0, 0};
     if (my_tiles > 2) fetch_blocks(2, phys2);
 
-    const float c2 = p.scale * kLog2e;
-    const float tau = fminf(kTau / c2, 1e30f);
+    const float c2 = p.c2, tau = p.tau;
     // K fragments of a tile (A operand): lane (key l32, half hf) holds dims 16c + 8hf .. +7; the query rows likewise
     uint32_t kaddr[NC];
 #pragma unroll
@@ -319,28 +319,6 @@ __device__ __forceinline__ void attend(const StreamsParams& p) {
             anc_hi[qb] = __builtin_amdgcn_ds_bpermute(node * 4, mhi);
         }
     }
-    // requested after the query rows: V0, K1, V1 (an early request) or K0, V0, K1, V1
-    if (my_tiles > 1) wait_vmcnt<3 * KLD>();
-    else if (my_tiles == 1) wait_vmcnt<KLD>();
-    else wait_vmcnt<0>();
-    __syncthreads();
-    if constexpr (PAGED) {
-        if (my_tiles > 0) read_ids();
-    }
-    bf16x8 qf[2][NC];
-#pragma unroll
-    for (int qb = 0; qb < 2; ++qb)
-#pragma unroll
-        for (int c = 0; c < NC; ++c) qf[qb][c] = *reinterpret_cast<const bf16x8*>(s_q + qb * 32 * ROWG * 16 + kaddr[c]);
-#pragma unroll
-    for (int qb = 0; qb < 2; ++qb)
-#pragma unroll
-        for (int c = 0; c < NC; ++c) asm volatile("" : "+a"(qf[qb][c]));
-    if (err) {                                             // the same in every wavefront of the request
-        if (tid == 0 && p.err_flag) atomicOr(p.err_flag, err);
-        wait_vmcnt<0>();
-        return;
-    }
     // Softmax state of query row 32 qb + l32 (both halves agree): reference maximum, the same times c2 (0 while no key was
     // seen), the maximum that moves it, and this lane's part of the sum of the row's weights.
     // acc[qb][t][i]: O^T row 32t + 8 (i / 4) + 4 hf + i % 4.
@@ -361,6 +339,28 @@ __device__ __forceinline__ void attend(const StreamsParams& p) {
     // 16-lane block four keys at dim i of the 16 that the block's lanes address (lane j: key j / 4, dims 4 (j % 4) ..)
     const int k0 = 4 * hf + ((lane & 15) >> 2);
     const uint32_t vaddr = kTileBytes + k0 * (ROWG * 16) + ((lane >> 4) & 1) * 32 + (lane & 3) * 8 + (vswz(k0) << 6);
+    // (all of this before the wait: the compiler would put it behind, where the first products wait for it)
+#pragma unroll
+    for (int c = 0; c < NC; ++c) asm volatile("" : "+v"(kaddr[c]));
+    asm volatile("" : : "v"(vaddr));
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) asm volatile("" : "+v"(acc[qb][t]));
+    // requested after the query rows: V0, K1, V1 (an early request) or K0, V0, K1, V1
+    if (my_tiles > 1) wait_vmcnt<3 * KLD>();
+    else if (my_tiles == 1) wait_vmcnt<KLD>();
+    else wait_vmcnt<0>();
+    __syncthreads();
+    if constexpr (PAGED) {
+        if (my_tiles > 0) read_ids();
+    }
+    bf16x8 qf[2][NC];
+    if (err) {                                             // the same in every wavefront of the request
+        if (tid == 0 && p.err_flag) atomicOr(p.err_flag, err);
+        wait_vmcnt<0>();
+        return;
+    }
     bf16x8 va[NT][2];
     auto read_v = [&](int t, int slot_off) __attribute__((always_inline)) {
         const uint32_t a = (vaddr ^ (t << 6)) + slot_off;
@@ -403,7 +403,16 @@ __device__ __forceinline__ void attend(const StreamsParams& p) {
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the K area of slot 0 is free
         if (my_tiles > 2) issue_k(2, phys2);
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb) scores(s[qb], qb);
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb) qf[qb][c] = *reinterpret_cast<const bf16x8*>(s_q + qb * 32 * ROWG * 16 + kaddr[c]);
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb) {
+                asm volatile("" : "+a"(qf[qb][c]));
+                s[qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[c], qf[qb][c], c ? s[qb] : zero, 0, 0, 0);
+            }
         // V0 and K1 (the requests after them: V1, K2)
         if (my_tiles > 2) wait_vmcnt<2 * KLD>();
         else if (my_tiles == 2) wait_vmcnt<KLD>();
@@ -774,6 +783,8 @@ int32_t launch_attn_streams(const AttnArgs& a) {
     p.magic_columns = divisor(p.columns);
     p.magic_each = divisor(p.each);
     p.inv_columns = 1.f / p.columns;
+    p.c2 = a.scale * kLog2e;
+    p.tau = std::fmin(kTau / p.c2, 1e30f);
     p.least_gain = a.d.D == 128 ? 1.3f : 2.5f;             // meeting of partial results, 1.5 us, in rounds
     workgroups = static_cast<unsigned>(p.columns) * a.d.H_kv * p.row_blocks;
     p.ws_acc = static_cast<unsigned char*>(a.workspace) + kCounterBytes + static_cast<size_t>(workgroups) * kQRows * 8;

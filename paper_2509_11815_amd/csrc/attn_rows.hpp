@@ -1,6 +1,8 @@
 // Shared by the bf16 attention kernels whose wavefronts have a key stream of their own (attn_wave.hip, attn_streams.hip):
 // parameters, divisions by constants of the call, direct-to-LDS loads of half a tile.
 #pragma once
+#include <cmath>
+
 #include "attn_common.hpp"
 
 namespace specvlm {
@@ -13,6 +15,7 @@ struct WaveParams {
     int N_max, H_q, H_kv, group, row_blocks, num_splits;
     uint32_t magic_splits, magic_rb, magic_hkv, magic_nmax, magic_nstream;   // divisors, see divide()
     float scale;                // softmax scale
+    float c2, tau;              // scale x log2 e; how far a score may lie above the reference before that moves
     const uint16_t *q, *k, *v;
     uint16_t* o;
     float* lse;
@@ -43,6 +46,8 @@ inline WaveParams wave_params(const AttnArgs& a, int block_rows, int splits, uns
     p.magic_splits = divisor(p.num_splits); p.magic_rb = divisor(p.row_blocks); p.magic_hkv = divisor(p.H_kv);
     p.magic_nmax = divisor(p.N_max); p.magic_nstream = divisor(kWaveWgs * p.num_splits);
     p.scale = a.scale;
+    p.c2 = a.scale * kLog2e;
+    p.tau = std::fmin(kTau / p.c2, 1e30f);
     p.q = static_cast<const uint16_t*>(a.q);
     p.k = static_cast<const uint16_t*>(a.k);
     p.v = static_cast<const uint16_t*>(a.v);

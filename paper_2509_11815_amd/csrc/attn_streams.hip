@@ -40,7 +40,6 @@ struct StreamsParams : WaveParams {
     int wide;                   // partial results in fp32
     uint32_t magic_columns, magic_each;
     float inv_columns, least_gain;   // rounds that a division must save
-    float c2, tau;              // scale x log2 e; how far a score may lie above the reference before that moves
 };
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -783,8 +782,6 @@ int32_t launch_attn_streams(const AttnArgs& a) {
     p.magic_columns = divisor(p.columns);
     p.magic_each = divisor(p.each);
     p.inv_columns = 1.f / p.columns;
-    p.c2 = a.scale * kLog2e;
-    p.tau = std::fmin(kTau / p.c2, 1e30f);
     p.least_gain = a.d.D == 128 ? 1.3f : 2.5f;             // meeting of partial results, 1.5 us, in rounds
     workgroups = static_cast<unsigned>(p.columns) * a.d.H_kv * p.row_blocks;
     p.ws_acc = static_cast<unsigned char*>(a.workspace) + kCounterBytes + static_cast<size_t>(workgroups) * kQRows * 8;

@@ -37,6 +37,16 @@ __device__ __forceinline__ float max8(f32x4 a, f32x4 b) {
     return max3(max3(a[0], a[1], a[2]), max3(a[3], b[0], b[1]), __builtin_elementwise_maximum(b[2], b[3]));
 }
 
+// op over the four lanes g = 0 .. 3 of a row, in every one of them: (0 1) (2 3), or (1 0) (3 2), then across.
+template <typename Op>
+__device__ __forceinline__ float across_row(float x, Op op) {
+    const uint32_t a = __float_as_uint(x);
+    const auto r = __builtin_amdgcn_permlane16_swap(a, a, false, false);     // lanes 16 apart
+    const uint32_t y = __float_as_uint(op(__uint_as_float(r[0]), __uint_as_float(r[1])));
+    const auto q = __builtin_amdgcn_permlane32_swap(y, y, false, false);     // lanes 32 apart
+    return op(__uint_as_float(q[0]), __uint_as_float(q[1]));
+}
+
 template <int D, int QB, bool PAGED>
 __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1, 1))) void attn_wave_kernel(WaveParams p) {
     constexpr int NC = D / 32;                 // QK^T contraction steps of 32
@@ -58,6 +68,7 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
     __shared__ __attribute__((aligned(1024))) unsigned char s_q[QB * 16 * D * 2];
     __shared__ float s_m[kWaveWgs][QB * 16];
     __shared__ float s_l[kWaveWgs][QB * 16];
+    __shared__ int s_par[kWaveWgs][64];
 
     // What the first requests need of the arguments, in one trip to memory (left to itself the compiler loads them where they
     // are used: two more trips, one of them the lengths', before the first request; 2 x 16 / 4 heads, 300 keys 6.50 -> 6.37 us)
@@ -85,13 +96,9 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
     typedef __attribute__((address_space(3))) unsigned char lds_byte;
     const uint32_t ring_lds = (uint32_t)(uintptr_t)(lds_byte*)ring;
 
-    // the parent array, lane i <- parent[i]: first in the queue, waited for on its own
-    int par;
-    {
-        const uint32_t voff = min(lane, p.N_max - 1) * 4;
-        const int32_t* src = p.parent + b * p.N_max;
-        asm volatile("global_load_dword %0, %1, %2" : "=v"(par) : "v"(voff), "s"(src) : "memory");
-    }
+    // the parent array, first in the queue and waited for on its own (every wavefront its own copy)
+    typedef __attribute__((address_space(3))) int lds_int;
+    dma4(p.parent + b * p.N_max + min(lane, p.N_max - 1), (uint32_t)(uintptr_t)(lds_int*)s_par[wave]);
 
     // ---- tile fetch -------------------------------------------------------------------------
     const int lrow = lane / ROWG, lpos = lane % ROWG;
@@ -203,15 +210,14 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
     int phys_k[2] = {0, 0}, phys_v[2] = {0, 0};            // block ids of the next K and V tile to request
     if (my_tiles > 2) { fetch_blocks(2, phys_k); phys_v[0] = phys_k[0]; phys_v[1] = phys_k[1]; }
 
-    const float c2 = p.scale * kLog2e;
-    const float tau = fminf(kTau / c2, 1e30f);
+    const float c2 = p.c2, tau = p.tau;
     // ---- the tree: every wavefront checks it and builds the ancestor masks in registers ----------
     // requested after the parent array: K0, the query rows, V0 (an early request) or the query rows, K0, V0,
     // and the second tile
     if (my_tiles > 1) wait_vmcnt<4 * KLD + NQ>();
     else if (my_tiles == 1 || early) wait_vmcnt<2 * KLD + NQ>();
     else wait_vmcnt<NQ>();
-    asm volatile("" : "+v"(par));
+    const int par = s_par[wave][lane];
     const bool bad_par = lane < n && (lane == 0 ? par != -1 : (par < 0 || par >= lane));
     if (__any(bad_par)) err |= SPECVLM_ERR_BAD_PARENT;
     if (err) {                                             // the same in every wavefront of the request
@@ -219,11 +225,10 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
         wait_vmcnt<0>();
         return;
     }
-    // Ancestor-or-self masks of this lane's query rows, built when the first tile that needs them comes up:
-    // pointer doubling over the lanes (lane i holds node i), at most six rounds.
+    // Ancestor-or-self masks of this lane's query rows, while the first tile is on its way (the tile that needs them is the last of its
+    // stream): pointer doubling over the lanes (lane i holds node i), at most six rounds.
     uint32_t anc_lo[QB], anc_hi[QB];
-    bool have_anc = false;                                 // uniform
-    auto build_anc = [&]() __attribute__((always_inline)) {
+    {
         uint32_t mlo = lane < 32 ? 1u << (lane & 31) : 0u, mhi = lane < 32 ? 0u : 1u << (lane & 31);
         int up = lane < n ? par : -1;
 #pragma unroll 1
@@ -240,8 +245,7 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
             anc_lo[qb] = __builtin_amdgcn_ds_bpermute(node * 4, mlo);
             anc_hi[qb] = __builtin_amdgcn_ds_bpermute(node * 4, mhi);
         }
-        have_anc = true;
-    };
+    }
 
     // ---- K fragments of a tile (A operand): lane (key 16x + l16, g) holds d = 32c + 8g .. +7 ------
     uint32_t kaddr[NC];
@@ -269,25 +273,6 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
         o_off = b * p.o_sb + node * p.o_sn + static_cast<int64_t>(h) * p.o_sh + 4 * (g & ~1) + osl * OT * 16;
         lse_off = (static_cast<int64_t>(b) * p.H_q + h) * p.N_max + node;
     }
-    // K0 and the query rows of this wavefront have landed; the barrier extends the latter to the workgroup
-    if (my_tiles > 1) wait_vmcnt<3 * KLD>();
-    else if (my_tiles == 1) wait_vmcnt<KLD>();
-    else wait_vmcnt<0>();
-    __syncthreads();
-    bf16x8 qf[QB][NC];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-        for (int c = 0; c < NC; ++c) {
-            const int r = qb * 16 + l16;
-            qf[qb][c] = *reinterpret_cast<const bf16x8*>(s_q + r * (ROWG * 16) + (((4 * c + g) ^ (r & (ROWG - 1))) << 4));
-        }
-    // Query fragments live in accumulation registers (a matrix instruction takes its operands from there as well):
-    // with 64 rows per wavefront the output accumulators alone fill half of the architectural registers.
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-        for (int c = 0; c < NC; ++c) asm volatile("" : "+a"(qf[qb][c]));
     // Softmax state of query row 16 qb + l16 (the four lanes of a row agree): reference maximum, the same times
     // c2 (0 while no key was seen), and this lane's part of the sum of the row's weights.
     // acc[qb][t]: O^T rows 16t + 4g .. + 3.
@@ -305,6 +290,20 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
     // V operands: lane supplies key 4g + l16/4 (and 16 keys further), dims 16t + 4 (l16 % 4)
     const int k0 = 4 * g + (l16 >> 2);
     const uint32_t vaddr = kTileBytes + k0 * (ROWG * 16) + (l16 & 3) * 8 + (vswz(k0) << 5);
+    // (all of this before the wait: the compiler would put it behind, where the first products wait for it)
+#pragma unroll
+    for (int c = 0; c < NC; ++c) asm volatile("" : "+v"(kaddr[c]));
+    asm volatile("" : : "v"(vaddr));
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) asm volatile("" : "+v"(acc[qb][t]));
+    // K0 and the query rows of this wavefront have landed; the barrier extends the latter to the workgroup
+    if (my_tiles > 1) wait_vmcnt<3 * KLD>();
+    else if (my_tiles == 1) wait_vmcnt<KLD>();
+    else wait_vmcnt<0>();
+    __syncthreads();
+    bf16x8 qf[QB][NC];
     bf16x8 va[NT];
     auto read_v = [&](int t, int slot_off) __attribute__((always_inline)) {
         const uint32_t a = (vaddr ^ (t << 5)) + slot_off;
@@ -344,7 +343,19 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");     // the K area of slot 0 is free
         if (my_tiles > 2) { issue_k(2, phys_k); if (my_tiles > 3) fetch_blocks(3, phys_k); }
 #pragma unroll
-        for (int qb = 0; qb < QB; ++qb) scores(qb);
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) qf[qb][c] = *reinterpret_cast<const bf16x8*>(s_q + qb * 16 * ROWG * 16 + kaddr[c]);
+        // Query fragments live in accumulation registers (a matrix instruction takes its operands from there as well).
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) {
+                asm volatile("" : "+a"(qf[qb][c]));
+#pragma unroll
+                for (int x = 0; x < 2; ++x)
+                    s[qb][x] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[x][c], qf[qb][c], c ? s[qb][x] : f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+            }
         // V0 and K1 (the requests after them: V1, K2)
         if (my_tiles > 2) wait_vmcnt<2 * KLD>();
         else if (my_tiles == 2) wait_vmcnt<KLD>();
@@ -353,28 +364,40 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
 #pragma unroll
         for (int t = 0; t < NT; ++t) read_v(t, 0);
         maxima();
+        // The first reference, where every key is visible: as in the loop, with nothing accumulated that it would scale
+        if (stream * kKeys + kKeys <= P) {
+            bool any = false;
+#pragma unroll
+            for (int qb = 0; qb < QB; ++qb) any = any | (lmax[qb] > -INFINITY);
+            if (__any(any)) {
+#pragma unroll
+                for (int qb = 0; qb < QB; ++qb) {
+                    m_run[qb] = fmaxf(-INFINITY, across_row(lmax[qb], fmaxf));
+                    mrc[qb] = (m_run[qb] == -INFINITY ? 0.f : m_run[qb]) * c2;
+                }
+            }
+        }
     }
     for (int j = 0; j < my_tiles; ++j) {
         const int left = my_tiles - 1 - j;                 // tiles after this one
         const int slot0 = (stream + j * nstream) * kKeys;
         // s holds tile j's scores, va its V operands, ka the next tile's K operands; both their areas are free
         if (slot0 + kKeys > P) {                           // reaches past the prefix: tree region or tail
-            if (!have_anc) build_anc();
-            // branch-free on purpose: plain integer logic and one select per score
+            // bit k of `visible`: key slot0 + k.  Its place among this lane's scores is a constant once the lane's group is shifted out, so a
+            // score takes two instructions (a sign-extended bit and a bitwise select)
+            const int before = P - slot0;                  // keys of the tile in the prefix, < 32
+            const uint32_t exist = S - slot0 < 32 ? (1u << (S - slot0)) - 1u : ~0u;
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) {
                 const unsigned long long anc = (static_cast<unsigned long long>(anc_hi[qb]) << 32) | anc_lo[qb];
+                uint32_t visible = before > 0 ? (anc_lo[qb] << before) | ((1u << before) - 1u) : static_cast<uint32_t>(anc >> -before);
+                visible = (visible & exist) >> (4 * g);
 #pragma unroll
                 for (int x = 0; x < 2; ++x)
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const int slot_key = slot0 + x * 16 + 4 * g + i;
-                        const int rel = slot_key - P;
-                        const uint32_t in_prefix = static_cast<uint32_t>(rel) >> 31;
-                        const uint32_t is_anc = static_cast<uint32_t>(anc >> (rel & 63)) & 1u;
-                        const uint32_t in_range = static_cast<uint32_t>(slot_key - S) >> 31;
-                        const uint32_t vis = in_range & (in_prefix | is_anc);
-                        s[qb][x][i] = vis ? s[qb][x][i] : -INFINITY;
+                        const uint32_t seen = static_cast<uint32_t>(static_cast<int32_t>(visible << (31 - (16 * x + i))) >> 31);
+                        s[qb][x][i] = __uint_as_float((seen & __float_as_uint(s[qb][x][i])) | (~seen & 0xFF800000u));
                     }
             }
             maxima();
@@ -402,10 +425,7 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
         if (__builtin_expect(__any(trig), 0)) {
 #pragma unroll
             for (int qb = 0; qb < QB; ++qb) {
-                float mx = lmax[qb];
-                mx = fmaxf(mx, __shfl_xor(mx, 16));
-                mx = fmaxf(mx, __shfl_xor(mx, 32));
-                const float m_new = fmaxf(m_run[qb], mx);
+                const float m_new = fmaxf(m_run[qb], across_row(lmax[qb], fmaxf));
                 const float m_safe = m_new == -INFINITY ? 0.f : m_new;
                 const float alpha = m_run[qb] == -INFINITY ? 1.f : fast_exp2((m_run[qb] - m_safe) * c2);
                 m_run[qb] = m_new;
@@ -460,8 +480,7 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
     // ---- merge the four streams --------------------------------------------------------------------
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
-        l_run[qb] += __shfl_xor(l_run[qb], 16);
-        l_run[qb] += __shfl_xor(l_run[qb], 32);
+        l_run[qb] = across_row(l_run[qb], [](float x, float y) { return x + y; });
         if (g == 0) {
             s_m[wave][qb * 16 + l16] = m_run[qb];
             s_l[wave][qb * 16 + l16] = l_run[qb];
@@ -519,9 +538,10 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
             const uint32_t e1 = pack_bf16x2(out[2 * u][2] * inv, out[2 * u][3] * inv);
             const uint32_t o0 = pack_bf16x2(out[2 * u + 1][0] * inv, out[2 * u + 1][1] * inv);
             const uint32_t o1 = pack_bf16x2(out[2 * u + 1][2] * inv, out[2 * u + 1][3] * inv);
-            const uint32_t r0 = __shfl_xor(odd ? e0 : o0, 16);
-            const uint32_t r1 = __shfl_xor(odd ? e1 : o1, 16);
-            const u32x4 w = odd ? u32x4{r0, r1, o0, o1} : u32x4{e0, e1, r0, r1};
+            // an even group's lane holds dims 0-3 of two blocks of 16, its odd neighbour 4-7: even keeps the first block, odd the second
+            const auto r0 = __builtin_amdgcn_permlane16_swap(e0, o0, false, false);
+            const auto r1 = __builtin_amdgcn_permlane16_swap(e1, o1, false, false);
+            const u32x4 w = u32x4{r0[0], r1[0], r0[1], r1[1]};
             if (real) *reinterpret_cast<u32x4*>(orow + 16 * (2 * u + (odd ? 1 : 0))) = w;
         }
         if (real && p.lse && g == 0 && osl == 0)

@@ -211,42 +211,6 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
     if (my_tiles > 2) { fetch_blocks(2, phys_k); phys_v[0] = phys_k[0]; phys_v[1] = phys_k[1]; }
 
     const float c2 = p.c2, tau = p.tau;
-    // ---- the tree: every wavefront checks it and builds the ancestor masks in registers ----------
-    // requested after the parent array: K0, the query rows, V0 (an early request) or the query rows, K0, V0,
-    // and the second tile
-    if (my_tiles > 1) wait_vmcnt<4 * KLD + NQ>();
-    else if (my_tiles == 1 || early) wait_vmcnt<2 * KLD + NQ>();
-    else wait_vmcnt<NQ>();
-    const int par = s_par[wave][lane];
-    const bool bad_par = lane < n && (lane == 0 ? par != -1 : (par < 0 || par >= lane));
-    if (__any(bad_par)) err |= SPECVLM_ERR_BAD_PARENT;
-    if (err) {                                             // the same in every wavefront of the request
-        if (tid == 0 && p.err_flag) atomicOr(p.err_flag, err);
-        wait_vmcnt<0>();
-        return;
-    }
-    // Ancestor-or-self masks of this lane's query rows, while the first tile is on its way (the tile that needs them is the last of its
-    // stream): pointer doubling over the lanes (lane i holds node i), at most six rounds.
-    uint32_t anc_lo[QB], anc_hi[QB];
-    {
-        uint32_t mlo = lane < 32 ? 1u << (lane & 31) : 0u, mhi = lane < 32 ? 0u : 1u << (lane & 31);
-        int up = lane < n ? par : -1;
-#pragma unroll 1
-        while (__any(up >= 0)) {
-            const int src = max(up, 0) * 4;
-            const uint32_t alo = __builtin_amdgcn_ds_bpermute(src, mlo), ahi = __builtin_amdgcn_ds_bpermute(src, mhi);
-            const int up2 = __builtin_amdgcn_ds_bpermute(src, up);
-            if (up >= 0) { mlo |= alo; mhi |= ahi; up = up2; }
-        }
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) {
-            const int R = min(row0 + qb * 16 + l16, rows_total - 1);
-            const int node = R - divide(R, p.magic_nmax) * p.N_max;
-            anc_lo[qb] = __builtin_amdgcn_ds_bpermute(node * 4, mlo);
-            anc_hi[qb] = __builtin_amdgcn_ds_bpermute(node * 4, mhi);
-        }
-    }
-
     // ---- K fragments of a tile (A operand): lane (key 16x + l16, g) holds d = 32c + 8g .. +7 ------
     uint32_t kaddr[NC];
 #pragma unroll
@@ -290,14 +254,54 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
     // V operands: lane supplies key 4g + l16/4 (and 16 keys further), dims 16t + 4 (l16 % 4)
     const int k0 = 4 * g + (l16 >> 2);
     const uint32_t vaddr = kTileBytes + k0 * (ROWG * 16) + (l16 & 3) * 8 + (vswz(k0) << 5);
-    // (all of this before the wait: the compiler would put it behind, where the first products wait for it)
+    int row_node[QB];                                      // the node of this lane's query rows
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+        const int R = min(row0 + qb * 16 + l16, rows_total - 1);
+        row_node[qb] = R - divide(R, p.magic_nmax) * p.N_max;
+    }
+    // (all of this before the waits: the compiler would put it behind, where the tree and the first products wait for it)
 #pragma unroll
     for (int c = 0; c < NC; ++c) asm volatile("" : "+v"(kaddr[c]));
-    asm volatile("" : : "v"(vaddr));
+    asm volatile("" : : "v"(vaddr), "v"(row_node[0]), "v"(row_node[QB - 1]), "v"(o_off), "v"(lse_off), "s"(real_rows));
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb)
 #pragma unroll
         for (int t = 0; t < NT; ++t) asm volatile("" : "+v"(acc[qb][t]));
+    // ---- the tree: every wavefront checks it and builds the ancestor masks in registers ----------
+    // requested after the parent array: K0, the query rows, V0 (an early request) or the query rows, K0, V0,
+    // and the second tile
+    if (my_tiles > 1) wait_vmcnt<4 * KLD + NQ>();
+    else if (my_tiles == 1 || early) wait_vmcnt<2 * KLD + NQ>();
+    else wait_vmcnt<NQ>();
+    const int par = s_par[wave][lane];
+    const bool bad_par = lane < n && (lane == 0 ? par != -1 : (par < 0 || par >= lane));
+    if (__any(bad_par)) err |= SPECVLM_ERR_BAD_PARENT;
+    if (err) {                                             // the same in every wavefront of the request
+        if (tid == 0 && p.err_flag) atomicOr(p.err_flag, err);
+        wait_vmcnt<0>();
+        return;
+    }
+    // Ancestor-or-self masks of this lane's query rows, while the first tile is on its way (the tile that needs them is the last of its
+    // stream): pointer doubling over the lanes (lane i holds node i), at most six rounds.
+    uint32_t anc_lo[QB], anc_hi[QB];
+    {
+        uint32_t mlo = lane < 32 ? 1u << (lane & 31) : 0u, mhi = lane < 32 ? 0u : 1u << (lane & 31);
+        int up = lane < n ? par : -1;
+#pragma unroll 1
+        while (__any(up >= 0)) {
+            const int src = max(up, 0) * 4;
+            const uint32_t alo = __builtin_amdgcn_ds_bpermute(src, mlo), ahi = __builtin_amdgcn_ds_bpermute(src, mhi);
+            const int up2 = __builtin_amdgcn_ds_bpermute(src, up);
+            if (up >= 0) { mlo |= alo; mhi |= ahi; up = up2; }
+        }
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) {
+            anc_lo[qb] = __builtin_amdgcn_ds_bpermute(row_node[qb] * 4, mlo);
+            anc_hi[qb] = __builtin_amdgcn_ds_bpermute(row_node[qb] * 4, mhi);
+        }
+    }
+
     // K0 and the query rows of this wavefront have landed; the barrier extends the latter to the workgroup
     if (my_tiles > 1) wait_vmcnt<3 * KLD>();
     else if (my_tiles == 1) wait_vmcnt<KLD>();

@@ -38,9 +38,12 @@ struct StreamsParams : WaveParams {
     int B, columns, each;       // workgroups per row block of a KV head; as many per request (attn_plan.hpp)
     int by_length;              // columns go to the requests by their lengths, not `each` to everyone
     int wide;                   // partial results in fp32
+    int help;                   // short requests' workgroups bring keys of the longest one into the L2
     uint32_t magic_columns, magic_each;
     float inv_columns, least_gain;   // rounds that a division must save
 };
+
+constexpr int kMostHelped = 8;      // rounds of a request that others bring into the L2: 64 KB each, of four or five heads on an XCD
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
@@ -84,6 +87,8 @@ __device__ __forceinline__ void attend(const StreamsParams& p) {
     static_assert(kWaveWgs * kRingBytes >= 4 * 3 * OWN * 4096, "merge scratch must fit in the rings");
     static_assert(kSharesRound == kWaveWgs * kKeys, "a round is a tile of every stream");
 
+    constexpr bool HELPS = !SHARES && !PAGED && D == 128;      // (paged 0 - 2 % faster, head size 64 up to 1 % slower)
+
     __shared__ __attribute__((aligned(1024))) unsigned char s_ring[kWaveWgs * kRingBytes];
     __shared__ __attribute__((aligned(1024))) unsigned char s_q[kQRows * D * 2];
     __shared__ float s_m[kWaveWgs][kQRows];
@@ -116,7 +121,7 @@ __device__ __forceinline__ void attend(const StreamsParams& p) {
     typedef __attribute__((address_space(3))) int lds_int;
     const uint32_t ring_lds = (uint32_t)(uintptr_t)(lds_byte*)ring;
 
-    if (SHARES && p.by_length) {                           // lane i (mod 16): request i
+    if (SHARES ? p.by_length : HELPS && p.help) {          // lane i (mod 16): request i
         const int at = min(lane & 15, p.B - 1);
         dma4(p.prefix_len + at, (uint32_t)(uintptr_t)(lds_byte*)s_m[wave]);
         if (p.num_nodes) dma4(p.num_nodes + at, (uint32_t)(uintptr_t)(lds_byte*)s_l[wave]);
@@ -395,6 +400,34 @@ __device__ __forceinline__ void attend(const StreamsParams& p) {
             pf[qb][x] = __builtin_bit_cast(bf16x8, w);
         }
     };
+    // A column a request: where one is longer than the mean, its workgroups are still at work when the others have ended, and what bounds them
+    // is what one compute unit takes in of HBM, 57 GB/s; from the L2 it is 109.  So the workgroups of a head's other requests, on the same
+    // XCD, touch every 128-byte line of its last rounds as soon as their own first tiles are on their way: as many rounds as they are shorter
+    // than the mean, one at least.  Touched lines go to LDS that nothing reads any more.  us per call (8 x 32 heads unless said; boxes differ):
+    // 170 - 906 keys 19.2 -> 18.4 and 21.5 -> 18.2; 900 and seven of 200 18.2 -> 17.1; 90 - 2000 31.1 -> 28.3; 5 x 48 heads, 200 - 1200
+    // 21.8 -> 21.4; equal lengths 0 - 4 % more where 256 workgroups walk in step, else even.  Tried: only what is beyond the mean (half the
+    // gain), after the workgroup's last tile or one before (half), the lengths through the scalar cache (even).
+    auto help = [&]() __attribute__((always_inline)) {
+        const int my_P = __float_as_int(s_m[wave][lane]);
+        const int my_n = p.num_nodes ? __float_as_int(s_l[wave][lane]) : p.N_max;
+        const int keys = keys_of(my_P, my_n, p.N_max, p.g.capacity);
+        const int rounds = (lane & 15) < p.B ? (keys + kSharesRound - 1) / kSharesRound : 0;
+        const int longest = __builtin_amdgcn_readlane(row_scan(rounds, [](int x, int y) { return max(x, y); }), 15);
+        const int total = __builtin_amdgcn_readlane(row_scan(rounds, [](int x, int y) { return x + y; }), 15);
+        const int mean = static_cast<int>(ceilf(total * p.inv_columns - 0.01f));
+        if (longest - mean < 2) return;
+        const int mine = (lane & 15) < p.B && rounds <= mean ? max(mean - rounds, 1) : 0;
+        const int upto = row_scan(mine, [](int x, int y) { return x + y; });
+        const int to = __builtin_ctzll(__ballot(rounds == longest)), last = __builtin_amdgcn_readlane(keys, to) - 1;
+        const int first = max(longest - __builtin_amdgcn_readlane(upto, 15), 2), all = min(longest - first, kMostHelped);
+        const int64_t off = hk * p.g.stride_h + to * p.g.stride_b + (64 * (lane & 1));
+        const int end = min(__builtin_amdgcn_readlane(upto, b), all);
+        for (int j = __builtin_amdgcn_readlane(upto - mine, b); j < end; ++j) {
+            const int key = min((first + j) * kSharesRound + wave * kKeys + (lane >> 1), last);
+            dma4(p.k + off + key * p.g.stride_t, (uint32_t)(uintptr_t)(lds_int*)s_par[wave]);
+            dma4(p.v + off + key * p.g.stride_t, (uint32_t)(uintptr_t)(lds_int*)s_par[wave]);
+        }
+    };
     float lmax[2];
 
     if (my_tiles > 0) {
@@ -412,7 +445,10 @@ __device__ __forceinline__ void attend(const StreamsParams& p) {
                 asm volatile("" : "+a"(qf[qb][c]));
                 s[qb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[c], qf[qb][c], c ? s[qb] : zero, 0, 0, 0);
             }
-        // V0 and K1 (the requests after them: V1, K2)
+        if constexpr (HELPS) {
+            if (p.help && rb == 0) help();
+        }
+        // V0 and K1 (the requests after them: V1, K2; touched lines come on top, their workgroup can wait)
         if (my_tiles > 2) wait_vmcnt<2 * KLD>();
         else if (my_tiles == 2) wait_vmcnt<KLD>();
         else wait_vmcnt<0>();
@@ -779,6 +815,7 @@ int32_t launch_attn_streams(const AttnArgs& a) {
     p.each = std::min(p.columns / p.B, kMostRanges);
     p.by_length = a.plan.by_length;
     p.wide = a.plan.splits == 1;
+    p.help = p.B <= kMostByLength;
     p.magic_columns = divisor(p.columns);
     p.magic_each = divisor(p.each);
     p.inv_columns = 1.f / p.columns;

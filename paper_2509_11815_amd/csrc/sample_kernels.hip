@@ -4,6 +4,7 @@
 
 #include "common.hpp"
 #include "compact_plan.hpp"
+#include "wave_ops.hpp"
 
 namespace specvlm {
 
@@ -18,21 +19,33 @@ struct ValIdx {
     int i;
 };
 
-__device__ __forceinline__ void take_better(ValIdx& a, float v, int i) {
-    // -0 == +0 under the float compare, as the definition asks.
-    if (v > a.v || (v == a.v && i < a.i)) {
-        a.v = v;
-        a.i = i;
-    }
-}
-
-// The same when i is known to be greater than every index taken so far (a thread scans its entries
-// in increasing order): equal values keep the earlier index, so only "greater" replaces.
+// i is greater than every index taken so far (a thread scans its entries in increasing order), so only "greater" replaces.
+// -0 == +0 under the float compare, as the definition asks.
 __device__ __forceinline__ void take_later(ValIdx& a, float v, int i) {
     if (v > a.v) {
         a.v = v;
         a.i = i;
     }
+}
+
+// op over the 64 lanes, in every one of them: rows of 16 by DPP, then across rows (6 LDS permutes in a row take 0.4 us, this 0.05).
+template <typename Op>
+__device__ __forceinline__ int over_wave(int x, Op op) {
+    x = op(x, dpp<kRor8>(x));
+    x = op(x, dpp<kRor4>(x));
+    x = op(x, dpp<kRor2>(x));
+    x = op(x, dpp<kRor1>(x));
+    const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = op(static_cast<int>(r[0]), static_cast<int>(r[1]));
+    const auto q = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return op(static_cast<int>(q[0]), static_cast<int>(q[1]));
+}
+
+// The best of the 64 lanes, in every one: the greatest value, the lowest index among its equals (no lane holds NaN).
+__device__ __forceinline__ ValIdx best_of_wave(ValIdx a) {
+    const int bits = over_wave(__float_as_int(a.v), [](int x, int y) { return __float_as_int(fmaxf(__int_as_float(x), __int_as_float(y))); });
+    const float v = __int_as_float(bits);
+    return ValIdx{v, over_wave(a.v == v ? a.i : INT_MAX, [](int x, int y) { return min(x, y); })};
 }
 
 template <typename T>
@@ -55,12 +68,10 @@ struct Elem<float> {
 
 // (defined with the acceptance kernel below)
 template <bool COHERENT>
-__device__ __forceinline__ void accept_walk(int b, int N_max, int path_cap, const int32_t* __restrict__ parent,
-                                            const int32_t* __restrict__ draft_tok, const int32_t* amax,
-                                            const int32_t* __restrict__ num_nodes, int32_t* __restrict__ accept_len,
-                                            int32_t* __restrict__ path, int32_t* __restrict__ bonus_tok,
-                                            int32_t* __restrict__ committed_tok, int32_t* __restrict__ err_flag,
-                                            int (&s_par)[64], int (&s_tok)[64], int (&s_am)[64]);
+__device__ __forceinline__ void accept_walk(int b, int n, int N_max, int path_cap, int par, int tok, const int32_t* amax,
+                                            int32_t* __restrict__ accept_len, int32_t* __restrict__ path,
+                                            int32_t* __restrict__ bonus_tok, int32_t* __restrict__ committed_tok,
+                                            int32_t* __restrict__ err_flag);
 
 // What the fused form needs on top of the arg-max: the acceptance walk's arguments and one
 // arrival counter per request (zero between calls).
@@ -78,35 +89,37 @@ __global__ __launch_bounds__(1024) void node_argmax_kernel(int N_max, int V, con
                                                            int64_t stride_b, int64_t stride_n,
                                                            const int32_t* __restrict__ num_nodes,
                                                            int32_t* amax, AcceptArgs acc) {
-    __shared__ int s_last;
-    __shared__ int s_par[64], s_tok[64], s_am[64];
     const int row = blockIdx.x;
     const int b = row / N_max, i = row % N_max;
-    const int tid = threadIdx.x;
-    int n = num_nodes ? num_nodes[b] : N_max;
-    // publishes this row's result; FUSED: then draws the request's ticket, and the workgroup that
-    // draws the last one walks the tree (called by all threads of the workgroup)
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int n = num_nodes ? num_nodes[b] : N_max;
+    // what the walk will need of the tree: requested ahead of the row (the request's last row walks, and any may be the last)
+    int par = -1, tok = -1;
+    if (FUSED && tid < N_max) {
+        par = acc.parent[b * N_max + tid];
+        tok = acc.draft_tok[b * N_max + tid];
+    }
+    // publishes this row's result; FUSED: then draws the request's ticket, and the wavefront that
+    // draws the last one walks the tree (called by wavefront 0)
     auto finish = [&](int result) {
         if constexpr (!FUSED) {
-            if (tid == 0) amax[row] = result;
+            if (lane == 0) amax[row] = result;
         } else {
-            if (tid == 0) {
+            int last = 0;
+            if (lane == 0) {
                 __hip_atomic_store(amax + row, result, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 asm volatile("s_waitcnt vmcnt(0)" ::: "memory");        // the store has been acknowledged
                 int32_t* cnt = acc.counters + b * SPECVLM_COUNTER_STRIDE;     // a cache line per request
-                const int ticket = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const int last = ticket == N_max - 1;
+                last = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == N_max - 1;
                 if (last) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                s_last = last;
             }
-            __syncthreads();
-            if (s_last)                                                   // uniform
-                accept_walk<true>(b, N_max, acc.path_cap, acc.parent, acc.draft_tok, amax, num_nodes, acc.accept_len,
-                                  acc.path, acc.bonus_tok, acc.committed_tok, acc.err_flag, s_par, s_tok, s_am);
+            if (__builtin_amdgcn_readfirstlane(last))
+                accept_walk<true>(b, n, N_max, acc.path_cap, par, tok, amax, acc.accept_len, acc.path, acc.bonus_tok, acc.committed_tok,
+                                  acc.err_flag);
         }
     };
     if (i >= n) {
-        finish(-1);
+        if (wave == 0) finish(-1);
         return;
     }
     const T* p = logits + b * stride_b + i * stride_n;
@@ -142,33 +155,14 @@ __global__ __launch_bounds__(1024) void node_argmax_kernel(int N_max, int V, con
     for (int v = head + nvec * VEC + tid; v < V; v += blockDim.x) take_later(best, Elem<T>::one(p + v), v);
 
     // wavefront (64 lanes) reduction, then across the 16 wavefronts through LDS
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        float ov = __shfl_xor(best.v, off);
-        int oi = __shfl_xor(best.i, off);
-        take_better(best, ov, oi);
-    }
-    __shared__ float s_v[16];
-    __shared__ int s_i[16];
-    const int wave = tid >> 6, lane = tid & 63;
-    if (lane == 0) {
-        s_v[wave] = best.v;
-        s_i[wave] = best.i;
-    }
+    if constexpr (FUSED) asm volatile("" : "+v"(par), "+v"(tok));       // not to be loaded where they are used
+    best = best_of_wave(best);
+    __shared__ ValIdx s_best[16];
+    if (lane == 0) s_best[wave] = best;
     __syncthreads();
-    if (wave == 0) {
-        const int nw = blockDim.x >> 6;
-        ValIdx r{lane < nw ? s_v[lane] : -INFINITY, lane < nw ? s_i[lane] : INT_MAX};
-#pragma unroll
-        for (int off = 8; off >= 1; off >>= 1) {
-            float ov = __shfl_xor(r.v, off);
-            int oi = __shfl_xor(r.i, off);
-            take_better(r, ov, oi);
-        }
-        if (lane == 0) s_i[0] = r.i == INT_MAX ? 0 : r.i;
-    }
-    __syncthreads();
-    finish(s_i[0]);
+    if (wave) return;
+    const ValIdx r = best_of_wave(s_best[lane & 15]);
+    finish(r.i == INT_MAX ? 0 : r.i);
 }
 
 int32_t launch_node_argmax(int32_t dtype, int32_t B, int32_t N_max, int32_t V, const void* logits,
@@ -202,98 +196,78 @@ int32_t launch_node_argmax_accept(int32_t dtype, int32_t B, int32_t N_max, int32
 }
 
 // ---------------------------------------------------------------------------------------
-// tree_accept: one wavefront per request, lane i owns node i.  Every lane walks its own
-// root path (parent[i] < i bounds the walk by i steps), so a lane knows whether its node
-// is accepted and how deep it is; a wavefront max over (depth, -index) picks the node.
-// accept_walk is called by ALL threads of a workgroup (it contains a workgroup barrier);
-// only the first 64 act.  COHERENT: amax was written by other workgroups of the same
+// tree_accept: one wavefront per request, lane i owns node i.  Pointer doubling tells every lane whether its
+// node's path to the root is accepted and how deep it is (parent[i] < i: at most six rounds, three for
+// trees of depth 7); a wavefront max over (depth, -index) picks the node, whose path is read back lane by lane.
+// Registers and permutes only: the chain of the last row of a request in the fused form.  One wavefront calls.
+// par, tok: node lane's, anything where lane >= n.  COHERENT: amax was written by other workgroups of the same
 // kernel (device-coherent loads); otherwise by an earlier kernel.
 // ---------------------------------------------------------------------------------------
 template <bool COHERENT>
-__device__ __forceinline__ void accept_walk(int b, int N_max, int path_cap, const int32_t* __restrict__ parent,
-                                            const int32_t* __restrict__ draft_tok, const int32_t* amax,
-                                            const int32_t* __restrict__ num_nodes, int32_t* __restrict__ accept_len,
-                                            int32_t* __restrict__ path, int32_t* __restrict__ bonus_tok,
-                                            int32_t* __restrict__ committed_tok, int32_t* __restrict__ err_flag,
-                                            int (&s_par)[64], int (&s_tok)[64], int (&s_am)[64]) {
+__device__ __forceinline__ void accept_walk(int b, int n, int N_max, int path_cap, int par, int tok, const int32_t* amax,
+                                            int32_t* __restrict__ accept_len, int32_t* __restrict__ path,
+                                            int32_t* __restrict__ bonus_tok, int32_t* __restrict__ committed_tok,
+                                            int32_t* __restrict__ err_flag) {
     const int lane = threadIdx.x;
-    const bool active = lane < 64;                          // uniform per wavefront
     int err = 0;
-    int n = num_nodes ? num_nodes[b] : N_max;
     if (n < 1 || n > N_max) {
         err |= SPECVLM_ERR_BAD_NUM_NODES;
         n = min(max(n, 1), N_max);
     }
-    bool bad = false;
-    if (active) {
-        int par = -1, tok = -1, am = -1;
-        if (lane < n) {
-            par = parent[b * N_max + lane];
-            tok = draft_tok[b * N_max + lane];
-            if constexpr (COHERENT)
-                am = __hip_atomic_load(amax + b * N_max + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            else
-                am = amax[b * N_max + lane];
-            bad = lane == 0 ? par != -1 : (par < 0 || par >= lane);
-        }
-        s_par[lane] = par;
-        s_tok[lane] = tok;
-        s_am[lane] = am;
+    const bool real = lane < n;
+    int am = -1;
+    if (real) {
+        if constexpr (COHERENT)
+            am = __hip_atomic_load(amax + b * N_max + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else
+            am = amax[b * N_max + lane];
     }
-    __syncthreads();
-    if (!active) return;
-    int32_t* prow = path + b * path_cap;
-    int32_t* crow = committed_tok + b * path_cap;
+    const bool bad = real && (lane == 0 ? par != -1 : (par < 0 || par >= lane));
+    int best = 0, m = 0;
     if (__any(bad)) {                       // malformed tree: commit the root only
         err |= SPECVLM_ERR_BAD_PARENT;
-        if (lane == 0) {
-            accept_len[b] = 0;
-            bonus_tok[b] = s_am[0];
-            if (err_flag) atomicOr(err_flag, err);
+    } else {
+        int up = real ? par : -1, depth = up >= 0 ? 1 : 0;
+        const int wanted = __builtin_amdgcn_ds_bpermute(max(up, 0) * 4, am);      // (every lane takes part)
+        bool ok = real && (up < 0 || tok == wanted);
+        while (__any(up >= 0)) {
+            const int at = __builtin_amdgcn_ds_bpermute(max(up, 0) * 4, (up + 1) | depth << 8 | static_cast<int>(ok) << 16);
+            if (up >= 0) {
+                ok = ok && (at >> 16);
+                depth += (at >> 8) & 255;
+                up = (at & 255) - 1;
+            }
         }
-        for (int j = lane; j < path_cap; j += 64) {
-            prow[j] = j == 0 ? 0 : -1;
-            crow[j] = j == 0 ? s_am[0] : -1;
-        }
-        return;
+        const bool too_long = ok && depth > path_cap - 1;
+        if (__any(too_long)) err |= SPECVLM_ERR_PATH_TOO_LONG;
+        const int key = over_wave(ok && !too_long ? depth * 64 + (63 - lane) : -1, [](int x, int y) { return max(x, y); });   // deeper first, then lower index
+        best = __builtin_amdgcn_readfirstlane(63 - (key & 63));
+        m = __builtin_amdgcn_readfirstlane(key >> 6);
     }
-    bool ok = lane < n;
-    int depth = 0;
-    if (lane < n) {
-        int t = lane;
-        while (s_par[t] != -1) {
-            int p = s_par[t];
-            ok = ok && (s_tok[t] == s_am[p]);
-            t = p;
-            ++depth;
-        }
+    // lane j: the path's node j, and the token it commits
+    int node = -1, t = best;
+    for (int j = m; j >= 0; --j) {
+        if (lane == j) node = t;
+        t = __builtin_amdgcn_readlane(par, t);
     }
-    if (ok && depth > path_cap - 1) {
-        err |= SPECVLM_ERR_PATH_TOO_LONG;
-        ok = false;
+    const int bonus = __builtin_amdgcn_readlane(am, best);
+    const int node_tok = __builtin_amdgcn_ds_bpermute(max(node, 0) * 4, tok);
+    const int next_tok = __builtin_amdgcn_ds_bpermute((lane + 1) * 4, node_tok);
+    int32_t* prow = path + b * path_cap;
+    int32_t* crow = committed_tok + b * path_cap;
+    if (lane < path_cap) {
+        prow[lane] = node;
+        crow[lane] = lane < m ? next_tok : lane == m ? bonus : -1;
     }
-    int key = ok ? depth * 64 + (63 - lane) : -1;   // deeper first, then lower index
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) key = max(key, __shfl_xor(key, off));
-    const int best = 63 - (key & 63), m = key >> 6;
-    if (lane == best) {
-        int t = lane;
-        for (int j = m; j >= 0; --j) {
-            prow[j] = t;
-            if (j >= 1) crow[j - 1] = s_tok[t];
-            t = s_par[t];
-        }
-        crow[m] = s_am[best];
-        accept_len[b] = m;
-        bonus_tok[b] = s_am[best];
-    }
-    for (int j = m + 1 + lane; j < path_cap; j += 64) {
+    for (int j = 64 + lane; j < path_cap; j += 64) {
         prow[j] = -1;
         crow[j] = -1;
     }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) err |= __shfl_xor(err, off);
-    if (lane == 0 && err && err_flag) atomicOr(err_flag, err);
+    if (lane == 0) {
+        accept_len[b] = m;
+        bonus_tok[b] = bonus;
+        if (err && err_flag) atomicOr(err_flag, err);
+    }
 }
 
 __global__ __launch_bounds__(64) void tree_accept_kernel(int N_max, int path_cap,
@@ -306,9 +280,14 @@ __global__ __launch_bounds__(64) void tree_accept_kernel(int N_max, int path_cap
                                                          int32_t* __restrict__ bonus_tok,
                                                          int32_t* __restrict__ committed_tok,
                                                          int32_t* __restrict__ err_flag) {
-    __shared__ int s_par[64], s_tok[64], s_am[64];
-    accept_walk<false>(blockIdx.x, N_max, path_cap, parent, draft_tok, amax, num_nodes, accept_len, path, bonus_tok,
-                       committed_tok, err_flag, s_par, s_tok, s_am);
+    const int b = blockIdx.x, lane = threadIdx.x;
+    int par = -1, tok = -1;
+    if (lane < N_max) {
+        par = parent[b * N_max + lane];
+        tok = draft_tok[b * N_max + lane];
+    }
+    accept_walk<false>(b, num_nodes ? num_nodes[b] : N_max, N_max, path_cap, par, tok, amax, accept_len, path, bonus_tok, committed_tok,
+                       err_flag);
 }
 
 int32_t launch_tree_accept(int32_t B, int32_t N_max, int32_t path_cap, const int32_t* parent,

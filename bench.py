@@ -25,7 +25,7 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBPS = 8000.0          # MI355X published HBM3E peak
 # the kernel that the library chooses for a workload's attention call (--splits 0)
-ATTENTION_KERNELS = {"C2": "attn_wave_kernel<128, 2, false>", "C3": "attn_mfma_kernel<128, 2>",
+ATTENTION_KERNELS = {"C2": "attn_wave_kernel<128, 2, false>", "C3": "attn_wave_kernel<128, 2, false>",
                      "C4": "attn_streams_kernel<128, false>", "C5": "attn_shares_kernel<128, true>"}
 
 
@@ -461,7 +461,7 @@ def main():
                      "frac": round(achieved / HBM_PEAK_GBPS, 4),
                      "algorithmic_bytes_per_launch": kv_bytes_layer,
                      "avg_launch_us": round(attn_launch_us, 3),
-                     "traffic": measured_traffic("attn_mfma_kernel_C3.txt", "attn_mfma.hip", "attn_mfma_body.inc") if cfg.name == "C3" else None},
+                     "traffic": measured_traffic("attn_wave_kernel_C3.txt", "attn_wave.hip", "attn_rows.hpp") if cfg.name == "C3" else None},
         "configs": dict({cfg.name: {"attn_us_per_launch": round(attn_launch_us, 3), "algorithmic_bytes_per_launch": kv_bytes_layer,
                                     "GBps": round(achieved, 1), "frac": round(achieved / HBM_PEAK_GBPS, 4),
                                     "key_ranges_of_even_division": sv.specvlm_tree_verify_attn_num_splits(desc), "layers_timed": L}},

@@ -58,15 +58,13 @@ inline int32_t single_round_ranges(const specvlm_attn_desc& d) {
 // of a head meet at the end.  Query rows as well (attn_wave.hip): workgroups of 16 or 32 rows, whose
 // K and V come from L2 for all but the first of a head's row blocks, with a quarter or half of the
 // arithmetic each, so that fewer or no partial results have to meet, and those are a quarter or half the size.
-// The model below was fitted to measured calls; as the kernels are now (us; 1 x 32 heads x 128, 60 nodes, all on 256 workgroups):
-//   260 keys   key ranges 11.1 (1 split)   32 rows  8.4 (4)   16 rows  7.8 (1)
-//   828        key ranges 11.5 (8)         32 rows  9.8 (4)   16 rows  9.9 (2)
-//   1600       key ranges 13.2 (8)         32 rows 11.6 (4)   16 rows 13.2 (2)
-//   2940       key ranges 15.4 (8)         32 rows 15.1 (4)   16 rows 19.4 (2)
-//   3324       key ranges 16.4 (8)         32 rows 16.3 (4)   16 rows 21.2 (2)
-//   3600       key ranges 17.6 (8)         32 rows 17.6 (4)
-// so rows win until the repeated K and V traffic (at most ~14 TB/s from L2) costs more than the merge.  The choice is the best of
-// these to 1 % at every length (the model crosses near 3300 keys, the calls near 3600).
+// As the kernels are now (us; 1 x 32 heads x 128, 60 nodes, on 256 workgroups; by key ranges 8, 32 rows 4, 16 rows 2 ranges):
+//   keys        828   1160   1660   2160   2660   3060   3324   3660   4060   4560
+//   key ranges 11.1   12.0   13.0   13.8   14.9   15.2   16.3   17.2   17.6   18.6
+//   32 rows     8.9   10.1   10.7   12.2   13.7   14.5   15.5   17.0   17.6   18.9
+//   16 rows     9.3          13.0   15.6   17.9   19.9   20.6   22.7   24.7   26.5
+// so rows win until the repeated K and V traffic (at most ~14 TB/s from L2) costs more than the merge.  plan_rows() was fitted to earlier forms of
+// the kernels (it crosses near 3300 keys, and near 2100, where it counts seven ranges); fit_rows() below puts that right.
 struct AttnPlan {
     int32_t ranges;        // key ranges per head that the workspace holds
     int32_t block_rows;    // query rows per workgroup, 0: all (key ranges only)

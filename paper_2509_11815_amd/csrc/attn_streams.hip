@@ -18,12 +18,15 @@
 //   fetch     as in attn_wave.hip: direct-to-LDS, two K and two V areas per wavefront, K three tiles and V two tiles ahead
 //   merge     the four streams meet in LDS, every wavefront owns 32 head dims of all rows; key ranges as in attn_wave.hip
 //
-// us per call (HIP-graph replay), attn_mfma / attn_wave -> here; head size 128, 60 - 64 nodes unless said: 4 x 32 query / 8
+//   tree      ancestor masks while the first tile is on its way, two instructions a masked score; what needs no tile before the wait for
+//             the first (8 x 32 heads, 170 - 906 keys 20.1 -> 19.2, eight of 443 17.0 -> 15.7, 4 x 32 / 8 heads below 20.6 -> 19.7)
+//
+// us per call (HIP-graph replay), attn_mfma / attn_wave -> here, before the last point; head size 128, 60 - 64 nodes unless said: 4 x 32 query / 8
 // KV heads, 2048, 1311, 3000, 777 keys 27.6 -> 20.1 (23.5 with two ranges each); 8 x 32 / 16 heads, 4788 keys 82.4 -> 65.7; 3 x 32 / 16 heads,
 // 3664 - 500 keys 34.8 -> 20.4 (27.2); 4 x 40 heads, 671 keys 18.5 -> 16.4; 6 x 32 heads, 2800 - 300 keys 44.7 -> 33.8 (35.6); 5 x 40 heads of
 // 64, 1935 keys 26.0 -> 20.4.  Tried and slower: two wavefronts sharing a stream of 128 rows (26.3 at the first of these), wavefronts
 // instead of whole workgroups dealt out by length (24.4), the row blocks of a head walking their tiles in different orders so that each finds
-// in L2 what another fetched (28.1; by one to three tiles of every four 25.0), loads that stay in L2 where blocks share them (a branch in
+// in L2 what another fetched (28.1; by one to three tiles of every four 25.0), tiles touched three steps ahead by one of them (+ 1.7), loads that stay in L2 where blocks share them (a branch in
 // the loop: + 1; without one 22.8 - 24.6 against 23.9 - 24.4).
 #include <type_traits>
 

@@ -17,14 +17,16 @@
 //             pipe has work while the vector ALU does exponentials; a row's weights are summed in fp32 before
 //             they are packed (one more matrix product, with ones, in place of the eight additions is 0.1 - 0.6 %
 //             faster per step, but sums bf16 weights: log-sum-exp off by up to 1e-3 in place of 1e-6)
-//   tree      ancestor masks from a register copy of the parent array by pointer doubling across lanes, built
-//             only by wavefronts that meet a tile past the prefix
+//   tree      ancestor masks by pointer doubling across lanes, built by every wavefront while the first tile is on its
+//             way: the tile that needs them is the last of its stream, where nothing hides them; a masked score takes
+//             two instructions of the tile's visibility word (masks on demand, eight instructions a score, and the
+//             addresses, accumulators and query operands behind the wait for the first tile: 828 keys 9.46 us, so 9.03)
 //   merge     as in attn_mfma.hip: streams through LDS, key ranges through the workspace and tickets; the last
 //             arrival reads up to four partials at once, more in batches of eight (a caller's 9 - 64 splits too)
 //
-// Measured per call (HIP-graph replay), key ranges only -> here: 1 x 32 heads, 828 keys 11.3 -> 9.25 us; 4 x 8
-// heads, 144 keys 8.8 -> 5.8; 2 x 8 heads, 1197 keys, paged 16.6 -> 10.2; 1 x 8 heads of 64, 4200 keys 21.4 -> 8.5;
-// 4 x 32 query / 16 KV heads of 64, 13 nodes 9.0 -> 6.0.
+// Measured per call (HIP-graph replay), key ranges only -> here: 1 x 32 heads, 828 keys 11.1 -> 9.0 us, 3324 keys 16.3 -> 15.5;
+// 4 x 8 heads, 144 keys 8.8 -> 5.8; 2 x 8 heads, 1197 keys, paged 16.6 -> 10.2; 1 x 8 heads of 64, 4200 keys 21.4 -> 8.5;
+// 4 x 32 query / 16 KV heads of 64, 13 nodes 9.0 -> 6.0 (the last four before the line above).
 #include "attn_rows.hpp"
 
 namespace specvlm {

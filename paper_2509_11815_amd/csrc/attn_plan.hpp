@@ -272,39 +272,47 @@ inline void plan_columns(const specvlm_attn_desc& d, AttnPlan& plan) {
 // The division into row blocks once more, for head size 128 and one round of workgroups, with the times of the kernels as they are: a
 // workgroup's constant, another where partial results meet, and a step that lasts as long as one compute unit needs for its bytes while
 // `active` of them fetch (the row blocks of a head, or the heads of a group, fetch together).  Fitted to 2200 random calls (1 - 8 requests,
-// 2 - 64 KV heads shared by 1 - 8, 8 - 64 nodes, 64 - 9000 keys) in all their divisions; the 166 whose division changes take 0.94 of their time in
-// the mean, 134 less than 0.98, none more than 1.02 (1300 others: key ranges -> row blocks 0.92 of 181 calls, 6 above 1.02, up to 1.08).  us per call, key ranges -> row blocks: 1 x 32 heads, 2160 keys 13.7 -> 12.3, 2660: 14.6 ->
-// 13.7, 3324: 16.6 -> 16.1; paged 3324: 17.7 -> 16.2; 1060 keys in a cache of 3328: 12.1 -> 9.9; 32 / 8 heads, 2660: 14.2 -> 12.1, 4060: 16.2 -> 14.6.
-// Key ranges fetch K and V once, so they win again where streams are long: more than 7 tiles a stream of the row blocks with heads of
-// their own (8 - 9 tiles 0.96 - 1.09 of their time, above 15 1.01), 8 where two or three heads share K and V (10 - 11 tiles up to 1.09), 10 where more do.  Not for more than 16 ranges, whose meeting
-// the model prices too high.  plan_rows() stays for what was measured against its choice: which batches go to the kernel with four streams,
-// and whether a call has partial results at all.  Those are rounded to bf16: a call without them does not gain them here.
+// 2 - 64 KV heads shared by 1 - 8, 8 - 64 nodes, 64 - 9000 keys) in all their divisions, and held against 1000 others:
+//   key ranges -> row blocks, where these are 3 % faster by the model, take about as many compute units (fewer: up to 1.06) and have at most 7
+//     tiles a stream (10 where four or more heads share K and V; beyond, K and V fetched once win again: 8 - 11 tiles up to 1.09 of the time of
+//     key ranges): 0.91 of their time in the mean of 282 calls, none above 1.02; requests of a half to an eighth of the capacity 0.80, none above 0.88
+//   32 -> 16 rows and back, as many ranges, where 5 % faster: 0.92 of 385, none above 0.99; shorter requests 0.90
+// us per call: 1 x 32 heads, 2160 keys 13.7 -> 12.3, 2660: 14.6 -> 13.7, 3324: 16.6 -> 16.1; paged 3324: 17.7 -> 16.2; 1060 keys in a cache of
+// 3328: 12.1 -> 9.9; 32 / 8 heads, 2660: 14.2 -> 12.1, 4060: 16.2 -> 14.6.  Not taken: other numbers of ranges of row blocks (more: 0.94, but up to 1.22
+// where requests are short; fewer: 0.95, and up to 4 % further from 64 bits; here 0.98 - 1.008 of the error before), row blocks -> key ranges (1.07).
+// plan_rows() stays for what was measured against its choice: which batches go to the kernel with four streams, and whether a call has
+// partial results at all.  Those are rounded to bf16: a call without them does not gain them here.
 inline void fit_rows(const specvlm_attn_desc& d, AttnPlan& plan) {
     const int group = d.H_q / d.H_kv, rows = group * d.N_max;
     const int cap = d.paged ? d.max_blocks_per_req * SPECVLM_PAGE_SIZE : d.kv_capacity;
     const int ntile = (cap + kTile - 1) / kTile;
     const int64_t items = static_cast<int64_t>(d.B) * d.H_q * plan.ranges;
-    if (d.D != 128 || d.num_splits > 0 || items > 256 || plan.ranges > 16) return;
+    if (d.D != 128 || d.num_splits > 0 || items > 256 || plan.ranges > 16) return;        // (more ranges: their meeting is priced too high here)
     if (d.kv_stride_t >= (1 << 22) || (d.N_max * d.q_stride_n + group * d.q_stride_h) >= (1ll << 30)) return;      // as in plan_rows()
-    const bool partials = plan.splits > 1;
-    double best = 1e30;
-    int most_steps = ntile;
-    if (!plan.block_rows) {
+    auto units_of = [&](int br) { return static_cast<int64_t>(d.B) * d.H_kv * ((rows + br - 1) / br); };
+    auto steps_of = [&](int s) { return (ntile + 4 * s - 1) / (4 * s); };
+    auto row_time = [&](int br, int s) {
+        const double meet = s > 1 ? (br == 16 ? 1.65 : 1.85) + 1.35 * ((s - 1) / 8) : 0.0;
+        return (br == 16 ? 3.8 : 4.7) + meet + steps_of(s) * (1.02 + 0.0025 * units_of(br) * s / ((rows + br - 1) / br));
+    };
+    const bool from_rows = plan.block_rows != 0;
+    int least = plan.splits, most = plan.splits;
+    double best;
+    if (from_rows) {
+        best = 0.95 * row_time(plan.block_rows, plan.splits);
+    } else {
         // (workgroups that are no multiple of 8 are dealt out to the XCDs in turn: the heads of a group then share no L2)
         if (items % 8 != 0 && group > 1) return;
         const int steps = (ntile + kStreamsPerWg * plan.ranges - 1) / (kStreamsPerWg * plan.ranges);
         best = 0.97 * (7.0 + (plan.ranges > 1 ? 1.86 + 1.55 * std::max(0, plan.ranges - 8) : 0.0) + steps * (0.894 + 0.00115 * items / group));
-        most_steps = group == 1 ? 7 : group < 4 ? 8 : 10;
+        least = 1;
     }
     for (int br = 16; br <= 32; br *= 2) {
         if (br == 32 && rows <= 16) break;
-        const int rb = (rows + br - 1) / br;
-        const int64_t units = static_cast<int64_t>(d.B) * d.H_kv * rb;
-        for (int s = 1; s <= (partials ? plan.ranges : 1) && units * s <= 256; ++s) {
-            const int r = (ntile + 4 * s - 1) / (4 * s);
-            const double meet = s > 1 ? (br == 16 ? 1.65 : 1.85) + 1.35 * ((s - 1) / 8) : 0.0;
-            const double t = (br == 16 ? 3.8 : 4.7) + meet + r * (1.02 + 0.0025 * units * s / rb);
-            if (r <= most_steps && t < best) { best = t; plan.block_rows = br; plan.splits = s; }
+        for (int s = least; s <= most && units_of(br) * s <= 256; ++s) {
+            if (!from_rows && (steps_of(s) > (group < 4 ? 7 : 10) || 10 * units_of(br) * s < 9 * items)) continue;
+            const double t = row_time(br, s);
+            if (t < best) { best = t; plan.block_rows = br; plan.splits = s; }
         }
     }
 }

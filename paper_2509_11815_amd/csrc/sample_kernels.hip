@@ -117,9 +117,11 @@ __global__ __launch_bounds__(1024) void node_argmax_kernel(int N_max, int V, con
                 last = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == N_max - 1;
                 if (last) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
-            if (__builtin_amdgcn_readfirstlane(last))
+            if (__builtin_amdgcn_readfirstlane(last)) {
+                asm volatile("" ::: "memory");                          // the other rows' results are not read before the ticket was seen
                 accept_walk<true>(b, n, N_max, acc.path_cap, par, tok, amax, acc.accept_len, acc.path, acc.bonus_tok, acc.committed_tok,
                                   acc.err_flag);
+            }
         }
     };
     if (i >= n) {

@@ -586,6 +586,7 @@ __global__ __launch_bounds__(kWaveWgs * 64) __attribute__((amdgpu_waves_per_eu(1
         if (is_last) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (!__builtin_amdgcn_readfirstlane(is_last)) return;
+    asm volatile("" ::: "memory");                         // no partial result is read before the ticket was seen
     if (p.num_splits <= 4) {                               // uniform; what the library chooses by itself, mostly
         // (four partials in place of eight: half the instructions of the chain's last link: 1 x 32 heads, 828 keys 9.85 -> 9.25 us)
         constexpr int kFew = 4, kCoherent = 16;            // sc1; buffer loads, which the compiler counts

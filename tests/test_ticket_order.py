@@ -11,8 +11,8 @@ ORDERS = re.compile(r"\bfence\b|~\{memory\}")
 READS = re.compile(r"\bload atomic\b|@llvm\.amdgcn\.raw\.ptr\.buffer\.load")
 
 
-@pytest.mark.parametrize("source,at_least", [("sample_kernels.hip", 4), ("draft_tree.hip", 4), ("head_argmax.hip", 4), ("attn_streams.hip", 4),
-                                             ("attn_mfma.hip", 4)])
+@pytest.mark.parametrize("source,at_least", [("sample_kernels.hip", 4), ("draft_tree.hip", 4), ("head_argmax.hip", 4), ("attn_wave.hip", 8),
+                                             ("attn_streams.hip", 4), ("attn_mfma.hip", 4)])
 def test_what_orders_the_reads_behind_the_ticket(tmp_path, source, at_least):
     from paper_2509_11815_amd import build
     out = str(tmp_path / "k.ll")

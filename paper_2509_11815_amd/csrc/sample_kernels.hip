@@ -261,13 +261,9 @@ __device__ __forceinline__ void accept_walk(int b, int n, int N_max, int path_ca
     const int next_tok = __builtin_amdgcn_ds_bpermute((lane + 1) * 4, node_tok);
     int32_t* prow = path + b * path_cap;
     int32_t* crow = committed_tok + b * path_cap;
-    if (lane < path_cap) {
+    if (lane < path_cap) {                  // (at most 64: checked on the host)
         prow[lane] = node;
         crow[lane] = lane < m ? next_tok : lane == m ? bonus : -1;
-    }
-    for (int j = 64 + lane; j < path_cap; j += 64) {
-        prow[j] = -1;
-        crow[j] = -1;
     }
     if (lane == 0) {
         accept_len[b] = m;

@@ -46,8 +46,6 @@ struct StreamsParams : WaveParams {
     float inv_columns, least_gain;   // rounds that a division must save
 };
 
-constexpr int kMostHelped = 8;      // rounds of a request that others bring into the L2: 64 KB each, of four or five heads on an XCD
-
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 // The greatest of sixteen scores, NaN where one is.
@@ -404,12 +402,16 @@ __device__ __forceinline__ void attend(const StreamsParams& p) {
         }
     };
     // A column a request: where one is longer than the mean, its workgroups are still at work when the others have ended, and what bounds them
-    // is what one compute unit takes in of HBM, 57 GB/s; from the L2 it is 109.  So the workgroups of a head's other requests, on the same
-    // XCD, touch every 128-byte line of its last rounds as soon as their own first tiles are on their way: as many rounds as they are shorter
-    // than the mean, one at least.  Touched lines go to LDS that nothing reads any more.  us per call (8 x 32 heads unless said; boxes differ):
-    // 170 - 906 keys 19.2 -> 18.4 and 21.5 -> 18.2; 900 and seven of 200 18.2 -> 17.1; 90 - 2000 31.1 -> 28.3; 5 x 48 heads, 200 - 1200
-    // 21.8 -> 21.4; equal lengths 0 - 4 % more where 256 workgroups walk in step, else even.  Tried: only what is beyond the mean (half the
-    // gain), after the workgroup's last tile or one before (half), the lengths through the scalar cache (even).
+    // is what one compute unit takes in of HBM, 57 GB/s; from the L2 it is 109.  So the workgroups of a head's other requests touch every
+    // 128-byte line of rounds that it has yet to come to (which ones: lengths.hpp) as soon as their own first tiles are on their way.  Touched
+    // lines go to LDS that nothing reads any more.  Where the workgroups of a head are all on one XCD (KV heads a multiple of 8) they find that
+    // one's L2; where a head lies across two of them (8 x 32 / 4: every one) some touch for an L2 that the longest request does not use.
+    // us per call without -> with, same box (8 x 32 heads unless said): 170 - 906 keys 19.7 -> 19.4, another box 19.8 -> 19.2; 900 and seven of 200
+    // 18.3 -> 18.0; 90 - 2000 31.3 -> 30.4; heads across two XCDs: 8 x 32 / 4, 170 - 906 14.8 -> 14.7, 90 - 2000 22.3 -> 22.0; 4 x 40 / 10,
+    // 200 - 1000 15.7 -> 15.5; 5 x 28, 200 - 1000 17.4 -> 16.5; 7 x 36, 100 - 1800 27.5 -> 26.7; equal lengths even (443 keys 16.4 | 16.5, 503
+    // 17.4 | 17.3, 700 21.2 | 21.2).  Tried: only what is beyond the mean (half the gain), after the workgroup's last tile or one before (half),
+    // the last rounds where shares are more than eight (7 x 36, 100 - 1800 26.6 -> 27.1; 8 x 32 / 4, 90 - 4000 34.2 -> 34.5; else even), all of
+    // this worked out before the wait for the first tile (even; 443 keys 16.5 -> 16.8), the lengths through the scalar cache (even).
     auto help = [&]() __attribute__((always_inline)) {
         const int my_P = __float_as_int(s_m[wave][lane]);
         const int my_n = p.num_nodes ? __float_as_int(s_l[wave][lane]) : p.N_max;
@@ -419,10 +421,10 @@ __device__ __forceinline__ void attend(const StreamsParams& p) {
         const int total = __builtin_amdgcn_readlane(row_scan(rounds, [](int x, int y) { return x + y; }), 15);
         const int mean = static_cast<int>(ceilf(total * p.inv_columns - 0.01f));
         if (longest - mean < 2) return;
-        const int mine = (lane & 15) < p.B && rounds <= mean ? max(mean - rounds, 1) : 0;
+        const int mine = (lane & 15) < p.B ? rounds_read_ahead(rounds, longest, mean) : 0;
         const int upto = row_scan(mine, [](int x, int y) { return x + y; });
         const int to = __builtin_ctzll(__ballot(rounds == longest)), last = __builtin_amdgcn_readlane(keys, to) - 1;
-        const int first = max(longest - __builtin_amdgcn_readlane(upto, 15), 2), all = min(longest - first, kMostHelped);
+        const int first = first_read_ahead(longest, __builtin_amdgcn_readlane(upto, 15)), all = min(longest - first, kMostReadAhead);
         const int64_t off = hk * p.g.stride_h + to * p.g.stride_b + (64 * (lane & 1));
         const int end = min(__builtin_amdgcn_readlane(upto, b), all);
         for (int j = __builtin_amdgcn_readlane(upto - mine, b); j < end; ++j) {

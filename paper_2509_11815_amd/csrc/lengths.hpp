@@ -22,4 +22,11 @@ constexpr bool slot_inside(int prefix, int node, int capacity) { return prefix >
 // ceil(rounds / len), inverse = 1 / len to a few ulp
 constexpr int columns_of(int rounds, float len, float inverse) { return static_cast<int>((static_cast<float>(rounds) - 0.5f + len) * inverse); }
 
+// A column a request (attn_streams.hip): the workgroups of the requests up to the mean read rounds of the longest one ahead, each as many as it
+// is shorter than the mean, one at least; nothing where the longest has less than two rounds beyond the mean.  These rounds follow one
+// another in the order of the requests from first_read_ahead() on, up to the longest request's end and kMostReadAhead at most.
+constexpr int kMostReadAhead = 8;   // 64 KB each, of four or five heads on an XCD
+constexpr int rounds_read_ahead(int rounds, int longest, int mean) { return longest - mean < 2 || rounds > mean ? 0 : mean - rounds > 1 ? mean - rounds : 1; }
+constexpr int first_read_ahead(int longest, int all) { return longest - all > 2 ? longest - all : 2; }
+
 }  // namespace specvlm

@@ -64,7 +64,9 @@ inline int32_t single_round_ranges(const specvlm_attn_desc& d) {
 //   32 rows     8.9   10.1   10.7   12.2   13.7   14.5   15.5   17.0   17.6   18.9
 //   16 rows     9.3          13.0   15.6   17.9   19.9   20.6   22.7   24.7   26.5
 // so rows win until the repeated K and V traffic (at most ~14 TB/s from L2) costs more than the merge.  plan_rows() was fitted to earlier forms of
-// the kernels (it crosses near 3300 keys, and near 2100, where it counts seven ranges); fit_rows() below puts that right.
+// the kernels (it crosses near 3300 keys, and near 2100, where it counts seven ranges); fit_rows() below puts that right for head size 128 in one
+// round of workgroups with up to 16 ranges.  Elsewhere (head size 64, more rounds or ranges) plan_rows() decides alone, and its choice has not been
+// measured against the kernels as they are.
 struct AttnPlan {
     int32_t ranges;        // key ranges per head that the workspace holds
     int32_t block_rows;    // query rows per workgroup, 0: all (key ranges only)
@@ -156,10 +158,17 @@ inline AttnPlan plan_of_heads_and_rows(const specvlm_attn_desc& d) {
 //   8 x 40 query / 10 KV heads, 22 nodes, 503 keys 10.3 | 12.3; 6 x 64 / 8 of 64, 18 nodes, 828: 9.4 | 11.6; 4 x 40 / 20, 46 nodes, 3869:
 //   40.7 | 43.5 (42 such shapes, all slower here, 6 - 27 %); two ranges | three: 5 x 28 / 4, 24 nodes, 2900: 21.1 | 23.0; but 8 x 20 / 5,
 //   22 nodes, 3390: 24.8 | 22.4 (three ranges on 216 workgroups or more, long streams); three | four: 3 x 16 / 8, 36 nodes, 2750: 16.0 | 16.7
-// Where they do not, every XCD fetches a head's K and V again: long streams then lose to the streams' kernel (5 x 50 / 10, 30 nodes,
-// 2600 keys 60.0 | 34.6; 1330: 22 - 25 | 21.4), and so do six or more blocks of a unit (9 x 20 / 4, 40 nodes, 472: 13.8 | 13.0).
-// Short ones are near even (21 shapes of 15 - 30 tiles: here 0.78 - 1.05 of their time at equal lengths, 0.92 - 1.16 at very different
-// ones, paged the most) and stay, and paged requests of head size 64 with them.
+// That condition and the lines for other numbers of workgroups date from when only a multiple of 8 gave an XCD a contiguous range of the row blocks
+// (other numbers: every XCD fetched a head's K and V again, 5 x 50 / 10, 30 nodes, 2600 keys 60.0 | 34.6; 9 x 20 / 4, 40 nodes, 472: 13.8 | 13.0).
+// attn_wave.hip now does so whatever the number, and it makes no difference any more.  Time of row blocks over that of the even division here, 1926
+// random shapes, requests as long as the cache (and at a quarter of it); one range: least - most, else the mean:
+//     ranges, tiles          one                        three: 40 - 56  56 - 70      70 - 90      90 - 120     four: 70 - 90  90 - 120
+//     128, multiple of 8     0.81 - 0.91 (0.77 - 0.85)  0.96 (0.84)     1.01 (0.87)  1.04 (0.87)  1.08 (0.86)  0.93 (0.82)    0.98 (0.86)
+//     128, other numbers     0.82 - 0.94 (0.78 - 0.86)  0.98 (0.85)     1.04 (0.87)  1.07 (0.88)  1.11 (0.87)  0.97 (0.85)    1.02 (0.88)
+//     64, multiple of 8      0.85 - 1.03 (0.83 - 1.06)  0.98 (0.89)     1.02 (0.90)  1.03 (0.92)  1.07 (0.92)  0.94 (0.87)    0.97 (0.91)
+//     64, other numbers      0.85 - 0.97 (0.82 - 0.91)  0.98 (0.89)     1.01 (0.90)  1.05 (0.93)  1.09 (0.93)  0.96 (0.88)    1.01 (0.92)
+// So for other numbers of workgroups the line lies too low: of the calls that it sends here evenly divided, those of one range, and of four up
+// to 90 tiles, would be better off with row blocks (9 x 20 / 4, 40 nodes, 472 keys among them); not drawn again yet.
 inline bool rows_in_one_round_win(const specvlm_attn_desc& d, const AttnPlan& plan, int64_t units, int s) {
     const int ntile = ((d.paged ? d.max_blocks_per_req * SPECVLM_PAGE_SIZE : d.kv_capacity) + kTile - 1) / kTile;
     if (!plan.block_rows) return false;
@@ -223,7 +232,11 @@ constexpr int kMostByLength = 16;   // requests that it deals columns out to
 //                                   64 50 - 80  0.85   0.85   0.84     0.80   0.83;   above: 0.87
 //   row blocks, one round of a     128 20 - 38  0.90   1.10   1.33     1.36   1.16;   38 - 44: 1.06;   44 - 60: 0.94;   above: 0.87
 //     multiple of 8 workgroups      64 26 - 44  0.85   1.05   1.22     1.28   1.09;   44 - 50: 1.04;   50 - 60: 0.97;   above: 0.91
-//   row blocks, otherwise          128 34 - 60  0.52   0.68   0.88     1.13   0.77;   above: 0.57;     64 from 30 on: 0.83 and less
+//   row blocks, one round of       128 20 - 30  0.84  1.06  1.28     1.32   1.11;   30 - 38: 1.04;   38 - 44: 0.96;   44 - 60: 0.90;   above: 0.84
+//     another number                64 20 - 30  0.85  1.03  1.18     1.24   1.07;   30 - 38: 1.03;   38 - 50: 0.99;   50 - 60: 0.94;   above: 0.90
+// (The last two rows are measured with the kernels as they are, 2587 shapes, the others with earlier ones.  A multiple of 8 made a difference to row
+// blocks then: 0.77 from 34 on, 0.83 from 30 on, together with calls of more than one round, which share the line of 20 and 26.  With today's figures
+// it would be at 38 for one round.  Not drawn again yet: at 20 - 38 requests that fill the cache would lose 1.2 - 1.3, shorter ones gain as much.)
 // (3 x 40, 1744 slots: 1700 keys 23.1 -> 19.6, 376 - 58 keys 10.2 -> 14.4 us; so it keeps its row blocks.)  Not where heads are shared and
 // equal lengths would leave more than a fifth of the columns idle (5 x 32 / 16, 4916 keys 53.6 | 63.9), and blocks at least 70 % full.
 // Below, short unsplit calls with shared heads gain from a column each (x < 12, at 64 16); at 128 from 7 tiles on (140 shapes, equal lengths of the whole
@@ -277,8 +290,8 @@ inline void plan_columns(const specvlm_attn_desc& d, AttnPlan& plan) {
 //     tiles a stream (10 where four or more heads share K and V; beyond, K and V fetched once win again: 8 - 11 tiles up to 1.09 of the time of
 //     key ranges): 0.91 of their time in the mean of 282 calls, none above 1.02; requests of a half to an eighth of the capacity 0.80, none above 0.88
 //   32 -> 16 rows and back, as many ranges, where 5 % faster: 0.92 of 385, none above 0.99; shorter requests 0.90
-// us per call: 1 x 32 heads, 2160 keys 13.7 -> 12.3, 2660: 14.6 -> 13.7, 3324: 16.6 -> 16.1; paged 3324: 17.7 -> 16.2; 1060 keys in a cache of
-// 3328: 12.1 -> 9.9; 32 / 8 heads, 2660: 14.2 -> 12.1, 4060: 16.2 -> 14.6.  Not taken: other numbers of ranges of row blocks (more: 0.94, but up to 1.22
+// us per call: 1 x 32 heads, 2160 keys 13.7 -> 12.3, 2660: 14.6 -> 13.7, 3324: 16.3 -> 15.5 (as the step was made 16.6 -> 16.1); paged 3324:
+// 17.7 -> 16.2; 1060 keys in a cache of 3328: 12.1 -> 9.9; 32 / 8 heads, 2660: 14.2 -> 12.1, 4060: 16.2 -> 14.6.  Not taken: other numbers of ranges of row blocks (more: 0.94, but up to 1.22
 // where requests are short; fewer: 0.95, and up to 4 % further from 64 bits; here 0.98 - 1.008 of the error before), row blocks -> key ranges (1.07).
 // plan_rows() stays for what was measured against its choice: which batches go to the kernel with four streams, and whether a call has
 // partial results at all.  Those are rounded to bf16: a call without them does not gain them here.
@@ -301,7 +314,8 @@ inline void fit_rows(const specvlm_attn_desc& d, AttnPlan& plan) {
     if (from_rows) {
         best = 0.95 * row_time(plan.block_rows, plan.splits);
     } else {
-        // (workgroups that are no multiple of 8 are dealt out to the XCDs in turn: the heads of a group then share no L2)
+        // (attn_mfma.hip deals workgroups that are no multiple of 8 out to the XCDs in turn, so that the heads of a group share no L2 and key ranges
+        // take longer than the model below says.  Row blocks took 0.55 - 0.93 of their time in 164 such calls; not taken yet)
         if (items % 8 != 0 && group > 1) return;
         const int steps = (ntile + kStreamsPerWg * plan.ranges - 1) / (kStreamsPerWg * plan.ranges);
         best = 0.97 * (7.0 + (plan.ranges > 1 ? 1.86 + 1.55 * std::max(0, plan.ranges - 8) : 0.0) + steps * (0.894 + 0.00115 * items / group));

@@ -15,8 +15,10 @@ namespace specvlm {
 // result does not depend on the reduction shape.  Bound by a row's bytes into one compute unit and,
 // fused, by the chain from the last row to the walk: wavefronts meet once in LDS, the first one goes on
 // alone in registers.  us per launch, with LDS permutes, two more barriers and a walk of dependent LDS reads
-// -> now: 60 rows of 32000 bf16 7.1 -> 6.1, 480 10.95 -> 10.0, 256 of 152064 19.1 -> 18.3.  (The next four loads
-// ahead of these: 152064 entries + 0.8.)
+// -> now, launches back to back: 60 rows of 32000 bf16 7.3 -> 6.3, 480 11.1 -> 10.3, 256 of 152064 19.65 -> 18.7; behind a
+// step's attention calls in a kernel trace 7.25 -> 6.0, 13.0 -> 11.6, 17.6 -> 15.6 (a whole step of eight requests,
+// 634 us, shows no difference).  (The next four loads ahead of these: 152064 entries + 0.8; the tree behind the row's
+// first loads: even.)
 // ---------------------------------------------------------------------------------------
 struct ValIdx {
     float v;
